@@ -47,23 +47,23 @@ def listed():
         # fp32 models under load: concurrent users whose lists and histories differ in length
         dict(name="f32 16 ragged users", path="score", model="C1", dtype="f32", users=16, cand=10_000, seq=50, items=1_000_000, ragged=True, slices=False),
         # a bf16 model whose head and attention widths are not among the tuned ones
-        dict(name="bf16 small model, 16 users", path="score", model="C1", dtype="bf16", users=16, cand=10_000, seq=50, items=1_000_000, ragged=False, slices=False),
+        dict(name="bf16 small model 16 users", path="score", model="C1", dtype="bf16", users=16, cand=10_000, seq=50, items=1_000_000, ragged=False, slices=False),
         # the latency of one whole request over a long history
-        dict(name="one request, L=1000", path="score", model="C2", dtype="bf16", users=1, cand=10_000, seq=1000, items=1_000_000, ragged=False, slices=False),
+        dict(name="one request L=1000", path="score", model="C2", dtype="bf16", users=1, cand=10_000, seq=1000, items=1_000_000, ragged=False, slices=False),
         # the batched serving load
         dict(name="64 users", path="score", model="C3", dtype="bf16", users=64, cand=10_000, seq=500, items=10_000_000, ragged=False, slices=False),
         # a table far beyond the caches, uniform ids, short histories, several heads
-        dict(name="16 users, 12.8 GB table", path="score", model="C4", dtype="bf16", users=16, cand=20_000, seq=200, items=50_000_000, ragged=False, slices=False),
+        dict(name="16 users 12.8 GB table", path="score", model="C4", dtype="bf16", users=16, cand=20_000, seq=200, items=50_000_000, ragged=False, slices=False),
         # the wide model: projected queries, 8 heads, long histories, three wide layers
-        dict(name="32 users, wide model", path="score", model="C5", dtype="bf16", users=32, cand=10_000, seq=2000, items=10_000_000, ragged=False, slices=False),
+        dict(name="32 users wide model", path="score", model="C5", dtype="bf16", users=32, cand=10_000, seq=2000, items=10_000_000, ragged=False, slices=False),
         # bridge-embedding cross, odd counts: 37 users with lists and histories of every length
-        dict(name="37 ragged users, bridges", path="score", model="B3", dtype="bf16", users=37, cand=9_973, seq=499, items=10_000_000, ragged=True, slices=False),
+        dict(name="37 ragged users bridges", path="score", model="B3", dtype="bf16", users=37, cand=9_973, seq=499, items=10_000_000, ragged=True, slices=False),
         # the asynchronous user side of the batched load
-        dict(name="user network, 64 users", path="user", dtype="bf16", users=64, seq=500, raw=128, d=64),
+        dict(name="user network 64 users", path="user", dtype="bf16", users=64, seq=500, raw=128, d=64),
         # signature modelling of a 10^4-item history for 64 users
-        dict(name="signatures, 10^4 history", path="lsh", dtype="bf16", users=64, cand=10_000, seq=10_000, items=10_000_000, bits=64, d=64, tiers=8, ragged=False),
+        dict(name="signatures 10^4 history", path="lsh", dtype="bf16", users=64, cand=10_000, seq=10_000, items=10_000_000, bits=64, d=64, tiers=8, ragged=False),
         # ... and of a 10^5-item history with wider signatures for 8
-        dict(name="signatures, 10^5 history", path="lsh", dtype="bf16", users=8, cand=10_000, seq=100_000, items=10_000_000, bits=128, d=128, tiers=8, ragged=False),
+        dict(name="signatures 10^5 history", path="lsh", dtype="bf16", users=8, cand=10_000, seq=100_000, items=10_000_000, bits=128, d=128, tiers=8, ragged=False),
         # the nearline refresh of a tenth of the table
         dict(name="update 10^6 rows", path="update", dtype="bf16", items=10_000_000, rows=1_000_000, d=64),
     ]
