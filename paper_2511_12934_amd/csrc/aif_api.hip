@@ -80,7 +80,9 @@ struct aif_ctx {
     // repacked weights (owned)
     DevBuf w1u;                       // fp32 [d_user, H1]: user columns of layer 1, transposed
     DevBuf wq;                        // fp32 [d_attn, d_item] (generic attention)
+    DevBuf wq_pieces;                 // W_q as bf16 pieces (generic attention)
     DevBuf wt[MAX_LAYERS];            // fp32 transposed [K_l, N_l] (generic MLP)
+    DevBuf w_pieces[MAX_LAYERS];      // the same as bf16 pieces (generic MLP)
     DevBuf bias[MAX_LAYERS];          // fp32 [N_l]
     bool has_bias[MAX_LAYERS] = {};
     bool has_wq = false;
@@ -150,6 +152,8 @@ void destroy(aif_ctx *c)
     if (!c) return;
     c->w1u.release();
     c->wq.release();
+    c->wq_pieces.release();
+    for (auto &b : c->w_pieces) b.release();
     for (auto &b : c->wt) b.release();
     for (auto &b : c->bias) b.release();
     mfma_release(c->mfma);
@@ -278,6 +282,16 @@ aif_status init_impl(const aif_config *cfg, const aif_weights *wts, aif_ctx *c)
     }
     c->x_rows = (size_t)c->max_users * round_up(c->max_candidates, ROW_BLOCK);
     HIP_TRY(nullptr, mfma_plan(m, c->max_seq_len, c->max_users, c->x_rows, wts->w_q, wts->w, c->mfma, s));
+    if (!c->mfma.attn && c->has_wq && attn_generic_gathers(m)) {
+        HIP_TRY(nullptr, c->wq_pieces.alloc(pieces_bytes(m.dtype, m.n_heads, m.d_head, m.d_item)));
+        HIP_TRY(nullptr, launch_pack_pieces(m.dtype, wts->w_q, m.n_heads, m.d_head, m.d_item, 0, m.d_item, c->wq_pieces.p, s));
+    }
+    if (!c->mfma.mlp)
+        for (int l = 0; l < m.n_layers; ++l) {
+            const int col0 = l == 0 ? m.d_user : 0, ncols = m.dims[l] - col0;
+            HIP_TRY(nullptr, c->w_pieces[l].alloc(pieces_bytes(m.dtype, 1, m.dims[l + 1], ncols)));
+            HIP_TRY(nullptr, launch_pack_pieces(m.dtype, wts->w[l], 1, m.dims[l + 1], m.dims[l], col0, ncols, c->w_pieces[l].p, s));
+        }
     // both consumers of the workspace read MFMA fragments: keep it in fragment order (x_offset)
     {
         const char *rm = getenv("AIF_X_ROW_MAJOR");      // testing: the MFMA kernels on the row-major layout
@@ -473,7 +487,7 @@ static aif_status score_impl(aif_ctx *c, const aif_request *reqs, int32_t n_req,
     const bool fused = stage_fusable(m, c->mfma);
     const bool staged_proj = !fused && stage_proj_fusable(m, c->mfma);
     // where it can, the attention kernel takes the item vectors from the table itself
-    const bool attn_indexes = c->mfma.attn && !c->separate_gather && attn_gathers(m, b, c->mfma);
+    const bool attn_indexes = !c->separate_gather && (c->mfma.attn ? attn_gathers(m, b, c->mfma) : attn_generic_gathers(m));
     c->attn_indexed = attn_indexes;
     // A few requests (the latency cases: one request, or one cut into mini-batches) send their descriptors in the
     // staging launch's arguments and that launch writes the tables on the device: nothing is uploaded.  Otherwise, when
@@ -539,7 +553,8 @@ static aif_status score_impl(aif_ctx *c, const aif_request *reqs, int32_t n_req,
         HIP_TRY(c, launch_attn_mfma(m, b, c->X.p, c->mfma, fused || staged_proj, s, attn_indexes ? c->table : nullptr,
                                     attn_indexes ? (int32_t *)c->bad.p : nullptr));
     else
-        HIP_TRY(c, launch_attn_generic(m, b, c->X.p, c->has_wq ? (const float *)c->wq.p : nullptr, c->max_seq_len, s));
+        HIP_TRY(c, launch_attn_generic(m, b, c->X.p, c->has_wq ? (const float *)c->wq.p : nullptr, c->wq_pieces.p,
+                                       attn_indexes ? c->table : nullptr, (int32_t *)c->bad.p, c->max_seq_len, s));
     HIP_TRY(c, mark(3));
     if (c->mfma.mlp) {
         const float *bf[MAX_LAYERS];
@@ -550,6 +565,7 @@ static aif_status score_impl(aif_ctx *c, const aif_request *reqs, int32_t n_req,
         MlpGenericWeights gw{};
         for (int l = 0; l < m.n_layers; ++l) {
             gw.wt[l] = (const float *)c->wt[l].p;
+            gw.pieces[l] = c->w_pieces[l].p;
             gw.bias[l] = c->has_bias[l] ? (const float *)c->bias[l].p : nullptr;
         }
         HIP_TRY(c, launch_mlp_generic(m, b, c->X.p, gw, (const float *)c->bias1.p, s));
@@ -709,7 +725,7 @@ aif_status aif_score_topk_static(aif_ctx *c, const aif_request *req, int32_t k, 
 
     c->row_base.clear();                         // aif_peek_features has nothing to show for this call
     c->last_slots = 1;
-    const bool attn_indexes = plan.attn && !c->separate_gather && attn_gathers(m, b, plan);
+    const bool attn_indexes = !c->separate_gather && (plan.attn ? attn_gathers(m, b, plan) : attn_generic_gathers(m));
     const bool staged_proj = !fused && stage_proj_fusable(m, plan);
     c->attn_indexed = attn_indexes;
     if (fused) {
@@ -726,7 +742,8 @@ aif_status aif_score_topk_static(aif_ctx *c, const aif_request *req, int32_t k, 
     if (plan.attn)
         HIP_TRY(c, launch_attn_mfma(m, b, X, plan, fused || staged_proj, s, attn_indexes ? c->table : nullptr, attn_indexes ? bad : nullptr));
     else
-        HIP_TRY(c, launch_attn_generic(m, b, X, c->has_wq ? (const float *)c->wq.p : nullptr, c->max_seq_len, s));
+        HIP_TRY(c, launch_attn_generic(m, b, X, c->has_wq ? (const float *)c->wq.p : nullptr, c->wq_pieces.p,
+                                       attn_indexes ? c->table : nullptr, bad, c->max_seq_len, s));
     if (plan.mlp) {
         const float *bf[MAX_LAYERS];
         for (int l = 0; l < m.n_layers; ++l) bf[l] = c->has_bias[l] ? (const float *)c->bias[l].p : nullptr;
@@ -735,6 +752,7 @@ aif_status aif_score_topk_static(aif_ctx *c, const aif_request *req, int32_t k, 
         MlpGenericWeights gw{};
         for (int l = 0; l < m.n_layers; ++l) {
             gw.wt[l] = (const float *)c->wt[l].p;
+            gw.pieces[l] = c->w_pieces[l].p;
             gw.bias[l] = c->has_bias[l] ? (const float *)c->bias[l].p : nullptr;
         }
         HIP_TRY(c, launch_mlp_generic(m, b, X, gw, bias1, s));

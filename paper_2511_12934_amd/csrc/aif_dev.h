@@ -122,15 +122,20 @@ hipError_t launch_update_rows(const Model &m, void *table, const int32_t *ids, c
 hipError_t launch_user_fold(const Model &m, const Batch &b, const float *w1u, const float *b1,
                             float *bias1, hipStream_t s);
 
-// a3-a5, any shape, fp32 arithmetic: X[row, d_item:] = [attention | cross].
-hipError_t launch_attn_generic(const Model &m, const Batch &b, void *X, const float *wq, int max_seq_len,
-                               hipStream_t s);
+// a3-a5, any shape, fp32 precision: X[row, d_item:] = [attention | cross].  wq: W_q in fp32 (null: the model has none)
+// and wq_pieces: the same as launch_pack_pieces leaves it, a group per head (used where attn_generic_gathers(m)).
+// table: non-null only where attn_generic_gathers(m): the kernel then takes the item rows from the table itself (a1),
+// writes them to the workspace and counts ids outside the table in *bad.
+hipError_t launch_attn_generic(const Model &m, const Batch &b, void *X, const float *wq, const void *wq_pieces, const void *table,
+                               int32_t *bad, int max_seq_len, hipStream_t s);
+bool attn_generic_gathers(const Model &m);
 size_t attn_generic_lds_bytes(const Model &m, int max_seq_len);
 
-// a6-a7, any shape, fp32 arithmetic.  wt[l] = transposed fp32 weights [K_l, N_l].
+// a6-a7, any shape, fp32 precision.
 struct MlpGenericWeights {
-    const float *wt[MAX_LAYERS];
+    const float *wt[MAX_LAYERS];        // transposed fp32 weights [K_l, N_l]
     const float *bias[MAX_LAYERS];      // bias[0] unused (folded into bias1)
+    const void *pieces[MAX_LAYERS];     // the same weights as launch_pack_pieces leaves them
 };
 hipError_t launch_mlp_generic(const Model &m, const Batch &b, const void *X, const MlpGenericWeights &w,
                               const float *bias1, hipStream_t s);
@@ -152,6 +157,9 @@ hipError_t launch_topk_few(const TopkDesc *descs /*host*/, int n_req, int k, int
 // init-time repacking (device -> device, any storage type -> fp32)
 hipError_t launch_pack_transposed(int dtype, const void *w, int n_out, int n_in, int col0, int ncols,
                                   float *wt /*[ncols, n_out]*/, hipStream_t s);
+// ... and as bf16 pieces in MFMA fragment order (k_generic.hip): `groups` matrices of `rows` rows each, one below the other
+size_t pieces_bytes(int dtype, int groups, int rows, int ncols);
+hipError_t launch_pack_pieces(int dtype, const void *w, int groups, int rows, int n_in, int col0, int ncols, void *out, hipStream_t s);
 hipError_t launch_to_f32(int dtype, const void *src, int64_t rows, int cols, int ld_src, int col0,
                          float *dst /*[rows, cols]*/, hipStream_t s);
 

@@ -267,7 +267,7 @@ aif_status aif_user_precompute(aif_user_ctx *c, const aif_user_request *users, i
     if (c->mfma.attn)
         USER_TRY(c, launch_attn_mfma(m, b, c->X, c->mfma, false, s));
     else
-        USER_TRY(c, launch_attn_generic(m, b, c->X, nullptr, c->max_seq_len, s));
+        USER_TRY(c, launch_attn_generic(m, b, c->X, nullptr, nullptr, nullptr, nullptr, c->max_seq_len, s));
     if (pe) USER_TRY(c, hipEventRecord(pe[2], s));
     USER_TRY(c, launch_user_ffn_partial(c->w, du, b.blk_req, b.n_blk, c->X, (float *)c->part, s));
     USER_TRY(c, launch_user_combine(c->w, du, n_users, c->X, (const float *)c->part, s));

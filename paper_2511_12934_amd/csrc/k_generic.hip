@@ -1,9 +1,17 @@
-// Shape-agnostic fp32-arithmetic kernels: the whole path for fp32 models and
-// for any model whose sizes the MFMA kernels do not cover.  Plain, one
-// candidate per wave (attention) or sixteen per block (MLP); accumulation in
-// fp32 in a fixed order per candidate, so results do not depend on how a
-// candidate list is sliced into requests.
+// Shape-agnostic kernels of fp32 precision: the whole path for fp32 models and
+// for any model whose sizes the bf16 MFMA kernels do not cover.  The
+// contractions run on the bf16 matrix instruction all the same: an fp32 value
+// is the sum of three bf16 values (8 + 8 + 8 significant bits), and of the
+// nine products of two such sums the six that reach fp32's last bit are
+// accumulated in fp32 -- 2.6 times the rate of the fp32 matrix instruction,
+// which has 1/16 of the bf16 one's.  Tensors stored in bf16 are one piece and
+// cost accordingly less (three products against an fp32 activation).  Every
+// candidate is a column of its own: results do not depend on how a candidate
+// list is sliced into requests.
 #include "k_stage.h"
+
+#include <algorithm>
+#include <type_traits>
 
 namespace aif {
 
@@ -46,9 +54,94 @@ hipError_t launch_user_fold(const Model &m, const Batch &b, const float *w1u, co
 }
 
 // ---------------------------------------------------------------------------
+// Values as bf16 pieces, and the products of pieces.
+// ---------------------------------------------------------------------------
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+template <typename T> struct stored;
+template <> struct stored<float> { static constexpr int P = 3; };       // pieces of a tensor of this storage type
+template <> struct stored<uint16_t> { static constexpr int P = 1; };
+
+template <int P> struct Pieces { bf16x8 p[P]; };
+
+// x = p[0] + p[1] + p[2], each piece the rest so far rounded to bf16: exact for three pieces.  A value that is not
+// finite (or rounds to infinity) makes NaN pieces: whoever multiplies them sees a NaN and takes the plain route.
+template <int P> __device__ __forceinline__ Pieces<P> split8(const float *v)
+{
+    Pieces<P> o;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        float r = v[j];
+#pragma unroll
+        for (int q = 0; q < P; ++q) {
+            const __bf16 h = (__bf16)r;
+            o.p[q][j] = h;
+            if (q + 1 < P) r -= (float)h;
+        }
+    }
+    return o;
+}
+
+// acc += a * b over the k-step's 32 terms.  The product of the leading pieces goes to `big`, the others, at most 2^-8 of
+// it, to `small`: they are added to each other first, so `big` is rounded once per k-step.
+template <int PA, int PB>
+__device__ __forceinline__ void mfma_pieces(const Pieces<PA> &a, const Pieces<PB> &b, f32x4 &big, f32x4 &small)
+{
+#pragma unroll
+    for (int i = PA - 1; i >= 0; --i)
+#pragma unroll
+        for (int j = PB - 1; j >= 0; --j)
+            if (i + j > 0 && i + j <= 2) small = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.p[i], b.p[j], small, 0, 0, 0);
+    big = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.p[0], b.p[0], big, 0, 0, 0);
+}
+
+// eight consecutive elements (16-byte aligned for fp32 in halves of four) as fp32; elements at and past `n` are zero
+template <typename T> __device__ __forceinline__ void load8(const T *p, int n, float *v);
+template <> __device__ __forceinline__ void load8<float>(const float *p, int n, float *v)
+{
+    float4 a = make_float4(0, 0, 0, 0), b = a;
+    if (n > 0) a = *(const float4 *)p;
+    if (n > 4) b = *(const float4 *)(p + 4);
+    v[0] = a.x, v[1] = a.y, v[2] = a.z, v[3] = a.w, v[4] = b.x, v[5] = b.y, v[6] = b.z, v[7] = b.w;
+}
+template <> __device__ __forceinline__ void load8<uint16_t>(const uint16_t *p, int n, float *v)
+{
+    uint4 a = make_uint4(0, 0, 0, 0);
+    if (n > 0) a = *(const uint4 *)p;
+    const uint32_t w[4] = {a.x, a.y, a.z, a.w};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        v[2 * j] = __uint_as_float(w[j] << 16);
+        v[2 * j + 1] = __uint_as_float(w[j] & 0xFFFF0000u);
+    }
+}
+// four consecutive elements at p + f of a row of n; `quad`: n is a multiple of four and the row 4-element aligned
+template <typename T> __device__ __forceinline__ void load4(const T *p, int f, int n, bool quad, float *v)
+{
+    if (quad) {
+        float4 a = make_float4(0, 0, 0, 0);
+        if (f < n) {
+            if constexpr (sizeof(T) == 4) a = *(const float4 *)(p + f);
+            else {
+                const uint2 w = *(const uint2 *)(p + f);
+                a = make_float4(__uint_as_float(w.x << 16), __uint_as_float(w.x & 0xFFFF0000u), __uint_as_float(w.y << 16),
+                                __uint_as_float(w.y & 0xFFFF0000u));
+            }
+        }
+        v[0] = a.x, v[1] = a.y, v[2] = a.z, v[3] = a.w;
+    } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] = f + j < n ? ld_f<T>(p + f + j) : 0.f;
+    }
+}
+
+// ---------------------------------------------------------------------------
 // a3-a5 -- query, target attention (Eq. 3 form, query := candidate) and the
-// real-time half of the cross features (Sec. 3.3).  One wave per candidate,
-// ATTN_TS candidates per block, all waves step through the phases together.
+// real-time half of the cross features (Sec. 3.3) for heads wider than
+// GEN_MAX_HEAD: one wave per candidate, ATTN_TS candidates per block, all
+// waves step through the phases together.
 // Per wave LDS: e[d_item], q[d_attn], score[max_seq_len].
 // ---------------------------------------------------------------------------
 constexpr int ATTN_TS = 16;
@@ -177,15 +270,435 @@ __global__ __launch_bounds__(256) void k_attn_generic(Model m, Batch b, T *__res
     }
 }
 
+// ---------------------------------------------------------------------------
+// The same for heads of up to GEN_MAX_HEAD, on the matrix cores and with the
+// gather (a1) inside.  A wave owns 16 NC candidates, the columns of every
+// product, and a block of WV waves shares the request's keys:
+//   Q^T = W_q E^T (a head's features in tiles of 16), S^T = K Q^T, O^T = V^T P^T.
+// A 16x16 result leaves features (keys) 4 g + i of one candidate in a lane
+// (g = lane / 16), and two such tiles are, in place, the eight k-values a lane
+// owes the next product's B operand once K (V) is read in the same order:
+// k-value j of group g is feature (key) 4 g + j of the first tile, or
+// 16 + 4 g + j - 4 of the second.  Nothing is exchanged between lanes but the
+// softmax maximum.  32 keys at a time go through LDS as pieces in fragment
+// order, split by the block's threads (the next 32 are on their way from
+// memory meanwhile); the softmax is the running one, its rescaling skipped by a
+// wave none of whose candidates found a larger score (a factor of exactly one
+// otherwise: same bits).
+//
+// What bounds it: the vector ALU -- per key and candidate one expf and three
+// pieces of the weight, about 20 instructions -- and on short histories (L = 50,
+// d = 32) the chain row -> query -> scores of a wave.  Measured (fp32, L <= 50,
+// d_attn 32 of W_q, rows of 64): 16 users of 6,200 candidates on average 51 us,
+// where a wave per candidate on the vector ALU and a gather launch before it
+// took 230 + 13; one request of 1,000: 14 against 22 + 6; bf16, 16 x 10^4: 62
+// against 312 + 10.
+// ---------------------------------------------------------------------------
+constexpr int GEN_MAX_HEAD = 128;
+constexpr int GEN_KEYS = 32;
+
+// One head of one candidate by one wave in plain fp32 arithmetic: where a product of pieces met a value that is not
+// finite (an infinity is not the sum of three pieces), so that infinities and NaN propagate as plain fp32 has them.
+template <typename T>
+__device__ __noinline__ void attn_plain(const T *e, const T *K, const T *V, const float *wq, int d_item, int da, int dh, int o,
+                                        int L, float scale, T *out)
+{
+    const int lane = threadIdx.x & 63;
+    float q[2], acc[2] = {0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        const int k = lane + 64 * s;
+        q[s] = 0.f;
+        if (k < dh) {
+            if (wq)
+                for (int j = 0; j < d_item; ++j) q[s] += wq[(size_t)(o + k) * d_item + j] * ld_f<T>(e + j);
+            else
+                q[s] = ld_f<T>(e + o + k);
+        }
+    }
+    auto score = [&](int t) {
+        const T *kr = K + (size_t)(t < L ? t : 0) * da + o;
+        float a = 0.f;
+        for (int k = 0; k < dh; ++k) a += __shfl(k < 64 ? q[0] : q[1], k & 63, 64) * ld_f<T>(kr + k);
+        return a * scale;
+    };
+    float mx = -INFINITY, sum = 0.f;
+    for (int t0 = 0; t0 < L; t0 += 64) {
+        const float s = score(t0 + lane);
+        if (t0 + lane < L) mx = fmaxf(mx, s);
+    }
+    mx = wave_max(mx);
+    for (int t0 = 0; t0 < L; t0 += 64) {
+        const float s = score(t0 + lane), p = t0 + lane < L ? expf(s - mx) : 0.f;
+        sum += p;
+        for (int i = 0; i < 64 && t0 + i < L; ++i) {
+            const float pi = __shfl(p, i, 64);
+#pragma unroll
+            for (int s2 = 0; s2 < 2; ++s2)
+                if (lane + 64 * s2 < dh) acc[s2] += pi * ld_f<T>(V + (size_t)(t0 + i) * da + o + lane + 64 * s2);
+        }
+    }
+    sum = wave_sum(sum);
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+        if (lane + 64 * s < dh) st_f<T>(out + lane + 64 * s, L > 0 ? acc[s] / sum : 0.f);
+}
+
+// FT: tiles of 16 features a head has.  wqp: W_q as pieces, [head][FT'][k-step of 32][piece][64 lanes][8], FT' = FT
+// rounded up to even, rows past the head's width zero (pack_pieces).  table null: the item rows are in the workspace.
+template <typename T, int FT, int NC, int WV, bool WQ>
+__global__ __launch_bounds__(64 * WV) void k_attn_gen(Model m, Batch b, T *__restrict__ X, const T *__restrict__ table,
+                                                      const bf16x8 *__restrict__ wqp, const float *__restrict__ wq,
+                                                      int32_t *__restrict__ bad)
+{
+    constexpr int P = stored<T>::P, PQ = WQ ? 3 : P, KS = (FT + 1) / 2, VEC = 16 / sizeof(T);
+    constexpr int ITEMS = (2 * KS + FT) * 64;                  // 16-byte fragment pieces (of P) per chunk of keys
+    constexpr int PER = (ITEMS + 64 * WV - 1) / (64 * WV);
+    __shared__ bf16x8 frag[ITEMS * P];                          // [fragment][piece][lane]: K (key tile, k-step), then V (feature tile)
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, col = lane & 15, g = lane >> 4;
+    const int row0 = blockIdx.x * (16 * NC * WV);
+    const int r = b.blk_req[row0 / ROW_BLOCK];
+    if (r < 0) return;
+    const ReqDesc rd = b.reqs[r];
+    const int local0 = row0 - rd.row_base;
+    if (local0 >= rd.n_cand) return;
+    const int L = rd.seq_len, dh = m.d_head, da = m.d_attn;
+    const bool quad = (dh & 3) == 0;
+    const float scale = 1.0f / sqrtf((float)dh);
+    const T *K = (const T *)rd.seq_keys, *V = (const T *)rd.seq_vals;
+
+    // a1: the lane's candidates and their item rows
+    const T *er[NC];
+    T *xr[NC];
+    bool live[NC];
+    int n_bad = 0;
+#pragma unroll
+    for (int n = 0; n < NC; ++n) {
+        const int at = local0 + (wave * NC + n) * 16 + col;
+        live[n] = at < rd.n_cand;
+        const int c = live[n] ? at : rd.n_cand - 1;
+        xr[n] = X + (size_t)(rd.row_base + c) * m.ldx;
+        if (table) {
+            int64_t id = rd.cand_ids[c];
+            if (id < 0 || id >= m.n_items) {
+                id = 0;
+                if (live[n] && g == 0) ++n_bad;
+            }
+            er[n] = table + (size_t)id * m.d_item;
+        } else
+            er[n] = xr[n];
+    }
+    // the row into the workspace, and the Hadamard block beside it
+    {
+        const T *uc = (const T *)rd.cross_vecs;
+        const bool had = m.cross_mode == 1 && !m.cross_in_mlp;
+        constexpr int U = 4;
+        const int pieces = m.d_item / VEC;
+        if (table || had)
+            for (int p0 = 0; p0 < pieces; p0 += 4 * U) {
+                uint4 v[U][NC];
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+#pragma unroll
+                    for (int n = 0; n < NC; ++n) {
+                        const int p = p0 + 4 * u + g;
+                        v[u][n] = *(const uint4 *)(er[n] + (size_t)(p < pieces ? p : 0) * VEC);
+                    }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int p = p0 + 4 * u + g;
+                    if (p >= pieces) continue;
+#pragma unroll
+                    for (int n = 0; n < NC; ++n)
+                        if (live[n]) {
+                            if (table) *(uint4 *)(xr[n] + (size_t)p * VEC) = v[u][n];
+                            if (had) {
+                                const T *e = (const T *)&v[u][n];
+                                T *c = xr[n] + m.d_item + da + p * VEC;
+#pragma unroll
+                                for (int k = 0; k < VEC; ++k) st_f<T>(c + k, ld_f<T>(uc + p * VEC + k) * ld_f<T>(e + k));
+                            }
+                        }
+                }
+            }
+    }
+    if (n_bad) atomicAdd(bad, n_bad);
+    if (!m.cross_in_mlp && (m.cross_mode == 2 || m.cross_mode == 3)) {
+        const T *uc = (const T *)rd.cross_vecs;
+        const int S = m.cross_mode == 2 ? m.d_item / m.d_cv : 1;
+#pragma unroll
+        for (int n = 0; n < NC; ++n) {
+            T *xc = xr[n] + m.d_item + da;
+            if (live[n])
+                for (int idx = g; idx < m.d_cross; idx += 4) {
+                    float acc;
+                    if (m.cross_mode == 2) {
+                        const int j = idx / S, sg = idx - j * S;
+                        acc = dot_in_order(m.d_cv, 0.f, [&](int k) { return ld_f<T>(uc + (size_t)j * m.d_cv + k); },
+                                           [&](int k) { return ld_f<T>(er[n] + sg * m.d_cv + k); });
+                    } else      // Algorithm 1 step 4: the row's trailing n_cross entries weigh the user-side vectors
+                        acc = dot_in_order(m.n_cross, 0.f, [&](int j) { return ld_f<T>(er[n] + m.d_item - m.n_cross + j); },
+                                           [&](int j) { return ld_f<T>(uc + (size_t)j * m.d_cv + idx); });
+                    st_f<T>(xc + idx, acc);
+                }
+        }
+    }
+
+    for (int h = 0; h < m.n_heads; ++h) {
+        const int o = h * dh;
+        // the first keys on their way
+        float kv[PER][8];
+        auto fetch = [&](int t0) {
+#pragma unroll
+            for (int it = 0; it < PER; ++it) {
+                const int f = (threadIdx.x >> 6) + WV * it;      // fragment, the same for a whole wave
+                if (f < 2 * KS) {
+                    const int kt = f / KS, s = f - kt * KS, t = t0 + 16 * kt + col;
+                    const T *kr = K + (size_t)(t < L ? t : L - 1) * da + o;
+                    load4<T>(kr, 32 * s + 4 * g, dh, quad, kv[it]);
+                    load4<T>(kr, 32 * s + 16 + 4 * g, dh, quad, kv[it] + 4);
+                } else if (f < 2 * KS + FT) {
+                    const int k = 16 * (f - 2 * KS) + col;
+                    const T *vr = V + o + (k < dh ? k : 0);
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) {
+                        const int t = t0 + 4 * g + (j & 3) + 16 * (j >> 2);
+                        kv[it][j] = ld_f<T>(vr + (size_t)(t < L ? t : L - 1) * da);
+                    }
+                }
+            }
+        };
+        auto put = [&](int t0) {
+#pragma unroll
+            for (int it = 0; it < PER; ++it) {
+                const int f = (threadIdx.x >> 6) + WV * it;
+                if (f >= 2 * KS + FT) continue;
+                if (f < 2 * KS) {
+                    const int t = t0 + 16 * (f / KS) + col;
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) kv[it][j] = t < L ? kv[it][j] : 0.f;
+                } else {
+                    const bool on = 16 * (f - 2 * KS) + col < dh;
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) kv[it][j] = on && t0 + 4 * g + (j & 3) + 16 * (j >> 2) < L ? kv[it][j] : 0.f;
+                }
+                const Pieces<P> pc = split8<P>(kv[it]);
+#pragma unroll
+                for (int q = 0; q < P; ++q) frag[(f * P + q) * 64 + lane] = pc.p[q];
+            }
+        };
+        if (L > 0) fetch(0);
+
+        // a3: the query, as pieces in the order of K's fragments
+        Pieces<PQ> qf[KS][NC];
+        if constexpr (WQ) {
+            f32x4 qb[2 * KS][NC], qs[2 * KS][NC];
+#pragma unroll
+            for (int f = 0; f < 2 * KS; ++f)
+#pragma unroll
+                for (int n = 0; n < NC; ++n) qb[f][n] = qs[f][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+            const int ksn = (m.d_item + 31) / 32;
+            const bf16x8 *wh = wqp + (size_t)h * (2 * KS) * ksn * P * 64 + lane;
+            for (int ks = 0; ks < ksn; ++ks) {
+                Pieces<P> e[NC];
+#pragma unroll
+                for (int n = 0; n < NC; ++n) {
+                    float v[8];
+                    load8<T>(er[n] + 32 * ks + 8 * g, m.d_item - 32 * ks - 8 * g, v);
+                    e[n] = split8<P>(v);
+                }
+#pragma unroll
+                for (int f = 0; f < 2 * KS; ++f) {
+                    Pieces<P> w;
+#pragma unroll
+                    for (int q = 0; q < P; ++q) w.p[q] = wh[((size_t)(f * ksn + ks) * P + q) * 64];
+#pragma unroll
+                    for (int n = 0; n < NC; ++n) mfma_pieces(w, e[n], qb[f][n], qs[f][n]);
+                }
+            }
+#pragma unroll
+            for (int s = 0; s < KS; ++s)
+#pragma unroll
+                for (int n = 0; n < NC; ++n) {
+                    float v[8];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        v[j] = qb[2 * s][n][j] + qs[2 * s][n][j];
+                        v[4 + j] = qb[2 * s + 1][n][j] + qs[2 * s + 1][n][j];
+                    }
+                    qf[s][n] = split8<PQ>(v);
+                }
+        } else {
+#pragma unroll
+            for (int s = 0; s < KS; ++s)
+#pragma unroll
+                for (int n = 0; n < NC; ++n) {
+                    float v[8];
+                    load4<T>(er[n] + o, 32 * s + 4 * g, dh, quad, v);
+                    load4<T>(er[n] + o, 32 * s + 16 + 4 * g, dh, quad, v + 4);
+                    qf[s][n] = split8<PQ>(v);
+                }
+        }
+
+        // a4: the keys, 32 at a time
+        f32x4 ob[FT][NC], os[FT][NC];
+        float mx[NC], sum[NC];
+#pragma unroll
+        for (int n = 0; n < NC; ++n) {
+            mx[n] = -INFINITY;
+            sum[n] = 0.f;
+#pragma unroll
+            for (int f = 0; f < FT; ++f) ob[f][n] = os[f][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+        for (int t0 = 0; t0 < L; t0 += GEN_KEYS) {
+            __syncthreads();                                    // the chunk before has been read
+            put(t0);
+            __syncthreads();
+            if (t0 + GEN_KEYS < L) fetch(t0 + GEN_KEYS);
+            float sc[NC][8];
+#pragma unroll
+            for (int kt = 0; kt < 2; ++kt) {
+                f32x4 sb[NC], ss[NC];
+#pragma unroll
+                for (int n = 0; n < NC; ++n) sb[n] = ss[n] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int s = 0; s < KS; ++s) {
+                    Pieces<P> k;
+#pragma unroll
+                    for (int q = 0; q < P; ++q) k.p[q] = frag[((kt * KS + s) * P + q) * 64 + lane];
+#pragma unroll
+                    for (int n = 0; n < NC; ++n) mfma_pieces(k, qf[s][n], sb[n], ss[n]);
+                }
+#pragma unroll
+                for (int n = 0; n < NC; ++n)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        sc[n][4 * kt + i] = t0 + 16 * kt + 4 * g + i < L ? (sb[n][i] + ss[n][i]) * scale : -INFINITY;
+            }
+            Pieces<3> pf[NC];
+#pragma unroll
+            for (int n = 0; n < NC; ++n) {
+                float top = fmaxf(fmaxf(fmaxf(sc[n][0], sc[n][1]), fmaxf(sc[n][2], sc[n][3])),
+                                  fmaxf(fmaxf(sc[n][4], sc[n][5]), fmaxf(sc[n][6], sc[n][7])));
+                top = fmaxf(top, __shfl_xor(top, 16, 64));
+                top = fmaxf(top, __shfl_xor(top, 32, 64));
+                if (__any(top > mx[n])) {
+                    const float now = fmaxf(mx[n], top), ref = now == -INFINITY ? 0.f : now, f = expf(mx[n] - ref);
+                    mx[n] = now;
+                    sum[n] *= f;
+#pragma unroll
+                    for (int k = 0; k < FT; ++k)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            ob[k][n][i] *= f;
+                            os[k][n][i] *= f;
+                        }
+                }
+                const float ref = mx[n] == -INFINITY ? 0.f : mx[n];
+                float p[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    p[j] = expf(sc[n][j] - ref);
+                    sum[n] += p[j];
+                }
+                pf[n] = split8<3>(p);
+            }
+#pragma unroll
+            for (int f = 0; f < FT; ++f) {
+                Pieces<P> v;
+#pragma unroll
+                for (int q = 0; q < P; ++q) v.p[q] = frag[((2 * KS + f) * P + q) * 64 + lane];
+#pragma unroll
+                for (int n = 0; n < NC; ++n) mfma_pieces(v, pf[n], ob[f][n], os[f][n]);
+            }
+        }
+        // the block's result; `odd` is NaN if a lane met a value that is not finite
+#pragma unroll
+        for (int n = 0; n < NC; ++n) {
+            sum[n] += __shfl_xor(sum[n], 16, 64);
+            sum[n] += __shfl_xor(sum[n], 32, 64);
+            float odd = sum[n] * 0.f;
+#pragma unroll
+            for (int f = 0; f < FT; ++f) {
+                float v[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    v[i] = ob[f][n][i] + os[f][n][i];
+                    odd = fmaf(v[i], 0.f, odd);
+                    v[i] = L > 0 ? v[i] / sum[n] : 0.f;
+                }
+                const int k = 16 * f + 4 * g;
+                T *out = xr[n] + m.d_item + o + k;
+                if (live[n] && k < dh) {
+                    if (!quad) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            if (k + i < dh) st_f<T>(out + i, v[i]);
+                    } else if constexpr (sizeof(T) == 4)
+                        *(float4 *)out = make_float4(v[0], v[1], v[2], v[3]);
+                    else
+                        *(uint2 *)out = make_uint2(f2bf(v[0]) | ((uint32_t)f2bf(v[1]) << 16), f2bf(v[2]) | ((uint32_t)f2bf(v[3]) << 16));
+                }
+            }
+            unsigned long long again = __ballot(live[n] && odd != odd);
+            again = (again | again >> 16 | again >> 32 | again >> 48) & 0xFFFFull;       // per candidate
+            while (again) {
+                const int c = __ffsll((unsigned long long)again) - 1;
+                again &= again - 1;
+                const uint64_t ep = __shfl((unsigned long long)(uintptr_t)er[n], c, 64), xp = __shfl((unsigned long long)(uintptr_t)xr[n], c, 64);
+                attn_plain<T>((const T *)ep, K, V, WQ ? wq : nullptr, m.d_item, da, dh, o, L, scale, (T *)xp + m.d_item + o);
+            }
+        }
+    }
+}
+
 size_t attn_generic_lds_bytes(const Model &m, int max_seq_len)
 {
     return (size_t)4 * (m.d_item + m.d_attn + max_seq_len) * sizeof(float);
 }
 
-hipError_t launch_attn_generic(const Model &m, const Batch &b, void *X, const float *wq, int max_seq_len,
-                               hipStream_t s)
+bool attn_generic_gathers(const Model &m) { return m.d_head <= GEN_MAX_HEAD; }
+
+template <typename T, int FT, int NC, int WV>
+static void attn_gen_go(const Model &m, const Batch &b, void *X, const void *table, const void *wqp, const float *wq, int32_t *bad,
+                        hipStream_t s)
+{
+    const dim3 grid(b.n_blk * (ROW_BLOCK / (16 * NC * WV)));
+    if (wq)
+        hipLaunchKernelGGL((k_attn_gen<T, FT, NC, WV, true>), grid, dim3(64 * WV), 0, s, m, b, (T *)X, (const T *)table, (const bf16x8 *)wqp, wq, bad);
+    else
+        hipLaunchKernelGGL((k_attn_gen<T, FT, NC, WV, false>), grid, dim3(64 * WV), 0, s, m, b, (T *)X, (const T *)table, nullptr, nullptr, bad);
+}
+
+// Blocks of four waves with 32 candidates each share the splitting of the keys; a batch too small to give every compute
+// unit such a block takes one-wave blocks of 16 candidates (C1's single request: 63 blocks instead of eight).
+constexpr int GEN_SMALL = 256;
+template <typename T>
+static hipError_t attn_gen_launch(const Model &m, const Batch &b, void *X, const void *table, const void *wqp, const float *wq,
+                                  int32_t *bad, hipStream_t s)
+{
+    const bool small = b.n_blk * (ROW_BLOCK / 128) < GEN_SMALL;
+#define AIF_GO(FT)                                                                                                     \
+    do {                                                                                                               \
+        if (small) attn_gen_go<T, FT, 1, FT <= 2 ? 1 : 4>(m, b, X, table, wqp, wq, bad, s);                            \
+        else attn_gen_go<T, FT, 2, 4>(m, b, X, table, wqp, wq, bad, s);                                                \
+    } while (0)
+    if (m.d_head <= 16) AIF_GO(1);
+    else if (m.d_head <= 32) AIF_GO(2);
+    else if (m.d_head <= 64) AIF_GO(4);
+    else AIF_GO(8);
+#undef AIF_GO
+    return hipGetLastError();
+}
+
+hipError_t launch_attn_generic(const Model &m, const Batch &b, void *X, const float *wq, const void *wq_pieces, const void *table,
+                               int32_t *bad, int max_seq_len, hipStream_t s)
 {
     if (b.n_blk == 0) return hipSuccess;
+    if (m.d_head <= GEN_MAX_HEAD)
+        return m.dtype == 0 ? attn_gen_launch<float>(m, b, X, table, wq_pieces, wq, bad, s)
+                            : attn_gen_launch<uint16_t>(m, b, X, table, wq_pieces, wq, bad, s);
+    if (table) return hipErrorInvalidValue;                 // this kernel finds the item rows in the workspace
     const int per_wave = m.d_item + m.d_attn + max_seq_len;
     const size_t lds = attn_generic_lds_bytes(m, max_seq_len);
     dim3 grid(b.n_blk * (ROW_BLOCK / ATTN_TS));
@@ -200,84 +713,65 @@ hipError_t launch_attn_generic(const Model &m, const Batch &b, void *X, const fl
 }
 
 // ---------------------------------------------------------------------------
-// a6-a7 -- MLP head (Sec. 1: a small MLP) over the
-// virtual input [u | e | a | c]: the u block arrives as bias1 (user fold), the
-// rest is the workspace row.  MLP_TS candidates per block; activations live
-// in two LDS buffers laid out [feature][candidate]; thread n owns output
-// feature n for all MLP_TS candidates and walks the transposed weights.
+// a6-a7 -- MLP head (Sec. 1: a small MLP) over the virtual input
+// [u | e | a | c]: the u block arrives as bias1 (user fold), the rest is the
+// workspace row.  H^T = W X^T: a block holds 16 NC candidates (columns), its
+// eight waves share out the row tiles; the activations of the layer that is
+// read and of the one that is written lie in LDS in B-fragment order, and
+// weights come as ready-made pieces from the L2s, two k-steps ahead.
+// SPLIT: the activations lie there as their bf16 pieces (written once, read by
+// every wave), 96 bytes a feature and 16 candidates; without it as fp32, split
+// by each wave that reads them, 64 bytes: for layers so wide that only this
+// fits a compute unit's LDS.
+// What bounds it: the weights' way from the L2s (every block streams them all:
+// 6 bytes a weight in fp32) and the LDS reads of the activations.  Measured (160
+// -> 128 -> 64 -> 1, fp32): 10^5 candidates 78 us, where a thread per feature and
+// 16 candidates on the vector ALU took 210; 1,000 candidates 6.6 against 30;
+// bf16, 160,000 candidates 74 against 301.
 // ---------------------------------------------------------------------------
-constexpr int MLP_TS = 16;
+constexpr int MLP_WAVES = 8;
+constexpr int MLP_TS = 16;              // candidates of a column tile
 
-template <typename T>
-__global__ __launch_bounds__(256) void k_mlp_generic(Model m, Batch b, const T *__restrict__ X,
-                                                     MlpGenericWeights w, const float *__restrict__ bias1,
-                                                     int buf_floats)
+// widest activation of the plain route, per candidate
+__host__ __device__ inline int mlp_plain_widest(const Model &m)
 {
-    extern __shared__ __align__(16) float smem[];
-    float *bufA = smem, *bufB = smem + buf_floats;
-    const int tile = blockIdx.x;
-    const int r = b.blk_req[tile / (ROW_BLOCK / MLP_TS)];
-    if (r < 0) return;
-    const ReqDesc rd = b.reqs[r];
-    const int us = rd.slot;                 // the folded layer-1 bias is kept per user slot
-    const int row0 = tile * MLP_TS;
-    const int local0 = row0 - rd.row_base;
-    int nrows = rd.n_cand - local0;
-    if (nrows <= 0) return;
-    if (nrows > MLP_TS) nrows = MLP_TS;
+    int widest = m.k1;
+    for (int l = 1; l <= m.n_layers; ++l) widest = m.dims[l] > widest ? m.dims[l] : widest;
+    return widest;
+}
 
+struct GenMlp {
+    MlpGenericWeights w;
+    int32_t off1;                       // bytes: where the second activation buffer starts
+};
+
+// MLP_TS candidates in plain fp32 arithmetic (see attn_plain), the results of those in `mask` stored: activations in LDS
+// as [feature][MLP_TS].
+template <typename T>
+__device__ __forceinline__ void mlp_plain(const Model &m, const T *X, const MlpGenericWeights &w, const float *bias1, int us, int row0,
+                                       int nrows, uint32_t mask, float *bufA, float *bufB, const ReqDesc &rd, int local0)
+{
     const int k1 = m.k1;
-    for (int idx = threadIdx.x; idx < k1 * MLP_TS; idx += 256) {
+    for (int idx = threadIdx.x; idx < k1 * MLP_TS; idx += 64 * MLP_WAVES) {
         const int c = idx / k1, k = idx - c * k1;
         bufA[k * MLP_TS + c] = c < nrows ? ld_f<T>(X + (size_t)(row0 + c) * m.ldx + k) : 0.f;
     }
     __syncthreads();
-
     for (int l = 0; l < m.n_layers; ++l) {
-        const int K = l == 0 ? k1 : m.dims[l];
-        const int N = m.dims[l + 1];
+        const int K = l == 0 ? k1 : m.dims[l], N = m.dims[l + 1];
         const float *wt = w.wt[l];
-        const bool last = l + 1 == m.n_layers;
-        for (int n = threadIdx.x; n < N; n += 256) {
-            float acc[MLP_TS];
-            const float b0 = l == 0 ? bias1[(size_t)us * N + n] : (w.bias[l] ? w.bias[l][n] : 0.f);
-#pragma unroll
-            for (int c = 0; c < MLP_TS; ++c) acc[c] = b0;
-            auto term = [&](int k, float wv) {
-                const float4 *xp = (const float4 *)(bufA + k * MLP_TS);
-#pragma unroll
-                for (int c4 = 0; c4 < MLP_TS / 4; ++c4) {
-                    const float4 x = xp[c4];
-                    acc[c4 * 4 + 0] += wv * x.x;
-                    acc[c4 * 4 + 1] += wv * x.y;
-                    acc[c4 * 4 + 2] += wv * x.z;
-                    acc[c4 * 4 + 3] += wv * x.w;
-                }
-            };
-            // sixteen weights in flight (terms still added in order of k): one at a time is a memory round trip per k
-            int k = 0;
-            for (; k + 16 <= K; k += 16) {
-                float wv[16];
-#pragma unroll
-                for (int j = 0; j < 16; ++j) wv[j] = wt[(size_t)(k + j) * N + n];
-#pragma unroll
-                for (int j = 0; j < 16; ++j) term(k + j, wv[j]);
-            }
-            for (; k + 4 <= K; k += 4) {
-                float wv[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) wv[j] = wt[(size_t)(k + j) * N + n];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) term(k + j, wv[j]);
-            }
-            for (; k < K; ++k) term(k, wt[(size_t)k * N + n]);
-#pragma unroll
-            for (int c = 0; c < MLP_TS; ++c) bufB[n * MLP_TS + c] = last ? acc[c] : fmaxf(acc[c], 0.f);
+        for (int i = threadIdx.x; i < N * MLP_TS; i += 64 * MLP_WAVES) {
+            const int n = i / MLP_TS, c = i - n * MLP_TS;
+            float acc = l == 0 ? bias1[(size_t)us * N + n] : (w.bias[l] ? w.bias[l][n] : 0.f);
+            for (int k = 0; k < K; ++k) acc += wt[(size_t)k * N + n] * bufA[k * MLP_TS + c];
+            bufB[i] = l + 1 == m.n_layers ? acc : fmaxf(acc, 0.f);
         }
         __syncthreads();
-        float *t = bufA; bufA = bufB; bufB = t;
+        float *t = bufA;
+        bufA = bufB;
+        bufB = t;
     }
-    if (threadIdx.x < nrows) {
+    if ((int)threadIdx.x < nrows && (mask >> threadIdx.x & 1u)) {
         const int c = threadIdx.x;
         float z = bufA[c];
         const int64_t id = rd.cand_ids[local0 + c];
@@ -285,30 +779,288 @@ __global__ __launch_bounds__(256) void k_mlp_generic(Model m, Batch b, const T *
         rd.logits_out[local0 + c] = z;
         if (rd.scores_out) rd.scores_out[local0 + c] = 1.0f / (1.0f + expf(-z));
     }
+    __syncthreads();
 }
 
-static int mlp_generic_buf_floats(const Model &m)
+// one row tile's (RT = 1) or two row tiles' results for NW column tiles: W rows x activations over ksn k-steps
+template <int PW, int PX, int RT, int NW, int NC, bool SPLIT>
+__device__ __forceinline__ void mlp_rows(const bf16x8 *__restrict__ wp, int ksn, const char *act, int ct0, int lane,
+                                         Pieces<PW> (&w)[2][RT], f32x4 (&big)[RT][NW], f32x4 (&small)[RT][NW])
 {
-    int widest = m.k1;
-    for (int l = 1; l <= m.n_layers; ++l) widest = m.dims[l] > widest ? m.dims[l] : widest;
-    return widest * MLP_TS;
+    auto step = [&](int ks, const Pieces<PW> (&a)[RT]) {
+#pragma unroll
+        for (int n = 0; n < NW; ++n) {
+            Pieces<PX> x;
+            if constexpr (SPLIT) {
+                const bf16x8 *f = (const bf16x8 *)act + (size_t)(ks * PX * NC + ct0 + n) * 64 + lane;
+#pragma unroll
+                for (int q = 0; q < PX; ++q) x.p[q] = f[q * NC * 64];
+            } else {
+                const float4 *f = (const float4 *)act + (size_t)(ks * NC + ct0 + n) * 128 + lane;
+                const float4 a0 = f[0], a1 = f[64];
+                const float v[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
+                x = split8<PX>(v);
+            }
+#pragma unroll
+            for (int i = 0; i < RT; ++i) mfma_pieces(a[i], x, big[i][n], small[i][n]);
+        }
+    };
+    auto load = [&](int ks, Pieces<PW> (&a)[RT]) {
+        ks = ks < ksn ? ks : ksn - 1;
+#pragma unroll
+        for (int i = 0; i < RT; ++i)
+#pragma unroll
+            for (int q = 0; q < PW; ++q) a[i].p[q] = wp[((size_t)(i * ksn + ks) * PW + q) * 64 + lane];
+    };
+    // w holds k-steps 0 and 1; two more are asked for before each pair is used
+    for (int ks = 0; ks < ksn; ks += 4) {
+        Pieces<PW> w2[2][RT];
+        load(ks + 2, w2[0]);
+        load(ks + 3, w2[1]);
+        step(ks, w[0]);
+        if (ks + 1 < ksn) step(ks + 1, w[1]);
+        if (ks + 2 < ksn) {
+            load(ks + 4, w[0]);
+            load(ks + 5, w[1]);
+            step(ks + 2, w2[0]);
+            if (ks + 3 < ksn) step(ks + 3, w2[1]);
+        }
+    }
 }
-size_t mlp_generic_lds_bytes(const Model &m) { return (size_t)2 * mlp_generic_buf_floats(m) * sizeof(float); }
+
+template <typename T, int NC, bool SPLIT>
+__global__ __launch_bounds__(64 * MLP_WAVES) void k_mlp_gen(Model m, Batch b, const T *__restrict__ X, GenMlp gm,
+                                                            const float *__restrict__ bias1)
+{
+    extern __shared__ __align__(16) char act[];
+    constexpr int P = stored<T>::P, CG = NC >= 2 ? 2 : 1, RG = MLP_WAVES / CG, NW = NC / CG;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, col = lane & 15, g = lane >> 4;
+    const int cg = wave % CG, rg = wave / CG, ct0 = cg * NW;
+    const int row0 = blockIdx.x * (16 * NC);
+    const int r = b.blk_req[row0 / ROW_BLOCK];
+    if (r < 0) return;
+    const ReqDesc rd = b.reqs[r];
+    const int local0 = row0 - rd.row_base, nrows = min(rd.n_cand - local0, 16 * NC);
+    if (nrows <= 0) return;
+    const MlpGenericWeights &w = gm.w;
+
+    // layer 1's input: the workspace rows as fragments (rows past the request's end zero)
+    {
+        const int ksn = (m.k1 + 31) / 32;
+        for (int i = wave; i < ksn * NC; i += MLP_WAVES) {
+            const int ks = i / NC, ct = i - ks * NC, c = ct * 16 + col;
+            float v[8];
+            load8<T>(X + (size_t)(row0 + (c < nrows ? c : 0)) * m.ldx + 32 * ks + 8 * g, c < nrows ? m.k1 - 32 * ks - 8 * g : 0, v);
+            if constexpr (SPLIT) {
+                const Pieces<P> p = split8<P>(v);
+#pragma unroll
+                for (int q = 0; q < P; ++q) ((bf16x8 *)act)[((size_t)(ks * P + q) * NC + ct) * 64 + lane] = p.p[q];
+            } else {
+                float4 *f = (float4 *)act + (size_t)(ks * NC + ct) * 128 + lane;
+                f[0] = make_float4(v[0], v[1], v[2], v[3]);
+                f[64] = make_float4(v[4], v[5], v[6], v[7]);
+            }
+        }
+    }
+    float odd[NW];                      // per candidate of the lane: NaN once a value that is not finite has come up
+#pragma unroll
+    for (int n = 0; n < NW; ++n) odd[n] = 0.f;
+    char *in = act, *out = act + gm.off1;
+    for (int l = 0; l < m.n_layers; ++l) {
+        const int K = l == 0 ? m.k1 : m.dims[l], N = m.dims[l + 1], ksn = (K + 31) / 32;
+        const bool last = l + 1 == m.n_layers;
+        const int nrt = last ? 1 : (N + 31) / 32 * 2;           // row tiles: the next layer reads whole k-steps
+        const bf16x8 *wl = (const bf16x8 *)w.pieces[l];
+        const float *bl = l == 0 ? bias1 + (size_t)rd.slot * N : w.bias[l];
+        auto rows = [&](auto rt_c, auto px_c, int rt, bool first) __attribute__((always_inline)) {
+            constexpr int RT = decltype(rt_c)::value, PX = decltype(px_c)::value;
+            const bf16x8 *wp = wl + (size_t)rt * ksn * P * 64;
+            Pieces<P> a[2][RT];
+            f32x4 big[RT][NW], small[RT][NW];
+            const bool on = rt < nrt;
+            if (on) {
+#pragma unroll
+                for (int s = 0; s < 2; ++s)
+#pragma unroll
+                    for (int i = 0; i < RT; ++i)
+#pragma unroll
+                        for (int q = 0; q < P; ++q) a[s][i].p[q] = wp[((size_t)(i * ksn + min(s, ksn - 1)) * P + q) * 64 + lane];
+#pragma unroll
+                for (int i = 0; i < RT; ++i)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const int f = 16 * (rt + i) + 4 * g + j;
+                        const float b0 = bl && f < N ? bl[f] : 0.f;
+#pragma unroll
+                        for (int n = 0; n < NW; ++n) {
+                            big[i][n][j] = b0;
+                            small[i][n][j] = 0.f;
+                        }
+                    }
+            }
+            if (first) __syncthreads();                         // the weights are on their way while the layer's input settles
+            if (!on) return;
+            mlp_rows<P, PX, RT, NW, NC, SPLIT>(wp, ksn, in, ct0, lane, a, big, small);
+#pragma unroll
+            for (int i = 0; i < RT; ++i)
+#pragma unroll
+                for (int n = 0; n < NW; ++n) {
+                    float v[4];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        v[j] = big[i][n][j] + small[i][n][j];
+                        odd[n] = fmaf(v[j], 0.f, odd[n]);
+                    }
+                    const int f = 16 * (rt + i) + 4 * g, ct = ct0 + n;
+                    if (last) {
+                        const int c = ct * 16 + col;
+                        if (g == 0 && c < nrows) {
+                            float z = v[0];
+                            const int64_t id = rd.cand_ids[local0 + c];
+                            if (id < 0 || id >= m.n_items) z = __uint_as_float(0x7FC00000u);
+                            rd.logits_out[local0 + c] = z;
+                            if (rd.scores_out) rd.scores_out[local0 + c] = 1.0f / (1.0f + expf(-z));
+                        }
+                    } else {
+                        const int ks = f >> 5, dst = ((f & 31) >> 3) * 16 + col, half = (f >> 2) & 1;
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) v[j] = fmaxf(v[j], 0.f);
+                        if constexpr (SPLIT) {
+                            float rest[4] = {v[0], v[1], v[2], v[3]};
+#pragma unroll
+                            for (int q = 0; q < 3; ++q) {
+                                bf16x4 p;
+#pragma unroll
+                                for (int j = 0; j < 4; ++j) {
+                                    p[j] = (__bf16)rest[j];
+                                    rest[j] -= (float)p[j];
+                                }
+                                *(bf16x4 *)(out + (((size_t)(ks * 3 + q) * NC + ct) * 64 + dst) * 16 + half * 8) = p;
+                            }
+                        } else
+                            ((float4 *)out)[(size_t)(ks * NC + ct) * 128 + half * 64 + dst] = make_float4(v[0], v[1], v[2], v[3]);
+                    }
+                }
+        };
+        auto all = [&](auto px_c) __attribute__((always_inline)) {
+            if (nrt >= 2 * RG) {
+                rows(std::integral_constant<int, 2>{}, px_c, 2 * rg, true);
+                for (int rt = 2 * (rg + RG); rt < nrt; rt += 2 * RG) rows(std::integral_constant<int, 2>{}, px_c, rt, false);
+            } else {
+                rows(std::integral_constant<int, 1>{}, px_c, rg, true);
+                for (int rt = rg + RG; rt < nrt; rt += RG) rows(std::integral_constant<int, 1>{}, px_c, rt, false);
+            }
+        };
+        if (P == 1 && l == 0) all(std::integral_constant<int, 1>{});
+        else all(std::integral_constant<int, 3>{});
+        char *t = in;
+        in = out;
+        out = t;
+    }
+    // a candidate that met one is done again in plain arithmetic -- it alone, whatever shares its block
+    uint32_t *flag = (uint32_t *)act, again[NC];
+    __syncthreads();
+    if (threadIdx.x < NC) flag[threadIdx.x] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int n = 0; n < NW; ++n)
+        if (odd[n] != odd[n]) atomicOr(&flag[ct0 + n], 1u << col);
+    __syncthreads();
+#pragma unroll
+    for (int n = 0; n < NC; ++n) again[n] = flag[n];
+    __syncthreads();
+#pragma unroll
+    for (int n = 0; n < NC; ++n)
+        if (again[n] && n * MLP_TS < nrows)
+            mlp_plain<T>(m, X, w, bias1, rd.slot, row0 + n * MLP_TS, min(nrows - n * MLP_TS, MLP_TS), again[n], (float *)act,
+                         (float *)act + (size_t)mlp_plain_widest(m) * MLP_TS, rd, local0 + n * MLP_TS);
+}
+
+// Bytes of LDS a block of k_mlp_gen takes: two activation buffers (the first takes the inputs of layers 1, 3, ..), and at
+// least what the plain route needs.
+static size_t mlp_gen_lds(const Model &m, int nc, bool split, int32_t *off1)
+{
+    size_t need[2] = {0, 0};
+    for (int l = 0; l < m.n_layers; ++l) {
+        const size_t ks = ((l == 0 ? m.k1 : m.dims[l]) + 31) / 32;
+        const size_t bytes = ks * nc * (split ? 1024u * (l == 0 && m.dtype == 1 ? 1 : 3) : 2048u);
+        need[l & 1] = std::max(need[l & 1], bytes);
+    }
+    *off1 = (int32_t)need[0];
+    return std::max(need[0] + need[1], mlp_generic_lds_bytes(m));
+}
+
+size_t mlp_generic_lds_bytes(const Model &m) { return (size_t)2 * mlp_plain_widest(m) * MLP_TS * sizeof(float); }
+
+template <typename T, int NC, bool SPLIT>
+static hipError_t mlp_gen_go(const Model &m, const Batch &b, const void *X, GenMlp &gm, const float *bias1, hipStream_t s)
+{
+    const size_t lds = mlp_gen_lds(m, NC, SPLIT, &gm.off1);
+    (void)hipFuncSetAttribute((const void *)k_mlp_gen<T, NC, SPLIT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipLaunchKernelGGL((k_mlp_gen<T, NC, SPLIT>), dim3(b.n_blk * (ROW_BLOCK / (16 * NC))), dim3(64 * MLP_WAVES), lds, s, m, b, (const T *)X,
+                       gm, bias1);
+    return hipGetLastError();
+}
+
+// 64 candidates a block where the batch fills the chip with such blocks and they fit, else 16.
+template <typename T>
+static hipError_t mlp_gen_launch(const Model &m, const Batch &b, const void *X, const MlpGenericWeights &w, const float *bias1, hipStream_t s)
+{
+    constexpr size_t LDS = 160 * 1024;
+    GenMlp gm{w, 0};
+    int32_t off;
+    if (b.n_blk * (ROW_BLOCK / 64) >= GEN_SMALL && mlp_gen_lds(m, 4, true, &off) <= LDS) return mlp_gen_go<T, 4, true>(m, b, X, gm, bias1, s);
+    if (mlp_gen_lds(m, 1, true, &off) <= LDS) return mlp_gen_go<T, 1, true>(m, b, X, gm, bias1, s);
+    return mlp_gen_go<T, 1, false>(m, b, X, gm, bias1, s);
+}
 
 hipError_t launch_mlp_generic(const Model &m, const Batch &b, const void *X, const MlpGenericWeights &w,
                               const float *bias1, hipStream_t s)
 {
     if (b.n_blk == 0) return hipSuccess;
-    const int bf = mlp_generic_buf_floats(m);
-    const size_t lds = mlp_generic_lds_bytes(m);
-    dim3 grid(b.n_blk * (ROW_BLOCK / MLP_TS));
-    if (m.dtype == 0) {
-        (void)hipFuncSetAttribute((const void *)k_mlp_generic<float>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        hipLaunchKernelGGL(k_mlp_generic<float>, grid, dim3(256), lds, s, m, b, (const float *)X, w, bias1, bf);
-    } else {
-        (void)hipFuncSetAttribute((const void *)k_mlp_generic<uint16_t>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        hipLaunchKernelGGL(k_mlp_generic<uint16_t>, grid, dim3(256), lds, s, m, b, (const uint16_t *)X, w, bias1, bf);
+    return m.dtype == 0 ? mlp_gen_launch<float>(m, b, X, w, bias1, s) : mlp_gen_launch<uint16_t>(m, b, X, w, bias1, s);
+}
+
+// ---------------------------------------------------------------------------
+// Weights as pieces in A-fragment order: [group][row tile of 16][k-step of 32][piece][lane][8], lane (row = lane % 16,
+// g = lane / 16) holding W[group rows_per_group + 16 rt + row][32 ks + 8 g + j]; zero outside the matrix.
+// ---------------------------------------------------------------------------
+template <typename T>
+__global__ void k_pack_pieces(const T *__restrict__ w, int n_in, int col0, int rows, int ncols, int ksn, int rt_n, size_t total,
+                              bf16x8 *__restrict__ out)
+{
+    constexpr int P = stored<T>::P;
+    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= total) return;
+    const int lane = (int)(i & 63);
+    const size_t f = i >> 6;                                    // (group, row tile, k-step)
+    const int ks = (int)(f % ksn), rt = (int)(f / ksn % rt_n), group = (int)(f / ksn / rt_n);
+    const int row = 16 * rt + (lane & 15);
+    float v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const int k = 32 * ks + 8 * (lane >> 4) + j;
+        v[j] = row < rows && k < ncols ? ld_f<T>(w + ((size_t)group * rows + row) * n_in + col0 + k) : 0.f;
     }
+    const Pieces<P> p = split8<P>(v);
+#pragma unroll
+    for (int q = 0; q < P; ++q) out[(f * P + q) * 64 + lane] = p.p[q];
+}
+
+size_t pieces_bytes(int dtype, int groups, int rows, int ncols)
+{
+    return (size_t)groups * ((rows + 31) / 32 * 2) * ((ncols + 31) / 32) * (dtype == 0 ? 3 : 1) * 1024;
+}
+
+hipError_t launch_pack_pieces(int dtype, const void *w, int groups, int rows, int n_in, int col0, int ncols, void *out, hipStream_t s)
+{
+    const int ksn = (ncols + 31) / 32, rt_n = (rows + 31) / 32 * 2;
+    const size_t total = (size_t)groups * rt_n * ksn * 64;
+    const dim3 grid((unsigned)((total + 255) / 256));
+    if (dtype == 0)
+        hipLaunchKernelGGL(k_pack_pieces<float>, grid, dim3(256), 0, s, (const float *)w, n_in, col0, rows, ncols, ksn, rt_n, total, (bf16x8 *)out);
+    else
+        hipLaunchKernelGGL(k_pack_pieces<uint16_t>, grid, dim3(256), 0, s, (const uint16_t *)w, n_in, col0, rows, ncols, ksn, rt_n, total, (bf16x8 *)out);
     return hipGetLastError();
 }
 

@@ -1,0 +1,120 @@
+"""The shape-agnostic kernels of fp32 precision (bf16 pieces on the matrix cores) at the edges of their tiles, against the
+oracle, and the plain route they take where an input is not finite."""
+import numpy as np
+import pytest
+
+from paper_2511_12934_amd import workloads as wl
+
+from helpers import assert_features_close, assert_logits_close, key_rounding_term, oracle_scores
+from test_gpu_parity import R, _say, run_batch, small_cfg, torch  # noqa: F401  (fixtures)
+
+pytestmark = pytest.mark.gpu
+
+# head widths around the 16-feature tiles and 32-wide k-steps, item widths around a k-step, layer widths around the row
+# tiles, and heads too wide for the matrix-core form (132) or layers for split activations in LDS (1280 -> 900)
+SHAPES = {
+    "head_3": dict(d_item=12, d_user=12, d_attn=12, n_heads=4, mlp_dims=(48, 17, 1)),
+    "head_16": dict(d_item=16, d_user=16, d_attn=16, mlp_dims=(64, 16, 15, 1)),
+    "head_20_wq": dict(d_item=36, d_user=36, d_attn=40, n_heads=2, use_wq=True, mlp_dims=(148, 33, 1)),
+    "head_64": dict(d_item=64, d_user=64, d_attn=64, mlp_dims=(256, 129, 65, 1)),
+    "head_68_wq": dict(d_item=28, d_user=28, d_attn=68, use_wq=True, mlp_dims=(152, 1)),
+    "head_128_none": dict(d_item=128, d_user=4, d_attn=128, cross_mode=wl.CROSS_NONE, mlp_dims=(260, 40, 1)),
+    "head_132": dict(d_item=132, d_user=132, d_attn=132, mlp_dims=(528, 64, 1)),
+    "wide_layers": dict(mlp_dims=(56, 1280, 900, 1)),
+    "segdot": dict(d_item=48, d_user=12, d_attn=32, use_wq=True, cross_mode=wl.CROSS_SEGDOT, n_cross=8, d_cross_vec=24, mlp_dims=(108, 31, 1)),
+}
+SIZES = [(1, 65), (15, 1), (16, 0), (17, 31), (63, 32), (65, 33), (256, 64), (257, 63), (300, 65)]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape", list(SHAPES))
+def test_pieces_kernels_at_tile_edges(R, torch, monkeypatch, dtype, shape):  # noqa: F811
+    kw = dict(SHAPES[shape])
+    if dtype == "bf16":
+        if any(kw.get(k, 16) % 8 for k in ("d_item", "d_attn")):
+            pytest.skip("widths are multiples of eight in bf16")
+        monkeypatch.setenv("AIF_FORCE_GENERIC", "1")
+    cfg = small_cfg(dtype, seq_len=65, n_items=400, **kw)
+    _say(f"pieces {shape} {dtype}")
+    rng = np.random.default_rng(99)
+    model = wl.make_model(cfg, seed=5, bias_scale=0.3)
+    table = wl.make_table_host(cfg, rng, sigma=1.0)
+    users_ids = [(wl.make_user(cfg, rng, sigma=1.0, seq_len=L), rng.integers(0, cfg.n_items, n).astype(np.int32)) for n, L in SIZES]
+    zs, _, drs, ctx = run_batch(R, torch, cfg, model, R.to_device(table, dtype), users_ids, max_seq_len=65)
+    assert ctx.aif_stage_kind("attention") == 0 and ctx.aif_stage_kind("mlp") == 0
+    for r, ((u, ids), z) in enumerate(zip(users_ids, zs)):
+        ref = oracle_scores(cfg, model, table, u, ids)
+        X = R.peek_features(ctx, cfg, r, ids.size)
+        assert np.array_equal(X[:, :cfg.d_item], table[ids])
+        assert_features_close(dtype, X[:, cfg.d_item:cfg.d_item + cfg.d_attn], ref.attn, f"req {r} attention", key_rounding_term(cfg, model, table[ids], u))
+        if dtype == "f32":
+            assert_logits_close(dtype, z, ref.logits, f"req {r}")
+        else:
+            assert np.abs(z - ref.logits).max() <= 2e-2 * max(1.0, float(np.abs(ref.logits).max())), f"req {r}"
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_large_batches_give_the_bits_of_single_requests(R, torch, monkeypatch, dtype):  # noqa: F811
+    """140 requests take the kernels with 64 (MLP) and 128 (attention) candidates a block, one alone those with 16."""
+    if dtype == "bf16":
+        monkeypatch.setenv("AIF_FORCE_GENERIC", "1")
+    cfg = small_cfg(dtype, seq_len=40, n_items=3000, d_item=32, d_user=32, d_attn=32, use_wq=True, mlp_dims=(128, 70, 20, 1))
+    rng = np.random.default_rng(3)
+    model = wl.make_model(cfg, seed=5, bias_scale=0.3)
+    table = wl.make_table_host(cfg, rng, sigma=1.0)
+    users_ids = [(wl.make_user(cfg, rng, sigma=1.0, seq_len=int(rng.integers(0, 41))), rng.integers(0, 3000, int(rng.integers(1, 257))).astype(np.int32))
+                 for _ in range(140)]
+    zs, _, drs, ctx = run_batch(R, torch, cfg, model, R.to_device(table, dtype), users_ids, max_seq_len=40)
+    for r in (0, 1, 70, 139):
+        alone = R.upload_request(cfg, *users_ids[r])
+        ctx.aif_score_request(alone.req)
+        torch.cuda.synchronize()
+        assert np.array_equal(alone.logits.cpu().numpy(), zs[r]), r
+
+
+def plain_logits(cfg, model, rows, u):
+    """The path in numpy, in 64 bits, with the kernels' maxima: fmax(NaN, x) = x (ReLU turns a NaN into zero)."""
+    f = lambda a: np.asarray(a, np.float64)  # noqa: E731
+    e, K, V = f(rows), f(u.seq_keys), f(u.seq_vals)
+    s = e[:, :cfg.d_attn] @ K.T / np.sqrt(cfg.d_attn)
+    p = np.exp(s - np.fmax.reduce(s, axis=1, keepdims=True))
+    a = (p @ V) / p.sum(1, keepdims=True)
+    y = np.concatenate([np.broadcast_to(f(u.user_vec), e.shape), e, a, e * f(u.user_vec)], 1)
+    for i, (w, b) in enumerate(zip(model.weights, model.biases)):
+        y = (y[:, None, :] * f(w)).sum(2) + f(b)
+        y = y if i + 1 == len(model.weights) else np.fmax(y, 0)
+    return y[:, 0]
+
+
+@pytest.mark.parametrize("where", ["row", "key", "value", "weight"])
+def test_values_that_are_not_finite_propagate_as_in_plain_fp32(R, torch, where):  # noqa: F811
+    """An infinity is no sum of bf16 pieces: such candidates take plain fp32 arithmetic, and the others are untouched."""
+    cfg = small_cfg("f32", seq_len=40, n_items=300, d_item=32, d_user=32, d_attn=32, mlp_dims=(128, 40, 20, 1))
+    rng = np.random.default_rng(4)
+    model = wl.make_model(cfg, seed=5, bias_scale=0.3)
+    table = wl.make_table_host(cfg, rng, sigma=1.0)
+    u = wl.make_user(cfg, rng, sigma=1.0)
+    ids = np.arange(200, dtype=np.int32)
+    z0 = run_batch(R, torch, cfg, model, R.to_device(table, "f32"), [(u, ids)])[0][0]
+    odd = np.zeros(ids.size, bool)
+    if where == "row":
+        odd[[5, 18, 40]] = True
+        table[5, 3], table[18, 31], table[40, 0] = np.inf, -np.inf, np.nan
+    elif where == "key":
+        odd[:] = True
+        u.seq_keys[33, 5] = np.inf
+    elif where == "value":
+        odd[:] = True
+        u.seq_vals[2, 5] = -np.inf
+    else:
+        odd[:] = True
+        model.weights[1][7, 3] = np.inf
+    z = run_batch(R, torch, cfg, model, R.to_device(table, "f32"), [(u, ids)])[0][0]
+    with np.errstate(all="ignore"):
+        ref = plain_logits(cfg, model, table[ids], u)
+    assert np.array_equal(z[~odd], z0[~odd])
+    assert np.array_equal(np.isnan(z), np.isnan(ref)) and np.array_equal(np.isinf(z), np.isinf(ref))
+    assert np.array_equal(np.sign(z[np.isinf(z)]), np.sign(ref[np.isinf(z)]))
+    ok = np.isfinite(ref)
+    if ok.any():
+        assert_logits_close("f32", z[ok], ref[ok], where)
