@@ -25,7 +25,7 @@ thread_local std::string g_lsh_init_error = "";
 struct aif_lsh_ctx {
     LshModel m{};
     int device = 0;
-    int max_seq_len = 0, max_candidates = 0, max_users = 0, max_chunks = 0;
+    int max_seq_len = 0, max_candidates = 0, max_users = 0, max_chunks = 0, part_stride = 0;
     const uint8_t *table = nullptr;
     void *part = nullptr, *A = nullptr, *bad = nullptr;     // device workspace (owned)
     void *hist = nullptr;                                   // the requests' history signatures as matrix operands (or null: SimTier on the vector ALU)
@@ -117,8 +117,9 @@ aif_status linit(const aif_lsh_config *cfg, const uint8_t *table, aif_lsh_ctx *c
     c->max_users = cfg->max_users;
     c->max_chunks = std::min(LSH_MAX_CHUNKS, (cfg->max_seq_len + LSH_TCHUNK - 1) / LSH_TCHUNK);   // a shorter history never has more chunks than a longer one's cap
     LSH_TRY(nullptr, hipGetDevice(&c->device));
-    const size_t tab = (size_t)2 * m.d_bits * m.d_out * 4;
-    LSH_TRY(nullptr, hipMalloc(&c->part, tab * (size_t)c->max_users * (c->max_chunks > 0 ? c->max_chunks : 1)));
+    const size_t tab = (size_t)lsh_rows(m.d_bits) * m.d_out * 4;
+    c->part_stride = (c->max_chunks > 0 ? c->max_chunks : 1) * lsh_user_split(m.d_bits);
+    LSH_TRY(nullptr, hipMalloc(&c->part, tab * (size_t)c->max_users * c->part_stride));
     LSH_TRY(nullptr, hipMalloc(&c->A, tab * (size_t)c->max_users));
     {
         const char *valu = getenv("AIF_LSH_SIMTIER_VALU");      // testing and measurement: SimTier on the vector ALU whatever the shape
@@ -226,8 +227,11 @@ aif_status aif_lsh_batch(aif_lsh_ctx *c, const aif_lsh_request *reqs, int32_t n_
     hipEvent_t *pe = nullptr;
     if (c->prof_on && c->prof_calls < c->prof_max) pe = &c->prof[(size_t)LSH_EV_PER_CALL * c->prof_calls++];
     if (pe) LSH_TRY(c, hipEventRecord(pe[0], s));
-    LSH_TRY(c, launch_lsh_user_partial(m, b, max_chunks, c->max_chunks, (float *)c->part, s));
-    LSH_TRY(c, launch_lsh_user_reduce(m, b, c->max_chunks, (const float *)c->part, (float *)c->A, s));
+    LSH_TRY(c, launch_lsh_user_sums(m, b, max_chunks, c->part_stride, (float *)c->part, s));
+    if (c->din_pieces)
+        LSH_TRY(c, launch_lsh_din_pieces(m, b, c->part_stride, (const float *)c->part, (float *)c->A, c->din_pieces, s));
+    else
+        LSH_TRY(c, launch_lsh_user_reduce(m, b, c->part_stride, (const float *)c->part, (float *)c->A, s));
     if (pe) LSH_TRY(c, hipEventRecord(pe[1], s));
     if (c->din_pieces)
         LSH_TRY(c, launch_lsh_din_mfma(m, b, c->table, (const float *)c->A, c->din_pieces, (int32_t *)c->bad, s));

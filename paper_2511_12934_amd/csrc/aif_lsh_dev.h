@@ -6,16 +6,14 @@
 namespace aif {
 
 constexpr int LSH_BLOCK = 256;          // candidates per scheduling block
-constexpr int LSH_TCHUNK = 512;         // history items whose user-side sums one block forms (more for a long history)
+constexpr int LSH_TCHUNK = 1024;        // history items whose user-side sums one block forms (more for a long history)
 constexpr int LSH_MAX_CHUNKS = 64;      // chunks of one history at most
-// Chunk length of a history of L items: LSH_TCHUNK times the smallest whole factor that keeps the chunks within
-// LSH_MAX_CHUNKS -- every chunk's partial sums (2 d' d floats) are written to memory and read back, which a history of
-// 10^5 items would otherwise do 196 times.  A function of the request's own history only, like everything that
-// decides the order of its sums.
+// Chunk length of a history of L items, a multiple of 64: LSH_TCHUNK, or an even share of a history that would have more
+// than LSH_MAX_CHUNKS chunks -- every chunk's partial sums ((d' + 2) d floats) are written to memory and read back.  A
+// function of the request's own history only, like everything that decides the order of its sums.
 __host__ __device__ inline int lsh_chunk_len(int L)
 {
-    const int chunks = (L + LSH_TCHUNK - 1) / LSH_TCHUNK;
-    return LSH_TCHUNK * ((chunks + LSH_MAX_CHUNKS - 1) / LSH_MAX_CHUNKS > 1 ? (chunks + LSH_MAX_CHUNKS - 1) / LSH_MAX_CHUNKS : 1);
+    return L <= LSH_TCHUNK * LSH_MAX_CHUNKS ? LSH_TCHUNK : ((L - 1) / LSH_MAX_CHUNKS + 64) / 64 * 64;
 }
 __host__ __device__ inline int lsh_chunks(int L)
 {
@@ -23,6 +21,45 @@ __host__ __device__ inline int lsh_chunks(int L)
     return (L + len - 1) / len;
 }
 constexpr int LSH_MAX_TIERS = 8;
+// How many ways a block of k_lsh_user_sums shares out its chunk's items: its four waves take a row tile of 32 bits each,
+// and signatures of 32 (64) bits have one (two).  Every share leaves partial sums of its own.
+__host__ __device__ inline int lsh_user_split(int d_bits) { return d_bits == 32 ? 4 : d_bits == 64 ? 2 : 1; }
+// Rows of d floats in a request's user-side sums: D's d', then total as hi + lo.  An error in D[k] reaches a candidate
+// divided by 2 d' and mixed with the others'; one in total reaches all of them whole, so total alone is summed in 64 bits.
+__host__ __device__ inline int lsh_rows(int d_bits) { return d_bits + 2; }
+// the n partial sums at p, p + stride, .. added in order, eight loads in flight
+__device__ __forceinline__ float lsh_sum_parts(const float *p, size_t stride, int n)
+{
+    float acc = 0.f;
+    int c = 0;
+    for (; c + 8 <= n; c += 8) {
+        float v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = p[(size_t)(c + i) * stride];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) acc += v[i];
+    }
+    for (; c < n; ++c) acc += p[(size_t)c * stride];
+    return acc;
+}
+// the same for total: each partial is p[0] + p[d]
+__device__ __forceinline__ double lsh_sum_totals(const float *p, size_t stride, int d, int n)
+{
+    double acc = 0.0;
+    int c = 0;
+    for (; c + 4 <= n; c += 4) {
+        float hi[4], lo[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            hi[i] = p[(size_t)(c + i) * stride];
+            lo[i] = p[(size_t)(c + i) * stride + d];
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc += (double)hi[i] + (double)lo[i];
+    }
+    for (; c < n; ++c) acc += (double)p[(size_t)c * stride] + (double)p[(size_t)c * stride + d];
+    return acc;
+}
 
 struct LshReqDesc {
     const uint8_t *seq_sigs;
@@ -50,22 +87,22 @@ struct LshModel {
     int32_t tier_mul;           // ceil(2^20 / d_bits): (x * tier_mul) >> 20 == x / d_bits for x <= 2048
 };
 
-// a2 of this path -- per request and chunk of the history:
-// part[r][chunk][s][k][j] = sum over the chunk's t with bit k of signature t equal to s of U~[t][j]   (s = 0, 1)
-// (grid_chunks: chunks of the longest history in the batch; max_chunks: chunk stride of `part`)
-hipError_t launch_lsh_user_partial(const LshModel &m, const LshBatch &b, int grid_chunks, int max_chunks, float *part,
-                                   hipStream_t s);
-// A[r][s][k][j] = sum of the partial sums over the chunks, in chunk order
-hipError_t launch_lsh_user_reduce(const LshModel &m, const LshBatch &b, int max_chunks, const float *part, float *A,
-                                  hipStream_t s);
-// Eq. 8: din[i][j] = (1 / d') sum_k A[b_ik][k][j]
+// a2 of this path (k_lsh_user_mfma.hip) -- per request and share of its history, lsh_rows(d') rows of d floats:
+// part[r][share][k] = sum of c_tk U~_t (c = 1 where bit k of signature t is 0, else -1), part[r][share][d'], [d' + 1] = sum of U~_t (hi, lo)
+// (grid_chunks: chunks of the longest history in the batch; part_stride: shares a request has room for)
+hipError_t launch_lsh_user_sums(const LshModel &m, const LshBatch &b, int grid_chunks, int part_stride, float *part, hipStream_t s);
+// A[r] = the shares of request r added up, in order: D [d'][d], then total (hi, lo) [2][d]
+hipError_t launch_lsh_user_reduce(const LshModel &m, const LshBatch &b, int part_stride, const float *part, float *A, hipStream_t s);
+// Eq. 8: din[i] = total / 2 + (1 / 2 d') sum_k c_ik D[k]
 hipError_t launch_lsh_din(const LshModel &m, const LshBatch &b, const uint8_t *sig_table, const float *A, int32_t *bad,
                           hipStream_t s);
-// Eq. 8 on the matrix cores (d a multiple of 32 up to 128): the candidates' bits one-hot against the tables cut into three
-// bf16 pieces.  pieces: workspace of lsh_din_pieces_stride() 16-byte pieces per request, written by the launch itself.
+// Eq. 8 on the matrix cores (d a multiple of 32 up to 128): the candidates' signs against D cut into three bf16 pieces.
+// launch_lsh_din_pieces takes launch_lsh_user_reduce's place: it adds the shares up itself and leaves D as pieces
+// (lsh_din_pieces_stride() 16-byte pieces per request) and total in A's last rows.
 bool lsh_din_on_mfma(const LshModel &m);
 size_t lsh_din_pieces_stride(const LshModel &m);
-hipError_t launch_lsh_din_mfma(const LshModel &m, const LshBatch &b, const uint8_t *sig_table, const float *A, void *pieces,
+hipError_t launch_lsh_din_pieces(const LshModel &m, const LshBatch &b, int part_stride, const float *part, float *A, void *pieces, hipStream_t s);
+hipError_t launch_lsh_din_mfma(const LshModel &m, const LshBatch &b, const uint8_t *sig_table, const float *A, const void *pieces,
                                int32_t *bad, hipStream_t s);
 // Eq. 6, 7, 9: equal-bit counts against every history item, counted into tiers
 hipError_t launch_lsh_simtier(const LshModel &m, const LshBatch &b, const uint8_t *sig_table, hipStream_t s);

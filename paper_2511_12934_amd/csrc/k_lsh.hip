@@ -8,254 +8,17 @@
 // byte of a packed 64-bit histogram (eight tiers, flushed before a byte can
 // overflow).  Plain integer work, bound by the vector ALU.
 //
-// LSH-DIN does NOT need the pairs.  Eq. 8 has no softmax: the weight of
-// history item t is (number of equal bits) / d' = (1/d') sum_k [b_ik == b_tk],
-// so
-//     DIN_i = (1/d') sum_k A[b_ik][k],   A[s][k] = sum over t with b_tk == s of U~_t,
-// and the 2 d' vectors A[s][k] belong to the user alone.  They are formed once
-// per request (a2 of this path: user-side staging, in chunks of the history
-// summed in a fixed order), after which a candidate costs d' additions per
-// output feature instead of l multiply-adds.  Same value as Eq. 8 up to the
-// order of the fp32 additions.
+// LSH-DIN does NOT need the pairs: Eq. 8 has no softmax, so it factors into
+// d' + 1 vectors of the user alone (k_lsh_user_mfma.hip) and, per candidate,
+// d' additions per output feature.  Same value as Eq. 8 up to the order of the
+// fp32 additions.
 #include "aif_lsh_dev.h"
-
-#include <cstdlib>
 
 namespace aif {
 
-__device__ __forceinline__ float lsh_ld(const void *p, int dtype, size_t i)
-{
-    return dtype == 0 ? ((const float *)p)[i] : __uint_as_float(((uint32_t)((const uint16_t *)p)[i]) << 16);
-}
-
-// ---------------------------------------------------------------------------
-// user side, partial sums.  Block (chunk, request); a work item is (bit k, group of 16 features).
-// ---------------------------------------------------------------------------
-constexpr int LSH_TSUB = 128;           // history items staged in LDS at a time
-
-__global__ __launch_bounds__(256) void k_lsh_user_partial(LshModel m, LshBatch b, int max_chunks, float *__restrict__ part)
-{
-    extern __shared__ __align__(16) char lds[];
-    const int r = blockIdx.y, chunk = blockIdx.x;
-    const LshReqDesc rd = b.reqs[r];
-    const int chunk_len = lsh_chunk_len(rd.seq_len);
-    const int t_lo = chunk * chunk_len;
-    if (t_lo >= rd.seq_len) return;
-    const int t_hi = min(rd.seq_len, t_lo + chunk_len);
-    const int d = m.d_out, nb = m.d_bits / 8, jg = d / 16, items = m.d_bits * jg;
-    float *su = (float *)lds;                               // [LSH_TSUB][d]
-    uint8_t *ss = (uint8_t *)(su + LSH_TSUB * d);           // [LSH_TSUB][nb]
-    float *out = part + ((size_t)r * max_chunks + chunk) * 2 * m.d_bits * d;
-
-    for (int item0 = 0; item0 < items; item0 += 256) {
-        const int item = item0 + threadIdx.x;
-        const bool work = item < items;
-        const int k = work ? item / jg : 0, j0 = work ? (item - k * jg) * 16 : 0;
-        float a0[16], a1[16];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) a0[i] = a1[i] = 0.f;
-        for (int ts = t_lo; ts < t_hi; ts += LSH_TSUB) {
-            const int nt = min(LSH_TSUB, t_hi - ts);
-            __syncthreads();
-            for (int i = threadIdx.x; i < nt * d; i += 256) su[i] = lsh_ld(rd.seq_emb, m.dtype, (size_t)ts * d + i);
-            for (int i = threadIdx.x; i < nt * nb; i += 256) ss[i] = rd.seq_sigs[(size_t)ts * nb + i];
-            __syncthreads();
-            if (work) {
-                // sums of the staged items first, then into the chunk's sums: short chains of additions
-                float s0[16], s1[16];
-#pragma unroll
-                for (int i = 0; i < 16; ++i) s0[i] = s1[i] = 0.f;
-                for (int t = 0; t < nt; ++t) {
-                    // bit k of a signature: byte k / 8, first bit most significant
-                    const float bit = (float)((ss[t * nb + (k >> 3)] >> (7 - (k & 7))) & 1);
-                    const float4 *u4 = (const float4 *)(su + t * d + j0);
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const float4 u = u4[q];
-                        s1[4 * q + 0] = fmaf(bit, u.x, s1[4 * q + 0]);
-                        s1[4 * q + 1] = fmaf(bit, u.y, s1[4 * q + 1]);
-                        s1[4 * q + 2] = fmaf(bit, u.z, s1[4 * q + 2]);
-                        s1[4 * q + 3] = fmaf(bit, u.w, s1[4 * q + 3]);
-                        s0[4 * q + 0] = fmaf(1.f - bit, u.x, s0[4 * q + 0]);
-                        s0[4 * q + 1] = fmaf(1.f - bit, u.y, s0[4 * q + 1]);
-                        s0[4 * q + 2] = fmaf(1.f - bit, u.z, s0[4 * q + 2]);
-                        s0[4 * q + 3] = fmaf(1.f - bit, u.w, s0[4 * q + 3]);
-                    }
-                }
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    a0[i] += s0[i];
-                    a1[i] += s1[i];
-                }
-            }
-        }
-        if (work) {
-            float4 *o0 = (float4 *)(out + (size_t)k * d + j0);
-            float4 *o1 = (float4 *)(out + (size_t)(m.d_bits + k) * d + j0);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                o0[q] = make_float4(a0[4 * q], a0[4 * q + 1], a0[4 * q + 2], a0[4 * q + 3]);
-                o1[q] = make_float4(a1[4 * q], a1[4 * q + 1], a1[4 * q + 2], a1[4 * q + 3]);
-            }
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------
-// The same partial sums on the matrix cores, for bf16 embeddings.  part[s][k][j] = sum_t [b_tk == s] U~[t][j] is a
-// contraction over the history: (bits as 0/1, inverted for s = 0) [2 d' x l] times U~ [l x d].  0, 1 and the
-// embeddings are exact in bf16 and the MFMA accumulates in fp32, so the values are those of the loop above up to the
-// order of the additions.  The contraction index t is the slow axis of both inputs as the caller stores them, so
-// both pass through LDS: 64 history items at a time, the embeddings set down transposed ([j][t]: a lane's eight
-// consecutive t are one 16-byte read), the signatures turned into bit planes over t by wave ballots (lane = t), from
-// which an A fragment -- eight consecutive t of one bit position -- is one byte, expanded to eight bf16 through a
-// 256-entry table in LDS.  Block = (chunk of lsh_chunk_len items, request), four waves; the 2 d' / 32 x d / 32 result
-// tiles are dealt round the waves, TPW each.
-// ---------------------------------------------------------------------------
-typedef __bf16 lsh_bf16x8 __attribute__((ext_vector_type(8)));
-typedef float lsh_f32x16 __attribute__((ext_vector_type(16)));
-constexpr int LSH_TS = 64;              // history items per trip through LDS: four MFMA k-steps
-
-template <int TPW>
-__global__ __launch_bounds__(256) void k_lsh_user_partial_mfma(LshModel m, LshBatch b, int max_chunks, float *__restrict__ part)
-{
-    extern __shared__ __align__(16) char lds[];
-    const int r = blockIdx.y, chunk = blockIdx.x;
-    const LshReqDesc rd = b.reqs[r];
-    const int chunk_len = lsh_chunk_len(rd.seq_len);
-    const int t_lo = chunk * chunk_len;
-    if (t_lo >= rd.seq_len) return;
-    const int t_hi = min(rd.seq_len, t_lo + chunk_len);
-    const int d = m.d_out, db = m.d_bits, nb = db / 8, CT = d / 32;
-    constexpr int USTR = LSH_TS * 2 + 16;                        // bytes per transposed embedding row (64 t + padding)
-    uint4 *lut = (uint4 *)lds;                                   // [256] byte -> eight bf16 of 0 / 1, first bit = first slot
-    char *su = lds + 4096;                                       // [d][USTR]: U~ of the trip, transposed
-    uint32_t *bp = (uint32_t *)(su + (size_t)d * USTR);          // [d'][2]: bit k of the trip's 64 signatures, lane t = bit t
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, col = lane & 31, h = lane >> 5;
-    {
-        const uint32_t v = threadIdx.x;                          // slot s of the fragment = bit s of the byte (t0 + s)
-        uint32_t w[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) w[i] = ((v >> (2 * i)) & 1u) * 0x3F80u + ((v >> (2 * i + 1)) & 1u) * 0x3F800000u;
-        lut[threadIdx.x] = make_uint4(w[0], w[1], w[2], w[3]);
-    }
-    lsh_f32x16 acc[TPW];
-#pragma unroll
-    for (int i = 0; i < TPW; ++i)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc[i][e] = 0.f;
-    const uint16_t *emb = (const uint16_t *)rd.seq_emb;
-
-    for (int ts = t_lo; ts < t_hi; ts += LSH_TS) {
-        __syncthreads();                                         // the last trip's fragments have been read
-        // embeddings: 16-byte pieces (eight features of one item) read in row order, written transposed
-        for (int pc = threadIdx.x; pc < LSH_TS * d / 8; pc += 256) {
-            const int t = pc / (d / 8), j0 = (pc - t * (d / 8)) * 8;
-            uint4 v = make_uint4(0, 0, 0, 0);
-            if (ts + t < t_hi) v = *(const uint4 *)(emb + (size_t)(ts + t) * d + j0);
-            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-            for (int i = 0; i < 8; ++i)
-                *(uint16_t *)(su + (size_t)(j0 + i) * USTR + 2 * t) = (uint16_t)(w[i >> 1] >> (16 * (i & 1)));
-        }
-        // signatures: lane = history item; bit k of all 64 items by one ballot; the waves share the bit positions
-        {
-            const int t = ts + lane;
-            const uint8_t *sg = rd.seq_sigs + (size_t)t * nb;
-            for (int k = wave; k < db; k += 4) {
-                const uint32_t byte = t < t_hi ? sg[k >> 3] : 0u;            // first bit most significant
-                const unsigned long long mask = __ballot((byte >> (7 - (k & 7))) & 1u);
-                if (lane == 0) {
-                    bp[2 * k] = (uint32_t)mask;
-                    bp[2 * k + 1] = (uint32_t)(mask >> 32);
-                }
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int ks = 0; ks < LSH_TS / 16; ++ks) {
-            const int tb = 16 * ks + 8 * h;                      // this lane's eight items of the k-step
-#pragma unroll
-            for (int i = 0; i < TPW; ++i) {
-                const int idx = wave + 4 * i, rt = idx / CT, ct = idx - rt * CT;
-                const int row = 32 * rt + col, sbit = row / db, k = row - sbit * db;        // row = s d' + k
-                uint32_t byte = (bp[2 * k + (tb >> 5)] >> (tb & 31)) & 0xFFu;
-                if (sbit == 0) byte ^= 0xFFu;                    // the items whose bit is 0
-                const lsh_bf16x8 A = __builtin_bit_cast(lsh_bf16x8, lut[byte]);
-                const lsh_bf16x8 B = *(const lsh_bf16x8 *)(su + (size_t)(32 * ct + col) * USTR + 2 * tb);
-                acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A, B, acc[i], 0, 0, 0);
-            }
-        }
-    }
-    float *out = part + ((size_t)r * max_chunks + chunk) * 2 * db * d;
-#pragma unroll
-    for (int i = 0; i < TPW; ++i) {
-        const int idx = wave + 4 * i, rt = idx / CT, ct = idx - rt * CT;
-#pragma unroll
-        for (int e = 0; e < 16; ++e) out[(size_t)(32 * rt + 8 * (e >> 2) + 4 * h + (e & 3)) * d + 32 * ct + col] = acc[i][e];
-    }
-}
-
-// bf16 embeddings, whole 32-tiles, a number of result tiles the four waves share evenly: the matrix-core form
-static int lsh_user_mfma_tpw(const LshModel &m)
-{
-    if (m.dtype != 1 || m.d_out % 32 || m.d_bits % 32) return 0;
-    const int nt = (2 * m.d_bits / 32) * (m.d_out / 32);
-    return (nt == 8 || nt == 16 || nt == 32) ? nt / 4 : 0;
-}
-
-hipError_t launch_lsh_user_partial(const LshModel &m, const LshBatch &b, int grid_chunks, int max_chunks, float *part,
-                                   hipStream_t s)
-{
-    if (b.n_req == 0 || grid_chunks == 0) return hipSuccess;
-    if (const int tpw = lsh_user_mfma_tpw(m)) {
-        const char *off = getenv("AIF_LSH_USER_VALU");           // testing: the vector-ALU form on a shape the matrix cores serve
-        if (!(off && off[0] == '1')) {
-            const size_t bytes = 4096 + (size_t)m.d_out * (LSH_TS * 2 + 16) + (size_t)m.d_bits * 8;
-            const dim3 grid(grid_chunks, b.n_req), block(256);
-            if (tpw == 2) hipLaunchKernelGGL(k_lsh_user_partial_mfma<2>, grid, block, bytes, s, m, b, max_chunks, part);
-            else if (tpw == 4) hipLaunchKernelGGL(k_lsh_user_partial_mfma<4>, grid, block, bytes, s, m, b, max_chunks, part);
-            else hipLaunchKernelGGL(k_lsh_user_partial_mfma<8>, grid, block, bytes, s, m, b, max_chunks, part);
-            return hipGetLastError();
-        }
-    }
-    const size_t lds = (size_t)LSH_TSUB * (m.d_out * 4 + m.d_bits / 8);
-    static bool attr_set = false;
-    if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void *)k_lsh_user_partial, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-        if (e != hipSuccess) return e;
-        attr_set = true;
-    }
-    hipLaunchKernelGGL(k_lsh_user_partial, dim3(grid_chunks, b.n_req), dim3(256), lds, s, m, b, max_chunks, part);
-    return hipGetLastError();
-}
-
-__global__ __launch_bounds__(256) void k_lsh_user_reduce(LshModel m, LshBatch b, int max_chunks, const float *__restrict__ part,
-                                                         float *__restrict__ A)
-{
-    const int r = blockIdx.y;
-    const size_t n = (size_t)2 * m.d_bits * m.d_out;
-    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    const int L = b.reqs[r].seq_len;
-    const int chunks = lsh_chunks(L);
-    float acc = 0.f;
-    for (int c = 0; c < chunks; ++c) acc += part[((size_t)r * max_chunks + c) * n + i];
-    A[(size_t)r * n + i] = acc;
-}
-
-hipError_t launch_lsh_user_reduce(const LshModel &m, const LshBatch &b, int max_chunks, const float *part, float *A,
-                                  hipStream_t s)
-{
-    if (b.n_req == 0) return hipSuccess;
-    const size_t n = (size_t)2 * m.d_bits * m.d_out;
-    hipLaunchKernelGGL(k_lsh_user_reduce, dim3((unsigned)((n + 255) / 256), b.n_req), dim3(256), 0, s, m, b, max_chunks, part, A);
-    return hipGetLastError();
-}
-
 // ---------------------------------------------------------------------------
 // Eq. 8.  Block = LSH_BLOCK candidates of one request; d / 16 threads per candidate, 16 features each.
-// The user's table A[2][d'][d] is staged in LDS in slices of KC bits.
+// The user's table D[d'][d] is staged in LDS in slices of KC bits and added with the candidate's sign.
 // ---------------------------------------------------------------------------
 constexpr int LSH_DIN_LDS = 64 * 1024;
 
@@ -263,7 +26,7 @@ __global__ __launch_bounds__(256) void k_lsh_din(LshModel m, LshBatch b, const u
                                                  const float *__restrict__ A, int32_t *__restrict__ bad)
 {
     extern __shared__ __align__(16) char lds[];
-    float *sa = (float *)lds;                                   // [2][kc][d]
+    float *sa = (float *)lds;                                   // [kc][d]
     int blk = blockIdx.x;                                       // a contiguous run of blocks per XCD, as in k_lsh_simtier: a user's table in one L2
     {
         const int per_xcd = b.n_blk >> 3;
@@ -277,10 +40,10 @@ __global__ __launch_bounds__(256) void k_lsh_din(LshModel m, LshBatch b, const u
     if (nrows <= 0) return;
     const int d = m.d_out, jg = d / 16, nb = m.d_bits / 8;
     const int per_round = 256 / jg;                             // candidates served at once
-    const int kc = min(m.d_bits, LSH_DIN_LDS / (2 * d * 4)) & ~7;   // bits per slice, whole bytes
-    const float *Ar = A + (size_t)r * 2 * m.d_bits * d;
+    const int kc = min(m.d_bits, LSH_DIN_LDS / (d * 4)) & ~7;       // bits per slice, whole bytes
+    const float *Ar = A + (size_t)r * lsh_rows(m.d_bits) * d;
     const int sub = threadIdx.x / jg, j0 = (threadIdx.x - sub * jg) * 16;
-    const float inv = 1.0f / (float)m.d_bits;
+    const float inv = 0.5f / (float)m.d_bits;
     int n_bad = 0;
 
     for (int c0 = 0; c0 < nrows; c0 += per_round) {
@@ -300,10 +63,7 @@ __global__ __launch_bounds__(256) void k_lsh_din(LshModel m, LshBatch b, const u
             const int kn = min(kc, m.d_bits - k0);
             __syncthreads();
             if (c0 == 0 || kc < m.d_bits) {                     // the whole table fits: staged once
-                for (int i = threadIdx.x; i < 2 * kn * d / 4; i += 256) {
-                    const int s = i / (kn * d / 4), rem = i - s * (kn * d / 4);
-                    ((float4 *)sa)[i] = ((const float4 *)(Ar + ((size_t)s * m.d_bits + k0) * d))[rem];
-                }
+                for (int i = threadIdx.x; i < kn * d / 4; i += 256) ((float4 *)sa)[i] = ((const float4 *)(Ar + (size_t)k0 * d))[i];
             }
             __syncthreads();
             if (live) {
@@ -311,15 +71,15 @@ __global__ __launch_bounds__(256) void k_lsh_din(LshModel m, LshBatch b, const u
                     const uint32_t byte = sig[(k0 + kb) >> 3];
 #pragma unroll
                     for (int u = 0; u < 8; ++u) {
-                        const int bit = (byte >> (7 - u)) & 1;
-                        const float4 *a4 = (const float4 *)(sa + ((size_t)bit * kn + kb + u) * d + j0);
+                        const float c = (byte >> (7 - u)) & 1 ? -1.f : 1.f;
+                        const float4 *a4 = (const float4 *)(sa + (size_t)(kb + u) * d + j0);
 #pragma unroll
                         for (int q = 0; q < 4; ++q) {
                             const float4 v = a4[q];
-                            acc[4 * q + 0] += v.x;
-                            acc[4 * q + 1] += v.y;
-                            acc[4 * q + 2] += v.z;
-                            acc[4 * q + 3] += v.w;
+                            acc[4 * q + 0] = fmaf(c, v.x, acc[4 * q + 0]);
+                            acc[4 * q + 1] = fmaf(c, v.y, acc[4 * q + 1]);
+                            acc[4 * q + 2] = fmaf(c, v.z, acc[4 * q + 2]);
+                            acc[4 * q + 3] = fmaf(c, v.w, acc[4 * q + 3]);
                         }
                     }
                 }
@@ -328,10 +88,14 @@ __global__ __launch_bounds__(256) void k_lsh_din(LshModel m, LshBatch b, const u
         if (live) {
             float4 *o = (float4 *)(rd.din_out + (size_t)(local0 + cand) * d + j0);
             const float nanv = __uint_as_float(0x7FC00000u);
+            const float4 *hi = (const float4 *)(Ar + (size_t)m.d_bits * d + j0), *lo = (const float4 *)(Ar + (size_t)(m.d_bits + 1) * d + j0);
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-                o[q] = ok ? make_float4(acc[4 * q] * inv, acc[4 * q + 1] * inv, acc[4 * q + 2] * inv, acc[4 * q + 3] * inv)
+            for (int q = 0; q < 4; ++q) {
+                const float4 x = hi[q], y = lo[q];
+                o[q] = ok ? make_float4(0.5f * x.x + fmaf(acc[4 * q], inv, 0.5f * y.x), 0.5f * x.y + fmaf(acc[4 * q + 1], inv, 0.5f * y.y),
+                                        0.5f * x.z + fmaf(acc[4 * q + 2], inv, 0.5f * y.z), 0.5f * x.w + fmaf(acc[4 * q + 3], inv, 0.5f * y.w))
                           : make_float4(nanv, nanv, nanv, nanv);
+            }
         }
     }
     if (n_bad) atomicAdd(bad, n_bad);

@@ -1,17 +1,19 @@
 // Eq. 8 on the matrix cores.
 //
-// DIN_i = (1 / d') sum_k A[b_ik][k] is a contraction once the candidate's bits are written one-hot: with
-// X[i][(k, s)] = [b_ik == s] (2 d' columns of 0 / 1) and W[(k, s)][j] = A[s][k][j], DIN = X W / d'.  X is exact in bf16; the
-// fp32 table W is not, so it is cut into three bf16 pieces, W = hi + mid + lo (hi = bf16(W), mid = bf16(W - hi), lo = the
-// rest: 8 + 8 + 8 significant bits, exact), each a contraction of its own into the SAME fp32 accumulator: every lo
-// product first, then every mid, then every hi, so that the d' additions at full magnitude are what they are in the
-// vector-ALU kernel and the two small pieces cost rounding errors 2^-8 and 2^-16 as large.  The vector-ALU kernel reads
-// its tables from LDS once per (candidate, bit, feature) -- 16 KB per candidate, which is what bound it; here a
-// workgroup's 256 candidates share every fragment read.
+// DIN_i = total / 2 + (1 / 2 d') sum_k c_ik D[k] (k_lsh_user_mfma.hip) is a contraction of the candidates' signs c = +-1,
+// exact in bf16, with the user's fp32 table D [d'][d], which is not: it is cut into three bf16 pieces, D = hi + mid + lo
+// (hi = bf16(D), mid = bf16(D - hi), lo = the rest: 8 + 8 + 8 significant bits, exact), each a contraction of its own into
+// the SAME fp32 accumulator: every lo product first, then every mid, then every hi, so that the d' additions at full
+// magnitude are what they are in the vector-ALU kernel and the two small pieces cost rounding errors 2^-8 and 2^-16 as
+// large.
 //
-// k_lsh_din_pieces writes W's pieces once per request in the order the instruction reads its column operand:
-// [piece][k-step of 16 columns (k, s) = 8 bits][feature tile of 32][lane] of 16 bytes.  k_lsh_din_mfma stages them through
-// LDS a run of k-steps at a time; a wave owns 64 candidates (two row tiles) and every feature tile.
+// k_lsh_din_pieces adds the history's shares up and writes D's pieces once per request in the order the instruction
+// reads its column operand: [piece lo, mid, hi][k-step of 16 bits][feature tile of 32][lane] of 16 bytes -- the order in
+// which a wave of k_lsh_din_mfma, 64 candidates (two row tiles) and every feature tile, reads them: one stream, three
+// fragments ahead, no LDS and no barrier (at most 192 KB, read by every wave of a compute unit: from L1 and L2).
+// What bounds it: the bytes.  64 x 10^4 candidates, d' = d = 64: 71 us for 164 MB of results and 82 MB of signature lines
+// (8 of 128 bytes used); 8 x 10^4, d' = d = 128: 36 us, where twice the columns, staged through LDS, took 64 (79 above).
+// Streaming stores: 75.
 #include "aif_lsh_dev.h"
 
 namespace aif {
@@ -19,30 +21,41 @@ namespace aif {
 typedef __bf16 din_bf16x8 __attribute__((ext_vector_type(8)));
 typedef float din_f32x16 __attribute__((ext_vector_type(16)));
 
-constexpr int DIN_STAGE_KB = 48;            // fragments (1 KB each) staged in LDS at a time
-
 __device__ __forceinline__ uint32_t bf16_rne_bits(float x)
 {
     const uint32_t u = __float_as_uint(x);
     return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;          // finite inputs (sums of embeddings)
 }
 
-// lane = (feature of the tile, which 8 of the k-step's 16 columns); column K = (bit k = K / 2, value s = K % 2)
-__global__ __launch_bounds__(256) void k_lsh_din_pieces(LshModel m, const float *__restrict__ A, uint4 *__restrict__ out, size_t req_stride)
+// Block = (k-step, feature tile): 16 bits x 32 features, a thread per sum; the blocks past the last k-step add up `total`.
+__global__ __launch_bounds__(512) void k_lsh_din_pieces(LshModel m, LshBatch b, int part_stride, const float *__restrict__ part,
+                                                        float *__restrict__ A, uint4 *__restrict__ out, size_t req_stride)
 {
-    const int ft_n = m.d_out / 32, ks_n = m.d_bits / 8;
-    const int idx = blockIdx.x * 256 + threadIdx.x;
-    if (idx >= ks_n * ft_n * 64) return;
-    const int lane = idx & 63, ft = (idx >> 6) % ft_n, ks = idx / (64 * ft_n);
-    const int j = ft * 32 + (lane & 31), h = lane >> 5;
-    const float *Ar = A + (size_t)blockIdx.y * 2 * m.d_bits * m.d_out;
+    __shared__ float D[16][33];
+    const int ft_n = m.d_out / 32, ks_n = m.d_bits / 16, ft = blockIdx.x % ft_n, ks = blockIdx.x / ft_n, r = blockIdx.y;
+    const int k = threadIdx.x >> 5, j = threadIdx.x & 31, shares = lsh_chunks(b.reqs[r].seq_len) * lsh_user_split(m.d_bits);
+    const size_t n = (size_t)lsh_rows(m.d_bits) * m.d_out;
+    const float *p = part + (size_t)r * part_stride * n + ft * 32 + j;
+    if (ks == ks_n) {
+        if (k == 0) {
+            const double t = lsh_sum_totals(p + (size_t)m.d_bits * m.d_out, n, m.d_out, shares);
+            float *a = A + (size_t)r * n + (size_t)m.d_bits * m.d_out + ft * 32 + j;
+            a[0] = (float)t;
+            a[m.d_out] = (float)(t - (double)(float)t);
+        }
+        return;
+    }
+    D[k][j] = lsh_sum_parts(p + (size_t)(16 * ks + k) * m.d_out, n, shares);
+    __syncthreads();
+    if (threadIdx.x >= 64) return;
+    const int lane = threadIdx.x, c = lane & 31, h = lane >> 5;    // lane = (feature of the tile, which 8 of the k-step's bits)
     uint32_t piece[3][4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
         uint32_t half[3][2];
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
-            const float w = Ar[((size_t)s * m.d_bits + ks * 8 + 4 * h + u) * m.d_out + j];
+            const float w = D[8 * h + 2 * u + s][c];
             const uint32_t hi = bf16_rne_bits(w);
             const float r1 = w - __uint_as_float(hi << 16);
             const uint32_t mid = bf16_rne_bits(r1);
@@ -52,22 +65,29 @@ __global__ __launch_bounds__(256) void k_lsh_din_pieces(LshModel m, const float 
             half[2][s] = hi;
         }
 #pragma unroll
-        for (int p = 0; p < 3; ++p) piece[p][u] = half[p][0] | (half[p][1] << 16);
+        for (int q = 0; q < 3; ++q) piece[q][u] = half[q][0] | (half[q][1] << 16);
     }
-    uint4 *o = out + (size_t)blockIdx.y * req_stride;
+    uint4 *o = out + (size_t)r * req_stride;
 #pragma unroll
-    for (int p = 0; p < 3; ++p)
-        o[((size_t)(p * ks_n + ks) * ft_n + ft) * 64 + lane] = make_uint4(piece[p][0], piece[p][1], piece[p][2], piece[p][3]);
+    for (int q = 0; q < 3; ++q)
+        o[((size_t)(q * ks_n + ks) * ft_n + ft) * 64 + lane] = make_uint4(piece[q][0], piece[q][1], piece[q][2], piece[q][3]);
 }
 
-// FT: feature tiles (d = 32 FT).  ksp: k-steps per staging; divides d' / 8.
+hipError_t launch_lsh_din_pieces(const LshModel &m, const LshBatch &b, int part_stride, const float *part, float *A, void *pieces, hipStream_t s)
+{
+    if (b.n_req == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_lsh_din_pieces, dim3((m.d_bits / 16 + 1) * (m.d_out / 32), b.n_req), dim3(512), 0, s, m, b, part_stride, part, A,
+                       (uint4 *)pieces, lsh_din_pieces_stride(m));
+    return hipGetLastError();
+}
+
+// FT: feature tiles (d = 32 FT)
 template <int FT>
-__global__ __launch_bounds__(256) void k_lsh_din_mfma(LshModel m, LshBatch b, const uint8_t *__restrict__ sig_table,
-                                                      const uint4 *__restrict__ pieces, size_t req_stride, int ksp,
+__global__ __launch_bounds__(256, 2) void k_lsh_din_mfma(LshModel m, LshBatch b, const uint8_t *__restrict__ sig_table,
+                                                      const float *__restrict__ A, const uint4 *__restrict__ pieces, size_t req_stride,
                                                       int32_t *__restrict__ bad)
 {
-    extern __shared__ __align__(16) char lds[];
-    uint4 *sw = (uint4 *)lds;                                   // [ksp][FT][64]
+    constexpr int RT = 2;
     int blk = blockIdx.x;                                       // a contiguous run of blocks per XCD: a user's pieces in one L2
     {
         const int per_xcd = b.n_blk >> 3;
@@ -76,80 +96,98 @@ __global__ __launch_bounds__(256) void k_lsh_din_mfma(LshModel m, LshBatch b, co
     const int r = b.blk_req[blk];
     if (r < 0) return;
     const LshReqDesc rd = b.reqs[r];
-    const int local0 = blk * LSH_BLOCK - rd.cand_base;
-    const int nrows = min(LSH_BLOCK, rd.n_cand - local0);
-    if (nrows <= 0) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, col = lane & 31, h = lane >> 5;
-    const int nw = m.d_bits / 32, ks_n = m.d_bits / 8;
+    const int local0 = blk * LSH_BLOCK - rd.cand_base + wave * 32 * RT;
+    const int nrows = min(32 * RT, rd.n_cand - local0);
+    if (nrows <= 0) return;
+    const int nw = m.d_bits / 32, ks_n = m.d_bits / 16;
 
-    // this lane's candidate in each of the wave's two row tiles: its signature, whether it exists, whether its id is valid
-    uint32_t sig[2][8];
-    uint32_t live_mask[2], ok_mask[2];
+    // the first fragments on their way, then this lane's candidate in each of the wave's row tiles: its signature,
+    // whether it exists, whether its id is valid
+    const uint4 *src = pieces + (size_t)r * req_stride + lane;
+    const int steps = 3 * ks_n;
+    uint4 w[3][FT];
+    auto fetch = [&](int i, uint4 (&f)[FT]) {
+        i = i < steps ? i : steps - 1;
 #pragma unroll
-    for (int rt = 0; rt < 2; ++rt) {
-        const int cand = wave * 64 + rt * 32 + col;
+        for (int ft = 0; ft < FT; ++ft) f[ft] = src[(size_t)(i * FT + ft) * 64];
+    };
+    fetch(0, w[0]);
+    fetch(1, w[1]);
+    fetch(2, w[2]);
+    uint32_t sig[RT][8];
+    uint32_t live_mask[RT], ok_mask[RT];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+        const int cand = rt * 32 + col;
         const bool live = cand < nrows;
         int64_t id = live ? rd.cand_ids[local0 + cand] : 0;
         const bool ok = id >= 0 && id < m.n_items;
         if (!ok) id = 0;
         const uint32_t *p = (const uint32_t *)(sig_table + (size_t)id * (nw * 4));
 #pragma unroll
-        for (int w = 0; w < 8; ++w) sig[rt][w] = w < nw ? p[w] : 0u;
+        for (int q = 0; q < 8; ++q) sig[rt][q] = q < nw ? p[q] : 0u;
         live_mask[rt] = (uint32_t)__ballot(live);               // lanes 0..31: one bit per candidate of the row tile
         ok_mask[rt] = (uint32_t)__ballot(ok);
     }
-    din_f32x16 acc[2][FT];
+    din_f32x16 acc[RT][FT];
 #pragma unroll
-    for (int rt = 0; rt < 2; ++rt)
+    for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
         for (int ft = 0; ft < FT; ++ft)
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[rt][ft][i] = 0.f;
 
-    const uint4 *src = pieces + (size_t)r * req_stride;
-    const int stage_frags = ksp * FT * 64;                      // 16-byte pieces per staging
-    for (int p = 0; p < 3; ++p) {
-        for (int ks0 = 0; ks0 < ks_n; ks0 += ksp) {
-            __syncthreads();
-            const uint4 *from = src + (size_t)(p * ks_n + ks0) * FT * 64;
-            for (int i = threadIdx.x; i < stage_frags; i += 256) sw[i] = from[i];
-            __syncthreads();
-            for (int ksl = 0; ksl < ksp; ++ksl) {
-                const int ks = ks0 + ksl;                       // byte ks of the signature, its high nibble for the first half
-                din_bf16x8 x[2];
+    int ks = 0;
+    auto step = [&](int i, const uint4 (&f)[FT]) __attribute__((always_inline)) {
+        if (i >= steps) return;
+        din_bf16x8 x[RT];
 #pragma unroll
-                for (int rt = 0; rt < 2; ++rt) {
-                    uint32_t word = sig[rt][0];
+        for (int rt = 0; rt < RT; ++rt) {
+            uint32_t word = sig[rt][0];
 #pragma unroll
-                    for (int w = 1; w < 8; ++w) word = (ks >> 2) == w ? sig[rt][w] : word;
-                    const uint32_t byte = (word >> (8 * (ks & 3))) & 0xFFu, nib = h ? (byte & 15u) : (byte >> 4);
-                    uint32_t xw[4];
+            for (int q = 1; q < 8; ++q) word = (ks >> 1) == q ? sig[rt][q] : word;
+            const uint32_t byte = word >> (16 * (ks & 1) + 8 * h);          // bits 16 ks + 8 h .. + 7, the first most significant
+            uint32_t xw[4];
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) xw[u] = (nib >> (3 - u)) & 1u ? 0x3F800000u : 0x00003F80u;     // (s = 0, s = 1): one of them 1.0
-                    x[rt] = __builtin_bit_cast(din_bf16x8, make_uint4(xw[0], xw[1], xw[2], xw[3]));
-                }
+            for (int u = 0; u < 4; ++u)                                     // (-1)^bit of two bits: their signs onto a pair of ones
+                xw[u] = ((byte << (8 + 2 * u)) & 0x8000u) | ((byte << (25 + 2 * u)) & 0x80000000u) | 0x3F803F80u;
+            x[rt] = __builtin_bit_cast(din_bf16x8, make_uint4(xw[0], xw[1], xw[2], xw[3]));
+        }
 #pragma unroll
-                for (int ft = 0; ft < FT; ++ft) {
-                    const din_bf16x8 w = __builtin_bit_cast(din_bf16x8, sw[(ksl * FT + ft) * 64 + lane]);
+        for (int ft = 0; ft < FT; ++ft)
 #pragma unroll
-                    for (int rt = 0; rt < 2; ++rt) acc[rt][ft] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[rt], w, acc[rt][ft], 0, 0, 0);
-                }
-            }
+            for (int rt = 0; rt < RT; ++rt)
+                acc[rt][ft] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[rt], __builtin_bit_cast(din_bf16x8, f[ft]), acc[rt][ft], 0, 0, 0);
+        ks = ks + 1 == ks_n ? 0 : ks + 1;
+    };
+    for (int i = 0; i < steps; i += 3) {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            step(i + q, w[q]);
+            fetch(i + q + 3, w[q]);
         }
     }
 
     // cell v of a lane: candidate 8 (v / 4) + 4 h + v % 4 of the row tile, feature `col` of the feature tile
-    const float inv = 1.0f / (float)m.d_bits, nanv = __uint_as_float(0x7FC00000u);
+    const float inv = 0.5f / (float)m.d_bits, nanv = __uint_as_float(0x7FC00000u);
+    const float *total = A + ((size_t)r * lsh_rows(m.d_bits) + m.d_bits) * m.d_out + col;
+    float hi[FT], lo[FT];
 #pragma unroll
-    for (int rt = 0; rt < 2; ++rt) {
+    for (int ft = 0; ft < FT; ++ft) {
+        hi[ft] = 0.5f * total[ft * 32];
+        lo[ft] = 0.5f * total[m.d_out + ft * 32];
+    }
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const int c = 8 * (v / 4) + 4 * h + (v % 4);
             if (!((live_mask[rt] >> c) & 1u)) continue;
             const bool ok = (ok_mask[rt] >> c) & 1u;
-            float *o = rd.din_out + (size_t)(local0 + wave * 64 + rt * 32 + c) * m.d_out + col;
+            float *o = rd.din_out + (size_t)(local0 + rt * 32 + c) * m.d_out + col;
 #pragma unroll
-            for (int ft = 0; ft < FT; ++ft) o[ft * 32] = ok ? acc[rt][ft][v] * inv : nanv;
+            for (int ft = 0; ft < FT; ++ft) o[ft * 32] = ok ? hi[ft] + fmaf(acc[rt][ft][v], inv, lo[ft]) : nanv;
         }
         if (lane == 0) {
             const int n_bad = __builtin_popcount(live_mask[rt] & ~ok_mask[rt]);
@@ -162,26 +200,22 @@ bool lsh_din_on_mfma(const LshModel &m) { return m.d_out % 32 == 0 && m.d_out <=
 
 size_t lsh_din_pieces_stride(const LshModel &m)                // 16-byte pieces per request
 {
-    return (size_t)3 * (m.d_bits / 8) * (m.d_out / 32) * 64;
+    return (size_t)3 * (m.d_bits / 16) * (m.d_out / 32) * 64;
 }
 
-hipError_t launch_lsh_din_mfma(const LshModel &m, const LshBatch &b, const uint8_t *sig_table, const float *A, void *pieces,
+hipError_t launch_lsh_din_mfma(const LshModel &m, const LshBatch &b, const uint8_t *sig_table, const float *A, const void *pieces,
                                int32_t *bad, hipStream_t s)
 {
     if (b.n_blk == 0) return hipSuccess;
     if (!lsh_din_on_mfma(m) || !pieces) return hipErrorInvalidValue;
-    const int ft = m.d_out / 32, ks_n = m.d_bits / 8;
-    const size_t stride = lsh_din_pieces_stride(m);
-    hipLaunchKernelGGL(k_lsh_din_pieces, dim3((ks_n * ft * 64 + 255) / 256, b.n_req), dim3(256), 0, s, m, A, (uint4 *)pieces, stride);
-    int ksp = ks_n;                                             // the largest run of k-steps that divides them and fits the staging
-    while (ksp * ft > DIN_STAGE_KB || ks_n % ksp) --ksp;
-    const size_t lds = (size_t)ksp * ft * 1024;
-    const dim3 grid(b.n_blk), blk(256);
-    switch (ft) {
-    case 1: hipLaunchKernelGGL(k_lsh_din_mfma<1>, grid, blk, lds, s, m, b, sig_table, (const uint4 *)pieces, stride, ksp, bad); break;
-    case 2: hipLaunchKernelGGL(k_lsh_din_mfma<2>, grid, blk, lds, s, m, b, sig_table, (const uint4 *)pieces, stride, ksp, bad); break;
-    case 3: hipLaunchKernelGGL(k_lsh_din_mfma<3>, grid, blk, lds, s, m, b, sig_table, (const uint4 *)pieces, stride, ksp, bad); break;
-    default: hipLaunchKernelGGL(k_lsh_din_mfma<4>, grid, blk, lds, s, m, b, sig_table, (const uint4 *)pieces, stride, ksp, bad); break;
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(b.n_blk), dim3(256), 0, s, m, b, sig_table, A, (const uint4 *)pieces, lsh_din_pieces_stride(m), bad);
+    };
+    switch (m.d_out / 32) {
+    case 1: go(k_lsh_din_mfma<1>); break;
+    case 2: go(k_lsh_din_mfma<2>); break;
+    case 3: go(k_lsh_din_mfma<3>); break;
+    default: go(k_lsh_din_mfma<4>); break;
     }
     return hipGetLastError();
 }
