@@ -1,20 +1,25 @@
 // Eq. 6, 7, 9 with the similarity on the matrix cores.
 //
-// The number of equal bits of two d'-bit signatures is a contraction: with the bits written as +1 / -1 their dot
-// product is (equal - unequal), so 2 * equal = d' + dot.  One v_mfma_i32_32x32x32_i8 forms 32 x 32 of those dots over
-// 32 bits; started from an accumulator of d' it leaves 2 * equal in every cell.  The candidates are the columns (a
-// lane owns one candidate and holds 16 history items' values of it), the history items the rows: their +1 / -1 bytes
-// are written once per request by k_lsh_expand in the order the instruction reads them, and every wave streams them
-// from there.  Only the product over ALL bits matters, so any assignment of bits to the instruction's k index serves,
-// as long as rows and columns use the same one.
+// The number of equal bits of two d'-bit signatures is a contraction: with the bits written as signs their dot product
+// is (equal - unequal), so 2 * equal = d' + dot.  The signs are fp4 values (+-1, four bits each), and one
+// v_mfma_scale_f32_32x32x64_f8f6f4 forms 32 x 32 cells over 64 of them in two blocks of 32, each with a scale of its own:
+// a row's first block is 32 bits of one history item, its second block the same 32 bits of another, the column holds the
+// candidate's bits twice.  With scales 2^(8 - SH) and 2^(16 - SH) and a start of 2^23 + d' (2^(8 - SH) + 2^(16 - SH)) a
+// cell's mantissa is, exactly, 2^(8 - SH) * 2 equal_1 + 2^(16 - SH) * 2 equal_2 -- two history items a cell at half the
+// matrix time and half the operand bytes an item takes as int8.  The candidates are the columns (a lane owns one and
+// gets 32 history items' values of it per tile), the history items the rows: written once per request by k_lsh_expand
+// in the order the instruction reads them, streamed by every wave from L2.  Only the product over ALL bits matters, so
+// any assignment of bits to the instruction's k index serves, as long as rows and columns use the same one.
 //
 // What is left per (candidate, history item) is Eq. 9's count into tiers, and the vector ALU is what binds, so it is
-// done on four values at a time.  N divides 2 d' to a power of two here, so tier = (2 * equal) >> SH; the candidates'
-// bytes are +-2^(8 - SH) instead of +-1, which puts the tier into the SECOND BYTE of the 32-bit cell.  Two byte permutes
-// and an OR bring the tiers of four cells into one word, a third permute (a table of eight bytes) turns them into
-// four one-hot bytes, and the words of one-hot bytes are summed bit position by bit position in a network of
-// carry-save adders (two 3-input bit operations each) whose planes hold the counts in binary.  The planes are read
-// out with population counts at the end (or every 960 words).  About 1.7 vector instructions per value instead of 10.
+// done on four values at a time.  N divides 2 d' to a power of two here, so tier = (2 * equal) >> SH: the scales put the
+// first item's tier into the low bits of the cell's second byte and the other's into its third.  One byte permute and a
+// mask bring the tiers of two cells into one word, a second permute (a table of eight bytes) turns them into four
+// one-hot bytes, and the words of one-hot bytes are summed bit position by bit position in a network of carry-save
+// adders (two 3-input bit operations each) whose planes hold the counts in binary.  The planes are read out with
+// population counts at the end (or every 992 words).  1.3 vector instructions per value (1.75 with one item a cell, as
+// +-1 int8 on v_mfma_i32_32x32x32_i8: 465 us for 64 x 10^4 candidates x 10^4 items of 64 bits, 836 for 8 x 10^4 x 10^5 of
+// 128, against 365 and 553).
 // Two corrections at the end: the rows past the history's end are zero vectors, which count as d' / 2 equal bits and
 // are taken off that tier again; a signature equal to the candidate's in every bit gives tier index N, whose one-hot
 // byte is empty -- the last tier's count is the history length less all the others.
@@ -23,43 +28,44 @@
 namespace aif {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v16i __attribute__((ext_vector_type(16)));
+typedef int v8i __attribute__((ext_vector_type(8)));
+typedef float v16f __attribute__((ext_vector_type(16)));
 
 constexpr int SMT_PART_BLOCKS = 2048; // a batch of fewer blocks than this has its histories cut into parts, a block each
 constexpr int SMT_MAX_PARTS = 16;
-constexpr int SMT_GROUP = 4;         // row tiles (32 history items each) per pass of the adder network
-constexpr int SMT_PLANES = 6;        // planes of weight 16 .. 512 above the network's ones, twos, fours, eights
-constexpr int SMT_FLUSH = 60;        // passes between read-outs: 60 * 16 words (+ 12 of a ragged end) <= 1023, what ten planes count
+constexpr int SMT_TILE = 64;         // history items of a row tile: two a row
+constexpr int SMT_GROUP = 4;         // row tiles per pass of the adder network: 32 words per column tile
+constexpr int SMT_PLANES = 5;        // planes of weight 32 .. 512 above the network's ones .. sixteens
+constexpr int SMT_FLUSH = 31;        // passes between read-outs: 31 * 32 words (+ 24 of a ragged end) <= 1023, what ten planes count
 
-// sixteen signature bits -> sixteen bytes of +scale (bit set) or -scale, bit j in byte j
-__device__ __forceinline__ v4i signed_bytes(uint32_t bits16, uint32_t scale)
+// thirty-two signature bits -> thirty-two fp4 values (-1)^bit, bit j in nibble j
+__device__ __forceinline__ v4i fp4_signs(uint32_t bits)
 {
-    const uint32_t minus = (0x100u - scale) * 0x01010101u, flip = scale ^ (0x100u - scale);
     v4i r;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        const uint32_t x = (((bits16 >> (4 * q)) & 15u) * 0x00204081u) & 0x01010101u;      // bit i of the four in byte i
-        r[q] = (int)(minus ^ (x * flip));                                                   // 1 -> scale, 0 -> 256 - scale
+        uint32_t x = (bits >> (8 * q)) & 0xFFu;                                             // bit i of the eight to nibble i
+        x = (x | x << 12) & 0x000F000Fu;
+        x = (x | x << 6) & 0x03030303u;
+        x = (x | x << 3) & 0x11111111u;
+        r[q] = (int)(x << 3 | 0x22222222u);                                                 // 1.0 is 0010, the sign bit on top
     }
     return r;
 }
 
-// The history of every request as the instruction's row operand: [row tile][k-step][lane] of 16 bytes; lane = (row of
-// the tile, which half of the k-step's 32 bits).  Rows past the end are zero vectors.
+// The history of every request as the instruction's row operand: [row tile][k-step of 32 bits][lane] of 16 bytes; lane =
+// (row of the tile, which of the row's two items: item 32 h + row of the tile).  Items past the end are zero vectors.
 template <int KS>
 __global__ __launch_bounds__(256) void k_lsh_expand(LshBatch b, v4i *__restrict__ out, size_t req_stride)
 {
     const LshReqDesc rd = b.reqs[blockIdx.y];
-    const int nrt = (rd.seq_len + 31) / 32;
+    const int nrt = (rd.seq_len + SMT_TILE - 1) / SMT_TILE;
     const int idx = blockIdx.x * 256 + threadIdx.x;
     if (idx >= nrt * KS * 64) return;
     const int lane = idx & 63, s = (idx >> 6) % KS, rt = idx / (64 * KS);
-    const int row = rt * 32 + (lane & 31), h = lane >> 5;
+    const int item = rt * SMT_TILE + lane;
     v4i v = {0, 0, 0, 0};
-    if (row < rd.seq_len) {
-        const uint32_t w = ((const uint32_t *)rd.seq_sigs)[(size_t)row * KS + s];
-        v = signed_bytes((w >> (16 * h)) & 0xFFFFu, 1u);
-    }
+    if (item < rd.seq_len) v = fp4_signs(((const uint32_t *)rd.seq_sigs)[(size_t)item * KS + s]);
     out[(size_t)blockIdx.y * req_stride + idx] = v;
 }
 
@@ -79,7 +85,7 @@ __device__ __forceinline__ void simtier_store(const LshModel &m, const LshReqDes
         for (int t = 0; t < m.n_tiers; ++t) o[t] = -1;
         return;
     }
-    const int pad_tier = m.d_bits >> sh, pad = (rd.seq_len + 31) / 32 * 32 - rd.seq_len;
+    const int pad_tier = m.d_bits >> sh, pad = (rd.seq_len + SMT_TILE - 1) / SMT_TILE * SMT_TILE - rd.seq_len;
     int32_t below = 0;
 #pragma unroll
     for (int t = 0; t < LSH_MAX_TIERS; ++t) {
@@ -97,9 +103,8 @@ __device__ __forceinline__ void simtier_store(const LshModel &m, const LshReqDes
 // (COLS = 4) two waves share a group and halve the history.  gridDim.y > 1: the history is cut into that many parts as
 // well, a block each, and the counts go to `parts` [part][candidate slot][tier] for k_lsh_simtier_finish -- for batches
 // too small to fill the chip otherwise (a handful of users with long histories).
-// Every wave reads its row tiles from L2 itself: with 128-bit signatures (4 KB a tile) that stream, not the vector ALU,
-// is what binds, and four column tiles a wave (a tile's bytes serve 128 candidates, two tiles in flight) is what the
-// registers allow.
+// Every wave reads its row tiles from L2 itself; four column tiles a wave (a tile's bytes serve 128 candidates, two to
+// four tiles in flight) is what the registers allow.
 template <int KS, int COLS>
 __global__ __launch_bounds__(256, 2) void k_lsh_simtier_mfma(LshModel m, LshBatch b, const uint8_t *__restrict__ sig_table,
                                                              const v4i *__restrict__ hist, size_t req_stride, int sh,
@@ -122,7 +127,7 @@ __global__ __launch_bounds__(256, 2) void k_lsh_simtier_mfma(LshModel m, LshBatc
     const int cg = wave % GROUPS, hh = wave / GROUPS;   // which candidates of the block, which share of the history
     const int first = blk * LSH_BLOCK - rd.cand_base;
 
-    // column operand: this lane's half of each k-step's 32 bits, for its candidate in each of the column tiles
+    // column operand: each k-step's 32 bits of this lane's candidate in each of the column tiles
     v4i bf[SMT_COLS][KS];
 #pragma unroll
     for (int ct = 0; ct < SMT_COLS; ++ct) {
@@ -131,13 +136,13 @@ __global__ __launch_bounds__(256, 2) void k_lsh_simtier_mfma(LshModel m, LshBatc
         if (id < 0 || id >= m.n_items) id = 0;
         const uint32_t *p = (const uint32_t *)(sig_table + (size_t)id * (KS * 4));
 #pragma unroll
-        for (int s = 0; s < KS; ++s) bf[ct][s] = signed_bytes((p[s] >> (16 * h)) & 0xFFFFu, 1u << (8 - sh));
+        for (int s = 0; s < KS; ++s) bf[ct][s] = fp4_signs(p[s]);              // the same bits for both of a row's items
     }
 #pragma unroll
     for (int t = 0; t < LSH_MAX_TIERS; ++t) cnt[t][tid] = 0;
     __syncthreads();
 
-    const int nrt = (rd.seq_len + 31) / 32;
+    const int nrt = (rd.seq_len + SMT_TILE - 1) / SMT_TILE;
     const int per_part = (nrt + (int)gridDim.y - 1) / (int)gridDim.y;          // row tiles of this block ...
     const int part_begin = min(nrt, (int)blockIdx.y * per_part), part_end = min(nrt, part_begin + per_part);
     const int per_wave = (part_end - part_begin + SHARE - 1) / SHARE;           // ... and of this wave
@@ -146,10 +151,10 @@ __global__ __launch_bounds__(256, 2) void k_lsh_simtier_mfma(LshModel m, LshBatc
 
     // one-hot byte of tier t: bit t; the permute's selectors 0..3 take the second operand's bytes, 4..7 the first's
     constexpr uint32_t HOT_LO = 0x08040201u, HOT_HI = 0x80402010u;
-    uint32_t ones[SMT_COLS], twos[SMT_COLS], fours[SMT_COLS], eights[SMT_COLS], plane[SMT_COLS][SMT_PLANES];
+    uint32_t ones[SMT_COLS], twos[SMT_COLS], fours[SMT_COLS], eights[SMT_COLS], sixteens[SMT_COLS], plane[SMT_COLS][SMT_PLANES];
 #pragma unroll
     for (int ct = 0; ct < SMT_COLS; ++ct) {
-        ones[ct] = twos[ct] = fours[ct] = eights[ct] = 0;
+        ones[ct] = twos[ct] = fours[ct] = eights[ct] = sixteens[ct] = 0;
 #pragma unroll
         for (int j = 0; j < SMT_PLANES; ++j) plane[ct][j] = 0;
     }
@@ -161,35 +166,41 @@ __global__ __launch_bounds__(256, 2) void k_lsh_simtier_mfma(LshModel m, LshBatc
             for (int t = 0; t < LSH_MAX_TIERS; ++t) {
                 const uint32_t mask = 0x01010101u << t;
                 uint32_t n = __builtin_popcount(ones[ct] & mask) + 2 * __builtin_popcount(twos[ct] & mask) +
-                             4 * __builtin_popcount(fours[ct] & mask) + 8 * __builtin_popcount(eights[ct] & mask);
+                             4 * __builtin_popcount(fours[ct] & mask) + 8 * __builtin_popcount(eights[ct] & mask) +
+                             16 * __builtin_popcount(sixteens[ct] & mask);
 #pragma unroll
-                for (int j = 0; j < SMT_PLANES; ++j) n += (uint32_t)__builtin_popcount(plane[ct][j] & mask) << (4 + j);
+                for (int j = 0; j < SMT_PLANES; ++j) n += (uint32_t)__builtin_popcount(plane[ct][j] & mask) << (5 + j);
                 if (n) atomicAdd(&cnt[t][cand], (int32_t)n);
             }
-            ones[ct] = twos[ct] = fours[ct] = eights[ct] = 0;
+            ones[ct] = twos[ct] = fours[ct] = eights[ct] = sixteens[ct] = 0;
 #pragma unroll
             for (int j = 0; j < SMT_PLANES; ++j) plane[ct][j] = 0;
         }
     };
 
-    // The one-hot words of one row tile against column tile ct.  The cells start from d' * 2^(8 - SH) and end as
-    // (2 * equal) << (8 - SH): their second byte is the tier.  The start value is kept in registers of its own (it is
-    // no inline constant; formed anew it would cost an instruction per cell).
-    v16i start;
+    // The one-hot words of one row tile against column tile ct.  The cells' start value is kept in registers of its own
+    // (it is no inline constant; formed anew it would cost an instruction per cell).
+    const uint32_t tier_mask = (uint32_t)(2 * m.n_tiers - 1) * 0x01010101u;
+    const int scale = 127 + (h ? 16 - sh : 8 - sh);             // this lane's block of the row: E8M0
+    v16f start;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) start[i] = (32 * KS) << (8 - sh);
+    for (int i = 0; i < 16; ++i) start[i] = (float)((1 << 23) + ((32 * KS) << (8 - sh)) + ((32 * KS) << (16 - sh)));
 #pragma unroll
     for (int i = 0; i < 16; ++i) asm volatile("" : "+v"(start[i]));
-    auto tile_words = [&](const v4i(&af)[KS], int ct, uint32_t(&w)[4]) {
-        v16i acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(af[0], bf[ct][0], start, 0, 0, 0);
+    auto tile_words = [&](const v4i(&af)[KS], int ct, uint32_t(&w)[8]) {
+        v16f acc = start;
 #pragma unroll
-        for (int s = 1; s < KS; ++s) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(af[s], bf[ct][s], acc, 0, 0, 0);
+        for (int s = 0; s < KS; ++s) {
+            const v8i a = {af[s][0], af[s][1], af[s][2], af[s][3], 0, 0, 0, 0};            // fp4 operands take four registers
+            const v8i c = {bf[ct][s][0], bf[ct][s][1], bf[ct][s][2], bf[ct][s][3], 0, 0, 0, 0};
+            acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, c, acc, 4, 4, 0, scale, 0, 127);
+        }
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            // second bytes of cells 4q, 4q + 1 into bytes 0, 1 and of 4q + 2, 4q + 3 into bytes 2, 3 (selector 12: a zero byte)
-            const uint32_t lo = __builtin_amdgcn_perm((uint32_t)acc[4 * q + 1], (uint32_t)acc[4 * q], 0x0C0C0501u);
-            const uint32_t hi = __builtin_amdgcn_perm((uint32_t)acc[4 * q + 3], (uint32_t)acc[4 * q + 2], 0x05010C0Cu);
-            w[q] = __builtin_amdgcn_perm(HOT_HI, HOT_LO, lo | hi);
+        for (int q = 0; q < 8; ++q) {
+            // second and third bytes of cells 2q and 2q + 1; the low bits of each are a tier, 0 .. N (above the second
+            // byte's tier lies what the other item's count leaves below its own tier: 2^(17 - SH) and up)
+            const uint32_t t = __builtin_amdgcn_perm(__float_as_uint(acc[2 * q + 1]), __float_as_uint(acc[2 * q]), 0x06050201u);
+            w[q] = __builtin_amdgcn_perm(HOT_HI, HOT_LO, t & tier_mask);
         }
     };
     auto load_rows = [&](int rt, v4i(&af)[KS]) {
@@ -208,29 +219,28 @@ __global__ __launch_bounds__(256, 2) void k_lsh_simtier_mfma(LshModel m, LshBatc
 #pragma unroll
         for (int u = 0; u < AHEAD; ++u) load_rows(rt0 + u, rows[u]);
     for (; rt0 + SMT_GROUP <= rt_end; rt0 += SMT_GROUP) {
-        uint32_t f[SMT_COLS], e[SMT_COLS];                      // carries of weight 4 and 8 waiting for their partner
+        uint32_t e[SMT_COLS], f[SMT_COLS];                      // carries of weight 8 and 16 waiting for their partner
 #pragma unroll
         for (int u = 0; u < SMT_GROUP; ++u) {
-            uint32_t w[SMT_COLS][4];
-#pragma unroll
-            for (int ct = 0; ct < SMT_COLS; ++ct) tile_words(rows[u % AHEAD], ct, w[ct]);
-            load_rows(min(rt0 + u + AHEAD, rt_last), rows[u % AHEAD]);
 #pragma unroll
             for (int ct = 0; ct < SMT_COLS; ++ct) {
-                uint32_t ca, cb, fu;
-                csa(ones[ct], ca, ones[ct], w[ct][0], w[ct][1]);
-                csa(ones[ct], cb, ones[ct], w[ct][2], w[ct][3]);
-                csa(twos[ct], fu, twos[ct], ca, cb);
+                uint32_t w[8], c[4], d[2], eu;
+                tile_words(rows[u % AHEAD], ct, w);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) csa(ones[ct], c[q], ones[ct], w[2 * q], w[2 * q + 1]);
+                csa(twos[ct], d[0], twos[ct], c[0], c[1]);
+                csa(twos[ct], d[1], twos[ct], c[2], c[3]);
+                csa(fours[ct], eu, fours[ct], d[0], d[1]);
                 if (u % 2 == 0)
-                    f[ct] = fu;
+                    e[ct] = eu;
                 else {
-                    uint32_t eu;
-                    csa(fours[ct], eu, fours[ct], f[ct], fu);
+                    uint32_t fu;
+                    csa(eights[ct], fu, eights[ct], e[ct], eu);
                     if (u == 1)
-                        e[ct] = eu;
+                        f[ct] = fu;
                     else {
-                        uint32_t up;                            // weight 16: rippled into the planes
-                        csa(eights[ct], up, eights[ct], e[ct], eu);
+                        uint32_t up;                            // weight 32: rippled into the planes
+                        csa(sixteens[ct], up, sixteens[ct], f[ct], fu);
 #pragma unroll
                         for (int j = 0; j < SMT_PLANES; ++j) {
                             const uint32_t next = plane[ct][j] & up;
@@ -240,27 +250,29 @@ __global__ __launch_bounds__(256, 2) void k_lsh_simtier_mfma(LshModel m, LshBatc
                     }
                 }
             }
+            load_rows(min(rt0 + u + AHEAD, rt_last), rows[u % AHEAD]);
         }
         if (++passes == SMT_FLUSH) {
             read_out();
             passes = 0;
         }
     }
-    // the last one to three row tiles: every word rippled through all the planes (16 more words: still within what they count)
+    // the last one to three row tiles: every word rippled through all the planes (24 more words: still within what they count)
     for (; rt0 < rt_end; ++rt0) {
         v4i af[KS];
         load_rows(rt0, af);
 #pragma unroll
         for (int ct = 0; ct < SMT_COLS; ++ct) {
-            uint32_t w[4];
+            uint32_t w[8];
             tile_words(af, ct, w);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
+            for (int q = 0; q < 8; ++q) {
                 uint32_t up = w[q], next;
                 next = ones[ct] & up, ones[ct] ^= up, up = next;
                 next = twos[ct] & up, twos[ct] ^= up, up = next;
                 next = fours[ct] & up, fours[ct] ^= up, up = next;
                 next = eights[ct] & up, eights[ct] ^= up, up = next;
+                next = sixteens[ct] & up, sixteens[ct] ^= up, up = next;
 #pragma unroll
                 for (int j = 0; j < SMT_PLANES; ++j) {
                     next = plane[ct][j] & up;
@@ -317,13 +329,13 @@ bool lsh_simtier_on_mfma(const LshModel &m)
 {
     static_assert(LSH_MAX_TIERS == 8, "eight one-hot bits a byte, eight counts a slot");
     const int sh = simtier_shift(m);
-    // the candidates' bytes are +-2^(8 - shift): at least 1
+    // the first item's scale is 2^(8 - shift), an integer
     return (m.d_bits == 32 || m.d_bits == 64 || m.d_bits == 128) && sh >= 0 && sh <= 8;
 }
 
 size_t lsh_hist_stride(const LshModel &m, int max_seq_len)      // 16-byte pieces per request
 {
-    return (size_t)((max_seq_len + 31) / 32) * (m.d_bits / 32) * 64;
+    return (size_t)((max_seq_len + SMT_TILE - 1) / SMT_TILE) * (m.d_bits / 32) * 64;
 }
 
 size_t lsh_simtier_parts_bytes() { return (size_t)(SMT_PART_BLOCKS + SMT_MAX_PARTS) * LSH_BLOCK * LSH_MAX_TIERS * 4; }
@@ -335,7 +347,7 @@ hipError_t launch_lsh_simtier_mfma(const LshModel &m, const LshBatch &b, const u
     if (!lsh_simtier_on_mfma(m) || !hist || !parts) return hipErrorInvalidValue;
     const int sh = simtier_shift(m);
     const int ks = m.d_bits / 32;
-    const int nrt = (longest + 31) / 32, pieces = nrt * ks * 64;
+    const int nrt = (longest + SMT_TILE - 1) / SMT_TILE, pieces = nrt * ks * 64;
     if (pieces > 0) {
         const dim3 grid((pieces + 255) / 256, b.n_req);
         switch (ks) {
