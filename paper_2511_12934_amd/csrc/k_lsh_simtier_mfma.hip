@@ -17,9 +17,9 @@
 // mask bring the tiers of two cells into one word, a second permute (a table of eight bytes) turns them into four
 // one-hot bytes, and the words of one-hot bytes are summed bit position by bit position in a network of carry-save
 // adders (two 3-input bit operations each) whose planes hold the counts in binary.  The planes are read out with
-// population counts at the end (or every 992 words).  1.3 vector instructions per value (1.75 with one item a cell, as
+// population counts at the end (or every 2016 words).  1.3 vector instructions per value (1.75 with one item a cell, as
 // +-1 int8 on v_mfma_i32_32x32x32_i8: 465 us for 64 x 10^4 candidates x 10^4 items of 64 bits, 836 for 8 x 10^4 x 10^5 of
-// 128, against 365 and 553).
+// 128, against 345 and 542).
 // Two corrections at the end: the rows past the history's end are zero vectors, which count as d' / 2 equal bits and
 // are taken off that tier again; a signature equal to the candidate's in every bit gives tier index N, whose one-hot
 // byte is empty -- the last tier's count is the history length less all the others.
@@ -35,8 +35,8 @@ constexpr int SMT_PART_BLOCKS = 2048; // a batch of fewer blocks than this has i
 constexpr int SMT_MAX_PARTS = 16;
 constexpr int SMT_TILE = 64;         // history items of a row tile: two a row
 constexpr int SMT_GROUP = 4;         // row tiles per pass of the adder network: 32 words per column tile
-constexpr int SMT_PLANES = 5;        // planes of weight 32 .. 512 above the network's ones .. sixteens
-constexpr int SMT_FLUSH = 31;        // passes between read-outs: 31 * 32 words (+ 24 of a ragged end) <= 1023, what ten planes count
+constexpr int SMT_PLANES = 6;        // planes of weight 32 .. 1024 above the network's ones .. sixteens
+constexpr int SMT_FLUSH = 63;        // passes between read-outs: 63 * 32 words (+ 24 of a ragged end) <= 2047, what eleven planes count
 
 // thirty-two signature bits -> thirty-two fp4 values (-1)^bit, bit j in nibble j
 __device__ __forceinline__ v4i fp4_signs(uint32_t bits)
@@ -106,7 +106,7 @@ __device__ __forceinline__ void simtier_store(const LshModel &m, const LshReqDes
 // Every wave reads its row tiles from L2 itself; four column tiles a wave (a tile's bytes serve 128 candidates, two to
 // four tiles in flight) is what the registers allow.
 template <int KS, int COLS>
-__global__ __launch_bounds__(256, 2) void k_lsh_simtier_mfma(LshModel m, LshBatch b, const uint8_t *__restrict__ sig_table,
+__global__ __launch_bounds__(256, KS <= 2 ? 3 : 2) void k_lsh_simtier_mfma(LshModel m, LshBatch b, const uint8_t *__restrict__ sig_table,
                                                              const v4i *__restrict__ hist, size_t req_stride, int sh,
                                                              int32_t *__restrict__ parts)
 {
@@ -211,26 +211,36 @@ __global__ __launch_bounds__(256, 2) void k_lsh_simtier_mfma(LshModel m, LshBatc
     int passes = 0, rt0 = rt_begin;
     // a row tile is asked for AHEAD tiles before its turn, into the registers of the tile just read (past the last
     // whole pass the last tile is asked for again)
-    constexpr int AHEAD = KS * COLS > 8 ? 2 : SMT_GROUP;        // the registers a long signature's operands leave
+    constexpr int AHEAD = KS >= 2 ? 2 : SMT_GROUP;              // what keeps 64-bit signatures at three waves a SIMD (2 % faster than four ahead at two)
     static_assert(SMT_GROUP % AHEAD == 0, "a tile's registers are the same in every pass");
     v4i rows[AHEAD][KS];
     const int rt_last = rt_begin + (rt_end - rt_begin) / SMT_GROUP * SMT_GROUP - 1;      // of the whole passes
     if (rt0 + SMT_GROUP <= rt_end)
 #pragma unroll
         for (int u = 0; u < AHEAD; ++u) load_rows(rt0 + u, rows[u]);
+    // one row tile's words into the ones, twos, fours of column tile ct; the carry has weight 8
+    auto add_tile = [&](const v4i(&af)[KS], int ct) __attribute__((always_inline)) {
+        uint32_t w[8], c[4], d[2], up;
+        tile_words(af, ct, w);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) csa(ones[ct], c[q], ones[ct], w[2 * q], w[2 * q + 1]);
+        csa(twos[ct], d[0], twos[ct], c[0], c[1]);
+        csa(twos[ct], d[1], twos[ct], c[2], c[3]);
+        csa(fours[ct], up, fours[ct], d[0], d[1]);
+        return up;
+    };
+    auto ripple = [&](uint32_t up, uint32_t &p) {
+        const uint32_t next = p & up;
+        p ^= up;
+        return next;
+    };
     for (; rt0 + SMT_GROUP <= rt_end; rt0 += SMT_GROUP) {
         uint32_t e[SMT_COLS], f[SMT_COLS];                      // carries of weight 8 and 16 waiting for their partner
 #pragma unroll
         for (int u = 0; u < SMT_GROUP; ++u) {
 #pragma unroll
             for (int ct = 0; ct < SMT_COLS; ++ct) {
-                uint32_t w[8], c[4], d[2], eu;
-                tile_words(rows[u % AHEAD], ct, w);
-#pragma unroll
-                for (int q = 0; q < 4; ++q) csa(ones[ct], c[q], ones[ct], w[2 * q], w[2 * q + 1]);
-                csa(twos[ct], d[0], twos[ct], c[0], c[1]);
-                csa(twos[ct], d[1], twos[ct], c[2], c[3]);
-                csa(fours[ct], eu, fours[ct], d[0], d[1]);
+                const uint32_t eu = add_tile(rows[u % AHEAD], ct);
                 if (u % 2 == 0)
                     e[ct] = eu;
                 else {
@@ -242,11 +252,7 @@ __global__ __launch_bounds__(256, 2) void k_lsh_simtier_mfma(LshModel m, LshBatc
                         uint32_t up;                            // weight 32: rippled into the planes
                         csa(sixteens[ct], up, sixteens[ct], f[ct], fu);
 #pragma unroll
-                        for (int j = 0; j < SMT_PLANES; ++j) {
-                            const uint32_t next = plane[ct][j] & up;
-                            plane[ct][j] ^= up;
-                            up = next;
-                        }
+                        for (int j = 0; j < SMT_PLANES; ++j) up = ripple(up, plane[ct][j]);
                     }
                 }
             }
@@ -257,29 +263,15 @@ __global__ __launch_bounds__(256, 2) void k_lsh_simtier_mfma(LshModel m, LshBatc
             passes = 0;
         }
     }
-    // the last one to three row tiles: every word rippled through all the planes (24 more words: still within what they count)
+    // the last one to three row tiles, their carries rippled from weight 8 up
     for (; rt0 < rt_end; ++rt0) {
         v4i af[KS];
         load_rows(rt0, af);
 #pragma unroll
         for (int ct = 0; ct < SMT_COLS; ++ct) {
-            uint32_t w[8];
-            tile_words(af, ct, w);
+            uint32_t up = ripple(ripple(add_tile(af, ct), eights[ct]), sixteens[ct]);
 #pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                uint32_t up = w[q], next;
-                next = ones[ct] & up, ones[ct] ^= up, up = next;
-                next = twos[ct] & up, twos[ct] ^= up, up = next;
-                next = fours[ct] & up, fours[ct] ^= up, up = next;
-                next = eights[ct] & up, eights[ct] ^= up, up = next;
-                next = sixteens[ct] & up, sixteens[ct] ^= up, up = next;
-#pragma unroll
-                for (int j = 0; j < SMT_PLANES; ++j) {
-                    next = plane[ct][j] & up;
-                    plane[ct][j] ^= up;
-                    up = next;
-                }
-            }
+            for (int j = 0; j < SMT_PLANES; ++j) up = ripple(up, plane[ct][j]);
         }
     }
     read_out();
