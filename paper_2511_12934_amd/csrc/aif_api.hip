@@ -69,6 +69,20 @@ struct DevBuf {
     }
 };
 
+// A range of a DevBuf: sized first, given its place once the whole has been allocated.
+struct DevRange {
+    void *p = nullptr;
+    size_t off = 0;
+    bool used = false;
+    void want(size_t bytes, size_t *total)
+    {
+        off = *total;
+        used = true;
+        *total = align_up(off + bytes, 256);
+    }
+    void place(const DevBuf &b) { p = used ? (char *)b.p + off : nullptr; }
+};
+
 }  // namespace
 
 struct aif_ctx {
@@ -77,13 +91,14 @@ struct aif_ctx {
     int max_seq_len = 0, max_candidates = 0, max_users = 0;
     const void *table = nullptr;
 
-    // repacked weights (owned)
-    DevBuf w1u;                       // fp32 [d_user, H1]: user columns of layer 1, transposed
-    DevBuf wq;                        // fp32 [d_attn, d_item] (generic attention)
-    DevBuf wq_pieces;                 // W_q as bf16 pieces (generic attention)
-    DevBuf wt[MAX_LAYERS];            // fp32 transposed [K_l, N_l] (generic MLP)
-    DevBuf w_pieces[MAX_LAYERS];      // the same as bf16 pieces (generic MLP)
-    DevBuf bias[MAX_LAYERS];          // fp32 [N_l]
+    // repacked weights: ranges of two allocations (owned) -- an allocation costs a context's creation some 30 us
+    DevBuf weights, weight_pieces;
+    DevRange w1u;                     // fp32 [d_user, H1]: user columns of layer 1, transposed
+    DevRange wq;                      // fp32 [d_attn, d_item] (generic attention)
+    DevRange wq_pieces;               // W_q as bf16 pieces (generic attention)
+    DevRange wt[MAX_LAYERS];          // fp32 transposed [K_l, N_l] (generic MLP)
+    DevRange w_pieces[MAX_LAYERS];    // the same as bf16 pieces (generic MLP)
+    DevRange bias[MAX_LAYERS];        // fp32 [N_l]
     bool has_bias[MAX_LAYERS] = {};
     bool has_wq = false;
     MfmaPlan mfma{};                  // MFMA kernels' packed weights and eligibility
@@ -150,12 +165,8 @@ int round_up(int v, int a) { return (v + a - 1) / a * a; }
 void destroy(aif_ctx *c)
 {
     if (!c) return;
-    c->w1u.release();
-    c->wq.release();
-    c->wq_pieces.release();
-    for (auto &b : c->w_pieces) b.release();
-    for (auto &b : c->wt) b.release();
-    for (auto &b : c->bias) b.release();
+    c->weights.release();
+    c->weight_pieces.release();
     mfma_release(c->mfma);
     c->X.release();
     c->bias1.release();
@@ -261,37 +272,51 @@ aif_status init_impl(const aif_config *cfg, const aif_weights *wts, aif_ctx *c)
     // ---- weight copies ---------------------------------------------------
     hipStream_t s = nullptr;
     const int H1 = m.dims[1];
-    HIP_TRY(nullptr, c->w1u.alloc((size_t)H1 * m.d_user * 4));
+    c->has_wq = wts->w_q != nullptr;
+    {
+        size_t total = 0;
+        c->w1u.want((size_t)H1 * m.d_user * 4, &total);
+        for (int l = 0; l < m.n_layers; ++l) {
+            c->wt[l].want((size_t)(m.dims[l] - (l == 0 ? m.d_user : 0)) * m.dims[l + 1] * 4, &total);
+            c->has_bias[l] = wts->b && wts->b[l];
+            if (c->has_bias[l]) c->bias[l].want((size_t)m.dims[l + 1] * 4, &total);
+        }
+        if (c->has_wq) c->wq.want((size_t)m.d_attn * m.d_item * 4, &total);
+        HIP_TRY(nullptr, c->weights.alloc(total));
+        c->w1u.place(c->weights);
+        c->wq.place(c->weights);
+        for (int l = 0; l < m.n_layers; ++l) {
+            c->wt[l].place(c->weights);
+            c->bias[l].place(c->weights);
+        }
+    }
     HIP_TRY(nullptr, launch_pack_transposed(m.dtype, wts->w[0], H1, m.dims[0], 0, m.d_user, (float *)c->w1u.p, s));
     for (int l = 0; l < m.n_layers; ++l) {
         const int n_in = m.dims[l], n_out = m.dims[l + 1];
         const int col0 = l == 0 ? m.d_user : 0, ncols = n_in - col0;
-        HIP_TRY(nullptr, c->wt[l].alloc((size_t)ncols * n_out * 4));
         HIP_TRY(nullptr, launch_pack_transposed(m.dtype, wts->w[l], n_out, n_in, col0, ncols, (float *)c->wt[l].p, s));
-        const void *bl = wts->b ? wts->b[l] : nullptr;
-        c->has_bias[l] = bl != nullptr;
-        if (bl) {
-            HIP_TRY(nullptr, c->bias[l].alloc((size_t)n_out * 4));
-            HIP_TRY(nullptr, launch_to_f32(m.dtype, bl, 1, n_out, n_out, 0, (float *)c->bias[l].p, s));
-        }
+        if (c->has_bias[l]) HIP_TRY(nullptr, launch_to_f32(m.dtype, wts->b[l], 1, n_out, n_out, 0, (float *)c->bias[l].p, s));
     }
-    c->has_wq = wts->w_q != nullptr;
     if (c->has_wq) {
-        HIP_TRY(nullptr, c->wq.alloc((size_t)m.d_attn * m.d_item * 4));
         HIP_TRY(nullptr, launch_to_f32(m.dtype, wts->w_q, m.d_attn, m.d_item, m.d_item, 0, (float *)c->wq.p, s));
     }
     c->x_rows = (size_t)c->max_users * round_up(c->max_candidates, ROW_BLOCK);
     HIP_TRY(nullptr, mfma_plan(m, c->max_seq_len, c->max_users, c->x_rows, wts->w_q, wts->w, c->mfma, s));
-    if (!c->mfma.attn && c->has_wq && attn_generic_gathers(m)) {
-        HIP_TRY(nullptr, c->wq_pieces.alloc(pieces_bytes(m.dtype, m.n_heads, m.d_head, m.d_item)));
-        HIP_TRY(nullptr, launch_pack_pieces(m.dtype, wts->w_q, m.n_heads, m.d_head, m.d_item, 0, m.d_item, c->wq_pieces.p, s));
-    }
-    if (!c->mfma.mlp)
-        for (int l = 0; l < m.n_layers; ++l) {
-            const int col0 = l == 0 ? m.d_user : 0, ncols = m.dims[l] - col0;
-            HIP_TRY(nullptr, c->w_pieces[l].alloc(pieces_bytes(m.dtype, 1, m.dims[l + 1], ncols)));
-            HIP_TRY(nullptr, launch_pack_pieces(m.dtype, wts->w[l], 1, m.dims[l + 1], m.dims[l], col0, ncols, c->w_pieces[l].p, s));
+    {
+        const bool wq_pieces = !c->mfma.attn && c->has_wq && attn_generic_gathers(m);
+        size_t total = 0;
+        if (wq_pieces) c->wq_pieces.want(pieces_bytes(m.dtype, m.n_heads, m.d_head, m.d_item), &total);
+        for (int l = 0; l < m.n_layers && !c->mfma.mlp; ++l)
+            c->w_pieces[l].want(pieces_bytes(m.dtype, 1, m.dims[l + 1], m.dims[l] - (l == 0 ? m.d_user : 0)), &total);
+        if (total) HIP_TRY(nullptr, c->weight_pieces.alloc(total));
+        c->wq_pieces.place(c->weight_pieces);
+        if (wq_pieces) HIP_TRY(nullptr, launch_pack_pieces(m.dtype, wts->w_q, m.n_heads, m.d_head, m.d_item, 0, m.d_item, c->wq_pieces.p, s));
+        for (int l = 0; l < m.n_layers && !c->mfma.mlp; ++l) {
+            const int col0 = l == 0 ? m.d_user : 0;
+            c->w_pieces[l].place(c->weight_pieces);
+            HIP_TRY(nullptr, launch_pack_pieces(m.dtype, wts->w[l], 1, m.dims[l + 1], m.dims[l], col0, m.dims[l] - col0, c->w_pieces[l].p, s));
         }
+    }
     // both consumers of the workspace read MFMA fragments: keep it in fragment order (x_offset)
     {
         const char *rm = getenv("AIF_X_ROW_MAJOR");      // testing: the MFMA kernels on the row-major layout
@@ -435,8 +460,9 @@ static aif_status score_impl(aif_ctx *c, const aif_request *reqs, int32_t n_req,
         }
     }
     c->last_slots = n_slots;
-    int rows = 0;
+    int rows = 0, longest = 0;
     for (int r = 0; r < n_req; ++r) {
+        longest = std::max(longest, reqs[r].seq_len);
         const aif_request &q = reqs[r];
         ReqDesc &e = hd[r];
         e.pad_ = 0;
@@ -554,7 +580,7 @@ static aif_status score_impl(aif_ctx *c, const aif_request *reqs, int32_t n_req,
                                     attn_indexes ? (int32_t *)c->bad.p : nullptr));
     else
         HIP_TRY(c, launch_attn_generic(m, b, c->X.p, c->has_wq ? (const float *)c->wq.p : nullptr, c->wq_pieces.p,
-                                       attn_indexes ? c->table : nullptr, (int32_t *)c->bad.p, c->max_seq_len, s));
+                                       attn_indexes ? c->table : nullptr, (int32_t *)c->bad.p, c->max_seq_len, longest, s));
     HIP_TRY(c, mark(3));
     if (c->mfma.mlp) {
         const float *bf[MAX_LAYERS];
@@ -743,7 +769,7 @@ aif_status aif_score_topk_static(aif_ctx *c, const aif_request *req, int32_t k, 
         HIP_TRY(c, launch_attn_mfma(m, b, X, plan, fused || staged_proj, s, attn_indexes ? c->table : nullptr, attn_indexes ? bad : nullptr));
     else
         HIP_TRY(c, launch_attn_generic(m, b, X, c->has_wq ? (const float *)c->wq.p : nullptr, c->wq_pieces.p,
-                                       attn_indexes ? c->table : nullptr, bad, c->max_seq_len, s));
+                                       attn_indexes ? c->table : nullptr, bad, c->max_seq_len, q.seq_len, s));
     if (plan.mlp) {
         const float *bf[MAX_LAYERS];
         for (int l = 0; l < m.n_layers; ++l) bf[l] = c->has_bias[l] ? (const float *)c->bias[l].p : nullptr;

@@ -125,9 +125,9 @@ hipError_t launch_user_fold(const Model &m, const Batch &b, const float *w1u, co
 // a3-a5, any shape, fp32 precision: X[row, d_item:] = [attention | cross].  wq: W_q in fp32 (null: the model has none)
 // and wq_pieces: the same as launch_pack_pieces leaves it, a group per head (used where attn_generic_gathers(m)).
 // table: non-null only where attn_generic_gathers(m): the kernel then takes the item rows from the table itself (a1),
-// writes them to the workspace and counts ids outside the table in *bad.
+// writes them to the workspace and counts ids outside the table in *bad.  longest: the longest history of the batch.
 hipError_t launch_attn_generic(const Model &m, const Batch &b, void *X, const float *wq, const void *wq_pieces, const void *table,
-                               int32_t *bad, int max_seq_len, hipStream_t s);
+                               int32_t *bad, int max_seq_len, int longest, hipStream_t s);
 bool attn_generic_gathers(const Model &m);
 size_t attn_generic_lds_bytes(const Model &m, int max_seq_len);
 

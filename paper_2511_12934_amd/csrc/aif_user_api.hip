@@ -226,8 +226,9 @@ aif_status aif_user_precompute(aif_user_ctx *c, const aif_user_request *users, i
     ReqDesc *hr = (ReqDesc *)h;
     UserDesc *hu = (UserDesc *)(h + (size_t)n_users * sizeof(ReqDesc));
     int32_t *hb = (int32_t *)(h + (size_t)n_users * (sizeof(ReqDesc) + sizeof(UserDesc)));
-    int rows = 0;
+    int rows = 0, longest = 0;
     for (int r = 0; r < n_users; ++r) {
+        longest = users[r].seq_len > longest ? users[r].seq_len : longest;
         const aif_user_request &q = users[r];
         ReqDesc &e = hr[r];
         memset(&e, 0, sizeof e);
@@ -267,7 +268,7 @@ aif_status aif_user_precompute(aif_user_ctx *c, const aif_user_request *users, i
     if (c->mfma.attn)
         USER_TRY(c, launch_attn_mfma(m, b, c->X, c->mfma, false, s));
     else
-        USER_TRY(c, launch_attn_generic(m, b, c->X, nullptr, nullptr, nullptr, nullptr, c->max_seq_len, s));
+        USER_TRY(c, launch_attn_generic(m, b, c->X, nullptr, nullptr, nullptr, nullptr, c->max_seq_len, longest, s));
     if (pe) USER_TRY(c, hipEventRecord(pe[2], s));
     USER_TRY(c, launch_user_ffn_partial(c->w, du, b.blk_req, b.n_blk, c->X, (float *)c->part, s));
     USER_TRY(c, launch_user_combine(c->w, du, n_users, c->X, (const float *)c->part, s));

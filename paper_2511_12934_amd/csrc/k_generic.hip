@@ -272,27 +272,28 @@ __global__ __launch_bounds__(256) void k_attn_generic(Model m, Batch b, T *__res
 
 // ---------------------------------------------------------------------------
 // The same for heads of up to GEN_MAX_HEAD, on the matrix cores and with the
-// gather (a1) inside.  A wave owns 16 NC candidates, the columns of every
-// product, and a block of WV waves shares the request's keys:
+// gather (a1) inside.  A wave owns 16 candidates, the columns of every product,
+// and a block of WV waves shares the request's keys:
 //   Q^T = W_q E^T (a head's features in tiles of 16), S^T = K Q^T, O^T = V^T P^T.
 // A 16x16 result leaves features (keys) 4 g + i of one candidate in a lane
 // (g = lane / 16), and two such tiles are, in place, the eight k-values a lane
 // owes the next product's B operand once K (V) is read in the same order:
 // k-value j of group g is feature (key) 4 g + j of the first tile, or
 // 16 + 4 g + j - 4 of the second.  Nothing is exchanged between lanes but the
-// softmax maximum.  32 keys at a time go through LDS as pieces in fragment
-// order, split by the block's threads (the next 32 are on their way from
-// memory meanwhile); the softmax is the running one, its rescaling skipped by a
-// wave none of whose candidates found a larger score (a factor of exactly one
-// otherwise: same bits).
+// softmax maximum.  Keys go through LDS as pieces in fragment order, split by
+// the block's threads: all at once where they fit, else 32 at a time (the next 32
+// are on their way from memory meanwhile); the softmax is the running one, its
+// rescaling skipped by a wave none of whose candidates found a larger score (a
+// factor of exactly one otherwise: same bits).
 //
-// What bounds it: the vector ALU -- per key and candidate one expf and three
-// pieces of the weight, about 20 instructions -- and on short histories (L = 50,
-// d = 32) the chain row -> query -> scores of a wave.  Measured (fp32, L <= 50,
-// d_attn 32 of W_q, rows of 64): 16 users of 6,200 candidates on average 51 us,
-// where a wave per candidate on the vector ALU and a gather launch before it
-// took 230 + 13; one request of 1,000: 14 against 22 + 6; bf16, 16 x 10^4: 62
-// against 312 + 10.
+// What bounds it: short histories (L = 50, d = 32) the chain id -> row -> query
+// -> scores of a wave, which is why a block of resident keys takes no barrier and
+// stays under 128 registers (four waves a SIMD); then the vector ALU -- per key
+// and candidate one exponential and three pieces of the weight.  Measured (L <=
+// 50, d_attn 32 of W_q, rows of 64): fp32, 16 users of 6,200 candidates on average
+// 36 us, bf16, 16 x 10^4: 38 -- 230 + 13 and 312 + 10 with a wave per candidate on
+// the vector ALU after a gather launch, 48 and 55 with the keys 32 at a time; fp32,
+// one request of 1,000: 11.5 against 22 + 6.
 // ---------------------------------------------------------------------------
 constexpr int GEN_MAX_HEAD = 128;
 constexpr int GEN_KEYS = 32;
@@ -344,292 +345,296 @@ __device__ __noinline__ void attn_plain(const T *e, const T *K, const T *V, cons
         if (lane + 64 * s < dh) st_f<T>(out + lane + 64 * s, L > 0 ? acc[s] / sum : 0.f);
 }
 
-// FT: tiles of 16 features a head has.  wqp: W_q as pieces, [head][FT'][k-step of 32][piece][64 lanes][8], FT' = FT
-// rounded up to even, rows past the head's width zero (pack_pieces).  table null: the item rows are in the workspace.
-template <typename T, int FT, int NC, int WV, bool WQ>
-__global__ __launch_bounds__(64 * WV) void k_attn_gen(Model m, Batch b, T *__restrict__ X, const T *__restrict__ table,
-                                                      const bf16x8 *__restrict__ wqp, const float *__restrict__ wq,
-                                                      int32_t *__restrict__ bad)
+// exp(x) for x <= 0 to about 1 ulp: the hardware's 2^t of the rounded t = x log2(e), corrected by what the rounding left.
+// NaN for -infinity and NaN: the caller's plain route then takes over.
+__device__ __forceinline__ float exp_neg(float x)
+{
+    constexpr float L = 1.44269502162933349609375f, L_LO = 1.925963033500011e-8f, LN2 = 0.693147182464599609375f;
+    const float t = x * L, e = fmaf(x, L_LO, fmaf(x, L, -t)), p = __builtin_amdgcn_exp2f(t);
+    return fmaf(p, e * LN2, p);
+}
+
+// FT: tiles of 16 features a head has.  WV: waves of the block, 16 candidates each at a time.  wqp: W_q as pieces,
+// [head][FT'][k-step of 32][piece][64 lanes][8], FT' = FT rounded up to even, rows past the head's width zero (pack_pieces).
+// table null: the item rows are in the workspace.
+// RES: the pieces of all the request's keys, of every head, are staged at once, in dynamic LDS, and the block walks a whole
+// ROW_BLOCK of candidates with no further barrier; else 32 keys of one head at a time for 16 WV candidates.
+template <typename T, int FT, int WV, bool WQ, bool RES>
+__global__ __launch_bounds__(64 * WV, FT <= 2 ? 4 : 2) void k_attn_gen(Model m, Batch b, T *__restrict__ X, const T *__restrict__ table,
+                                                                       const bf16x8 *__restrict__ wqp, const float *__restrict__ wq,
+                                                                       int32_t *__restrict__ bad)
 {
     constexpr int P = stored<T>::P, PQ = WQ ? 3 : P, KS = (FT + 1) / 2, VEC = 16 / sizeof(T);
-    constexpr int ITEMS = (2 * KS + FT) * 64;                  // 16-byte fragment pieces (of P) per chunk of keys
-    constexpr int PER = (ITEMS + 64 * WV - 1) / (64 * WV);
-    __shared__ bf16x8 frag[ITEMS * P];                          // [fragment][piece][lane]: K (key tile, k-step), then V (feature tile)
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, col = lane & 15, g = lane >> 4;
-    const int row0 = blockIdx.x * (16 * NC * WV);
+    constexpr int FRAGS = 2 * KS + FT;                          // fragments of a chunk of keys: K (key tile, k-step), then V (feature tile)
+    constexpr int PER = RES ? 2 : (FRAGS + WV - 1) / WV;        // fragments a wave has on their way
+    constexpr float NEVER = -1e30f;                             // the score of a key past the end
+    extern __shared__ __align__(16) char dyn[];
+    bf16x8 *frag;                                               // [head][chunk][fragment][piece][lane]; RES = false: one chunk
+    if constexpr (RES) frag = (bf16x8 *)dyn;
+    else {
+        __shared__ bf16x8 one[FRAGS * P * 64];
+        frag = one;
+    }
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), col = lane & 15, g = lane >> 4;
+    const int row0 = blockIdx.x * (RES ? ROW_BLOCK : 16 * WV);
     const int r = b.blk_req[row0 / ROW_BLOCK];
     if (r < 0) return;
     const ReqDesc rd = b.reqs[r];
     const int local0 = row0 - rd.row_base;
     if (local0 >= rd.n_cand) return;
-    const int L = rd.seq_len, dh = m.d_head, da = m.d_attn;
+    const int L = rd.seq_len, dh = m.d_head, da = m.d_attn, chunks = (L + GEN_KEYS - 1) / GEN_KEYS;
     const bool quad = (dh & 3) == 0;
     const float scale = 1.0f / sqrtf((float)dh);
     const T *K = (const T *)rd.seq_keys, *V = (const T *)rd.seq_vals;
 
-    // a1: the lane's candidates and their item rows
-    const T *er[NC];
-    T *xr[NC];
-    bool live[NC];
-    int n_bad = 0;
+    // fragment f of the chunk of keys from t0, head columns from o: its eight values of this lane, and as pieces to LDS
+    auto fetch = [&](int f, int t0, int o, float (&v)[8]) __attribute__((always_inline)) {
+        if (f < 2 * KS) {
+            const int kt = f / KS, s = f - kt * KS, t = t0 + 16 * kt + col;
+            const T *kr = K + (size_t)(t < L ? t : L - 1) * da + o;
+            load4<T>(kr, 32 * s + 4 * g, dh, quad, v);
+            load4<T>(kr, 32 * s + 16 + 4 * g, dh, quad, v + 4);
+        } else {
+            const int k = 16 * (f - 2 * KS) + col;
+            const T *vr = V + o + (k < dh ? k : 0);
 #pragma unroll
-    for (int n = 0; n < NC; ++n) {
-        const int at = local0 + (wave * NC + n) * 16 + col;
-        live[n] = at < rd.n_cand;
-        const int c = live[n] ? at : rd.n_cand - 1;
-        xr[n] = X + (size_t)(rd.row_base + c) * m.ldx;
+            for (int j = 0; j < 8; ++j) {
+                const int t = t0 + 4 * g + (j & 3) + 16 * (j >> 2);
+                v[j] = ld_f<T>(vr + (size_t)(t < L ? t : L - 1) * da);
+            }
+        }
+    };
+    auto put = [&](int f, int t0, float (&v)[8], bf16x8 *to) __attribute__((always_inline)) {
+        if (f < 2 * KS) {
+            const int t = t0 + 16 * (f / KS) + col;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = t < L ? v[j] : 0.f;
+        } else {
+            const bool on = 16 * (f - 2 * KS) + col < dh;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = on && t0 + 4 * g + (j & 3) + 16 * (j >> 2) < L ? v[j] : 0.f;
+        }
+        const Pieces<P> pc = split8<P>(v);
+#pragma unroll
+        for (int q = 0; q < P; ++q) to[(f * P + q) * 64 + lane] = pc.p[q];
+    };
+    float kv[PER][8];                                           // the chunk of keys on its way
+    auto fetch_chunk = [&](int t0, int o) __attribute__((always_inline)) {
+#pragma unroll
+        for (int it = 0; it < PER; ++it)
+            if (wave + WV * it < FRAGS) fetch(wave + WV * it, t0, o, kv[it]);
+    };
+    auto put_chunk = [&](int t0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int it = 0; it < PER; ++it)
+            if (wave + WV * it < FRAGS) put(wave + WV * it, t0, kv[it], frag);
+    };
+    if constexpr (RES) {
+        const int n = m.n_heads * chunks * FRAGS;               // dealt round the waves, PER at a time
+        for (int i0 = wave; i0 < n; i0 += PER * WV) {
+#pragma unroll
+            for (int it = 0; it < PER; ++it) {
+                const int i = i0 + it * WV, c = i / FRAGS, h = c / chunks;
+                if (i < n) fetch(i - c * FRAGS, (c - h * chunks) * GEN_KEYS, h * dh, kv[it]);
+            }
+#pragma unroll
+            for (int it = 0; it < PER; ++it) {
+                const int i = i0 + it * WV, c = i / FRAGS, h = c / chunks;
+                if (i < n) put(i - c * FRAGS, (c - h * chunks) * GEN_KEYS, kv[it], frag + (size_t)c * FRAGS * P * 64);
+            }
+        }
+    } else if (L > 0)
+        fetch_chunk(0, 0);
+
+    int n_bad = 0;
+    for (int tile = wave; tile < (RES ? ROW_BLOCK / 16 : WV); tile += WV) {
+        if (RES && local0 + tile * 16 >= rd.n_cand) {           // a wave past the end: nothing left but the barrier after the keys
+            if (tile == wave) __syncthreads();
+            break;
+        }
+        // a1: the lane's candidate and its item row
+        const int at = local0 + tile * 16 + col;
+        const bool live = at < rd.n_cand;
+        const int c = live ? at : rd.n_cand - 1;
+        T *xr = X + (size_t)(rd.row_base + c) * m.ldx;
+        const T *er = xr;
         if (table) {
             int64_t id = rd.cand_ids[c];
             if (id < 0 || id >= m.n_items) {
                 id = 0;
-                if (live[n] && g == 0) ++n_bad;
+                if (live && g == 0) ++n_bad;
             }
-            er[n] = table + (size_t)id * m.d_item;
-        } else
-            er[n] = xr[n];
-    }
-    // the row into the workspace, and the Hadamard block beside it
-    {
-        const T *uc = (const T *)rd.cross_vecs;
-        const bool had = m.cross_mode == 1 && !m.cross_in_mlp;
-        constexpr int U = 4;
-        const int pieces = m.d_item / VEC;
-        if (table || had)
-            for (int p0 = 0; p0 < pieces; p0 += 4 * U) {
-                uint4 v[U][NC];
+            er = table + (size_t)id * m.d_item;
+        }
+        // the row into the workspace, and the Hadamard block beside it
+        {
+            const T *uc = (const T *)rd.cross_vecs;
+            const bool had = m.cross_mode == 1 && !m.cross_in_mlp;
+            constexpr int U = 4;
+            const int pieces = m.d_item / VEC;
+            if (table || had)
+                for (int p0 = 0; p0 < pieces; p0 += 4 * U) {
+                    uint4 v[U];
 #pragma unroll
-                for (int u = 0; u < U; ++u)
-#pragma unroll
-                    for (int n = 0; n < NC; ++n) {
+                    for (int u = 0; u < U; ++u) {
                         const int p = p0 + 4 * u + g;
-                        v[u][n] = *(const uint4 *)(er[n] + (size_t)(p < pieces ? p : 0) * VEC);
+                        v[u] = *(const uint4 *)(er + (size_t)(p < pieces ? p : 0) * VEC);
                     }
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int p = p0 + 4 * u + g;
-                    if (p >= pieces) continue;
+                    for (int u = 0; u < U; ++u) {
+                        const int p = p0 + 4 * u + g;
+                        if (p >= pieces || !live) continue;
+                        if (table) *(uint4 *)(xr + (size_t)p * VEC) = v[u];
+                        if (had) {
+                            const uint4 w = *(const uint4 *)(uc + (size_t)p * VEC);
+                            const T *e = (const T *)&v[u], *x = (const T *)&w;
+                            __align__(16) T o[VEC];
 #pragma unroll
-                    for (int n = 0; n < NC; ++n)
-                        if (live[n]) {
-                            if (table) *(uint4 *)(xr[n] + (size_t)p * VEC) = v[u][n];
-                            if (had) {
-                                const T *e = (const T *)&v[u][n];
-                                T *c = xr[n] + m.d_item + da + p * VEC;
-#pragma unroll
-                                for (int k = 0; k < VEC; ++k) st_f<T>(c + k, ld_f<T>(uc + p * VEC + k) * ld_f<T>(e + k));
-                            }
+                            for (int k = 0; k < VEC; ++k) st_f<T>(o + k, ld_f<T>(x + k) * ld_f<T>(e + k));
+                            *(uint4 *)(xr + m.d_item + da + (size_t)p * VEC) = *(const uint4 *)o;
                         }
+                    }
                 }
-            }
-    }
-    if (n_bad) atomicAdd(bad, n_bad);
-    if (!m.cross_in_mlp && (m.cross_mode == 2 || m.cross_mode == 3)) {
-        const T *uc = (const T *)rd.cross_vecs;
-        const int S = m.cross_mode == 2 ? m.d_item / m.d_cv : 1;
-#pragma unroll
-        for (int n = 0; n < NC; ++n) {
-            T *xc = xr[n] + m.d_item + da;
-            if (live[n])
+        }
+        if (!m.cross_in_mlp && (m.cross_mode == 2 || m.cross_mode == 3)) {
+            const T *uc = (const T *)rd.cross_vecs;
+            const int S = m.cross_mode == 2 ? m.d_item / m.d_cv : 1;
+            T *xc = xr + m.d_item + da;
+            if (live)
                 for (int idx = g; idx < m.d_cross; idx += 4) {
                     float acc;
                     if (m.cross_mode == 2) {
                         const int j = idx / S, sg = idx - j * S;
                         acc = dot_in_order(m.d_cv, 0.f, [&](int k) { return ld_f<T>(uc + (size_t)j * m.d_cv + k); },
-                                           [&](int k) { return ld_f<T>(er[n] + sg * m.d_cv + k); });
+                                           [&](int k) { return ld_f<T>(er + sg * m.d_cv + k); });
                     } else      // Algorithm 1 step 4: the row's trailing n_cross entries weigh the user-side vectors
-                        acc = dot_in_order(m.n_cross, 0.f, [&](int j) { return ld_f<T>(er[n] + m.d_item - m.n_cross + j); },
+                        acc = dot_in_order(m.n_cross, 0.f, [&](int j) { return ld_f<T>(er + m.d_item - m.n_cross + j); },
                                            [&](int j) { return ld_f<T>(uc + (size_t)j * m.d_cv + idx); });
                     st_f<T>(xc + idx, acc);
                 }
         }
-    }
 
-    for (int h = 0; h < m.n_heads; ++h) {
-        const int o = h * dh;
-        // the first keys on their way
-        float kv[PER][8];
-        auto fetch = [&](int t0) {
+        for (int h = 0; h < m.n_heads; ++h) {
+            const int o = h * dh;
+            if (!RES && h > 0 && L > 0) fetch_chunk(0, o);      // the first keys on their way (head 0's: since the start)
+            // a3: the query, as pieces in the order of K's fragments
+            Pieces<PQ> qf[KS];
+            if constexpr (WQ) {
+                f32x4 qb[2 * KS], qs[2 * KS];
 #pragma unroll
-            for (int it = 0; it < PER; ++it) {
-                const int f = (threadIdx.x >> 6) + WV * it;      // fragment, the same for a whole wave
-                if (f < 2 * KS) {
-                    const int kt = f / KS, s = f - kt * KS, t = t0 + 16 * kt + col;
-                    const T *kr = K + (size_t)(t < L ? t : L - 1) * da + o;
-                    load4<T>(kr, 32 * s + 4 * g, dh, quad, kv[it]);
-                    load4<T>(kr, 32 * s + 16 + 4 * g, dh, quad, kv[it] + 4);
-                } else if (f < 2 * KS + FT) {
-                    const int k = 16 * (f - 2 * KS) + col;
-                    const T *vr = V + o + (k < dh ? k : 0);
+                for (int f = 0; f < 2 * KS; ++f) qb[f] = qs[f] = f32x4{0.f, 0.f, 0.f, 0.f};
+                const int ksn = (m.d_item + 31) / 32;
+                const bf16x8 *wh = wqp + (size_t)h * (2 * KS) * ksn * P * 64 + lane;
+                for (int ks = 0; ks < ksn; ++ks) {
+                    float v[8];
+                    load8<T>(er + 32 * ks + 8 * g, m.d_item - 32 * ks - 8 * g, v);
+                    const Pieces<P> e = split8<P>(v);
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) {
-                        const int t = t0 + 4 * g + (j & 3) + 16 * (j >> 2);
-                        kv[it][j] = ld_f<T>(vr + (size_t)(t < L ? t : L - 1) * da);
+                    for (int f = 0; f < 2 * KS; ++f) {
+                        Pieces<P> w;
+#pragma unroll
+                        for (int q = 0; q < P; ++q) w.p[q] = wh[((size_t)(f * ksn + ks) * P + q) * 64];
+                        mfma_pieces(w, e, qb[f], qs[f]);
                     }
                 }
-            }
-        };
-        auto put = [&](int t0) {
 #pragma unroll
-            for (int it = 0; it < PER; ++it) {
-                const int f = (threadIdx.x >> 6) + WV * it;
-                if (f >= 2 * KS + FT) continue;
-                if (f < 2 * KS) {
-                    const int t = t0 + 16 * (f / KS) + col;
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) kv[it][j] = t < L ? kv[it][j] : 0.f;
-                } else {
-                    const bool on = 16 * (f - 2 * KS) + col < dh;
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) kv[it][j] = on && t0 + 4 * g + (j & 3) + 16 * (j >> 2) < L ? kv[it][j] : 0.f;
-                }
-                const Pieces<P> pc = split8<P>(kv[it]);
-#pragma unroll
-                for (int q = 0; q < P; ++q) frag[(f * P + q) * 64 + lane] = pc.p[q];
-            }
-        };
-        if (L > 0) fetch(0);
-
-        // a3: the query, as pieces in the order of K's fragments
-        Pieces<PQ> qf[KS][NC];
-        if constexpr (WQ) {
-            f32x4 qb[2 * KS][NC], qs[2 * KS][NC];
-#pragma unroll
-            for (int f = 0; f < 2 * KS; ++f)
-#pragma unroll
-                for (int n = 0; n < NC; ++n) qb[f][n] = qs[f][n] = f32x4{0.f, 0.f, 0.f, 0.f};
-            const int ksn = (m.d_item + 31) / 32;
-            const bf16x8 *wh = wqp + (size_t)h * (2 * KS) * ksn * P * 64 + lane;
-            for (int ks = 0; ks < ksn; ++ks) {
-                Pieces<P> e[NC];
-#pragma unroll
-                for (int n = 0; n < NC; ++n) {
-                    float v[8];
-                    load8<T>(er[n] + 32 * ks + 8 * g, m.d_item - 32 * ks - 8 * g, v);
-                    e[n] = split8<P>(v);
-                }
-#pragma unroll
-                for (int f = 0; f < 2 * KS; ++f) {
-                    Pieces<P> w;
-#pragma unroll
-                    for (int q = 0; q < P; ++q) w.p[q] = wh[((size_t)(f * ksn + ks) * P + q) * 64];
-#pragma unroll
-                    for (int n = 0; n < NC; ++n) mfma_pieces(w, e[n], qb[f][n], qs[f][n]);
-                }
-            }
-#pragma unroll
-            for (int s = 0; s < KS; ++s)
-#pragma unroll
-                for (int n = 0; n < NC; ++n) {
+                for (int s = 0; s < KS; ++s) {
                     float v[8];
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
-                        v[j] = qb[2 * s][n][j] + qs[2 * s][n][j];
-                        v[4 + j] = qb[2 * s + 1][n][j] + qs[2 * s + 1][n][j];
+                        v[j] = qb[2 * s][j] + qs[2 * s][j];
+                        v[4 + j] = qb[2 * s + 1][j] + qs[2 * s + 1][j];
                     }
-                    qf[s][n] = split8<PQ>(v);
+                    qf[s] = split8<PQ>(v);
                 }
-        } else {
-#pragma unroll
-            for (int s = 0; s < KS; ++s)
-#pragma unroll
-                for (int n = 0; n < NC; ++n) {
-                    float v[8];
-                    load4<T>(er[n] + o, 32 * s + 4 * g, dh, quad, v);
-                    load4<T>(er[n] + o, 32 * s + 16 + 4 * g, dh, quad, v + 4);
-                    qf[s][n] = split8<PQ>(v);
-                }
-        }
-
-        // a4: the keys, 32 at a time
-        f32x4 ob[FT][NC], os[FT][NC];
-        float mx[NC], sum[NC];
-#pragma unroll
-        for (int n = 0; n < NC; ++n) {
-            mx[n] = -INFINITY;
-            sum[n] = 0.f;
-#pragma unroll
-            for (int f = 0; f < FT; ++f) ob[f][n] = os[f][n] = f32x4{0.f, 0.f, 0.f, 0.f};
-        }
-        for (int t0 = 0; t0 < L; t0 += GEN_KEYS) {
-            __syncthreads();                                    // the chunk before has been read
-            put(t0);
-            __syncthreads();
-            if (t0 + GEN_KEYS < L) fetch(t0 + GEN_KEYS);
-            float sc[NC][8];
-#pragma unroll
-            for (int kt = 0; kt < 2; ++kt) {
-                f32x4 sb[NC], ss[NC];
-#pragma unroll
-                for (int n = 0; n < NC; ++n) sb[n] = ss[n] = f32x4{0.f, 0.f, 0.f, 0.f};
+            } else {
 #pragma unroll
                 for (int s = 0; s < KS; ++s) {
-                    Pieces<P> k;
-#pragma unroll
-                    for (int q = 0; q < P; ++q) k.p[q] = frag[((kt * KS + s) * P + q) * 64 + lane];
-#pragma unroll
-                    for (int n = 0; n < NC; ++n) mfma_pieces(k, qf[s][n], sb[n], ss[n]);
+                    float v[8];
+                    load4<T>(er + o, 32 * s + 4 * g, dh, quad, v);
+                    load4<T>(er + o, 32 * s + 16 + 4 * g, dh, quad, v + 4);
+                    qf[s] = split8<PQ>(v);
                 }
-#pragma unroll
-                for (int n = 0; n < NC; ++n)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        sc[n][4 * kt + i] = t0 + 16 * kt + 4 * g + i < L ? (sb[n][i] + ss[n][i]) * scale : -INFINITY;
             }
-            Pieces<3> pf[NC];
+            if (RES && h == 0 && tile == wave) __syncthreads(); // the keys are staged
+
+            // a4: the keys, 32 at a time
+            f32x4 ob[FT], os[FT];
+            float mx = -INFINITY, sum = 0.f;
 #pragma unroll
-            for (int n = 0; n < NC; ++n) {
-                float top = fmaxf(fmaxf(fmaxf(sc[n][0], sc[n][1]), fmaxf(sc[n][2], sc[n][3])),
-                                  fmaxf(fmaxf(sc[n][4], sc[n][5]), fmaxf(sc[n][6], sc[n][7])));
+            for (int f = 0; f < FT; ++f) ob[f] = os[f] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int ch = 0; ch < chunks; ++ch) {
+                const int t0 = ch * GEN_KEYS;
+                const bf16x8 *fr = frag + lane;
+                if constexpr (RES) fr += (size_t)(h * chunks + ch) * FRAGS * P * 64;
+                else {
+                    __syncthreads();                            // the chunk before has been read
+                    put_chunk(t0);
+                    __syncthreads();
+                    if (ch + 1 < chunks) fetch_chunk(t0 + GEN_KEYS, o);
+                }
+                float sc[8];
+#pragma unroll
+                for (int kt = 0; kt < 2; ++kt) {
+                    f32x4 sb = {0.f, 0.f, 0.f, 0.f}, ss = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int s = 0; s < KS; ++s) {
+                        Pieces<P> k;
+#pragma unroll
+                        for (int q = 0; q < P; ++q) k.p[q] = fr[((kt * KS + s) * P + q) * 64];
+                        mfma_pieces(k, qf[s], sb, ss);
+                    }
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) sc[4 * kt + i] = (sb[i] + ss[i]) * scale;
+                }
+                if (t0 + GEN_KEYS > L)
+#pragma unroll
+                    for (int j = 0; j < 8; ++j)
+                        if (t0 + 4 * g + (j & 3) + 16 * (j >> 2) >= L) sc[j] = NEVER;
+                float top = fmaxf(fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3])), fmaxf(fmaxf(sc[4], sc[5]), fmaxf(sc[6], sc[7])));
                 top = fmaxf(top, __shfl_xor(top, 16, 64));
                 top = fmaxf(top, __shfl_xor(top, 32, 64));
-                if (__any(top > mx[n])) {
-                    const float now = fmaxf(mx[n], top), ref = now == -INFINITY ? 0.f : now, f = expf(mx[n] - ref);
-                    mx[n] = now;
-                    sum[n] *= f;
+                if (__any(top > mx)) {                          // (the first chunk: 0 times what is 0)
+                    const float now = fmaxf(mx, top), f = ch == 0 ? 0.f : exp_neg(mx - now);
+                    mx = now;
+                    sum *= f;
 #pragma unroll
                     for (int k = 0; k < FT; ++k)
 #pragma unroll
                         for (int i = 0; i < 4; ++i) {
-                            ob[k][n][i] *= f;
-                            os[k][n][i] *= f;
+                            ob[k][i] *= f;
+                            os[k][i] *= f;
                         }
                 }
-                const float ref = mx[n] == -INFINITY ? 0.f : mx[n];
                 float p[8];
 #pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    p[j] = expf(sc[n][j] - ref);
-                    sum[n] += p[j];
+                for (int j = 0; j < 8; ++j) p[j] = exp_neg(sc[j] - mx);
+                sum += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+                const Pieces<3> pf = split8<3>(p);
+#pragma unroll
+                for (int f = 0; f < FT; ++f) {
+                    Pieces<P> v;
+#pragma unroll
+                    for (int q = 0; q < P; ++q) v.p[q] = fr[((2 * KS + f) * P + q) * 64];
+                    mfma_pieces(v, pf, ob[f], os[f]);
                 }
-                pf[n] = split8<3>(p);
             }
-#pragma unroll
-            for (int f = 0; f < FT; ++f) {
-                Pieces<P> v;
-#pragma unroll
-                for (int q = 0; q < P; ++q) v.p[q] = frag[((2 * KS + f) * P + q) * 64 + lane];
-#pragma unroll
-                for (int n = 0; n < NC; ++n) mfma_pieces(v, pf[n], ob[f][n], os[f][n]);
-            }
-        }
-        // the block's result; `odd` is NaN if a lane met a value that is not finite
-#pragma unroll
-        for (int n = 0; n < NC; ++n) {
-            sum[n] += __shfl_xor(sum[n], 16, 64);
-            sum[n] += __shfl_xor(sum[n], 32, 64);
-            float odd = sum[n] * 0.f;
+            // the block's result; `odd` is NaN if a lane met a value that is not finite
+            sum += __shfl_xor(sum, 16, 64);
+            sum += __shfl_xor(sum, 32, 64);
+            float odd = sum * 0.f;
 #pragma unroll
             for (int f = 0; f < FT; ++f) {
                 float v[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    v[i] = ob[f][n][i] + os[f][n][i];
+                    v[i] = ob[f][i] + os[f][i];
                     odd = fmaf(v[i], 0.f, odd);
-                    v[i] = L > 0 ? v[i] / sum[n] : 0.f;
+                    v[i] = L > 0 ? v[i] / sum : 0.f;
                 }
                 const int k = 16 * f + 4 * g;
-                T *out = xr[n] + m.d_item + o + k;
-                if (live[n] && k < dh) {
+                T *out = xr + m.d_item + o + k;
+                if (live && k < dh) {
                     if (!quad) {
 #pragma unroll
                         for (int i = 0; i < 4; ++i)
@@ -640,16 +645,17 @@ __global__ __launch_bounds__(64 * WV) void k_attn_gen(Model m, Batch b, T *__res
                         *(uint2 *)out = make_uint2(f2bf(v[0]) | ((uint32_t)f2bf(v[1]) << 16), f2bf(v[2]) | ((uint32_t)f2bf(v[3]) << 16));
                 }
             }
-            unsigned long long again = __ballot(live[n] && odd != odd);
+            unsigned long long again = __ballot(live && odd != odd);
             again = (again | again >> 16 | again >> 32 | again >> 48) & 0xFFFFull;       // per candidate
             while (again) {
-                const int c = __ffsll((unsigned long long)again) - 1;
+                const int cc = __ffsll((unsigned long long)again) - 1;
                 again &= again - 1;
-                const uint64_t ep = __shfl((unsigned long long)(uintptr_t)er[n], c, 64), xp = __shfl((unsigned long long)(uintptr_t)xr[n], c, 64);
+                const uint64_t ep = __shfl((unsigned long long)(uintptr_t)er, cc, 64), xp = __shfl((unsigned long long)(uintptr_t)xr, cc, 64);
                 attn_plain<T>((const T *)ep, K, V, WQ ? wq : nullptr, m.d_item, da, dh, o, L, scale, (T *)xp + m.d_item + o);
             }
         }
     }
+    if (n_bad) atomicAdd(bad, n_bad);
 }
 
 size_t attn_generic_lds_bytes(const Model &m, int max_seq_len)
@@ -659,45 +665,51 @@ size_t attn_generic_lds_bytes(const Model &m, int max_seq_len)
 
 bool attn_generic_gathers(const Model &m) { return m.d_head <= GEN_MAX_HEAD; }
 
-template <typename T, int FT, int NC, int WV>
+template <typename T, int FT, int WV, bool RES>
 static void attn_gen_go(const Model &m, const Batch &b, void *X, const void *table, const void *wqp, const float *wq, int32_t *bad,
-                        hipStream_t s)
+                        size_t lds, hipStream_t s)
 {
-    const dim3 grid(b.n_blk * (ROW_BLOCK / (16 * NC * WV)));
-    if (wq)
-        hipLaunchKernelGGL((k_attn_gen<T, FT, NC, WV, true>), grid, dim3(64 * WV), 0, s, m, b, (T *)X, (const T *)table, (const bf16x8 *)wqp, wq, bad);
-    else
-        hipLaunchKernelGGL((k_attn_gen<T, FT, NC, WV, false>), grid, dim3(64 * WV), 0, s, m, b, (T *)X, (const T *)table, nullptr, nullptr, bad);
+    const dim3 grid(RES ? b.n_blk : b.n_blk * (ROW_BLOCK / (16 * WV)));
+    auto go = [&](auto kern, const void *wp, const float *w) {
+        if (RES) (void)hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        hipLaunchKernelGGL(kern, grid, dim3(64 * WV), RES ? lds : 0, s, m, b, (T *)X, (const T *)table, (const bf16x8 *)wp, w, bad);
+    };
+    if (wq) go(k_attn_gen<T, FT, WV, true, RES>, wqp, wq);
+    else go(k_attn_gen<T, FT, WV, false, RES>, nullptr, nullptr);
 }
 
-// Blocks of four waves with 32 candidates each share the splitting of the keys; a batch too small to give every compute
-// unit such a block takes one-wave blocks of 16 candidates (C1's single request: 63 blocks instead of eight).
+// Three forms of the same arithmetic (the same bits): a batch that fills half the chip with blocks of eight waves and a
+// whole ROW_BLOCK each, and whose longest keys leave room for two such blocks on a compute unit, keeps them resident; other
+// large batches take blocks of eight waves, 32 keys at a time; small ones blocks of four.
 constexpr int GEN_SMALL = 256;
+constexpr size_t GEN_RES_LDS = 64 * 1024;
+template <typename T, int FT>
+static void attn_gen_ft(const Model &m, const Batch &b, void *X, const void *table, const void *wqp, const float *wq, int32_t *bad,
+                        int longest, hipStream_t s)
+{
+    const size_t lds = (size_t)m.n_heads * ((longest + GEN_KEYS - 1) / GEN_KEYS) * ((FT + 1) / 2 * 2 + FT) * stored<T>::P * 1024;
+    if (b.n_blk >= GEN_SMALL / 2 && lds <= GEN_RES_LDS) attn_gen_go<T, FT, 8, true>(m, b, X, table, wqp, wq, bad, lds, s);
+    else if (b.n_blk >= GEN_SMALL / 2) attn_gen_go<T, FT, 8, false>(m, b, X, table, wqp, wq, bad, 0, s);
+    else attn_gen_go<T, FT, 4, false>(m, b, X, table, wqp, wq, bad, 0, s);
+}
 template <typename T>
 static hipError_t attn_gen_launch(const Model &m, const Batch &b, void *X, const void *table, const void *wqp, const float *wq,
-                                  int32_t *bad, hipStream_t s)
+                                  int32_t *bad, int longest, hipStream_t s)
 {
-    const bool small = b.n_blk * (ROW_BLOCK / 128) < GEN_SMALL;
-#define AIF_GO(FT)                                                                                                     \
-    do {                                                                                                               \
-        if (small) attn_gen_go<T, FT, 1, FT <= 2 ? 1 : 4>(m, b, X, table, wqp, wq, bad, s);                            \
-        else attn_gen_go<T, FT, 2, 4>(m, b, X, table, wqp, wq, bad, s);                                                \
-    } while (0)
-    if (m.d_head <= 16) AIF_GO(1);
-    else if (m.d_head <= 32) AIF_GO(2);
-    else if (m.d_head <= 64) AIF_GO(4);
-    else AIF_GO(8);
-#undef AIF_GO
+    if (m.d_head <= 16) attn_gen_ft<T, 1>(m, b, X, table, wqp, wq, bad, longest, s);
+    else if (m.d_head <= 32) attn_gen_ft<T, 2>(m, b, X, table, wqp, wq, bad, longest, s);
+    else if (m.d_head <= 64) attn_gen_ft<T, 4>(m, b, X, table, wqp, wq, bad, longest, s);
+    else attn_gen_ft<T, 8>(m, b, X, table, wqp, wq, bad, longest, s);
     return hipGetLastError();
 }
 
 hipError_t launch_attn_generic(const Model &m, const Batch &b, void *X, const float *wq, const void *wq_pieces, const void *table,
-                               int32_t *bad, int max_seq_len, hipStream_t s)
+                               int32_t *bad, int max_seq_len, int longest, hipStream_t s)
 {
     if (b.n_blk == 0) return hipSuccess;
     if (m.d_head <= GEN_MAX_HEAD)
-        return m.dtype == 0 ? attn_gen_launch<float>(m, b, X, table, wq_pieces, wq, bad, s)
-                            : attn_gen_launch<uint16_t>(m, b, X, table, wq_pieces, wq, bad, s);
+        return m.dtype == 0 ? attn_gen_launch<float>(m, b, X, table, wq_pieces, wq, bad, longest, s)
+                            : attn_gen_launch<uint16_t>(m, b, X, table, wq_pieces, wq, bad, longest, s);
     if (table) return hipErrorInvalidValue;                 // this kernel finds the item rows in the workspace
     const int per_wave = m.d_item + m.d_attn + max_seq_len;
     const size_t lds = attn_generic_lds_bytes(m, max_seq_len);
@@ -716,20 +728,21 @@ hipError_t launch_attn_generic(const Model &m, const Batch &b, void *X, const fl
 // a6-a7 -- MLP head (Sec. 1: a small MLP) over the virtual input
 // [u | e | a | c]: the u block arrives as bias1 (user fold), the rest is the
 // workspace row.  H^T = W X^T: a block holds 16 NC candidates (columns), its
-// eight waves share out the row tiles; the activations of the layer that is
+// WV waves share out the row tiles; the activations of the layer that is
 // read and of the one that is written lie in LDS in B-fragment order, and
 // weights come as ready-made pieces from the L2s, two k-steps ahead.
 // SPLIT: the activations lie there as their bf16 pieces (written once, read by
 // every wave), 96 bytes a feature and 16 candidates; without it as fp32, split
 // by each wave that reads them, 64 bytes: for layers so wide that only this
 // fits a compute unit's LDS.
-// What bounds it: the weights' way from the L2s (every block streams them all:
-// 6 bytes a weight in fp32) and the LDS reads of the activations.  Measured (160
-// -> 128 -> 64 -> 1, fp32): 10^5 candidates 78 us, where a thread per feature and
-// 16 candidates on the vector ALU took 210; 1,000 candidates 6.6 against 30;
-// bf16, 160,000 candidates 74 against 301.
+// What bounds it: a block's chain of round trips (descriptors, rows, weights from
+// the L2s), so several blocks share a compute unit: a layer overwrites its input
+// once every wave has read it, and a block is four waves and 32 candidates.
+// Measured (160 -> 128 -> 64 -> 1, fp32): 10^5 candidates 61 us, where a thread per
+// feature and 16 candidates on the vector ALU took 210 (78 with 64 candidates, eight
+// waves and two buffers a block); 1,000 candidates 7 against 30; bf16, 160,000
+// candidates 47 against 301.
 // ---------------------------------------------------------------------------
-constexpr int MLP_WAVES = 8;
 constexpr int MLP_TS = 16;              // candidates of a column tile
 
 // widest activation of the plain route, per candidate
@@ -742,17 +755,17 @@ __host__ __device__ inline int mlp_plain_widest(const Model &m)
 
 struct GenMlp {
     MlpGenericWeights w;
-    int32_t off1;                       // bytes: where the second activation buffer starts
+    int32_t off1;                       // bytes: where the second activation buffer starts; 0: layers overwrite their input
 };
 
 // MLP_TS candidates in plain fp32 arithmetic (see attn_plain), the results of those in `mask` stored: activations in LDS
 // as [feature][MLP_TS].
-template <typename T>
+template <typename T, int THREADS>
 __device__ __forceinline__ void mlp_plain(const Model &m, const T *X, const MlpGenericWeights &w, const float *bias1, int us, int row0,
                                        int nrows, uint32_t mask, float *bufA, float *bufB, const ReqDesc &rd, int local0)
 {
     const int k1 = m.k1;
-    for (int idx = threadIdx.x; idx < k1 * MLP_TS; idx += 64 * MLP_WAVES) {
+    for (int idx = threadIdx.x; idx < k1 * MLP_TS; idx += THREADS) {
         const int c = idx / k1, k = idx - c * k1;
         bufA[k * MLP_TS + c] = c < nrows ? ld_f<T>(X + (size_t)(row0 + c) * m.ldx + k) : 0.f;
     }
@@ -760,7 +773,7 @@ __device__ __forceinline__ void mlp_plain(const Model &m, const T *X, const MlpG
     for (int l = 0; l < m.n_layers; ++l) {
         const int K = l == 0 ? k1 : m.dims[l], N = m.dims[l + 1];
         const float *wt = w.wt[l];
-        for (int i = threadIdx.x; i < N * MLP_TS; i += 64 * MLP_WAVES) {
+        for (int i = threadIdx.x; i < N * MLP_TS; i += THREADS) {
             const int n = i / MLP_TS, c = i - n * MLP_TS;
             float acc = l == 0 ? bias1[(size_t)us * N + n] : (w.bias[l] ? w.bias[l][n] : 0.f);
             for (int k = 0; k < K; ++k) acc += wt[(size_t)k * N + n] * bufA[k * MLP_TS + c];
@@ -782,21 +795,22 @@ __device__ __forceinline__ void mlp_plain(const Model &m, const T *X, const MlpG
     __syncthreads();
 }
 
-// one row tile's (RT = 1) or two row tiles' results for NW column tiles: W rows x activations over ksn k-steps
-template <int PW, int PX, int RT, int NW, int NC, bool SPLIT>
-__device__ __forceinline__ void mlp_rows(const bf16x8 *__restrict__ wp, int ksn, const char *act, int ct0, int lane,
-                                         Pieces<PW> (&w)[2][RT], f32x4 (&big)[RT][NW], f32x4 (&small)[RT][NW])
+// one row tile's (RT = 1) or two row tiles' results for all NC column tiles: W rows x activations over ksn k-steps.  w holds
+// k-steps 0 and 1; the next but one is asked for as soon as a step is done.
+template <int PW, int PX, int RT, int NC, bool SPLIT>
+__device__ __forceinline__ void mlp_rows(const bf16x8 *__restrict__ wp, int ksn, const char *act, int lane, Pieces<PW> (&w)[2][RT],
+                                         f32x4 (&big)[RT][NC], f32x4 (&small)[RT][NC])
 {
-    auto step = [&](int ks, const Pieces<PW> (&a)[RT]) {
+    auto step = [&](int ks, const Pieces<PW> (&a)[RT]) __attribute__((always_inline)) {
 #pragma unroll
-        for (int n = 0; n < NW; ++n) {
+        for (int n = 0; n < NC; ++n) {
             Pieces<PX> x;
             if constexpr (SPLIT) {
-                const bf16x8 *f = (const bf16x8 *)act + (size_t)(ks * PX * NC + ct0 + n) * 64 + lane;
+                const bf16x8 *f = (const bf16x8 *)act + (size_t)(ks * PX * NC + n) * 64 + lane;
 #pragma unroll
                 for (int q = 0; q < PX; ++q) x.p[q] = f[q * NC * 64];
             } else {
-                const float4 *f = (const float4 *)act + (size_t)(ks * NC + ct0 + n) * 128 + lane;
+                const float4 *f = (const float4 *)act + (size_t)(ks * NC + n) * 128 + lane;
                 const float4 a0 = f[0], a1 = f[64];
                 const float v[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
                 x = split8<PX>(v);
@@ -805,37 +819,29 @@ __device__ __forceinline__ void mlp_rows(const bf16x8 *__restrict__ wp, int ksn,
             for (int i = 0; i < RT; ++i) mfma_pieces(a[i], x, big[i][n], small[i][n]);
         }
     };
-    auto load = [&](int ks, Pieces<PW> (&a)[RT]) {
+    auto load = [&](int ks, Pieces<PW> (&a)[RT]) __attribute__((always_inline)) {
         ks = ks < ksn ? ks : ksn - 1;
 #pragma unroll
         for (int i = 0; i < RT; ++i)
 #pragma unroll
             for (int q = 0; q < PW; ++q) a[i].p[q] = wp[((size_t)(i * ksn + ks) * PW + q) * 64 + lane];
     };
-    // w holds k-steps 0 and 1; two more are asked for before each pair is used
-    for (int ks = 0; ks < ksn; ks += 4) {
-        Pieces<PW> w2[2][RT];
-        load(ks + 2, w2[0]);
-        load(ks + 3, w2[1]);
+    for (int ks = 0; ks < ksn; ks += 2) {
         step(ks, w[0]);
-        if (ks + 1 < ksn) step(ks + 1, w[1]);
-        if (ks + 2 < ksn) {
-            load(ks + 4, w[0]);
-            load(ks + 5, w[1]);
-            step(ks + 2, w2[0]);
-            if (ks + 3 < ksn) step(ks + 3, w2[1]);
+        load(ks + 2, w[0]);
+        if (ks + 1 < ksn) {
+            step(ks + 1, w[1]);
+            load(ks + 3, w[1]);
         }
     }
 }
 
-template <typename T, int NC, bool SPLIT>
-__global__ __launch_bounds__(64 * MLP_WAVES) void k_mlp_gen(Model m, Batch b, const T *__restrict__ X, GenMlp gm,
-                                                            const float *__restrict__ bias1)
+template <typename T, int NC, int WV, bool SPLIT>
+__global__ __launch_bounds__(64 * WV, NC == 1 ? 2 : sizeof(T) == 4 ? 3 : 4) void k_mlp_gen(Model m, Batch b, const T *__restrict__ X, GenMlp gm, const float *__restrict__ bias1)
 {
     extern __shared__ __align__(16) char act[];
-    constexpr int P = stored<T>::P, CG = NC >= 2 ? 2 : 1, RG = MLP_WAVES / CG, NW = NC / CG;
+    constexpr int P = stored<T>::P;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, col = lane & 15, g = lane >> 4;
-    const int cg = wave % CG, rg = wave / CG, ct0 = cg * NW;
     const int row0 = blockIdx.x * (16 * NC);
     const int r = b.blk_req[row0 / ROW_BLOCK];
     if (r < 0) return;
@@ -843,28 +849,38 @@ __global__ __launch_bounds__(64 * MLP_WAVES) void k_mlp_gen(Model m, Batch b, co
     const int local0 = row0 - rd.row_base, nrows = min(rd.n_cand - local0, 16 * NC);
     if (nrows <= 0) return;
     const MlpGenericWeights &w = gm.w;
+    const bool in_place = gm.off1 == 0;
 
-    // layer 1's input: the workspace rows as fragments (rows past the request's end zero)
+    // layer 1's input: the workspace rows as fragments (rows past the request's end zero), a few loads at a time
     {
-        const int ksn = (m.k1 + 31) / 32;
-        for (int i = wave; i < ksn * NC; i += MLP_WAVES) {
-            const int ks = i / NC, ct = i - ks * NC, c = ct * 16 + col;
-            float v[8];
-            load8<T>(X + (size_t)(row0 + (c < nrows ? c : 0)) * m.ldx + 32 * ks + 8 * g, c < nrows ? m.k1 - 32 * ks - 8 * g : 0, v);
-            if constexpr (SPLIT) {
-                const Pieces<P> p = split8<P>(v);
+        constexpr int U = 3;
+        const int n_frag = (m.k1 + 31) / 32 * NC;
+        for (int i0 = wave; i0 < n_frag; i0 += U * WV) {
+            float v[U][8];
 #pragma unroll
-                for (int q = 0; q < P; ++q) ((bf16x8 *)act)[((size_t)(ks * P + q) * NC + ct) * 64 + lane] = p.p[q];
-            } else {
-                float4 *f = (float4 *)act + (size_t)(ks * NC + ct) * 128 + lane;
-                f[0] = make_float4(v[0], v[1], v[2], v[3]);
-                f[64] = make_float4(v[4], v[5], v[6], v[7]);
+            for (int u = 0; u < U; ++u) {
+                const int i = i0 + u * WV, ks = i / NC, c = (i - ks * NC) * 16 + col;
+                load8<T>(X + (size_t)(row0 + (c < nrows ? c : 0)) * m.ldx + 32 * ks + 8 * g, i < n_frag && c < nrows ? m.k1 - 32 * ks - 8 * g : 0, v[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int i = i0 + u * WV, ks = i / NC, ct = i - ks * NC;
+                if (i >= n_frag) break;
+                if constexpr (SPLIT) {
+                    const Pieces<P> p = split8<P>(v[u]);
+#pragma unroll
+                    for (int q = 0; q < P; ++q) ((bf16x8 *)act)[((size_t)(ks * P + q) * NC + ct) * 64 + lane] = p.p[q];
+                } else {
+                    float4 *f = (float4 *)act + (size_t)(ks * NC + ct) * 128 + lane;
+                    f[0] = make_float4(v[u][0], v[u][1], v[u][2], v[u][3]);
+                    f[64] = make_float4(v[u][4], v[u][5], v[u][6], v[u][7]);
+                }
             }
         }
     }
-    float odd[NW];                      // per candidate of the lane: NaN once a value that is not finite has come up
+    float odd[NC];                      // per candidate of the lane: NaN once a value that is not finite has come up
 #pragma unroll
-    for (int n = 0; n < NW; ++n) odd[n] = 0.f;
+    for (int n = 0; n < NC; ++n) odd[n] = 0.f;
     char *in = act, *out = act + gm.off1;
     for (int l = 0; l < m.n_layers; ++l) {
         const int K = l == 0 ? m.k1 : m.dims[l], N = m.dims[l + 1], ksn = (K + 31) / 32;
@@ -872,11 +888,12 @@ __global__ __launch_bounds__(64 * MLP_WAVES) void k_mlp_gen(Model m, Batch b, co
         const int nrt = last ? 1 : (N + 31) / 32 * 2;           // row tiles: the next layer reads whole k-steps
         const bf16x8 *wl = (const bf16x8 *)w.pieces[l];
         const float *bl = l == 0 ? bias1 + (size_t)rd.slot * N : w.bias[l];
+        // row tiles rt .. rt + RT - 1; `first` once per layer and wave, with the layer's barriers
         auto rows = [&](auto rt_c, auto px_c, int rt, bool first) __attribute__((always_inline)) {
             constexpr int RT = decltype(rt_c)::value, PX = decltype(px_c)::value;
             const bf16x8 *wp = wl + (size_t)rt * ksn * P * 64;
             Pieces<P> a[2][RT];
-            f32x4 big[RT][NW], small[RT][NW];
+            f32x4 big[RT][NC], small[RT][NC];
             const bool on = rt < nrt;
             if (on) {
 #pragma unroll
@@ -892,28 +909,29 @@ __global__ __launch_bounds__(64 * MLP_WAVES) void k_mlp_gen(Model m, Batch b, co
                         const int f = 16 * (rt + i) + 4 * g + j;
                         const float b0 = bl && f < N ? bl[f] : 0.f;
 #pragma unroll
-                        for (int n = 0; n < NW; ++n) {
+                        for (int n = 0; n < NC; ++n) {
                             big[i][n][j] = b0;
                             small[i][n][j] = 0.f;
                         }
                     }
             }
             if (first) __syncthreads();                         // the weights are on their way while the layer's input settles
+            if (on) mlp_rows<P, PX, RT, NC, SPLIT>(wp, ksn, in, lane, a, big, small);
+            if (first && in_place) __syncthreads();             // the input has been read by every wave
             if (!on) return;
-            mlp_rows<P, PX, RT, NW, NC, SPLIT>(wp, ksn, in, ct0, lane, a, big, small);
 #pragma unroll
             for (int i = 0; i < RT; ++i)
 #pragma unroll
-                for (int n = 0; n < NW; ++n) {
+                for (int n = 0; n < NC; ++n) {
                     float v[4];
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
                         v[j] = big[i][n][j] + small[i][n][j];
                         odd[n] = fmaf(v[j], 0.f, odd[n]);
                     }
-                    const int f = 16 * (rt + i) + 4 * g, ct = ct0 + n;
+                    const int f = 16 * (rt + i) + 4 * g;
                     if (last) {
-                        const int c = ct * 16 + col;
+                        const int c = n * 16 + col;
                         if (g == 0 && c < nrows) {
                             float z = v[0];
                             const int64_t id = rd.cand_ids[local0 + c];
@@ -935,20 +953,20 @@ __global__ __launch_bounds__(64 * MLP_WAVES) void k_mlp_gen(Model m, Batch b, co
                                     p[j] = (__bf16)rest[j];
                                     rest[j] -= (float)p[j];
                                 }
-                                *(bf16x4 *)(out + (((size_t)(ks * 3 + q) * NC + ct) * 64 + dst) * 16 + half * 8) = p;
+                                *(bf16x4 *)(out + (((size_t)(ks * 3 + q) * NC + n) * 64 + dst) * 16 + half * 8) = p;
                             }
                         } else
-                            ((float4 *)out)[(size_t)(ks * NC + ct) * 128 + half * 64 + dst] = make_float4(v[0], v[1], v[2], v[3]);
+                            ((float4 *)out)[(size_t)(ks * NC + n) * 128 + half * 64 + dst] = make_float4(v[0], v[1], v[2], v[3]);
                     }
                 }
         };
         auto all = [&](auto px_c) __attribute__((always_inline)) {
-            if (nrt >= 2 * RG) {
-                rows(std::integral_constant<int, 2>{}, px_c, 2 * rg, true);
-                for (int rt = 2 * (rg + RG); rt < nrt; rt += 2 * RG) rows(std::integral_constant<int, 2>{}, px_c, rt, false);
+            if (nrt >= 2 * WV) {
+                rows(std::integral_constant<int, 2>{}, px_c, 2 * wave, true);
+                for (int rt = 2 * (wave + WV); rt < nrt; rt += 2 * WV) rows(std::integral_constant<int, 2>{}, px_c, rt, false);
             } else {
-                rows(std::integral_constant<int, 1>{}, px_c, rg, true);
-                for (int rt = rg + RG; rt < nrt; rt += RG) rows(std::integral_constant<int, 1>{}, px_c, rt, false);
+                rows(std::integral_constant<int, 1>{}, px_c, wave, true);
+                for (int rt = wave + WV; rt < nrt; rt += WV) rows(std::integral_constant<int, 1>{}, px_c, rt, false);
             }
         };
         if (P == 1 && l == 0) all(std::integral_constant<int, 1>{});
@@ -963,8 +981,8 @@ __global__ __launch_bounds__(64 * MLP_WAVES) void k_mlp_gen(Model m, Batch b, co
     if (threadIdx.x < NC) flag[threadIdx.x] = 0;
     __syncthreads();
 #pragma unroll
-    for (int n = 0; n < NW; ++n)
-        if (odd[n] != odd[n]) atomicOr(&flag[ct0 + n], 1u << col);
+    for (int n = 0; n < NC; ++n)
+        if (odd[n] != odd[n]) atomicOr(&flag[n], 1u << col);
     __syncthreads();
 #pragma unroll
     for (int n = 0; n < NC; ++n) again[n] = flag[n];
@@ -972,46 +990,50 @@ __global__ __launch_bounds__(64 * MLP_WAVES) void k_mlp_gen(Model m, Batch b, co
 #pragma unroll
     for (int n = 0; n < NC; ++n)
         if (again[n] && n * MLP_TS < nrows)
-            mlp_plain<T>(m, X, w, bias1, rd.slot, row0 + n * MLP_TS, min(nrows - n * MLP_TS, MLP_TS), again[n], (float *)act,
-                         (float *)act + (size_t)mlp_plain_widest(m) * MLP_TS, rd, local0 + n * MLP_TS);
+            mlp_plain<T, 64 * WV>(m, X, w, bias1, rd.slot, row0 + n * MLP_TS, min(nrows - n * MLP_TS, MLP_TS), again[n], (float *)act,
+                                  (float *)act + (size_t)mlp_plain_widest(m) * MLP_TS, rd, local0 + n * MLP_TS);
 }
 
-// Bytes of LDS a block of k_mlp_gen takes: two activation buffers (the first takes the inputs of layers 1, 3, ..), and at
-// least what the plain route needs.
-static size_t mlp_gen_lds(const Model &m, int nc, bool split, int32_t *off1)
+// Bytes of LDS a block of k_mlp_gen takes: one activation buffer where every hidden layer is done in one go (its results
+// wait in registers until all waves have read its input), else two in turn; and at least what the plain route needs.
+static size_t mlp_gen_lds(const Model &m, int nc, int waves, bool split, int32_t *off1)
 {
     size_t need[2] = {0, 0};
+    bool in_place = true;
     for (int l = 0; l < m.n_layers; ++l) {
         const size_t ks = ((l == 0 ? m.k1 : m.dims[l]) + 31) / 32;
         const size_t bytes = ks * nc * (split ? 1024u * (l == 0 && m.dtype == 1 ? 1 : 3) : 2048u);
+        const int nrt = (m.dims[l + 1] + 31) / 32 * 2;
+        if (l + 1 < m.n_layers && nrt > (nrt >= 2 * waves ? 2 * waves : waves)) in_place = false;
         need[l & 1] = std::max(need[l & 1], bytes);
     }
-    *off1 = (int32_t)need[0];
-    return std::max(need[0] + need[1], mlp_generic_lds_bytes(m));
+    *off1 = in_place ? 0 : (int32_t)need[0];
+    return std::max(in_place ? std::max(need[0], need[1]) : need[0] + need[1], mlp_generic_lds_bytes(m));
 }
 
 size_t mlp_generic_lds_bytes(const Model &m) { return (size_t)2 * mlp_plain_widest(m) * MLP_TS * sizeof(float); }
 
-template <typename T, int NC, bool SPLIT>
+template <typename T, int NC, int WV, bool SPLIT>
 static hipError_t mlp_gen_go(const Model &m, const Batch &b, const void *X, GenMlp &gm, const float *bias1, hipStream_t s)
 {
-    const size_t lds = mlp_gen_lds(m, NC, SPLIT, &gm.off1);
-    (void)hipFuncSetAttribute((const void *)k_mlp_gen<T, NC, SPLIT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL((k_mlp_gen<T, NC, SPLIT>), dim3(b.n_blk * (ROW_BLOCK / (16 * NC))), dim3(64 * MLP_WAVES), lds, s, m, b, (const T *)X,
+    const size_t lds = mlp_gen_lds(m, NC, WV, SPLIT, &gm.off1);
+    (void)hipFuncSetAttribute((const void *)k_mlp_gen<T, NC, WV, SPLIT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipLaunchKernelGGL((k_mlp_gen<T, NC, WV, SPLIT>), dim3(b.n_blk * (ROW_BLOCK / (16 * NC))), dim3(64 * WV), lds, s, m, b, (const T *)X,
                        gm, bias1);
     return hipGetLastError();
 }
 
-// 64 candidates a block where the batch fills the chip with such blocks and they fit, else 16.
+// Blocks of four waves and 32 candidates where the batch fills the chip with such blocks and they fit, else eight waves
+// share 16 candidates: the shortest chain.
 template <typename T>
 static hipError_t mlp_gen_launch(const Model &m, const Batch &b, const void *X, const MlpGenericWeights &w, const float *bias1, hipStream_t s)
 {
     constexpr size_t LDS = 160 * 1024;
     GenMlp gm{w, 0};
     int32_t off;
-    if (b.n_blk * (ROW_BLOCK / 64) >= GEN_SMALL && mlp_gen_lds(m, 4, true, &off) <= LDS) return mlp_gen_go<T, 4, true>(m, b, X, gm, bias1, s);
-    if (mlp_gen_lds(m, 1, true, &off) <= LDS) return mlp_gen_go<T, 1, true>(m, b, X, gm, bias1, s);
-    return mlp_gen_go<T, 1, false>(m, b, X, gm, bias1, s);
+    if (b.n_blk * (ROW_BLOCK / 32) >= GEN_SMALL && mlp_gen_lds(m, 2, 4, true, &off) <= LDS) return mlp_gen_go<T, 2, 4, true>(m, b, X, gm, bias1, s);
+    if (mlp_gen_lds(m, 1, 8, true, &off) <= LDS) return mlp_gen_go<T, 1, 8, true>(m, b, X, gm, bias1, s);
+    return mlp_gen_go<T, 1, 8, false>(m, b, X, gm, bias1, s);
 }
 
 hipError_t launch_mlp_generic(const Model &m, const Batch &b, const void *X, const MlpGenericWeights &w,

@@ -54,17 +54,19 @@ def test_pieces_kernels_at_tile_edges(R, torch, monkeypatch, dtype, shape):  # n
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-def test_large_batches_give_the_bits_of_single_requests(R, torch, monkeypatch, dtype):  # noqa: F811
-    """140 requests take the kernels with 64 (MLP) and 128 (attention) candidates a block, one alone those with 16."""
+@pytest.mark.parametrize("seq_len", [40, 700])
+def test_large_batches_give_the_bits_of_single_requests(R, torch, monkeypatch, dtype, seq_len):  # noqa: F811
+    """140 requests take the kernels with 32 candidates a block (MLP) and all keys resident or, of 700, 32 at a time in
+    blocks of eight waves (attention); one alone those with 16 candidates and four waves."""
     if dtype == "bf16":
         monkeypatch.setenv("AIF_FORCE_GENERIC", "1")
-    cfg = small_cfg(dtype, seq_len=40, n_items=3000, d_item=32, d_user=32, d_attn=32, use_wq=True, mlp_dims=(128, 70, 20, 1))
+    cfg = small_cfg(dtype, seq_len=seq_len, n_items=3000, d_item=32, d_user=32, d_attn=32, use_wq=True, mlp_dims=(128, 70, 20, 1))
     rng = np.random.default_rng(3)
     model = wl.make_model(cfg, seed=5, bias_scale=0.3)
     table = wl.make_table_host(cfg, rng, sigma=1.0)
-    users_ids = [(wl.make_user(cfg, rng, sigma=1.0, seq_len=int(rng.integers(0, 41))), rng.integers(0, 3000, int(rng.integers(1, 257))).astype(np.int32))
+    users_ids = [(wl.make_user(cfg, rng, sigma=1.0, seq_len=int(rng.integers(0, seq_len + 1))), rng.integers(0, 3000, int(rng.integers(1, 257))).astype(np.int32))
                  for _ in range(140)]
-    zs, _, drs, ctx = run_batch(R, torch, cfg, model, R.to_device(table, dtype), users_ids, max_seq_len=40)
+    zs, _, drs, ctx = run_batch(R, torch, cfg, model, R.to_device(table, dtype), users_ids, max_seq_len=seq_len)
     for r in (0, 1, 70, 139):
         alone = R.upload_request(cfg, *users_ids[r])
         ctx.aif_score_request(alone.req)
