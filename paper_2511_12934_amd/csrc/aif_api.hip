@@ -518,7 +518,9 @@ static aif_status score_impl(aif_ctx *c, const aif_request *reqs, int32_t n_req,
     // A few requests (the latency cases: one request, or one cut into mini-batches) send their descriptors in the
     // staging launch's arguments and that launch writes the tables on the device: nothing is uploaded.  Otherwise, when
     // the staging launch has few blocks (no gather blocks) it carries the tables to the device itself.
-    const bool stage_fills = fused && n_req <= FEW_MAX;
+    // The shape-agnostic attention kernel's user fold can carry them as well (nothing but it precedes that kernel then).
+    const bool fold_fills = !c->mfma.attn && attn_indexes && m.cross_in_mlp != 2 && n_req <= FEW_MAX;
+    const bool stage_fills = (fused && n_req <= FEW_MAX) || fold_fills;
     const bool stage_uploads = fused && !stage_fills && attn_indexes && c->h_stage_dev;
     FewFill fill{};
     if (stage_fills) {
@@ -568,6 +570,9 @@ static aif_status score_impl(aif_ctx *c, const aif_request *reqs, int32_t n_req,
         if (staged_proj) {      // K/V packing, user fold and the users' layer-1 weights as one launch
             HIP_TRY(c, launch_stage_proj(m, b, (const float *)c->w1u.p, c->has_bias[0] ? (const float *)c->bias[0].p : nullptr,
                                          (float *)c->bias1.p, c->mfma, s));
+        } else if (fold_fills) {
+            HIP_TRY(c, launch_user_fold_few(m, fill, (const float *)c->w1u.p, c->has_bias[0] ? (const float *)c->bias[0].p : nullptr,
+                                            (float *)c->bias1.p, s));
         } else {
             HIP_TRY(c, launch_user_fold(m, b, (const float *)c->w1u.p, c->has_bias[0] ? (const float *)c->bias[0].p : nullptr,
                                         (float *)c->bias1.p, s));
@@ -722,7 +727,8 @@ aif_status aif_score_topk_static(aif_ctx *c, const aif_request *req, int32_t k, 
     f.per = plan_info.per;
     f.resident = plan_info.resident;
     const bool fused = stage_fusable(m, c->mfma);
-    if (!fused) {                                // else the staging launch writes the tables
+    const bool fold_fills = !c->mfma.attn && !c->separate_gather && attn_generic_gathers(m) && m.cross_in_mlp != 2;
+    if (!fused && !fold_fills) {                 // else the staging launch, or the user fold, writes the tables
         hipLaunchKernelGGL(k_static_fill, dim3((few_fill_items(f) + 255) / 256), dim3(256), 0, s, f);
         HIP_TRY(c, hipGetLastError());
     }
@@ -760,6 +766,8 @@ aif_status aif_score_topk_static(aif_ctx *c, const aif_request *req, int32_t k, 
         if (!attn_indexes) HIP_TRY(c, launch_gather(m, b, c->table, X, bad, s));
         if (staged_proj) {
             HIP_TRY(c, launch_stage_proj(m, b, (const float *)c->w1u.p, b1, bias1, plan, s));
+        } else if (fold_fills) {
+            HIP_TRY(c, launch_user_fold_few(m, f, (const float *)c->w1u.p, b1, bias1, s));
         } else {
             HIP_TRY(c, launch_user_fold(m, b, (const float *)c->w1u.p, b1, bias1, s));
             HIP_TRY(c, launch_fold_w0(m, b, plan, s));

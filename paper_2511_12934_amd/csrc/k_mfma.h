@@ -76,6 +76,8 @@ struct StageUpload {
 // arguments, the launch's blocks read them there and its first blocks write the device tables of the batch (k_stage.h:
 // FewFill), so no upload of any kind precedes the launch.
 struct FewFill;
+// k_generic.hip: the user fold of such a batch, the tables written by the same launch
+hipError_t launch_user_fold_few(const Model &m, const FewFill &f, const float *w1u, const float *b1, float *bias1, hipStream_t s);
 hipError_t launch_stage(const Model &m, const Batch &b, const void *table, void *X, int32_t *bad, const float *w1u,
                         const float *b1, float *bias1, const MfmaPlan &plan, bool gather, hipStream_t s,
                         const StageUpload *up = nullptr, const FewFill *few = nullptr);
