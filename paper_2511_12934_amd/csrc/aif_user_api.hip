@@ -263,15 +263,21 @@ aif_status aif_user_precompute(aif_user_ctx *c, const aif_user_request *users, i
     hipEvent_t *pe = nullptr;
     if (c->prof_on && c->prof_calls < c->prof_max) pe = &c->prof[(size_t)USER_EV_PER_CALL * c->prof_calls++];
     if (pe) USER_TRY(c, hipEventRecord(pe[0], s));
-    USER_TRY(c, launch_user_project(c->w, du, b.blk_req, b.n_blk, c->X, s));
+    const UserPack pack{c->mfma.kvpack, c->mfma.pack_stride, c->mfma.kmax, c->mfma.nktp};
+    const bool packs = c->mfma.attn && c->w.wseq_frag && (m.d_head == 64 || m.d_head == 32);
+    USER_TRY(c, launch_user_project(c->w, du, b.blk_req, b.n_blk, n_users, c->X, packs ? &pack : nullptr, s));
     if (pe) USER_TRY(c, hipEventRecord(pe[1], s));
     if (c->mfma.attn)
-        USER_TRY(c, launch_attn_mfma(m, b, c->X, c->mfma, false, s));
+        USER_TRY(c, launch_attn_mfma(m, b, c->X, c->mfma, packs, s));
     else
         USER_TRY(c, launch_attn_generic(m, b, c->X, nullptr, nullptr, nullptr, nullptr, c->max_seq_len, longest, s));
     if (pe) USER_TRY(c, hipEventRecord(pe[2], s));
-    USER_TRY(c, launch_user_ffn_partial(c->w, du, b.blk_req, b.n_blk, c->X, (float *)c->part, s));
-    USER_TRY(c, launch_user_combine(c->w, du, n_users, c->X, (const float *)c->part, s));
+    if (c->w.wffn_frag && longest <= 32 * USER_POOL_TILES)
+        USER_TRY(c, launch_user_ffn_pool(c->w, du, n_users, c->X, s));
+    else {
+        USER_TRY(c, launch_user_ffn_partial(c->w, du, b.blk_req, b.n_blk, c->X, (float *)c->part, s));
+        USER_TRY(c, launch_user_combine(c->w, du, n_users, c->X, (const float *)c->part, s));
+    }
     if (pe) USER_TRY(c, hipEventRecord(pe[3], s));
     USER_TRY(c, hipEventRecord(c->ev[slot], s));
     c->ev_live[slot] = true;

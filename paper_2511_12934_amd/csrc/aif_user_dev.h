@@ -32,9 +32,18 @@ struct UserWeights {
     int32_t part_rows;          // positions summed into one partial of the pooling (USER_FFN_ROWS, or 32 with MFMA)
 };
 
+// What the projection needs to pack its rows as the attention's keys and values (k_stage.h: pack_kv_stage, one head).
+struct UserPack {
+    char *kvpack;
+    size_t stride;
+    float *kmax;
+    int32_t nktp;
+};
+
 // Eq. 1: X[row, 0:d] = W x for every sequence position and the profile; U^_seq also to the user's seq_out.
+// pack (optional, MFMA projection, d = 32 or 64): the rows are left packed as well (launch_attn_mfma: kv_packed).
 hipError_t launch_user_project(const UserWeights &w, const UserDesc *users /*device*/, const int32_t *blk_req /*device*/,
-                               int n_blk, void *X, hipStream_t s);
+                               int n_blk, int n_users, void *X, const UserPack *pack, hipStream_t s);
 size_t user_project_lds_bytes(int d_raw);
 
 // FFN of Eq. 2 on the attention rows X[row, d:2d] of the sequence positions and their sum over each block of
@@ -42,6 +51,10 @@ size_t user_project_lds_bytes(int d_raw);
 hipError_t launch_user_ffn_partial(const UserWeights &w, const UserDesc *users, const int32_t *blk_req, int n_blk,
                                    const void *X, float *part, hipStream_t s);
 size_t user_ffn_lds_bytes(int d);
+
+// Both of these as one launch, a block per user (MFMA FFN; sequences of at most 32 USER_POOL_TILES positions).
+constexpr int USER_POOL_TILES = 64;
+hipError_t launch_user_ffn_pool(const UserWeights &w, const UserDesc *users, int n_users, const void *X, hipStream_t s);
 
 // Pooling of Eq. 2 (mean of the partial sums, in block order) and the combined vector
 // [U_self_attention | U_profile_attention] to each user's user_vec_out.

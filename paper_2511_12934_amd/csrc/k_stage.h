@@ -493,19 +493,15 @@ __device__ __forceinline__ uint4 scaled_bf16x8(uint4 v, float scale)
 // the softmax weight in base 2 (Sec. 3.3's scaled dot product, the scale and the change of base done once per user and
 // key instead of once per candidate and key; one more rounding of the key to bf16).
 constexpr float ATTN_LOG2E = 1.4426950408889634f;
-template <int DH, class Reqs>
-__device__ __forceinline__ void pack_kv_block(int slot, int hd, int st, const Model &m, const Reqs &src,
-                                              char *__restrict__ kvpack, size_t pack_stride,
-                                              float *__restrict__ kmax_part, int nktp)
+// key(t), val(t): where the head's slice of position t's key and value starts (16-byte aligned).
+template <int DH, class Key, class Val>
+__device__ __forceinline__ void pack_kv_stage(int slot, int hd, int st, int L, int n_heads, const Key &key, const Val &val,
+                                              char *__restrict__ kvpack, size_t pack_stride, float *__restrict__ kmax_part, int nktp)
 {
     constexpr int FR = DH / 8, JS = DH / 16, FT = DH / 32;
-    const ReqDesc rdv = src.slot_desc(slot), *rd = &rdv;
-    const int L = rd->seq_len;
     const int nkt2 = (((L + 31) >> 5) + 1) & ~1;
     if (2 * st >= nkt2) return;
     const float kscale = ATTN_LOG2E / sqrtf((float)DH);
-    const uint16_t *K = (const uint16_t *)rd->seq_keys, *V = (const uint16_t *)rd->seq_vals;
-    const int da = m.d_attn, o = hd * DH;
     uint4 *dst = (uint4 *)(kvpack + (size_t)slot * pack_stride + ((size_t)(hd * nktp + 2 * st) * FR) * 1024);
     // One 16-byte piece (a lane's share of a fragment) per thread and step.  Every load is issued before the first
     // is looked at: keys past the sequence's end re-read its last key and are zeroed afterwards (a load under a
@@ -521,14 +517,14 @@ __device__ __forceinline__ void pack_kv_block(int slot, int hd, int st, const Mo
         const int kt = 2 * st + k2, hh = lane >> 5;
         if (frag < JS) {                                        // the same for a whole wave
             const int t = 32 * kt + (lane & 31);
-            kpiece[it] = *(const uint4 *)(K + (size_t)(t < L ? t : L - 1) * da + o + 16 * frag + 8 * hh);
+            kpiece[it] = *(const uint4 *)(key(t < L ? t : L - 1) + 16 * frag + 8 * hh);
         } else {
             const int fv = frag - JS, jj = fv / FT, ft = fv - jj * FT;
-            const int f = o + 32 * ft + (lane & 31), t0 = 32 * kt + 16 * jj + 4 * hh;
+            const int f = 32 * ft + (lane & 31), t0 = 32 * kt + 16 * jj + 4 * hh;
 #pragma unroll
             for (int sl = 0; sl < 8; ++sl) {                   // slot sl <-> key t0 + 8 (sl / 4) + sl % 4
                 const int t = t0 + 8 * (sl >> 2) + (sl & 3);
-                ve[it][sl] = V[(size_t)(t < L ? t : L - 1) * da + f];
+                ve[it][sl] = val(t < L ? t : L - 1)[f];
             }
         }
     }
@@ -560,10 +556,10 @@ __device__ __forceinline__ void pack_kv_block(int slot, int hd, int st, const Mo
         const int t = 64 * st + threadIdx.x;
         float ss = 0.f;
         if (t < L) {
-            const uint4 *kr = (const uint4 *)(K + (size_t)t * da + o);
+            const auto *kr = key(t);
 #pragma unroll
             for (int i = 0; i < DH / 8; ++i) {
-                const uint4 q = kr[i];
+                const uint4 q = *(const uint4 *)(kr + 8 * i);
                 const uint32_t ws[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
@@ -577,8 +573,20 @@ __device__ __forceinline__ void pack_kv_block(int slot, int hd, int st, const Mo
         for (int off = 32; off; off >>= 1) nrm = fmaxf(nrm, __shfl_xor(nrm, off, 64));
         // the packed key is the key times kscale, rounded (each element at most 1 + 2^-8 times as large); the bound is
         // rounded up a little more: it must dominate the fp32-accumulated first product
-        if (threadIdx.x == 0) kmax_part[((size_t)slot * m.n_heads + hd) * (nktp / 2) + st] = nrm * kscale * (1.f + 1.f / 256.f) * 1.001f;
+        if (threadIdx.x == 0) kmax_part[((size_t)slot * n_heads + hd) * (nktp / 2) + st] = nrm * kscale * (1.f + 1.f / 256.f) * 1.001f;
     }
+}
+
+template <int DH, class Reqs>
+__device__ __forceinline__ void pack_kv_block(int slot, int hd, int st, const Model &m, const Reqs &src,
+                                              char *__restrict__ kvpack, size_t pack_stride,
+                                              float *__restrict__ kmax_part, int nktp)
+{
+    const ReqDesc rd = src.slot_desc(slot);
+    const uint16_t *K = (const uint16_t *)rd.seq_keys + hd * DH, *V = (const uint16_t *)rd.seq_vals + hd * DH;
+    const int da = m.d_attn;
+    pack_kv_stage<DH>(slot, hd, st, rd.seq_len, m.n_heads, [&](int t) { return K + (size_t)t * da; }, [&](int t) { return V + (size_t)t * da; },
+                      kvpack, pack_stride, kmax_part, nktp);
 }
 
 }  // namespace aif

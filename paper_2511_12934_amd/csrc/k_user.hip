@@ -7,6 +7,7 @@
 //
 // fp32 arithmetic over the storage type, fixed summation order per output.
 #include "aif_user_dev.h"
+#include "k_stage.h"
 
 namespace aif {
 
@@ -18,7 +19,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // features (d_raw is a multiple of four), they meet in a fixed two-step butterfly.  All of a thread's loads are
 // independent, so the row costs about one round trip to memory.
 template <typename T>
-__device__ __forceinline__ void project_profile(const UserWeights &w, const UserDesc &ud, T *__restrict__ X, int nthreads)
+__device__ __forceinline__ void project_profile(const UserWeights &w, const UserDesc &ud, T *X, int nthreads)
 {
     const T *pr = (const T *)ud.profile;
     const int d = w.d, q = threadIdx.x & 3, chunk = w.d_raw >> 2;
@@ -45,16 +46,26 @@ __device__ __forceinline__ void project_profile(const UserWeights &w, const User
 // that position per 32-feature tile (features 8 q + 4 h + i), which it writes as
 // four 8-byte pieces to the workspace row and to the user's seq_out.
 // ---------------------------------------------------------------------------
-template <int D>
+// The rows pass through LDS, so that they leave for the workspace and seq_out in whole lines.  PACK: they are two whole
+// 64-key stages of the attention that follows, and the block packs them from LDS as keys and values as well (one launch
+// where two were: 64 users of up to 500 positions 11.6 us instead of 12.2 + 5.9).  The blocks past the sequences' project the profiles, one user each, beside them instead of after a
+// block's own rows.
+template <int D, bool PACK>
 __global__ __launch_bounds__(256) void k_user_project_mfma(UserWeights w, const UserDesc *__restrict__ users,
-                                                           const int32_t *__restrict__ blk_req, uint16_t *__restrict__ X)
+                                                           const int32_t *__restrict__ blk_req, int n_row_blk, uint16_t *__restrict__ X, UserPack pk)
 {
     constexpr int FT = D / 32, ROWS = 128, SUB = ROW_BLOCK / ROWS;
+    if ((int)blockIdx.x >= n_row_blk) {
+        project_profile<uint16_t>(w, users[blockIdx.x - n_row_blk], X, 256);
+        return;
+    }
     const int u = blk_req[blockIdx.x / SUB];
     if (u < 0) return;
     const UserDesc ud = users[u];
     const int row0 = blockIdx.x * ROWS, local0 = row0 - ud.row_base, L = ud.seq_len;
-    if (local0 > L) return;
+    constexpr int LD = D + 8;                                   // LDS row: 16 bytes of padding
+    __shared__ __align__(16) uint16_t rows[ROWS * LD];
+    if (local0 >= L) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, col = lane & 31, h = lane >> 5;
     const int li = local0 + wave * 32 + col;
     const int KS = w.d_raw / 16;
@@ -70,34 +81,55 @@ __global__ __launch_bounds__(256) void k_user_project_mfma(UserWeights w, const 
         // round trip to memory per group instead of one per k-step is what this short kernel's time is made of
         constexpr int G = 8;
         for (int k0 = 0; k0 < KS; k0 += G) {
-            bf16x8 b[G];
+            // (and all of its weights: a k-step past the last reads the last again and multiplies it by zeros, so that no
+            // load hangs on a condition)
+            bf16x8 b[G], a[G][FT];
 #pragma unroll
-            for (int j = 0; j < G; ++j)
-                if (k0 + j < KS) b[j] = *(const bf16x8 *)(src + 16 * (k0 + j));
+            for (int j = 0; j < G; ++j) {
+                const int k = min(k0 + j, KS - 1);
+                b[j] = *(const bf16x8 *)(src + 16 * k);
 #pragma unroll
-            for (int j = 0; j < G; ++j)
-                if (k0 + j < KS) {
+                for (int ft = 0; ft < FT; ++ft) a[j][ft] = wf[(size_t)(ft * KS + k) * 64];
+            }
 #pragma unroll
-                    for (int ft = 0; ft < FT; ++ft)
-                        acc[ft] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[(size_t)(ft * KS + k0 + j) * 64], b[j], acc[ft], 0, 0, 0);
-                }
+            for (int j = 0; j < G; ++j) {
+                if (k0 + j >= KS)
+#pragma unroll
+                    for (int ft = 0; ft < FT; ++ft) a[j][ft] = b[j] = bf16x8{};
+#pragma unroll
+                for (int ft = 0; ft < FT; ++ft) acc[ft] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[j][ft], b[j], acc[ft], 0, 0, 0);
+            }
         }
-        if (li < L) {
-            uint16_t *xr = X + (size_t)(row0 + wave * 32 + col) * (2 * D), *so = (uint16_t *)ud.seq_out + (size_t)li * D;
+        uint16_t *dst = rows + (wave * 32 + col) * LD;
 #pragma unroll
-            for (int ft = 0; ft < FT; ++ft)
+        for (int ft = 0; ft < FT; ++ft)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    bf16x4 o4;
+            for (int q = 0; q < 4; ++q) {
+                bf16x4 o4;
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) o4[i] = (__bf16)acc[ft][4 * q + i];
-                    const int f = 32 * ft + 8 * q + 4 * h;
-                    *(bf16x4 *)(xr + f) = o4;
-                    *(bf16x4 *)(so + f) = o4;
-                }
+                for (int i = 0; i < 4; ++i) o4[i] = (__bf16)acc[ft][4 * q + i];
+                *(bf16x4 *)(dst + 32 * ft + 8 * q + 4 * h) = o4;
+            }
+    }
+    __syncthreads();
+    {
+        constexpr int PR = D / 8;                               // 16-byte pieces of a row
+        uint16_t *so = (uint16_t *)ud.seq_out + (size_t)local0 * D, *xr = X + (size_t)row0 * (2 * D);
+#pragma unroll
+        for (int it = 0; it < ROWS * PR / 256; ++it) {
+            const int i = it * 256 + (int)threadIdx.x, row = i / PR, pc = i - row * PR;
+            const uint4 v = *(const uint4 *)(rows + row * LD + 8 * pc);
+            if (local0 + row < L) {
+                *(uint4 *)(xr + (size_t)row * (2 * D) + 8 * pc) = v;
+                *(uint4 *)(so + (size_t)row * D + 8 * pc) = v;
+            }
         }
     }
-    if (L >= local0 && L < local0 + ROWS) project_profile<uint16_t>(w, ud, X, 256);
+    if constexpr (PACK) {
+        auto key = [&](int t) { return rows + (t - local0) * LD; };
+#pragma unroll
+        for (int s = 0; s < ROWS / 64; ++s) pack_kv_stage<D>(u, 0, local0 / 64 + s, L, 1, key, key, pk.kvpack, pk.stride, pk.kmax, pk.nktp);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -106,18 +138,27 @@ __global__ __launch_bounds__(256) void k_user_project_mfma(UserWeights w, const 
 // past the end zeroed, then the sum over the wave's 32 positions (the lanes of a
 // half) by a fixed butterfly.
 // ---------------------------------------------------------------------------
-template <int D>
-__global__ __launch_bounds__(256) void k_user_ffn_mfma(UserWeights w, const UserDesc *__restrict__ users,
-                                                       const int32_t *__restrict__ blk_req, const uint16_t *__restrict__ X,
-                                                       float *__restrict__ part)
+// y summed over the 32 lanes of a half: the butterfly xor 1, 2, 4, 8 on the vector ALU's own lane permutes (within four equal
+// lanes a mirror is as good as an xor), 16 through the LDS crossbar
+template <int CTRL> __device__ __forceinline__ float add_dpp(float y)
 {
-    constexpr int FT = D / 32, KS = D / 16, ROWS = 128, SUB = ROW_BLOCK / ROWS;
-    const int u = blk_req[blockIdx.x / SUB];
-    if (u < 0) return;
-    const UserDesc ud = users[u];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, col = lane & 31, h = lane >> 5;
-    const int row0 = blockIdx.x * ROWS + wave * 32, local0 = row0 - ud.row_base, L = ud.seq_len;
-    if (local0 >= L) return;
+    return y + __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(y), CTRL, 0xF, 0xF, true));
+}
+__device__ __forceinline__ float half_sum(float y)
+{
+    y = add_dpp<0xB1>(y);       // quad_perm 1,0,3,2
+    y = add_dpp<0x4E>(y);       // quad_perm 2,3,0,1
+    y = add_dpp<0x141>(y);      // row_half_mirror
+    y = add_dpp<0x140>(y);      // row_mirror
+    return y + __shfl_xor(y, 16, 64);
+}
+
+// The tile of 32 positions whose first workspace row is row0 (position local0 of L): dst[D] = the sum of its FFN outputs.
+template <int D>
+__device__ __forceinline__ void ffn_tile(const UserWeights &w, const uint16_t *__restrict__ X, int row0, int local0, int L, float *dst0)
+{
+    constexpr int FT = D / 32, KS = D / 16;
+    const int lane = threadIdx.x & 63, col = lane & 31, h = lane >> 5;
     const uint16_t *src = X + (size_t)(row0 + col) * (2 * D) + D + 8 * h;      // rows past L are inside the workspace
     const bf16x8 *wf = (const bf16x8 *)w.wffn_frag + lane;
     bf16x8 b[KS];
@@ -135,18 +176,49 @@ __global__ __launch_bounds__(256) void k_user_ffn_mfma(UserWeights w, const User
         for (int ks = 0; ks < KS; ++ks)
             acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[(size_t)(ft * KS + ks) * 64], b[ks], acc, 0, 0, 0);
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            float y = live ? fmaxf(acc[v], 0.f) : 0.f;
-#pragma unroll
-            for (int o = 1; o < 32; o <<= 1) y += __shfl_xor(y, o, 64);
-            acc[v] = y;
-        }
+        for (int v = 0; v < 16; ++v) acc[v] = half_sum(live ? fmaxf(acc[v], 0.f) : 0.f);
         if (col == 0) {
-            float *dst = part + (size_t)(row0 / 32) * D + 32 * ft + 4 * h;
+            float *dst = dst0 + 32 * ft + 4 * h;
 #pragma unroll
             for (int q = 0; q < 4; ++q) *(float4 *)(dst + 8 * q) = make_float4(acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]);
         }
     }
+}
+
+// a tile per wave, its sums to memory for k_user_combine: users of long sequences
+template <int D>
+__global__ __launch_bounds__(256) void k_user_ffn_mfma(UserWeights w, const UserDesc *__restrict__ users,
+                                                       const int32_t *__restrict__ blk_req, const uint16_t *__restrict__ X,
+                                                       float *__restrict__ part)
+{
+    constexpr int ROWS = 128, SUB = ROW_BLOCK / ROWS;
+    const int u = blk_req[blockIdx.x / SUB];
+    if (u < 0) return;
+    const UserDesc ud = users[u];
+    const int row0 = blockIdx.x * ROWS + (threadIdx.x >> 6) * 32, local0 = row0 - ud.row_base;
+    if (local0 >= ud.seq_len) return;
+    ffn_tile<D>(w, X, row0, local0, ud.seq_len, part + (size_t)(row0 / 32) * D);
+}
+
+// FFN, pooling and the combined vector of one user by one block of sixteen waves: the tiles' sums meet in LDS and are added
+// in the order k_user_combine adds them (the same bits).  One launch where two were, and no trip of the sums through
+// memory: 64 users of up to 500 positions 8 us instead of 6 + 8.  For sequences of up to USER_POOL_TILES tiles -- beyond,
+// a user's tiles want more than one compute unit.
+template <int D>
+__global__ __launch_bounds__(1024) void k_user_ffn_pool(UserWeights w, const UserDesc *__restrict__ users, const uint16_t *__restrict__ X)
+{
+    __shared__ float sums[USER_POOL_TILES][D];
+    const UserDesc ud = users[blockIdx.x];
+    const int L = ud.seq_len, nt = (L + 31) / 32;
+    for (int t = threadIdx.x >> 6; t < nt; t += 16) ffn_tile<D>(w, X, ud.row_base + 32 * t, 32 * t, L, sums[t]);
+    __syncthreads();
+    const int n = threadIdx.x;
+    if (n >= D) return;
+    float sum = 0.f;
+    for (int t = 0; t < nt; ++t) sum += sums[t][n];
+    uint16_t *out = (uint16_t *)ud.user_vec_out;
+    out[n] = f2bf(L > 0 ? sum / (float)L : 0.f);
+    out[D + n] = X[(size_t)(ud.row_base + L) * (2 * D) + D + n];               // Eq. 3: the profile row's attention
 }
 
 // ---------------------------------------------------------------------------
@@ -210,16 +282,22 @@ __global__ __launch_bounds__(256) void k_user_project(UserWeights w, const UserD
 
 size_t user_project_lds_bytes(int d_raw) { return (size_t)d_raw * USER_PROJ_ROWS * sizeof(float); }
 
-hipError_t launch_user_project(const UserWeights &w, const UserDesc *users, const int32_t *blk_req, int n_blk, void *X,
-                               hipStream_t s)
+hipError_t launch_user_project(const UserWeights &w, const UserDesc *users, const int32_t *blk_req, int n_blk, int n_users, void *X,
+                               const UserPack *pack, hipStream_t s)
 {
     if (n_blk == 0) return hipSuccess;
+    if (pack && !w.wseq_frag) return hipErrorInvalidValue;
     if (w.wseq_frag) {
-        const dim3 g(n_blk * (ROW_BLOCK / 128));
+        const int n_row_blk = n_blk * (ROW_BLOCK / 128);
+        const UserPack pk = pack ? *pack : UserPack{};
+        auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(n_row_blk + n_users), dim3(256), 0, s, w, users, blk_req, n_row_blk, (uint16_t *)X, pk); };
         switch (w.d) {
-        case 32: hipLaunchKernelGGL(k_user_project_mfma<32>, g, dim3(256), 0, s, w, users, blk_req, (uint16_t *)X); break;
-        case 64: hipLaunchKernelGGL(k_user_project_mfma<64>, g, dim3(256), 0, s, w, users, blk_req, (uint16_t *)X); break;
-        case 128: hipLaunchKernelGGL(k_user_project_mfma<128>, g, dim3(256), 0, s, w, users, blk_req, (uint16_t *)X); break;
+        case 32: pack ? go(k_user_project_mfma<32, true>) : go(k_user_project_mfma<32, false>); break;
+        case 64: pack ? go(k_user_project_mfma<64, true>) : go(k_user_project_mfma<64, false>); break;
+        case 128:
+            if (pack) return hipErrorInvalidValue;
+            go(k_user_project_mfma<128, false>);
+            break;
         default: return hipErrorInvalidValue;
         }
         return hipGetLastError();
@@ -337,6 +415,19 @@ __global__ __launch_bounds__(256) void k_user_combine(UserWeights w, const UserD
         st_f<T>(out + n, L > 0 ? sum / (float)L : 0.f);
         out[d + n] = X[(size_t)(ud.row_base + L) * (2 * d) + d + n];       // Eq. 3: the profile row's attention
     }
+}
+
+hipError_t launch_user_ffn_pool(const UserWeights &w, const UserDesc *users, int n_users, const void *X, hipStream_t s)
+{
+    if (n_users == 0) return hipSuccess;
+    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(n_users), dim3(1024), 0, s, w, users, (const uint16_t *)X); };
+    switch (w.wffn_frag ? w.d : 0) {
+    case 32: go(k_user_ffn_pool<32>); break;
+    case 64: go(k_user_ffn_pool<64>); break;
+    case 128: go(k_user_ffn_pool<128>); break;
+    default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
 }
 
 hipError_t launch_user_combine(const UserWeights &w, const UserDesc *users, int n_users, const void *X, const float *part,
