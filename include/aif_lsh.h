@@ -66,7 +66,9 @@ typedef struct {
 AIF_API aif_status aif_lsh_init(const aif_lsh_config *config, const uint8_t *sig_table, aif_lsh_ctx **out);
 
 /* Eq. 6-9 for n_req requests (HOST array, read during the call) on hip_stream.  Per request the
- * user-side sums the DIN needs are formed once, then every candidate is served.  A candidate id outside
+ * user-side sums the DIN needs are formed once, then every candidate is served.  A large call (from about 3 * 10^8
+ * candidate-item pairs) runs Eq. 8 beside Eq. 9 on a stream of the context's own, forked from hip_stream and joined to
+ * it again: work enqueued on hip_stream afterwards finds both results.  A candidate id outside
  * [0, n_items) cannot fault: it reads row 0, its DIN row is NaN, its tiers are -1 and a counter read by
  * aif_lsh_poll_device_errors is bumped.  Results do not depend on how a candidate list is cut into
  * requests.  Errors: AIF_EINVAL (NULL, negative sizes, misaligned tensors), AIF_ERANGE (beyond the limits
