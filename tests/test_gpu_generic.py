@@ -11,7 +11,8 @@ from test_gpu_parity import R, _say, run_batch, small_cfg, torch  # noqa: F401  
 pytestmark = pytest.mark.gpu
 
 # head widths around the 16-feature tiles and 32-wide k-steps, item widths around a k-step, layer widths around the row
-# tiles, and heads too wide for the matrix-core form (132) or layers for split activations in LDS (1280 -> 900)
+# tiles, and heads too wide for the matrix-core form (132) or layers for
+# split activations in LDS (1280 -> 1280 takes all of a compute unit's for the plain form)
 SHAPES = {
     "head_3": dict(d_item=12, d_user=12, d_attn=12, n_heads=4, mlp_dims=(48, 17, 1)),
     "head_16": dict(d_item=16, d_user=16, d_attn=16, mlp_dims=(64, 16, 15, 1)),
@@ -20,7 +21,7 @@ SHAPES = {
     "head_68_wq": dict(d_item=28, d_user=28, d_attn=68, use_wq=True, mlp_dims=(152, 1)),
     "head_128_none": dict(d_item=128, d_user=4, d_attn=128, cross_mode=wl.CROSS_NONE, mlp_dims=(260, 40, 1)),
     "head_132": dict(d_item=132, d_user=132, d_attn=132, mlp_dims=(528, 64, 1)),
-    "wide_layers": dict(mlp_dims=(56, 1280, 900, 1)),
+    "wide_layers": dict(mlp_dims=(56, 1280, 1280, 1)),
     "segdot": dict(d_item=48, d_user=12, d_attn=32, use_wq=True, cross_mode=wl.CROSS_SEGDOT, n_cross=8, d_cross_vec=24, mlp_dims=(108, 31, 1)),
 }
 SIZES = [(1, 65), (15, 1), (16, 0), (17, 31), (63, 32), (65, 33), (256, 64), (257, 63), (300, 65)]
