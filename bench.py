@@ -16,8 +16,8 @@ request shape the metric is quoted on.  Prints ONE JSON line.
 beside the real-time scoring of the current batch on another (and, for comparison, both on one stream).
 ``--workload N3`` times the nearline incremental update of the item table (aif_update_rows, Sec. 3.4): 10^6 rows
 of C3's 10^7-row table per step.
-``--workload L1..L3`` times the LSH behaviour-modelling path instead (aif_lsh_batch: user-side bit
-tables -> LSH-DIN -> SimTier over every candidate x history pair); same JSON contract, its own metric.
+``--workload L1..L3`` times the LSH behaviour-modelling path instead (aif_lsh_batch: user-side
+sums -> LSH-DIN -> SimTier over every candidate x history pair); same JSON contract, its own metric.
 """
 from __future__ import annotations
 
@@ -33,7 +33,7 @@ if ROOT not in sys.path:
 
 PEAK_HBM_GBS = 8000.0            # MI355X HBM3E
 PEAK_MFMA_BF16_TFLOPS = 2500.0   # dense bf16
-PEAK_MFMA_I8_TOPS = 5000.0       # dense int8
+PEAK_MFMA_FP4_TOPS = 10000.0     # dense fp4
 PEAK_FP32_VALU_TFLOPS = 157.3
 # 32-bit integer vector ALU: the fp32 figure counts 2 flops per FMA and 2 lanes per packed instruction
 PEAK_INT_VALU_TOPS = PEAK_FP32_VALU_TFLOPS / 4
@@ -373,16 +373,16 @@ def main_lsh(args):
     dom = max(kernels, key=lambda k: kernels[k]["avg_ms"])
     on_mfma = w.ctx.aif_lsh_simtier_kind() == 1
     if on_mfma:
-        # equal-bit counts as int8 dot products on the matrix cores: d' multiply-adds per pair; the tier counting left on
-        # the vector ALU is 448 instructions per 256 pairs and lane in the kernel's loop (1.75 per pair)
+        # equal-bit counts as dot products of fp4 signs on the matrix cores: d' multiply-adds per pair; the tier counting
+        # left on the vector ALU is 1.3 instructions per pair in the kernel's loop
         t = kernels["simtier"]["avg_ms"] * 1e-3
         kernels["simtier"]["mfma_tops"] = 2.0 * cfg.d_bits * pairs / t / 1e12
-        kernels["simtier"]["valu_tops"] = 1.75 * pairs / t / 1e12
+        kernels["simtier"]["valu_tops"] = 1.3 * pairs / t / 1e12
         kernels["simtier"]["valu_frac_of_int_peak"] = kernels["simtier"]["valu_tops"] / PEAK_INT_VALU_TOPS
         kernels["simtier"]["tops_note"] = ("tops = the vector-ALU kernel's algorithmic count (2 d'/32 + 4 per pair) over this "
                                            "kernel's time, for comparison with it only")
     if dom == "simtier" and on_mfma:
-        roof = {"kernel": "k_lsh_simtier_mfma", "bound": "mfma", "achieved": kernels[dom]["mfma_tops"], "peak": PEAK_MFMA_I8_TOPS,
+        roof = {"kernel": "k_lsh_simtier_mfma", "bound": "mfma", "achieved": kernels[dom]["mfma_tops"], "peak": PEAK_MFMA_FP4_TOPS,
                 "unit": "Top/s", "binding_unit": "vector ALU (tier counting), %.2f of its integer peak"
                                                  % kernels[dom]["valu_frac_of_int_peak"]}
     elif dom == "simtier":
@@ -391,9 +391,9 @@ def main_lsh(args):
     elif dom == "din":
         roof = {"kernel": "k_lsh_din", "bound": "hbm", "achieved": kernels[dom]["gbs"], "peak": PEAK_HBM_GBS, "unit": "GB/s"}
     else:
-        flops = 4.0 * cfg.d_bits * cfg.d_out * w.seq_len * w.n_users       # two masked multiply-adds per (t, k, j)
-        roof = {"kernel": "k_lsh_user_partial", "bound": "alu", "achieved": flops / (kernels[dom]["avg_ms"] * 1e-3) / 1e12,
-                "peak": PEAK_FP32_VALU_TFLOPS / 2, "unit": "TFLOP/s"}
+        flops = 2.0 * cfg.d_bits * cfg.d_out * w.seq_len * w.n_users       # a signed add per (t, k, j)
+        roof = {"kernel": "k_lsh_user_sums", "bound": "mfma", "achieved": flops / (kernels[dom]["avg_ms"] * 1e-3) / 1e12,
+                "peak": PEAK_MFMA_BF16_TFLOPS, "unit": "TFLOP/s"}
     roof["frac"] = roof["achieved"] / roof["peak"]
     roof["traffic"] = measured_traffic(cfg.name, dom)
     roof["traffic_source"] = traffic_note(cfg.name, dom)
@@ -402,7 +402,7 @@ def main_lsh(args):
         "metric": "candidates served/sec/GPU by the LSH behaviour modelling (LSH-DIN + SimTier)",
         "value": cands * args.steps / elapsed, "unit": "candidates/s", "n_gpus": 1, "steps": args.steps,
         "warmup": args.warmup, "ms_per_step": ms_per_step, "higher_is_better": True, "scaling": "weak",
-        "vs_baseline": None, "dtype": ("i8" if on_mfma else "u32") if dom == "simtier" else "f32", "data": "synthetic",
+        "vs_baseline": None, "dtype": ("fp4 signs (exact)" if on_mfma else "u32") if dom == "simtier" else "f32", "data": "synthetic",
         "config": {"workload": f"{cfg.name}: {w.n_users} users x {w.n_cand} candidates x {w.seq_len} history items, "
                                f"{cfg.d_bits}-bit signatures (table {cfg.n_items} rows), d={cfg.d_out} {cfg.dtype}, "
                                f"{cfg.n_tiers} tiers",

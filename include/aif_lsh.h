@@ -87,12 +87,12 @@ AIF_API aif_status aif_lsh_poll_device_errors(aif_lsh_ctx *ctx, int32_t *n_bad_i
 
 /* Which kernel forms the equal-bit counts of Eq. 6-7 and the tier counts of Eq. 9 in this context:
  * 0 = vector ALU (XNOR + population count; any signature width and tier count), 1 = matrix cores (the
- * bits as +1 / -1 int8, the count as a dot product; signatures of 32, 64 or 128 bits whose tiers are
- * 2 d' / N = a power of two equal-bit counts wide).  Same counts either way.  -1 for a NULL context. */
+ * bits as signs in fp4, the count from their dot product, exact; signatures of 32, 64 or 128 bits whose
+ * tiers are 2 d' / N = a power of two equal-bit counts wide).  Same counts either way.  -1 for a NULL context. */
 AIF_API int32_t aif_lsh_simtier_kind(const aif_lsh_ctx *ctx);
 
 /* Which kernel forms Eq. 8 in this context: 0 = vector ALU (one table row added per bit), 1 = matrix
- * cores (the candidates' bits one-hot against the fp32 tables cut exactly into three bf16 pieces;
+ * cores (the candidates' bits as signs against the fp32 table cut exactly into three bf16 pieces;
  * d_out a multiple of 32 up to 128).  Same value up to the order of the fp32 additions.  -1 for a NULL
  * context. */
 AIF_API int32_t aif_lsh_din_kind(const aif_lsh_ctx *ctx);
