@@ -16,10 +16,12 @@
 // first item's tier into the low bits of the cell's second byte and the other's into its third.  One byte permute and a
 // mask bring the tiers of two cells into one word, a second permute (a table of eight bytes) turns them into four
 // one-hot bytes, and the words of one-hot bytes are summed bit position by bit position in a network of carry-save
-// adders (two 3-input bit operations each) whose planes hold the counts in binary.  The planes are read out with
-// population counts at the end (or every 2016 words).  1.3 vector instructions per value (1.75 with one item a cell, as
-// +-1 int8 on v_mfma_i32_32x32x32_i8: 465 us for 64 x 10^4 candidates x 10^4 items of 64 bits, 836 for 8 x 10^4 x 10^5 of
-// 128, against 345 and 542).
+// adders (two 3-input bit operations each) whose planes hold the counts in binary; the carries of two passes go through
+// the upper planes in one trip.  At the end (or every 960 or 1,984 words) the planes are read out: the four bytes' counters
+// are added plane by plane, then gathered.  1.3 vector instructions per value in the loop, 1.6 with the ends (1.75 and 2.1 with
+// one item a cell, as +-1 int8 on v_mfma_i32_32x32x32_i8: 465 us for 64 x 10^4 candidates x 10^4 items of 64 bits, 836 for
+// 8 x 10^4 x 10^5 of 128, against 345 and 542; the paired carries and the read-out by planes, where every plane and tier took a
+// mask and a population count, took the two calls from 419 to 403 us and from 613 to 605).
 // Two corrections at the end: the rows past the history's end are zero vectors, which count as d' / 2 equal bits and
 // are taken off that tier again; a signature equal to the candidate's in every bit gives tier index N, whose one-hot
 // byte is empty -- the last tier's count is the history length less all the others.
@@ -35,8 +37,11 @@ constexpr int SMT_PART_BLOCKS = 2048; // a batch of fewer blocks than this has i
 constexpr int SMT_MAX_PARTS = 16;
 constexpr int SMT_TILE = 64;         // history items of a row tile: two a row
 constexpr int SMT_GROUP = 4;         // row tiles per pass of the adder network: 32 words per column tile
-constexpr int SMT_PLANES = 6;        // planes of weight 32 .. 1024 above the network's ones .. sixteens
-constexpr int SMT_FLUSH = 63;        // passes between read-outs: 63 * 32 words (+ 24 of a ragged end) <= 2047, what eleven planes count
+// Planes of weight 32 .. above the network's ones .. sixteens, and the passes between read-outs that they can count (an
+// even number, of 32 words each; + 24 of a ragged end).  Signatures of up to 64 bits keep to three waves a SIMD with one
+// plane fewer: its registers hold the carry that waits for its partner.
+constexpr int smt_planes(int ks) { return ks <= 2 ? 5 : 6; }
+constexpr int smt_flush(int ks) { return ks <= 2 ? 30 : 62; }
 
 // thirty-two signature bits -> thirty-two fp4 values (-1)^bit, bit j in nibble j
 __device__ __forceinline__ v4i fp4_signs(uint32_t bits)
@@ -111,6 +116,8 @@ __global__ __launch_bounds__(256, KS <= 2 ? 3 : 2) void k_lsh_simtier_mfma(LshMo
                                                              int32_t *__restrict__ parts)
 {
     constexpr int SMT_COLS = COLS, GROUPS = 8 / COLS, SHARE = 4 / GROUPS;      // waves that share a group of columns
+    constexpr int SMT_PLANES = smt_planes(KS), SMT_FLUSH = smt_flush(KS);
+    static_assert(SMT_FLUSH % 2 == 0 && 32 * SMT_FLUSH + 24 < 32 << SMT_PLANES, "the planes count every word between read-outs");
     static_assert(COLS == 2 || COLS == 4, "column tiles per wave");
     __shared__ int32_t cnt[LSH_MAX_TIERS][LSH_BLOCK];
     // as in the vector-ALU kernel: the blocks of one user go to one XCD, whose L2 then holds that user's history
@@ -158,19 +165,36 @@ __global__ __launch_bounds__(256, KS <= 2 ? 3 : 2) void k_lsh_simtier_mfma(LshMo
 #pragma unroll
         for (int j = 0; j < SMT_PLANES; ++j) plane[ct][j] = 0;
     }
+    // The planes' 32 counters, a byte's bit each, to eight counts: the bytes are added as the planes stand (a full adder
+    // per plane, twice), then a counter's bits are gathered, tiers t and t + 4 side by side.  A count fits sixteen bits:
+    // four bytes of at most 2,047 words.
     auto read_out = [&]() {
 #pragma unroll
         for (int ct = 0; ct < SMT_COLS; ++ct) {
             const int cand = cg * (SMT_COLS * 32) + ct * 32 + col;
+            constexpr int NP = 5 + SMT_PLANES;
+            uint32_t p[NP + 2] = {ones[ct], twos[ct], fours[ct], eights[ct], sixteens[ct]};
 #pragma unroll
-            for (int t = 0; t < LSH_MAX_TIERS; ++t) {
-                const uint32_t mask = 0x01010101u << t;
-                uint32_t n = __builtin_popcount(ones[ct] & mask) + 2 * __builtin_popcount(twos[ct] & mask) +
-                             4 * __builtin_popcount(fours[ct] & mask) + 8 * __builtin_popcount(eights[ct] & mask) +
-                             16 * __builtin_popcount(sixteens[ct] & mask);
+            for (int j = 0; j < SMT_PLANES; ++j) p[5 + j] = plane[ct][j];
 #pragma unroll
-                for (int j = 0; j < SMT_PLANES; ++j) n += (uint32_t)__builtin_popcount(plane[ct][j] & mask) << (5 + j);
-                if (n) atomicAdd(&cnt[t][cand], (int32_t)n);
+            for (int fold = 0; fold < 2; ++fold) {
+                uint32_t carry = 0;
+#pragma unroll
+                for (int j = 0; j < NP + fold; ++j) csa(p[j], carry, carry, p[j], p[j] >> (fold ? 8 : 16));
+                p[NP + fold] = carry;
+            }
+            uint32_t n[LSH_MAX_TIERS / 2] = {};
+#pragma unroll
+            for (int j = 0; j < NP + 2; ++j) {
+                const uint32_t y = (p[j] & 0xFFFFu) | (p[j] << 12 & 0xFFFF0000u);               // tiers 4 .. 7 from bit 16 up
+#pragma unroll
+                for (int t = 0; t < LSH_MAX_TIERS / 2; ++t) n[t] |= (y & 0x00010001u << t) << j;
+            }
+#pragma unroll
+            for (int t = 0; t < LSH_MAX_TIERS / 2; ++t) {
+                const uint32_t lo = (n[t] & 0xFFFFu) >> t, hi = n[t] >> (16 + t);
+                if (lo) atomicAdd(&cnt[t][cand], (int32_t)lo);
+                if (hi) atomicAdd(&cnt[t + LSH_MAX_TIERS / 2][cand], (int32_t)hi);
             }
             ones[ct] = twos[ct] = fours[ct] = eights[ct] = sixteens[ct] = 0;
 #pragma unroll
@@ -234,6 +258,9 @@ __global__ __launch_bounds__(256, KS <= 2 ? 3 : 2) void k_lsh_simtier_mfma(LshMo
         p ^= up;
         return next;
     };
+    uint32_t wait[SMT_COLS];                                    // a pass's carry of weight 32, until the next pass brings its partner
+#pragma unroll
+    for (int ct = 0; ct < SMT_COLS; ++ct) wait[ct] = 0;
     for (; rt0 + SMT_GROUP <= rt_end; rt0 += SMT_GROUP) {
         uint32_t e[SMT_COLS], f[SMT_COLS];                      // carries of weight 8 and 16 waiting for their partner
 #pragma unroll
@@ -248,21 +275,34 @@ __global__ __launch_bounds__(256, KS <= 2 ? 3 : 2) void k_lsh_simtier_mfma(LshMo
                     csa(eights[ct], fu, eights[ct], e[ct], eu);
                     if (u == 1)
                         f[ct] = fu;
-                    else {
-                        uint32_t up;                            // weight 32: rippled into the planes
-                        csa(sixteens[ct], up, sixteens[ct], f[ct], fu);
-#pragma unroll
-                        for (int j = 0; j < SMT_PLANES; ++j) up = ripple(up, plane[ct][j]);
-                    }
+                    else
+                        csa(sixteens[ct], f[ct], sixteens[ct], f[ct], fu);
                 }
             }
             load_rows(min(rt0 + u + AHEAD, rt_last), rows[u % AHEAD]);
         }
-        if (++passes == SMT_FLUSH) {
-            read_out();
-            passes = 0;
+        if (++passes & 1) {
+#pragma unroll
+            for (int ct = 0; ct < SMT_COLS; ++ct) wait[ct] = f[ct];
+        } else {
+#pragma unroll
+            for (int ct = 0; ct < SMT_COLS; ++ct) {
+                uint32_t up;
+                csa(plane[ct][0], up, plane[ct][0], wait[ct], f[ct]);
+#pragma unroll
+                for (int j = 1; j < SMT_PLANES; ++j) up = ripple(up, plane[ct][j]);
+            }
+            if (passes == SMT_FLUSH) {
+                read_out();
+                passes = 0;
+            }
         }
     }
+    if (passes & 1)
+#pragma unroll
+        for (int ct = 0; ct < SMT_COLS; ++ct)
+#pragma unroll
+            for (int j = 0; j < SMT_PLANES; ++j) wait[ct] = ripple(wait[ct], plane[ct][j]);
     // the last one to three row tiles, their carries rippled from weight 8 up
     for (; rt0 < rt_end; ++rt0) {
         v4i af[KS];
