@@ -211,21 +211,23 @@ __global__ __launch_bounds__(256, KS <= 2 ? 3 : 2) void k_lsh_simtier_mfma(LshMo
     for (int i = 0; i < 16; ++i) start[i] = (float)((1 << 23) + ((32 * KS) << (8 - sh)) + ((32 * KS) << (16 - sh)));
 #pragma unroll
     for (int i = 0; i < 16; ++i) asm volatile("" : "+v"(start[i]));
+    auto mfma_step = [&](const v16f &acc, const v4i &row, const v4i &cand) __attribute__((always_inline)) {
+        const v8i a = {row[0], row[1], row[2], row[3], 0, 0, 0, 0};                        // fp4 operands take four registers
+        const v8i c = {cand[0], cand[1], cand[2], cand[3], 0, 0, 0, 0};
+        return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, c, acc, 4, 4, 0, scale, 0, 127);
+    };
+    auto word = [&](const v16f &acc, int q) __attribute__((always_inline)) {
+        // second and third bytes of cells 2q and 2q + 1; the low bits of each are a tier, 0 .. N (above the second
+        // byte's tier lies what the other item's count leaves below its own tier: 2^(17 - SH) and up)
+        const uint32_t t = __builtin_amdgcn_perm(__float_as_uint(acc[2 * q + 1]), __float_as_uint(acc[2 * q]), 0x06050201u);
+        return __builtin_amdgcn_perm(HOT_HI, HOT_LO, t & tier_mask);
+    };
     auto tile_words = [&](const v4i(&af)[KS], int ct, uint32_t(&w)[8]) {
         v16f acc = start;
 #pragma unroll
-        for (int s = 0; s < KS; ++s) {
-            const v8i a = {af[s][0], af[s][1], af[s][2], af[s][3], 0, 0, 0, 0};            // fp4 operands take four registers
-            const v8i c = {bf[ct][s][0], bf[ct][s][1], bf[ct][s][2], bf[ct][s][3], 0, 0, 0, 0};
-            acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, c, acc, 4, 4, 0, scale, 0, 127);
-        }
+        for (int s = 0; s < KS; ++s) acc = mfma_step(acc, af[s], bf[ct][s]);
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            // second and third bytes of cells 2q and 2q + 1; the low bits of each are a tier, 0 .. N (above the second
-            // byte's tier lies what the other item's count leaves below its own tier: 2^(17 - SH) and up)
-            const uint32_t t = __builtin_amdgcn_perm(__float_as_uint(acc[2 * q + 1]), __float_as_uint(acc[2 * q]), 0x06050201u);
-            w[q] = __builtin_amdgcn_perm(HOT_HI, HOT_LO, t & tier_mask);
-        }
+        for (int q = 0; q < 8; ++q) w[q] = word(acc, q);
     };
     auto load_rows = [&](int rt, v4i(&af)[KS]) {
 #pragma unroll
@@ -253,6 +255,30 @@ __global__ __launch_bounds__(256, KS <= 2 ? 3 : 2) void k_lsh_simtier_mfma(LshMo
         csa(fours[ct], up, fours[ct], d[0], d[1]);
         return up;
     };
+    // The same with the matrix cores at work on the next (row tile, column tile), one product per share of this one's counting:
+    // left to itself the compiler issues a chain of four products in one go and waits it out (8 x 10^4 candidates, 10^5 items
+    // of 128 bits: 541 -> 510 us for the kernel, 605 -> 587 a call).  Not for shorter signatures: their chains are one or two
+    // products, covered by a third wave a SIMD, for which a second set of cells would leave no room.
+    constexpr bool BESIDE = KS == 4;
+    v16f cells = start;
+    if constexpr (BESIDE)
+        if (rt0 + SMT_GROUP <= rt_end)
+#pragma unroll
+            for (int s = 0; s < KS; ++s) cells = mfma_step(cells, rows[0][s], bf[0][s]);
+    auto add_beside = [&](const v4i(&next)[KS], int next_ct, int ct) __attribute__((always_inline)) {
+        v16f acc = start;
+        uint32_t c[4], d[2], up;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            __builtin_amdgcn_sched_barrier(0);
+            acc = mfma_step(acc, next[s % KS], bf[next_ct][s % KS]);
+            csa(ones[ct], c[s], ones[ct], word(cells, 2 * s), word(cells, 2 * s + 1));
+            if (s % 2) csa(twos[ct], d[s / 2], twos[ct], c[s - 1], c[s]);
+        }
+        csa(fours[ct], up, fours[ct], d[0], d[1]);
+        cells = acc;
+        return up;
+    };
     auto ripple = [&](uint32_t up, uint32_t &p) {
         const uint32_t next = p & up;
         p ^= up;
@@ -267,7 +293,12 @@ __global__ __launch_bounds__(256, KS <= 2 ? 3 : 2) void k_lsh_simtier_mfma(LshMo
         for (int u = 0; u < SMT_GROUP; ++u) {
 #pragma unroll
             for (int ct = 0; ct < SMT_COLS; ++ct) {
-                const uint32_t eu = add_tile(rows[u % AHEAD], ct);
+                uint32_t eu;
+                if constexpr (BESIDE) {
+                    if (ct == SMT_COLS - 1) load_rows(min(rt0 + u + AHEAD, rt_last), rows[u % AHEAD]);     // its last product is under way
+                    eu = add_beside(rows[(ct == SMT_COLS - 1 ? u + 1 : u) % AHEAD], (ct + 1) % SMT_COLS, ct);
+                } else
+                    eu = add_tile(rows[u % AHEAD], ct);
                 if (u % 2 == 0)
                     e[ct] = eu;
                 else {
@@ -279,7 +310,7 @@ __global__ __launch_bounds__(256, KS <= 2 ? 3 : 2) void k_lsh_simtier_mfma(LshMo
                         csa(sixteens[ct], f[ct], sixteens[ct], f[ct], fu);
                 }
             }
-            load_rows(min(rt0 + u + AHEAD, rt_last), rows[u % AHEAD]);
+            if constexpr (!BESIDE) load_rows(min(rt0 + u + AHEAD, rt_last), rows[u % AHEAD]);
         }
         if (++passes & 1) {
 #pragma unroll
