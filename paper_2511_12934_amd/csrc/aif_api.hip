@@ -305,16 +305,17 @@ aif_status init_impl(const aif_config *cfg, const aif_weights *wts, aif_ctx *c)
     {
         const bool wq_pieces = !c->mfma.attn && c->has_wq && attn_generic_gathers(m);
         size_t total = 0;
-        if (wq_pieces) c->wq_pieces.want(pieces_bytes(m.dtype, m.n_heads, m.d_head, m.d_item), &total);
+        const int head_tiles = query_tiles(attn_gen_tiles(m.d_head));
+        if (wq_pieces) c->wq_pieces.want(pieces_bytes(m.dtype, m.n_heads, head_tiles, m.d_item), &total);
         for (int l = 0; l < m.n_layers && !c->mfma.mlp; ++l)
-            c->w_pieces[l].want(pieces_bytes(m.dtype, 1, m.dims[l + 1], m.dims[l] - (l == 0 ? m.d_user : 0)), &total);
+            c->w_pieces[l].want(pieces_bytes(m.dtype, 1, layer_tiles(m.dims[l + 1]), m.dims[l] - (l == 0 ? m.d_user : 0)), &total);
         if (total) HIP_TRY(nullptr, c->weight_pieces.alloc(total));
         c->wq_pieces.place(c->weight_pieces);
-        if (wq_pieces) HIP_TRY(nullptr, launch_pack_pieces(m.dtype, wts->w_q, m.n_heads, m.d_head, m.d_item, 0, m.d_item, c->wq_pieces.p, s));
+        if (wq_pieces) HIP_TRY(nullptr, launch_pack_pieces(m.dtype, wts->w_q, m.n_heads, m.d_head, head_tiles, m.d_item, 0, m.d_item, c->wq_pieces.p, s));
         for (int l = 0; l < m.n_layers && !c->mfma.mlp; ++l) {
             const int col0 = l == 0 ? m.d_user : 0;
             c->w_pieces[l].place(c->weight_pieces);
-            HIP_TRY(nullptr, launch_pack_pieces(m.dtype, wts->w[l], 1, m.dims[l + 1], m.dims[l], col0, m.dims[l] - col0, c->w_pieces[l].p, s));
+            HIP_TRY(nullptr, launch_pack_pieces(m.dtype, wts->w[l], 1, m.dims[l + 1], layer_tiles(m.dims[l + 1]), m.dims[l], col0, m.dims[l] - col0, c->w_pieces[l].p, s));
         }
     }
     // both consumers of the workspace read MFMA fragments: keep it in fragment order (x_offset)

@@ -123,7 +123,7 @@ hipError_t launch_user_fold(const Model &m, const Batch &b, const float *w1u, co
                             float *bias1, hipStream_t s);
 
 // a3-a5, any shape, fp32 precision: X[row, d_item:] = [attention | cross].  wq: W_q in fp32 (null: the model has none)
-// and wq_pieces: the same as launch_pack_pieces leaves it, a group per head (used where attn_generic_gathers(m)).
+// and wq_pieces: the same as launch_pack_pieces leaves it, a group of query_tiles(attn_gen_tiles(d_head)) tiles per head (used where attn_generic_gathers(m)).
 // table: non-null only where attn_generic_gathers(m): the kernel then takes the item rows from the table itself (a1),
 // writes them to the workspace and counts ids outside the table in *bad.  longest: the longest history of the batch.
 hipError_t launch_attn_generic(const Model &m, const Batch &b, void *X, const float *wq, const void *wq_pieces, const void *table,
@@ -157,9 +157,17 @@ hipError_t launch_topk_few(const TopkDesc *descs /*host*/, int n_req, int k, int
 // init-time repacking (device -> device, any storage type -> fp32)
 hipError_t launch_pack_transposed(int dtype, const void *w, int n_out, int n_in, int col0, int ncols,
                                   float *wt /*[ncols, n_out]*/, hipStream_t s);
-// ... and as bf16 pieces in MFMA fragment order (k_generic.hip): `groups` matrices of `rows` rows each, one below the other
-size_t pieces_bytes(int dtype, int groups, int rows, int ncols);
-hipError_t launch_pack_pieces(int dtype, const void *w, int groups, int rows, int n_in, int col0, int ncols, void *out, hipStream_t s);
+// ... and as bf16 pieces in MFMA fragment order (k_generic.hip): `groups` matrices of `rows` rows each, one below the other,
+// each as `tiles` row tiles of 16 (zeros past its rows); pieces_bytes: what `out` has to hold
+size_t pieces_bytes(int dtype, int groups, int tiles, int ncols);
+hipError_t launch_pack_pieces(int dtype, const void *w, int groups, int rows, int tiles, int n_in, int col0, int ncols, void *out, hipStream_t s);
+// Row tiles of a layer's weights: whole k-steps of the layer that reads its outputs.
+constexpr int layer_tiles(int rows) { return (rows + 31) / 32 * 2; }
+// Row tiles of W_q per head.  Three places agree on it: the room for the pieces, their packing, and the kernel, whose
+// heads come in four sizes of `attn_gen_tiles` feature tiles and which contracts over pairs of them.
+constexpr int GEN_MAX_HEAD = 128;
+constexpr int attn_gen_tiles(int d_head) { return d_head <= 16 ? 1 : d_head <= 32 ? 2 : d_head <= 64 ? 4 : 8; }
+constexpr int query_tiles(int feature_tiles) { return (feature_tiles + 1) / 2 * 2; }
 hipError_t launch_to_f32(int dtype, const void *src, int64_t rows, int cols, int ld_src, int col0,
                          float *dst /*[rows, cols]*/, hipStream_t s);
 

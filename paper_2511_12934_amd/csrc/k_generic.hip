@@ -327,7 +327,6 @@ __global__ __launch_bounds__(256) void k_attn_generic(Model m, Batch b, T *__res
 // the vector ALU after a gather launch, 48 and 55 with the keys 32 at a time; fp32,
 // one request of 1,000: 11.5 against 22 + 6.
 // ---------------------------------------------------------------------------
-constexpr int GEN_MAX_HEAD = 128;
 constexpr int GEN_KEYS = 32;
 
 // One head of one candidate by one wave in plain fp32 arithmetic: where a product of pieces met a value that is not
@@ -387,7 +386,7 @@ __device__ __forceinline__ float exp_neg(float x)
 }
 
 // FT: tiles of 16 features a head has.  WV: waves of the block, 16 candidates each at a time.  wqp: W_q as pieces,
-// [head][FT'][k-step of 32][piece][64 lanes][8], FT' = FT rounded up to even, rows past the head's width zero (pack_pieces).
+// [head][query_tiles(FT)][k-step of 32][piece][64 lanes][8], rows past the head's width zero (pack_pieces).
 // table null: the item rows are in the workspace.
 // RES: the pieces of all the request's keys, of every head, are staged at once, in dynamic LDS, and the block walks a whole
 // ROW_BLOCK of candidates with no further barrier; else 32 keys of one head at a time for 16 WV candidates.
@@ -399,6 +398,7 @@ __global__ __launch_bounds__(64 * WV, FT <= 2 ? 4 : 2) void k_attn_gen(Model m, 
     constexpr int P = stored<T>::P, PQ = WQ ? 3 : P, KS = (FT + 1) / 2, VEC = 16 / sizeof(T);
     constexpr int FRAGS = 2 * KS + FT;                          // fragments of a chunk of keys: K (key tile, k-step), then V (feature tile)
     constexpr int PER = RES ? 2 : (FRAGS + WV - 1) / WV;        // fragments a wave has on their way
+    static_assert(2 * KS == query_tiles(FT), "the query's tiles are those that are packed");
     constexpr float NEVER = -1e30f;                             // the score of a key past the end
     extern __shared__ __align__(16) char dyn[];
     bf16x8 *frag;                                               // [head][chunk][fragment][piece][lane]; RES = false: one chunk
@@ -556,7 +556,7 @@ __global__ __launch_bounds__(64 * WV, FT <= 2 ? 4 : 2) void k_attn_gen(Model m, 
 #pragma unroll
                 for (int f = 0; f < 2 * KS; ++f) qb[f] = qs[f] = f32x4{0.f, 0.f, 0.f, 0.f};
                 const int ksn = (m.d_item + 31) / 32;
-                const bf16x8 *wh = wqp + (size_t)h * (2 * KS) * ksn * P * 64 + lane;
+                const bf16x8 *wh = wqp + (size_t)h * query_tiles(FT) * ksn * P * 64 + lane;
                 for (int ks = 0; ks < ksn; ++ks) {
                     float v[8];
                     load8<T>(er + 32 * ks + 8 * g, m.d_item - 32 * ks - 8 * g, v);
@@ -728,10 +728,14 @@ template <typename T>
 static hipError_t attn_gen_launch(const Model &m, const Batch &b, void *X, const void *table, const void *wqp, const float *wq,
                                   int32_t *bad, int longest, hipStream_t s)
 {
-    if (m.d_head <= 16) attn_gen_ft<T, 1>(m, b, X, table, wqp, wq, bad, longest, s);
-    else if (m.d_head <= 32) attn_gen_ft<T, 2>(m, b, X, table, wqp, wq, bad, longest, s);
-    else if (m.d_head <= 64) attn_gen_ft<T, 4>(m, b, X, table, wqp, wq, bad, longest, s);
-    else attn_gen_ft<T, 8>(m, b, X, table, wqp, wq, bad, longest, s);
+    static_assert(attn_gen_tiles(GEN_MAX_HEAD) * 16 == GEN_MAX_HEAD, "eight feature tiles hold the widest head");
+    switch (attn_gen_tiles(m.d_head)) {
+    case 1: attn_gen_ft<T, 1>(m, b, X, table, wqp, wq, bad, longest, s); break;
+    case 2: attn_gen_ft<T, 2>(m, b, X, table, wqp, wq, bad, longest, s); break;
+    case 4: attn_gen_ft<T, 4>(m, b, X, table, wqp, wq, bad, longest, s); break;
+    case 8: attn_gen_ft<T, 8>(m, b, X, table, wqp, wq, bad, longest, s); break;
+    default: return hipErrorInvalidValue;
+    }
     return hipGetLastError();
 }
 
@@ -921,7 +925,7 @@ __global__ __launch_bounds__(64 * WV, NC == 1 ? 2 : sizeof(T) == 4 ? 3 : 4) void
     for (int l = 0; l < m.n_layers; ++l) {
         const int K = l == 0 ? m.k1 : m.dims[l], N = m.dims[l + 1], ksn = (K + 31) / 32;
         const bool last = l + 1 == m.n_layers;
-        const int nrt = last ? 1 : (N + 31) / 32 * 2;           // row tiles: the next layer reads whole k-steps
+        const int nrt = last ? 1 : layer_tiles(N);
         const bf16x8 *wl = (const bf16x8 *)w.pieces[l];
         const float *bl = l == 0 ? bias1 + (size_t)rd.slot * N : w.bias[l];
         // row tiles rt .. rt + RT - 1; `first` once per layer and wave, with the layer's barriers
@@ -1054,7 +1058,7 @@ static size_t mlp_gen_lds(const Model &m, int nc, int waves, bool split, int32_t
     for (int l = 0; l < m.n_layers; ++l) {
         const size_t ks = ((l == 0 ? m.k1 : m.dims[l]) + 31) / 32;
         const size_t bytes = ks * nc * (split ? 1024u * (l == 0 && m.dtype == 1 ? 1 : 3) : 2048u);
-        const int nrt = (m.dims[l + 1] + 31) / 32 * 2;
+        const int nrt = layer_tiles(m.dims[l + 1]);
         if (l + 1 < m.n_layers && nrt > (nrt >= 2 * waves ? 2 * waves : waves)) in_place = false;
         need[l & 1] = std::max(need[l & 1], bytes);
     }
@@ -1120,14 +1124,24 @@ __global__ void k_pack_pieces(const T *__restrict__ w, int n_in, int col0, int r
     for (int q = 0; q < P; ++q) out[(f * P + q) * 64 + lane] = p.p[q];
 }
 
-size_t pieces_bytes(int dtype, int groups, int rows, int ncols)
+// Every head width: its feature tiles hold it, and the packed tiles hold its rows.
+constexpr bool head_tiles_hold()
 {
-    return (size_t)groups * ((rows + 31) / 32 * 2) * ((ncols + 31) / 32) * (dtype == 0 ? 3 : 1) * 1024;
+    for (int d = 1; d <= GEN_MAX_HEAD; ++d)
+        if (attn_gen_tiles(d) * 16 < d || query_tiles(attn_gen_tiles(d)) < attn_gen_tiles(d)) return false;
+    return true;
+}
+static_assert(head_tiles_hold(), "heads of every width up to GEN_MAX_HEAD");
+
+size_t pieces_bytes(int dtype, int groups, int tiles, int ncols)
+{
+    return (size_t)groups * tiles * ((ncols + 31) / 32) * (dtype == 0 ? 3 : 1) * 1024;
 }
 
-hipError_t launch_pack_pieces(int dtype, const void *w, int groups, int rows, int n_in, int col0, int ncols, void *out, hipStream_t s)
+hipError_t launch_pack_pieces(int dtype, const void *w, int groups, int rows, int tiles, int n_in, int col0, int ncols, void *out, hipStream_t s)
 {
-    const int ksn = (ncols + 31) / 32, rt_n = (rows + 31) / 32 * 2;
+    if (16 * tiles < rows) return hipErrorInvalidValue;
+    const int ksn = (ncols + 31) / 32, rt_n = tiles;
     const size_t total = (size_t)groups * rt_n * ksn * 64;
     const dim3 grid((unsigned)((total + 255) / 256));
     if (dtype == 0)

@@ -11,7 +11,8 @@ from test_gpu_parity import R, _say, run_batch, small_cfg, torch  # noqa: F401  
 pytestmark = pytest.mark.gpu
 
 # head widths around the 16-feature tiles and 32-wide k-steps, item widths around a k-step, layer widths around the row
-# tiles, and heads too wide for the matrix-core form (132) or layers for
+# tiles, several heads of a query projection at every tile count a head can have, and heads too wide for the matrix-core
+# form (132) or layers for
 # split activations in LDS (1280 -> 1280 takes all of a compute unit's for the plain form)
 SHAPES = {
     "head_3": dict(d_item=12, d_user=12, d_attn=12, n_heads=4, mlp_dims=(48, 17, 1)),
@@ -20,6 +21,10 @@ SHAPES = {
     "head_64": dict(d_item=64, d_user=64, d_attn=64, mlp_dims=(256, 129, 65, 1)),
     "head_68_wq": dict(d_item=28, d_user=28, d_attn=68, use_wq=True, mlp_dims=(152, 1)),
     "head_128_none": dict(d_item=128, d_user=4, d_attn=128, cross_mode=wl.CROSS_NONE, mlp_dims=(260, 40, 1)),
+    "heads_40_wq": dict(d_item=40, d_user=40, d_attn=160, n_heads=4, use_wq=True, mlp_dims=(280, 33, 1)),
+    "heads_72_wq": dict(d_item=40, d_user=40, d_attn=144, n_heads=2, use_wq=True, mlp_dims=(264, 33, 1)),
+    "heads_80_wq": dict(d_item=64, d_user=64, d_attn=240, n_heads=3, use_wq=True, mlp_dims=(432, 17, 1)),
+    "heads_96_wq": dict(d_item=72, d_user=72, d_attn=384, n_heads=4, use_wq=True, mlp_dims=(600, 1)),
     "head_132": dict(d_item=132, d_user=132, d_attn=132, mlp_dims=(528, 64, 1)),
     "wide_layers": dict(mlp_dims=(56, 1280, 1280, 1)),
     "segdot": dict(d_item=48, d_user=12, d_attn=32, use_wq=True, cross_mode=wl.CROSS_SEGDOT, n_cross=8, d_cross_vec=24, mlp_dims=(108, 31, 1)),
@@ -55,13 +60,13 @@ def test_pieces_kernels_at_tile_edges(R, torch, monkeypatch, dtype, shape):  # n
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("seq_len", [40, 700])
-def test_large_batches_give_the_bits_of_single_requests(R, torch, monkeypatch, dtype, seq_len):  # noqa: F811
-    """140 requests take the kernels with 32 candidates a block (MLP) and all keys resident or, of 700, 32 at a time in
-    blocks of eight waves (attention); one alone those with 16 candidates and four waves."""
+@pytest.mark.parametrize("seq_len,n_heads", [(40, 1), (700, 1), (40, 2), (30, 4)])
+def test_large_batches_give_the_bits_of_single_requests(R, torch, monkeypatch, dtype, seq_len, n_heads):  # noqa: F811
+    """140 requests take the kernels with 32 candidates a block (MLP) and all keys of every head resident or, of 700, 32 at a
+    time in blocks of eight waves (attention); one alone those with 16 candidates and four waves."""
     if dtype == "bf16":
         monkeypatch.setenv("AIF_FORCE_GENERIC", "1")
-    cfg = small_cfg(dtype, seq_len=seq_len, n_items=3000, d_item=32, d_user=32, d_attn=32, use_wq=True, mlp_dims=(128, 70, 20, 1))
+    cfg = small_cfg(dtype, seq_len=seq_len, n_items=3000, d_item=32, d_user=32, d_attn=32, n_heads=n_heads, use_wq=True, mlp_dims=(128, 70, 20, 1))
     rng = np.random.default_rng(3)
     model = wl.make_model(cfg, seed=5, bias_scale=0.3)
     table = wl.make_table_host(cfg, rng, sigma=1.0)
@@ -73,6 +78,11 @@ def test_large_batches_give_the_bits_of_single_requests(R, torch, monkeypatch, d
         ctx.aif_score_request(alone.req)
         torch.cuda.synchronize()
         assert np.array_equal(alone.logits.cpu().numpy(), zs[r]), r
+        if n_heads > 1:
+            ref = oracle_scores(cfg, model, table, *users_ids[r])
+            cols = slice(cfg.d_item, cfg.d_item + cfg.d_attn)
+            X = R.peek_features(ctx, cfg, 0, users_ids[r][1].size)
+            assert_features_close(dtype, X[:, cols], ref.attn, f"req {r} attention", key_rounding_term(cfg, model, table[users_ids[r][1]], users_ids[r][0]))
 
 
 def plain_logits(cfg, model, rows, u):
