@@ -399,7 +399,6 @@ __global__ __launch_bounds__(64 * WV, FT <= 2 ? 4 : 2) void k_attn_gen(Model m, 
     constexpr int FRAGS = 2 * KS + FT;                          // fragments of a chunk of keys: K (key tile, k-step), then V (feature tile)
     constexpr int PER = RES ? 2 : (FRAGS + WV - 1) / WV;        // fragments a wave has on their way
     static_assert(2 * KS == query_tiles(FT), "the query's tiles are those that are packed");
-    constexpr float NEVER = -1e30f;                             // the score of a key past the end
     extern __shared__ __align__(16) char dyn[];
     bf16x8 *frag;                                               // [head][chunk][fragment][piece][lane]; RES = false: one chunk
     if constexpr (RES) frag = (bf16x8 *)dyn;
@@ -619,10 +618,13 @@ __global__ __launch_bounds__(64 * WV, FT <= 2 ? 4 : 2) void k_attn_gen(Model m, 
 #pragma unroll
                     for (int i = 0; i < 4; ++i) sc[4 * kt + i] = (sb[i] + ss[i]) * scale;
                 }
-                if (t0 + GEN_KEYS > L)
+                // keys past the end: an infinitely low score, whatever the others' (a lane may hold no other: its maximum is
+                // then the other lanes'), and a weight of zero
+                const bool ragged = t0 + GEN_KEYS > L;
+                auto past = [&](int j) __attribute__((always_inline)) { return ragged && t0 + 4 * g + (j & 3) + 16 * (j >> 2) >= L; };
+                if (ragged)
 #pragma unroll
-                    for (int j = 0; j < 8; ++j)
-                        if (t0 + 4 * g + (j & 3) + 16 * (j >> 2) >= L) sc[j] = NEVER;
+                    for (int j = 0; j < 8; ++j) sc[j] = past(j) ? -INFINITY : sc[j];
                 float top = fmaxf(fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3])), fmaxf(fmaxf(sc[4], sc[5]), fmaxf(sc[6], sc[7])));
                 top = fmaxf(top, __shfl_xor(top, 16, 64));
                 top = fmaxf(top, __shfl_xor(top, 32, 64));
@@ -641,6 +643,9 @@ __global__ __launch_bounds__(64 * WV, FT <= 2 ? 4 : 2) void k_attn_gen(Model m, 
                 float p[8];
 #pragma unroll
                 for (int j = 0; j < 8; ++j) p[j] = exp_neg(sc[j] - mx);
+                if (ragged)
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) p[j] = past(j) ? 0.f : p[j];
                 sum += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
                 const Pieces<3> pf = split8<3>(p);
 #pragma unroll

@@ -85,6 +85,35 @@ def test_large_batches_give_the_bits_of_single_requests(R, torch, monkeypatch, d
             assert_features_close(dtype, X[:, cols], ref.attn, f"req {r} attention", key_rounding_term(cfg, model, table[users_ids[r][1]], users_ids[r][0]))
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("n_req,seq_len", [(3, 65), (130, 65), (130, 700)])
+def test_keys_past_the_end_weigh_nothing_however_low_the_real_scores(R, torch, monkeypatch, dtype, n_req, seq_len):  # noqa: F811
+    """Real scores of -1e32 and below, far enough apart that the softmax is one key's, whose value the attention then is:
+    histories that end inside a chunk of 32 keys, at its first and last key, and one key alone, in the small, the resident
+    and the streamed form."""
+    if dtype == "bf16":
+        monkeypatch.setenv("AIF_FORCE_GENERIC", "1")
+    cfg = small_cfg(dtype, seq_len=seq_len, n_items=300, d_item=32, d_user=32, d_attn=32, mlp_dims=(128, 16, 1))
+    _say(f"keys past the end {dtype} {n_req} x {seq_len}")
+    rng = np.random.default_rng(6)
+    model = wl.make_model(cfg, seed=5, bias_scale=0.3)
+    table = wl.round_storage((1e16 * (1 + rng.random((300, 32)))).astype(np.float32), dtype)
+    users_ids = []
+    for r in range(n_req):
+        L = (1, 31, 33, 40, 63, 64, 65, seq_len - 3)[r % 8] if n_req > 3 else (1, 33, 65)[r]
+        u = wl.make_user(cfg, rng, sigma=1.0, seq_len=L)
+        u.seq_keys[:] = wl.round_storage(-1e16 * (1 + rng.permutation(L)[:, None] / np.float32(L)) * np.ones((1, 32), np.float32), dtype)
+        # several keys may round to the same low value in 16 bits: one of them is made the highest
+        u.seq_keys[int(rng.integers(0, L))] *= 0.5
+        users_ids.append((u, rng.integers(0, 300, int(rng.integers(1, 257))).astype(np.int32)))
+    ctx = run_batch(R, torch, cfg, model, R.to_device(table, dtype), users_ids, max_seq_len=seq_len)[3]
+    for r in range(min(n_req, 16)):
+        u, ids = users_ids[r]
+        X = R.peek_features(ctx, cfg, r, ids.size)
+        want = u.seq_vals[np.argmax(u.seq_keys[:, 0])]
+        assert np.array_equal(X[:, 32:64], np.broadcast_to(want, (ids.size, 32))), (r, u.seq_keys.shape[0])
+
+
 def plain_logits(cfg, model, rows, u):
     """The path in numpy, in 64 bits, with the kernels' maxima: fmax(NaN, x) = x (ReLU turns a NaN into zero)."""
     f = lambda a: np.asarray(a, np.float64)  # noqa: E731
