@@ -24,9 +24,14 @@ constexpr int LSH_MAX_TIERS = 8;
 // How many ways a block of k_lsh_user_sums shares out its chunk's items: its four waves take a row tile of 32 bits each,
 // and signatures of 32 (64) bits have one (two).  Every share leaves partial sums of its own.
 __host__ __device__ inline int lsh_user_split(int d_bits) { return d_bits == 32 ? 4 : d_bits == 64 ? 2 : 1; }
-// Rows of d floats in a request's user-side sums: D's d', then total as hi + lo.  An error in D[k] reaches a candidate
-// divided by 2 d' and mixed with the others'; one in total reaches all of them whole, so total alone is summed in 64 bits.
-__host__ __device__ inline int lsh_rows(int d_bits) { return d_bits + 2; }
+// Rows of d floats in a request's user-side sums: D's d', then total and `lowest` as hi + lo each, then the majority word
+// (d' bits, in a row of their own).  An error in D[k] reaches a candidate divided by 2 d' and mixed with the others'; one
+// in total or lowest reaches it whole, so these two are summed in 64 bits.
+__host__ __device__ inline int lsh_rows(int d_bits) { return d_bits + 5; }
+constexpr int LSH_TOTAL = 0, LSH_LOWEST = 2, LSH_MAJORITY = 4;      // rows past D's
+// A candidate that has the history's majority bit in fewer than 5/16 of its places is served from `lowest` instead of
+// total / 2 (k_lsh_user_mfma.hip).
+__device__ __forceinline__ bool lsh_dissimilar(int n_majority_bits, int d_bits) { return 16 * n_majority_bits < 5 * d_bits; }
 // the n partial sums at p, p + stride, .. added in order, eight loads in flight
 __device__ __forceinline__ float lsh_sum_parts(const float *p, size_t stride, int n)
 {
@@ -42,7 +47,7 @@ __device__ __forceinline__ float lsh_sum_parts(const float *p, size_t stride, in
     for (; c < n; ++c) acc += p[(size_t)c * stride];
     return acc;
 }
-// the same for total: each partial is p[0] + p[d]
+// the same for a sum of 64 bits: each partial is p[0] + p[d]
 __device__ __forceinline__ double lsh_sum_totals(const float *p, size_t stride, int d, int n)
 {
     double acc = 0.0;
@@ -88,17 +93,19 @@ struct LshModel {
 };
 
 // a2 of this path (k_lsh_user_mfma.hip) -- per request and share of its history, lsh_rows(d') rows of d floats:
-// part[r][share][k] = sum of c_tk U~_t (c = 1 where bit k of signature t is 0, else -1), part[r][share][d'], [d' + 1] = sum of U~_t (hi, lo)
+// part[r][share][k] = sum of c_tk U~_t (c = 1 where bit k of signature t is 0, else -1), then the sum of U~_t, the sum of w_t U~_t
+// (w_t: places where signature t differs from the majority word; hi, lo each), and the majority word (share 0's alone)
 // (grid_chunks: chunks of the longest history in the batch; part_stride: shares a request has room for)
 hipError_t launch_lsh_user_sums(const LshModel &m, const LshBatch &b, int grid_chunks, int part_stride, float *part, hipStream_t s);
-// A[r] = the shares of request r added up, in order: D [d'][d], then total (hi, lo) [2][d]
+// A[r] = the shares of request r added up, in a fixed order: D [d'][d], total / 2 (hi, lo) [2][d], lowest = the weighted sum / d'
+// (hi, lo) [2][d], the majority word
 hipError_t launch_lsh_user_reduce(const LshModel &m, const LshBatch &b, int part_stride, const float *part, float *A, hipStream_t s);
-// Eq. 8: din[i] = total / 2 + (1 / 2 d') sum_k c_ik D[k]
+// Eq. 8: din[i] = total / 2 + (1 / 2 d') sum_k c_ik D[k], or the same from `lowest`
 hipError_t launch_lsh_din(const LshModel &m, const LshBatch &b, const uint8_t *sig_table, const float *A, int32_t *bad,
                           hipStream_t s);
 // Eq. 8 on the matrix cores (d a multiple of 32 up to 128): the candidates' signs against D cut into three bf16 pieces.
 // launch_lsh_din_pieces takes launch_lsh_user_reduce's place: it adds the shares up itself and leaves D as pieces
-// (lsh_din_pieces_stride() 16-byte pieces per request) and total in A's last rows.
+// (lsh_din_pieces_stride() 16-byte pieces per request) and the rest in A's last rows.
 bool lsh_din_on_mfma(const LshModel &m);
 size_t lsh_din_pieces_stride(const LshModel &m);
 hipError_t launch_lsh_din_pieces(const LshModel &m, const LshBatch &b, int part_stride, const float *part, float *A, void *pieces, hipStream_t s);

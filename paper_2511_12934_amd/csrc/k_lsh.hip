@@ -18,7 +18,8 @@ namespace aif {
 
 // ---------------------------------------------------------------------------
 // Eq. 8.  Block = LSH_BLOCK candidates of one request; d / 16 threads per candidate, 16 features each.
-// The user's table D[d'][d] is staged in LDS in slices of KC bits and added with the candidate's sign.
+// The user's table D[d'][d] is staged in LDS in slices of KC bits and added with the candidate's sign -- or, for a candidate
+// unlike the history, twice that where it has the majority bit and not at all elsewhere (k_lsh_user_mfma.hip).
 // ---------------------------------------------------------------------------
 constexpr int LSH_DIN_LDS = 64 * 1024;
 
@@ -38,10 +39,12 @@ __global__ __launch_bounds__(256) void k_lsh_din(LshModel m, LshBatch b, const u
     const int local0 = blk * LSH_BLOCK - rd.cand_base;
     const int nrows = min(LSH_BLOCK, rd.n_cand - local0);
     if (nrows <= 0) return;
-    const int d = m.d_out, jg = d / 16, nb = m.d_bits / 8;
+    const int d = m.d_out, jg = d / 16, nb = m.d_bits / 8, nw = m.d_bits / 32;
     const int per_round = 256 / jg;                             // candidates served at once
     const int kc = min(m.d_bits, LSH_DIN_LDS / (d * 4)) & ~7;       // bits per slice, whole bytes
     const float *Ar = A + (size_t)r * lsh_rows(m.d_bits) * d;
+    const float *last = Ar + (size_t)m.d_bits * d;
+    const uint8_t *maj = (const uint8_t *)(last + LSH_MAJORITY * d);
     const int sub = threadIdx.x / jg, j0 = (threadIdx.x - sub * jg) * 16;
     const float inv = 0.5f / (float)m.d_bits;
     int n_bad = 0;
@@ -56,6 +59,13 @@ __global__ __launch_bounds__(256) void k_lsh_din(LshModel m, LshBatch b, const u
             if (live && j0 == 0) ++n_bad;
         }
         const uint8_t *sig = sig_table + (size_t)id * nb;
+        uint32_t same[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) same[i] = ~(((const uint32_t *)sig)[min(i, nw - 1)] ^ ((const uint32_t *)maj)[min(i, nw - 1)]);
+        int n_maj = 0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) n_maj += i < nw ? __builtin_popcount(same[i]) : 0;
+        const bool low = lsh_dissimilar(n_maj, m.d_bits);
         float acc[16];
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[i] = 0.f;
@@ -68,10 +78,10 @@ __global__ __launch_bounds__(256) void k_lsh_din(LshModel m, LshBatch b, const u
             __syncthreads();
             if (live) {
                 for (int kb = 0; kb < kn; kb += 8) {
-                    const uint32_t byte = sig[(k0 + kb) >> 3];
+                    const uint32_t byte = sig[(k0 + kb) >> 3], equal = ~(byte ^ maj[(k0 + kb) >> 3]);
 #pragma unroll
                     for (int u = 0; u < 8; ++u) {
-                        const float c = (byte >> (7 - u)) & 1 ? -1.f : 1.f;
+                        const float mag = !low ? 1.f : (equal >> (7 - u)) & 1 ? 2.f : 0.f, c = (byte >> (7 - u)) & 1 ? -mag : mag;
                         const float4 *a4 = (const float4 *)(sa + (size_t)(kb + u) * d + j0);
 #pragma unroll
                         for (int q = 0; q < 4; ++q) {
@@ -88,14 +98,11 @@ __global__ __launch_bounds__(256) void k_lsh_din(LshModel m, LshBatch b, const u
         if (live) {
             float4 *o = (float4 *)(rd.din_out + (size_t)(local0 + cand) * d + j0);
             const float nanv = __uint_as_float(0x7FC00000u);
-            const float4 *hi = (const float4 *)(Ar + (size_t)m.d_bits * d + j0), *lo = (const float4 *)(Ar + (size_t)(m.d_bits + 1) * d + j0);
+            const float *hi = last + (low ? LSH_LOWEST : LSH_TOTAL) * d + j0, *lo = hi + d;
+            auto at = [&](int i) { return hi[i] + fmaf(acc[i], inv, lo[i]); };
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const float4 x = hi[q], y = lo[q];
-                o[q] = ok ? make_float4(0.5f * x.x + fmaf(acc[4 * q], inv, 0.5f * y.x), 0.5f * x.y + fmaf(acc[4 * q + 1], inv, 0.5f * y.y),
-                                        0.5f * x.z + fmaf(acc[4 * q + 2], inv, 0.5f * y.z), 0.5f * x.w + fmaf(acc[4 * q + 3], inv, 0.5f * y.w))
-                          : make_float4(nanv, nanv, nanv, nanv);
-            }
+            for (int q = 0; q < 4; ++q)
+                o[q] = ok ? make_float4(at(4 * q), at(4 * q + 1), at(4 * q + 2), at(4 * q + 3)) : make_float4(nanv, nanv, nanv, nanv);
         }
     }
     if (n_bad) atomicAdd(bad, n_bad);

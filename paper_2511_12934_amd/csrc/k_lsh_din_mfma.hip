@@ -1,7 +1,7 @@
 // Eq. 8 on the matrix cores.
 //
-// DIN_i = total / 2 + (1 / 2 d') sum_k c_ik D[k] (k_lsh_user_mfma.hip) is a contraction of the candidates' signs c = +-1,
-// exact in bf16, with the user's fp32 table D [d'][d], which is not: it is cut into three bf16 pieces, D = hi + mid + lo
+// DIN_i = total / 2 + (1 / 2 d') sum_k c_ik D[k], or from `lowest` with x_ik = 2 c_ik or 0 in c's place for a candidate unlike
+// the history (k_lsh_user_mfma.hip), is a contraction of the candidates' signs c = +-1 (or x), exact in bf16, with the user's fp32 table D [d'][d], which is not: it is cut into three bf16 pieces, D = hi + mid + lo
 // (hi = bf16(D), mid = bf16(D - hi), lo = the rest: 8 + 8 + 8 significant bits, exact), each a contraction of its own into
 // the SAME fp32 accumulator: every lo product first, then every mid, then every hi, so that the d' additions at full
 // magnitude are what they are in the vector-ALU kernel and the two small pieces cost rounding errors 2^-8 and 2^-16 as
@@ -16,6 +16,8 @@
 // Streaming stores: 75.
 #include "aif_lsh_dev.h"
 
+#include <type_traits>
+
 namespace aif {
 
 typedef __bf16 din_bf16x8 __attribute__((ext_vector_type(8)));
@@ -27,22 +29,32 @@ __device__ __forceinline__ uint32_t bf16_rne_bits(float x)
     return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;          // finite inputs (sums of embeddings)
 }
 
-// Block = (k-step, feature tile): 16 bits x 32 features, a thread per sum; the blocks past the last k-step add up `total`.
+// Block = (k-step, feature tile): 16 bits x 32 features, a thread per sum; the blocks past the last k-step add up total and
+// lowest, eight threads each per feature.
 __global__ __launch_bounds__(512) void k_lsh_din_pieces(LshModel m, LshBatch b, int part_stride, const float *__restrict__ part,
                                                         float *__restrict__ A, uint4 *__restrict__ out, size_t req_stride)
 {
     __shared__ float D[16][33];
+    __shared__ double S[16][33];
     const int ft_n = m.d_out / 32, ks_n = m.d_bits / 16, ft = blockIdx.x % ft_n, ks = blockIdx.x / ft_n, r = blockIdx.y;
     const int k = threadIdx.x >> 5, j = threadIdx.x & 31, shares = lsh_chunks(b.reqs[r].seq_len) * lsh_user_split(m.d_bits);
     const size_t n = (size_t)lsh_rows(m.d_bits) * m.d_out;
     const float *p = part + (size_t)r * part_stride * n + ft * 32 + j;
     if (ks == ks_n) {
-        if (k == 0) {
-            const double t = lsh_sum_totals(p + (size_t)m.d_bits * m.d_out, n, m.d_out, shares);
-            float *a = A + (size_t)r * n + (size_t)m.d_bits * m.d_out + ft * 32 + j;
+        float *a = A + (size_t)r * n + (size_t)m.d_bits * m.d_out;
+        const int row = k & 1 ? LSH_LOWEST : LSH_TOTAL, from = k >> 1;
+        S[k][j] = lsh_sum_totals(p + (size_t)(m.d_bits + row) * m.d_out + from * n, 8 * n, m.d_out, (shares - from + 7) / 8);
+        __syncthreads();
+        if (k < 2) {
+            double t = 0.0;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) t += S[2 * i + k][j];
+            t *= k == 0 ? 0.5 : 1.0 / m.d_bits;
+            a += row * m.d_out + ft * 32 + j;
             a[0] = (float)t;
             a[m.d_out] = (float)(t - (double)(float)t);
-        }
+        } else if (k == 2 && ft == 0 && j < 8)
+            a[LSH_MAJORITY * m.d_out + j] = shares > 0 ? p[(size_t)(m.d_bits + LSH_MAJORITY) * m.d_out] : 0.f;
         return;
     }
     D[k][j] = lsh_sum_parts(p + (size_t)(16 * ks + k) * m.d_out, n, shares);
@@ -115,8 +127,13 @@ __global__ __launch_bounds__(256, 2) void k_lsh_din_mfma(LshModel m, LshBatch b,
     fetch(0, w[0]);
     fetch(1, w[1]);
     fetch(2, w[2]);
+    const float *last = A + ((size_t)r * lsh_rows(m.d_bits) + m.d_bits) * m.d_out;
+    uint32_t maj[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) maj[q] = __float_as_uint(last[LSH_MAJORITY * m.d_out + q]);      // d >= 32; words past the signature's are not looked at
     uint32_t sig[RT][8];
-    uint32_t live_mask[RT], ok_mask[RT];
+    uint32_t live_mask[RT], ok_mask[RT], low_mask[RT];
+    uint32_t usual[RT], one[RT];                                // of this lane's candidate: see step()
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
         const int cand = rt * 32 + col;
@@ -129,6 +146,13 @@ __global__ __launch_bounds__(256, 2) void k_lsh_din_mfma(LshModel m, LshBatch b,
         for (int q = 0; q < 8; ++q) sig[rt][q] = q < nw ? p[q] : 0u;
         live_mask[rt] = (uint32_t)__ballot(live);               // lanes 0..31: one bit per candidate of the row tile
         ok_mask[rt] = (uint32_t)__ballot(ok);
+        int n_maj = 0;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) n_maj += q < nw ? __builtin_popcount(~(sig[rt][q] ^ maj[q])) : 0;
+        const bool low = live && lsh_dissimilar(n_maj, m.d_bits);
+        low_mask[rt] = (uint32_t)__ballot(low);
+        usual[rt] = low ? 0u : ~0u;
+        one[rt] = low ? 0u : 0x00800080u;
     }
     din_f32x16 acc[RT][FT];
 #pragma unroll
@@ -139,19 +163,31 @@ __global__ __launch_bounds__(256, 2) void k_lsh_din_mfma(LshModel m, LshBatch b,
             for (int i = 0; i < 16; ++i) acc[rt][ft][i] = 0.f;
 
     int ks = 0;
-    auto step = [&](int i, const uint4 (&f)[FT]) __attribute__((always_inline)) {
+    // ODD: one of the wave's candidates is unlike the history
+    auto step = [&](auto odd_c, int i, const uint4 (&f)[FT]) __attribute__((always_inline)) {
+        constexpr bool ODD = decltype(odd_c)::value;
         if (i >= steps) return;
         din_bf16x8 x[RT];
+        uint32_t mword = maj[0];
+        if constexpr (ODD)
+#pragma unroll
+            for (int q = 1; q < 8; ++q) mword = (ks >> 1) == q ? maj[q] : mword;
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
             uint32_t word = sig[rt][0];
 #pragma unroll
             for (int q = 1; q < 8; ++q) word = (ks >> 1) == q ? sig[rt][q] : word;
             const uint32_t byte = word >> (16 * (ks & 1) + 8 * h);          // bits 16 ks + 8 h .. + 7, the first most significant
+            const uint32_t twos = (~(word ^ mword) | usual[rt]) >> (16 * (ks & 1) + 8 * h);
             uint32_t xw[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u)                                     // (-1)^bit of two bits: their signs onto a pair of ones
-                xw[u] = ((byte << (8 + 2 * u)) & 0x8000u) | ((byte << (25 + 2 * u)) & 0x80000000u) | 0x3F803F80u;
+            for (int u = 0; u < 4; ++u) {
+                // two bits' signs onto a pair of ones -- or of magnitudes: 2 (0x4000) where `twos` has the bit, else 0; the usual
+                // candidate has every bit, and its twos less one exponent are ones
+                uint32_t mag = 0x3F803F80u;
+                if constexpr (ODD) mag = (((twos << (7 + 2 * u)) & 0x4000u) | ((twos << (24 + 2 * u)) & 0x40000000u)) - one[rt];
+                xw[u] = ((byte << (8 + 2 * u)) & 0x8000u) | ((byte << (25 + 2 * u)) & 0x80000000u) | mag;
+            }
             x[rt] = __builtin_bit_cast(din_bf16x8, make_uint4(xw[0], xw[1], xw[2], xw[3]));
         }
 #pragma unroll
@@ -161,33 +197,42 @@ __global__ __launch_bounds__(256, 2) void k_lsh_din_mfma(LshModel m, LshBatch b,
                 acc[rt][ft] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[rt], __builtin_bit_cast(din_bf16x8, f[ft]), acc[rt][ft], 0, 0, 0);
         ks = ks + 1 == ks_n ? 0 : ks + 1;
     };
-    for (int i = 0; i < steps; i += 3) {
+    auto all = [&](auto odd_c) __attribute__((always_inline)) {
+        for (int i = 0; i < steps; i += 3) {
 #pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            step(i + q, w[q]);
-            fetch(i + q + 3, w[q]);
+            for (int q = 0; q < 3; ++q) {
+                step(odd_c, i + q, w[q]);
+                fetch(i + q + 3, w[q]);
+            }
         }
-    }
+    };
+    uint32_t any_low = 0u;
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) any_low |= low_mask[rt];
+    if (__builtin_amdgcn_readfirstlane(any_low)) all(std::true_type{});
+    else all(std::false_type{});
 
     // cell v of a lane: candidate 8 (v / 4) + 4 h + v % 4 of the row tile, feature `col` of the feature tile
     const float inv = 0.5f / (float)m.d_bits, nanv = __uint_as_float(0x7FC00000u);
-    const float *total = A + ((size_t)r * lsh_rows(m.d_bits) + m.d_bits) * m.d_out + col;
-    float hi[FT], lo[FT];
+    float hi[2][FT], lo[2][FT];                                 // total / 2, lowest
 #pragma unroll
-    for (int ft = 0; ft < FT; ++ft) {
-        hi[ft] = 0.5f * total[ft * 32];
-        lo[ft] = 0.5f * total[m.d_out + ft * 32];
-    }
+    for (int ft = 0; ft < FT; ++ft)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const float *p = last + (size_t)(q ? LSH_LOWEST : LSH_TOTAL) * m.d_out + col + ft * 32;
+            hi[q][ft] = p[0];
+            lo[q][ft] = p[m.d_out];
+        }
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const int c = 8 * (v / 4) + 4 * h + (v % 4);
             if (!((live_mask[rt] >> c) & 1u)) continue;
-            const bool ok = (ok_mask[rt] >> c) & 1u;
+            const bool ok = (ok_mask[rt] >> c) & 1u, low = (low_mask[rt] >> c) & 1u;
             float *o = rd.din_out + (size_t)(local0 + rt * 32 + c) * m.d_out + col;
 #pragma unroll
-            for (int ft = 0; ft < FT; ++ft) o[ft * 32] = ok ? hi[ft] + fmaf(acc[rt][ft][v], inv, lo[ft]) : nanv;
+            for (int ft = 0; ft < FT; ++ft) o[ft * 32] = ok ? (low ? hi[1][ft] : hi[0][ft]) + fmaf(acc[rt][ft][v], inv, low ? lo[1][ft] : lo[0][ft]) : nanv;
         }
         if (lane == 0) {
             const int n_bad = __builtin_popcount(live_mask[rt] & ~ok_mask[rt]);

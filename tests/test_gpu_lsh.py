@@ -26,13 +26,18 @@ def torch():
 
 
 def din_tolerance(u_seq, L, d_bits):
-    """Per output feature j.  Every U~[t, j] enters the GPU's sum exactly d' times (once per bit, in the table
-    of the value the candidate's bit takes) through chains of at most 128 (staged items) + 4 (stagings per
-    chunk of 512) + chunks + d' (bits) fp32 additions, then one division by d'.  The standard bound for a sum,
-    n u sum|x| with u = 2^-24, over the d' copies and divided by d' gives  n 2^-24 sum_t |U~[t, j]|.
-    (A history of more than 64 chunks is cut into 64 longer ones: 4 m stagings and about chunks / m partial sums with
-    m = ceil(chunks / 64), fewer additions in a row than the 4 + chunks counted here.)"""
-    n = 128 + 4 + (L + 511) // 512 + d_bits + 2
+    """Per output feature j.  DIN = total / 2 + (1 / 2 d') sum_k c_k D[k] with D[k] = sum_t c_tk U~[t, j].  Every U~[t, j] enters
+    each of the d' sums D[k] once, and these enter the result divided by 2 d': the standard bound for a sum, n u sum|x| with
+    u = 2^-24, over the d' copies gives (n / 2) 2^-24 sum_t |U~[t, j]|.  n, fp32 additions in a row: a share of the history
+    (a chunk of 1,024 items, or of ceil(L / 64) if that is more, divided among the waves that have no bits of their own) takes
+    one matrix instruction per 16 items and piece of the embedding, three pieces at most, two roundings each; then the
+    shares' sums; then the d' bits.  Total is summed in 64 bits, eight items at a time in fp32 before that (8 / 2), and
+    the two terms are put together with two roundings.  A candidate unlike the history has weighted sums in total's
+    place, weights at most 1, and twice D[k] for fewer than 5/16 of the k: no more than this."""
+    chunk = 1024 if L <= 65536 else ((L - 1) // 64 + 64) // 64 * 64
+    split = {32: 4, 64: 2}.get(d_bits, 1)
+    steps, shares = -(-min(chunk, max(L, 1)) // (16 * split)), -(-L // chunk) * split
+    n = (2 * 3 * steps + shares + d_bits) / 2 + 8 / 2 + 2
     return n * 2.0 ** -24 * np.abs(u_seq.astype(np.float64)).sum(0) + 1e-30
 
 
