@@ -37,6 +37,9 @@ constexpr int SMT_PART_BLOCKS = 2048; // a batch of fewer blocks than this has i
 constexpr int SMT_MAX_PARTS = 16;
 constexpr int SMT_TILE = 64;         // history items of a row tile: two a row
 constexpr int SMT_GROUP = 4;         // row tiles per pass of the adder network: 32 words per column tile
+// Column tiles of 32 candidates a wave keeps (a row tile's bytes serve them all; what the registers allow): the block's 256
+// candidates are SMT_GROUPS groups of columns, and the SMT_SHARE waves that have a group in common halve the history.
+constexpr int SMT_COLS = 4, SMT_GROUPS = LSH_BLOCK / (32 * SMT_COLS), SMT_SHARE = 4 / SMT_GROUPS;
 // Planes of weight 32 .. above the network's ones .. sixteens, and the passes between read-outs that they can count (an
 // even number, of 32 words each; + 24 of a ragged end).  Signatures of up to 64 bits keep to three waves a SIMD with one
 // plane fewer: its registers hold the carry that waits for its partner.
@@ -103,22 +106,17 @@ __device__ __forceinline__ void simtier_store(const LshModel &m, const LshReqDes
     o[m.n_tiers - 1] = rd.seq_len - below;
 }
 
-// KS: k-steps of 32 bits (d' = 32 KS); COLS: column tiles of 32 candidates a wave keeps (its candidates' operands stay in
-// registers: 4 COLS KS of them).  The block's 256 candidates are 8 / COLS groups of columns; where that leaves waves over
-// (COLS = 4) two waves share a group and halve the history.  gridDim.y > 1: the history is cut into that many parts as
-// well, a block each, and the counts go to `parts` [part][candidate slot][tier] for k_lsh_simtier_finish -- for batches
-// too small to fill the chip otherwise (a handful of users with long histories).
-// Every wave reads its row tiles from L2 itself; four column tiles a wave (a tile's bytes serve 128 candidates, two to
-// four tiles in flight) is what the registers allow.
-template <int KS, int COLS>
+// KS: k-steps of 32 bits (d' = 32 KS); a wave's candidates' operands stay in registers, 16 KS of them.  gridDim.y > 1: the
+// history is cut into that many parts as well, a block each, and the counts go to `parts` [part][candidate slot][tier] for
+// k_lsh_simtier_finish -- for batches too small to fill the chip otherwise (a handful of users with long histories).
+// Every wave reads its row tiles from L2 itself, two to four tiles in flight.
+template <int KS>
 __global__ __launch_bounds__(256, KS <= 2 ? 3 : 2) void k_lsh_simtier_mfma(LshModel m, LshBatch b, const uint8_t *__restrict__ sig_table,
                                                              const v4i *__restrict__ hist, size_t req_stride, int sh,
                                                              int32_t *__restrict__ parts)
 {
-    constexpr int SMT_COLS = COLS, GROUPS = 8 / COLS, SHARE = 4 / GROUPS;      // waves that share a group of columns
     constexpr int SMT_PLANES = smt_planes(KS), SMT_FLUSH = smt_flush(KS);
     static_assert(SMT_FLUSH % 2 == 0 && 32 * SMT_FLUSH + 24 < 32 << SMT_PLANES, "the planes count every word between read-outs");
-    static_assert(COLS == 2 || COLS == 4, "column tiles per wave");
     __shared__ int32_t cnt[LSH_MAX_TIERS][LSH_BLOCK];
     // as in the vector-ALU kernel: the blocks of one user go to one XCD, whose L2 then holds that user's history
     int blk = blockIdx.x;
@@ -131,7 +129,7 @@ __global__ __launch_bounds__(256, KS <= 2 ? 3 : 2) void k_lsh_simtier_mfma(LshMo
     const LshReqDesc rd = b.reqs[r];
     const int tid = threadIdx.x, lane = tid & 63, col = lane & 31, h = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);             // the same in every lane: the loop's bounds are scalars
-    const int cg = wave % GROUPS, hh = wave / GROUPS;   // which candidates of the block, which share of the history
+    const int cg = wave % SMT_GROUPS, hh = wave / SMT_GROUPS;   // which candidates of the block, which share of the history
     const int first = blk * LSH_BLOCK - rd.cand_base;
 
     // column operand: each k-step's 32 bits of this lane's candidate in each of the column tiles
@@ -152,7 +150,7 @@ __global__ __launch_bounds__(256, KS <= 2 ? 3 : 2) void k_lsh_simtier_mfma(LshMo
     const int nrt = (rd.seq_len + SMT_TILE - 1) / SMT_TILE;
     const int per_part = (nrt + (int)gridDim.y - 1) / (int)gridDim.y;          // row tiles of this block ...
     const int part_begin = min(nrt, (int)blockIdx.y * per_part), part_end = min(nrt, part_begin + per_part);
-    const int per_wave = (part_end - part_begin + SHARE - 1) / SHARE;           // ... and of this wave
+    const int per_wave = (part_end - part_begin + SMT_SHARE - 1) / SMT_SHARE;           // ... and of this wave
     const int rt_begin = min(part_end, part_begin + hh * per_wave), rt_end = min(part_end, rt_begin + per_wave);
     const v4i *__restrict__ hrow = hist + (size_t)r * req_stride + lane;
 
@@ -426,9 +424,9 @@ hipError_t launch_lsh_simtier_mfma(const LshModel &m, const LshBatch &b, const u
     const dim3 grid(b.n_blk, n_parts);
     int32_t *pp = (int32_t *)parts;
     switch (ks) {
-    case 1: hipLaunchKernelGGL((k_lsh_simtier_mfma<1, 4>), grid, dim3(256), 0, s, m, b, sig_table, (const v4i *)hist, req_stride, sh, pp); break;
-    case 2: hipLaunchKernelGGL((k_lsh_simtier_mfma<2, 4>), grid, dim3(256), 0, s, m, b, sig_table, (const v4i *)hist, req_stride, sh, pp); break;
-    default: hipLaunchKernelGGL((k_lsh_simtier_mfma<4, 4>), grid, dim3(256), 0, s, m, b, sig_table, (const v4i *)hist, req_stride, sh, pp); break;
+    case 1: hipLaunchKernelGGL(k_lsh_simtier_mfma<1>, grid, dim3(256), 0, s, m, b, sig_table, (const v4i *)hist, req_stride, sh, pp); break;
+    case 2: hipLaunchKernelGGL(k_lsh_simtier_mfma<2>, grid, dim3(256), 0, s, m, b, sig_table, (const v4i *)hist, req_stride, sh, pp); break;
+    default: hipLaunchKernelGGL(k_lsh_simtier_mfma<4>, grid, dim3(256), 0, s, m, b, sig_table, (const v4i *)hist, req_stride, sh, pp); break;
     }
     if (n_parts > 1) hipLaunchKernelGGL(k_lsh_simtier_finish, dim3(b.n_blk), dim3(256), 0, s, m, b, sh, (const int32_t *)pp, n_parts);
     return hipGetLastError();
