@@ -272,7 +272,7 @@ aif_status aif_user_precompute(aif_user_ctx *c, const aif_user_request *users, i
     else
         USER_TRY(c, launch_attn_generic(m, b, c->X, nullptr, nullptr, nullptr, nullptr, c->max_seq_len, longest, s));
     if (pe) USER_TRY(c, hipEventRecord(pe[2], s));
-    if (c->w.wffn_frag && longest <= 32 * USER_POOL_TILES)
+    if (c->w.wffn_frag && c->w.d <= USER_POOL_MAX_D && longest <= 32 * USER_POOL_TILES)
         USER_TRY(c, launch_user_ffn_pool(c->w, du, n_users, c->X, s));
     else {
         USER_TRY(c, launch_user_ffn_partial(c->w, du, b.blk_req, b.n_blk, c->X, (float *)c->part, s));

@@ -52,8 +52,9 @@ hipError_t launch_user_ffn_partial(const UserWeights &w, const UserDesc *users, 
                                    const void *X, float *part, hipStream_t s);
 size_t user_ffn_lds_bytes(int d);
 
-// Both of these as one launch, a block per user (MFMA FFN; sequences of at most 32 USER_POOL_TILES positions).
-constexpr int USER_POOL_TILES = 64;
+// Both of these as one launch, a block per user (MFMA FFN of d <= USER_POOL_MAX_D; sequences of at most 32 USER_POOL_TILES
+// positions).
+constexpr int USER_POOL_TILES = 64, USER_POOL_MAX_D = 64;
 hipError_t launch_user_ffn_pool(const UserWeights &w, const UserDesc *users, int n_users, const void *X, hipStream_t s);
 
 // Pooling of Eq. 2 (mean of the partial sums, in block order) and the combined vector

@@ -202,8 +202,11 @@ __global__ __launch_bounds__(256) void k_user_ffn_mfma(UserWeights w, const User
 
 // FFN, pooling and the combined vector of one user by one block of sixteen waves: the tiles' sums meet in LDS and are added
 // in the order k_user_combine adds them (the same bits).  One launch where two were, and no trip of the sums through
-// memory: 64 users of up to 500 positions 8 us instead of 6 + 8.  For sequences of up to USER_POOL_TILES tiles -- beyond,
-// a user's tiles want more than one compute unit.
+// memory: 64 users of up to 500 positions 8 us instead of 6 + 8.  A user's tiles share one compute unit, which the launch
+// saved outweighs up to USER_POOL_TILES tiles: one user of 512, 1,024 and 2,048 positions, d = 64, 32.8, 30.4 and 40.8 us a
+// call against 34.4, 33.9 and 43.0 with two launches, d = 32 25.3, 34.1 and 26.5 against 30.8, 42.3 and 41.0; 64 users of
+// 2,048, d = 64, 189 against 195.  Not for d = 128, where the 128 registers that sixteen waves leave a lane do not hold
+// a tile's fragments (308 bytes spilled): 96, 157 and 279 against 80, 130 and 232, 64 users of 500 95 against 80.
 template <int D>
 __global__ __launch_bounds__(1024) void k_user_ffn_pool(UserWeights w, const UserDesc *__restrict__ users, const uint16_t *__restrict__ X)
 {
@@ -424,7 +427,6 @@ hipError_t launch_user_ffn_pool(const UserWeights &w, const UserDesc *users, int
     switch (w.wffn_frag ? w.d : 0) {
     case 32: go(k_user_ffn_pool<32>); break;
     case 64: go(k_user_ffn_pool<64>); break;
-    case 128: go(k_user_ffn_pool<128>); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

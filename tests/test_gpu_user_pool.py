@@ -1,4 +1,5 @@
-"""The user network's fused launches: keys packed by the projection, FFN and pooling as one launch up to 2,048 positions."""
+"""The user network's fused launches: keys packed by the projection, FFN and pooling as one launch up to 2,048 positions and
+64 features."""
 import numpy as np
 import pytest
 
