@@ -119,7 +119,7 @@ __global__ __launch_bounds__(256, 2) void k_lsh_din_mfma(LshModel m, LshBatch b,
     const uint4 *src = pieces + (size_t)r * req_stride + lane;
     const int steps = 3 * ks_n;
     uint4 w[3][FT];
-    auto fetch = [&](int i, uint4 (&f)[FT]) {
+    auto fetch = [&](int i, uint4 (&f)[FT]) __attribute__((always_inline)) {
         i = i < steps ? i : steps - 1;
 #pragma unroll
         for (int ft = 0; ft < FT; ++ft) f[ft] = src[(size_t)(i * FT + ft) * 64];
@@ -128,9 +128,9 @@ __global__ __launch_bounds__(256, 2) void k_lsh_din_mfma(LshModel m, LshBatch b,
     fetch(1, w[1]);
     fetch(2, w[2]);
     const float *last = A + ((size_t)r * lsh_rows(m.d_bits) + m.d_bits) * m.d_out;
-    uint32_t maj[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) maj[q] = __float_as_uint(last[LSH_MAJORITY * m.d_out + q]);      // d >= 32; words past the signature's are not looked at
+    // the majority word, a part per lane (d >= 32; those past the signature's are not looked at)
+    const int maj_lanes = (int)__float_as_uint(last[LSH_MAJORITY * m.d_out + (lane & 7)]);
+    auto maj = [&](int q) __attribute__((always_inline)) { return (uint32_t)__builtin_amdgcn_readlane(maj_lanes, q); };
     uint32_t sig[RT][8];
     uint32_t live_mask[RT], ok_mask[RT], low_mask[RT];
     uint32_t usual[RT], one[RT];                                // of this lane's candidate: see step()
@@ -148,7 +148,7 @@ __global__ __launch_bounds__(256, 2) void k_lsh_din_mfma(LshModel m, LshBatch b,
         ok_mask[rt] = (uint32_t)__ballot(ok);
         int n_maj = 0;
 #pragma unroll
-        for (int q = 0; q < 8; ++q) n_maj += q < nw ? __builtin_popcount(~(sig[rt][q] ^ maj[q])) : 0;
+        for (int q = 0; q < 8; ++q) n_maj += q < nw ? __builtin_popcount(~(sig[rt][q] ^ maj(q))) : 0;
         const bool low = live && lsh_dissimilar(n_maj, m.d_bits);
         low_mask[rt] = (uint32_t)__ballot(low);
         usual[rt] = low ? 0u : ~0u;
@@ -168,10 +168,7 @@ __global__ __launch_bounds__(256, 2) void k_lsh_din_mfma(LshModel m, LshBatch b,
         constexpr bool ODD = decltype(odd_c)::value;
         if (i >= steps) return;
         din_bf16x8 x[RT];
-        uint32_t mword = maj[0];
-        if constexpr (ODD)
-#pragma unroll
-            for (int q = 1; q < 8; ++q) mword = (ks >> 1) == q ? maj[q] : mword;
+        const uint32_t mword = ODD ? maj(ks >> 1) : 0u;
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
             uint32_t word = sig[rt][0];
