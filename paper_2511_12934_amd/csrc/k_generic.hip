@@ -715,17 +715,29 @@ static void attn_gen_go(const Model &m, const Batch &b, void *X, const void *tab
     else go(k_attn_gen<T, FT, WV, false, RES>, nullptr, nullptr);
 }
 
-// Three forms of the same arithmetic (the same bits): a batch that fills half the chip with blocks of eight waves and a
-// whole ROW_BLOCK each, and whose longest keys leave room for two such blocks on a compute unit, keeps them resident; other
-// large batches take blocks of eight waves, 32 keys at a time; small ones blocks of four.
-constexpr int GEN_SMALL = 256;
+// Three forms of the same arithmetic (the same bits): a batch of many ROW_BLOCKs whose longest keys leave room for two
+// blocks on a compute unit keeps them resident, a block of eight waves to a whole ROW_BLOCK; other large batches take blocks of
+// eight waves and half a ROW_BLOCK, 32 keys at a time; small ones blocks of four.
+// The lines, us a call with the keys resident | 32 at a time (queries of W_q; layers 72, 40, 1):
+// heads of up to 32, blocks   256: fp32, 50 keys  70.7 |  67.9   bf16, 50 keys 53.3 | 46.8   bf16, 512 keys  81.0 |  72.5
+//                             384:                90.0 |  89.3                 66.5 | 61.9                  112.3 |  97.6
+//                             512:               109.8 | 110.9                 73.4 | 73.3                  120.3 | 120.3
+//                           1,024:               191.5 | 191.0                123.3 | 124.0                 205.9 | 215.4
+//                           2,560:               492.7 | 486.5                265.9 | 274.2                 456.5 | 487.4
+// heads of 64, blocks         128: fp32, 50 keys  63.6 |  53.1   bf16, 128 keys 50.7 | 40.8
+//                             144:                70.4 |  73.2                  57.3 | 59.8
+//                             512:               143.0 | 152.4                  89.0 | 108.1
+// so from two blocks a compute unit on for narrow heads, and for wide ones as soon as half-ROW_BLOCKs, one to a unit, need a
+// second round.  LDS: two blocks fit up to 80 KB; at 64 to 80 KB resident keys are 7 % faster on
+// 2,560 blocks and 5 % slower on 640; at 96 to 128 KB (one block a unit) 7 to 35 % slower.
+constexpr int GEN_SMALL = 256, GEN_RES_BLOCKS = 512;
 constexpr size_t GEN_RES_LDS = 64 * 1024;
 template <typename T, int FT>
 static void attn_gen_ft(const Model &m, const Batch &b, void *X, const void *table, const void *wqp, const float *wq, int32_t *bad,
                         int longest, hipStream_t s)
 {
     const size_t lds = (size_t)m.n_heads * ((longest + GEN_KEYS - 1) / GEN_KEYS) * ((FT + 1) / 2 * 2 + FT) * stored<T>::P * 1024;
-    if (b.n_blk >= GEN_SMALL / 2 && lds <= GEN_RES_LDS) attn_gen_go<T, FT, 8, true>(m, b, X, table, wqp, wq, bad, lds, s);
+    if (b.n_blk >= (FT <= 2 ? GEN_RES_BLOCKS : GEN_SMALL / 2 + 1) && lds <= GEN_RES_LDS) attn_gen_go<T, FT, 8, true>(m, b, X, table, wqp, wq, bad, lds, s);
     else if (b.n_blk >= GEN_SMALL / 2) attn_gen_go<T, FT, 8, false>(m, b, X, table, wqp, wq, bad, 0, s);
     else attn_gen_go<T, FT, 4, false>(m, b, X, table, wqp, wq, bad, 0, s);
 }

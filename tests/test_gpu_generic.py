@@ -62,7 +62,7 @@ def test_pieces_kernels_at_tile_edges(R, torch, monkeypatch, dtype, shape):  # n
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("seq_len,n_heads", [(40, 1), (700, 1), (40, 2), (30, 4)])
 def test_large_batches_give_the_bits_of_single_requests(R, torch, monkeypatch, dtype, seq_len, n_heads):  # noqa: F811
-    """140 requests take the kernels with 32 candidates a block (MLP) and all keys of every head resident or, of 700, 32 at a
+    """520 requests take the kernels with 32 candidates a block (MLP) and all keys of every head resident or, of 700, 32 at a
     time in blocks of eight waves (attention); one alone those with 16 candidates and four waves."""
     if dtype == "bf16":
         monkeypatch.setenv("AIF_FORCE_GENERIC", "1")
@@ -71,9 +71,9 @@ def test_large_batches_give_the_bits_of_single_requests(R, torch, monkeypatch, d
     model = wl.make_model(cfg, seed=5, bias_scale=0.3)
     table = wl.make_table_host(cfg, rng, sigma=1.0)
     users_ids = [(wl.make_user(cfg, rng, sigma=1.0, seq_len=int(rng.integers(0, seq_len + 1))), rng.integers(0, 3000, int(rng.integers(1, 257))).astype(np.int32))
-                 for _ in range(140)]
+                 for _ in range(520)]
     zs, _, drs, ctx = run_batch(R, torch, cfg, model, R.to_device(table, dtype), users_ids, max_seq_len=seq_len)
-    for r in (0, 1, 70, 139):
+    for r in (0, 1, 70, 519):
         alone = R.upload_request(cfg, *users_ids[r])
         ctx.aif_score_request(alone.req)
         torch.cuda.synchronize()
@@ -86,7 +86,7 @@ def test_large_batches_give_the_bits_of_single_requests(R, torch, monkeypatch, d
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("n_req,seq_len", [(3, 65), (130, 65), (130, 700)])
+@pytest.mark.parametrize("n_req,seq_len", [(3, 65), (520, 65), (130, 700)])
 def test_keys_past_the_end_weigh_nothing_however_low_the_real_scores(R, torch, monkeypatch, dtype, n_req, seq_len):  # noqa: F811
     """Real scores of -1e32 and below, far enough apart that the softmax is one key's, whose value the attention then is:
     histories that end inside a chunk of 32 keys, at its first and last key, and one key alone, in the small, the resident
