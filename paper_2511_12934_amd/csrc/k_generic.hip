@@ -329,6 +329,14 @@ __global__ __launch_bounds__(256) void k_attn_generic(Model m, Batch b, T *__res
 // ---------------------------------------------------------------------------
 constexpr int GEN_KEYS = 32;
 
+// A product that is not contracted with the difference it goes into: exp(a s - max) with the rounded product in the maximum and
+// the exact one in the difference overflows from scores of 10^9 on.
+__device__ __forceinline__ float rounded_product(float a, float s)
+{
+#pragma clang fp contract(off)
+    return a * s;
+}
+
 // One head of one candidate by one wave in plain fp32 arithmetic: where a product of pieces met a value that is not
 // finite (an infinity is not the sum of three pieces), so that infinities and NaN propagate as plain fp32 has them.
 template <typename T>
@@ -352,7 +360,7 @@ __device__ __noinline__ void attn_plain(const T *e, const T *K, const T *V, cons
         const T *kr = K + (size_t)(t < L ? t : 0) * da + o;
         float a = 0.f;
         for (int k = 0; k < dh; ++k) a += __shfl(k < 64 ? q[0] : q[1], k & 63, 64) * ld_f<T>(kr + k);
-        return a * scale;
+        return rounded_product(a, scale);
     };
     float mx = -INFINITY, sum = 0.f;
     for (int t0 = 0; t0 < L; t0 += 64) {
@@ -616,7 +624,7 @@ __global__ __launch_bounds__(64 * WV, FT <= 2 ? 4 : 2) void k_attn_gen(Model m, 
                         mfma_pieces(k, qf[s], sb, ss);
                     }
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) sc[4 * kt + i] = (sb[i] + ss[i]) * scale;
+                    for (int i = 0; i < 4; ++i) sc[4 * kt + i] = rounded_product(sb[i] + ss[i], scale);
                 }
                 // keys past the end: an infinitely low score, whatever the others' (a lane may hold no other: its maximum is
                 // then the other lanes'), and a weight of zero

@@ -114,6 +114,31 @@ def test_keys_past_the_end_weigh_nothing_however_low_the_real_scores(R, torch, m
         assert np.array_equal(X[:, 32:64], np.broadcast_to(want, (ids.size, 32))), (r, u.seq_keys.shape[0])
 
 
+@pytest.mark.parametrize("seq_len", [40, 64, 700])
+@pytest.mark.parametrize("d_attn", [32, 64])
+def test_large_scores_beside_a_value_that_is_not_finite(R, torch, seq_len, d_attn):  # noqa: F811
+    """Scores around -1e12, one key's far above the rest: the attention is that key's value -- by the pieces, and by plain
+    arithmetic where an infinite value elsewhere sends the candidate there: zero times infinity in its own feature only."""
+    cfg = small_cfg("f32", seq_len=seq_len, n_items=300, d_item=64, d_user=64, d_attn=d_attn, mlp_dims=(192 + d_attn, 16, 1))
+    _say(f"large scores {seq_len} x {d_attn}")
+    rng = np.random.default_rng(7)
+    model = wl.make_model(cfg, seed=5, bias_scale=0.3)
+    table = (1e6 * (1 + rng.random((300, 64)))).astype(np.float32)
+    u = wl.make_user(cfg, rng, sigma=1.0)
+    u.seq_keys[:] = -1e6 * (1 + rng.permutation(seq_len)[:, None] / np.float32(seq_len)) * np.ones((1, d_attn), np.float32)
+    top = int(np.argmax(u.seq_keys[:, 0]))
+    ids = np.arange(100, dtype=np.int32)
+    for odd in (False, True):
+        if odd:
+            u.seq_vals[(top + 1) % seq_len, 5] = np.inf
+        ctx = run_batch(R, torch, cfg, model, R.to_device(table, "f32"), [(u, ids)])[3]
+        got = R.peek_features(ctx, cfg, 0, ids.size)[:, 64:64 + d_attn]
+        keep = np.arange(d_attn) != 5 if odd else np.ones(d_attn, bool)
+        same = bool(np.all(got[:, keep] == u.seq_vals[top][keep]))
+        assert same, odd
+        assert not odd or np.isnan(got[:, 5]).all()
+
+
 def plain_logits(cfg, model, rows, u):
     """The path in numpy, in 64 bits, with the kernels' maxima: fmax(NaN, x) = x (ReLU turns a NaN into zero)."""
     f = lambda a: np.asarray(a, np.float64)  # noqa: E731
