@@ -131,6 +131,20 @@ __global__ __launch_bounds__(256, 2) void k_lsh_din_mfma(LshModel m, LshBatch b,
     // the majority word, a part per lane (d >= 32; those past the signature's are not looked at)
     const int maj_lanes = (int)__float_as_uint(last[LSH_MAJORITY * m.d_out + (lane & 7)]);
     auto maj = [&](int q) __attribute__((always_inline)) { return (uint32_t)__builtin_amdgcn_readlane(maj_lanes, q); };
+    // total / 2 and lowest, hi and lo; total is asked for now where there are registers to hold it
+    auto load_base = [&](int row, float (&hi)[FT], float (&lo)[FT]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int ft = 0; ft < FT; ++ft) {
+            const float *p = last + (size_t)row * m.d_out + col + ft * 32;
+            hi[ft] = p[0];
+            lo[ft] = p[m.d_out];
+        }
+    };
+    // With few feature tiles a wave none of whose candidates is unlike the history has an end of its own, too (100 candidates, two
+    // tiles: 9.1 us instead of 11.2; four tiles: 21.2 instead of 16.5)
+    constexpr bool EARLY = FT <= 2;
+    float hi[FT], lo[FT];
+    if constexpr (EARLY) load_base(LSH_TOTAL, hi, lo);
     uint32_t sig[RT][8];
     uint32_t live_mask[RT], ok_mask[RT], low_mask[RT];
     uint32_t usual[RT], one[RT];                                // of this lane's candidate: see step()
@@ -203,38 +217,42 @@ __global__ __launch_bounds__(256, 2) void k_lsh_din_mfma(LshModel m, LshBatch b,
             }
         }
     };
+    // cell v of a lane: candidate 8 (v / 4) + 4 h + v % 4 of the row tile, feature `col` of the feature tile
+    auto finish = [&](auto odd_c) __attribute__((always_inline)) {
+        constexpr bool ODD = decltype(odd_c)::value;
+        const float inv = 0.5f / (float)m.d_bits, nanv = __uint_as_float(0x7FC00000u);
+        float low_hi[FT], low_lo[FT];
+        if constexpr (ODD) load_base(LSH_LOWEST, low_hi, low_lo);
+        if constexpr (!EARLY) load_base(LSH_TOTAL, hi, lo);
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int c = 8 * (v / 4) + 4 * h + (v % 4);
+                if (!((live_mask[rt] >> c) & 1u)) continue;
+                const bool ok = (ok_mask[rt] >> c) & 1u, low = ODD && ((low_mask[rt] >> c) & 1u);
+                float *o = rd.din_out + (size_t)(local0 + rt * 32 + c) * m.d_out + col;
+#pragma unroll
+                for (int ft = 0; ft < FT; ++ft)
+                    o[ft * 32] = ok ? (low ? low_hi[ft] : hi[ft]) + fmaf(acc[rt][ft][v], inv, low ? low_lo[ft] : lo[ft]) : nanv;
+            }
+    };
     uint32_t any_low = 0u;
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) any_low |= low_mask[rt];
-    if (__builtin_amdgcn_readfirstlane(any_low)) all(std::true_type{});
-    else all(std::false_type{});
-
-    // cell v of a lane: candidate 8 (v / 4) + 4 h + v % 4 of the row tile, feature `col` of the feature tile
-    const float inv = 0.5f / (float)m.d_bits, nanv = __uint_as_float(0x7FC00000u);
-    float hi[2][FT], lo[2][FT];                                 // total / 2, lowest
+    if (__builtin_amdgcn_readfirstlane(any_low)) {
+        all(std::true_type{});
+        if constexpr (EARLY) finish(std::true_type{});
+    } else {
+        all(std::false_type{});
+        if constexpr (EARLY) finish(std::false_type{});
+    }
+    if constexpr (!EARLY) finish(std::true_type{});
+    if (lane == 0) {
+        int n_bad = 0;
 #pragma unroll
-    for (int ft = 0; ft < FT; ++ft)
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const float *p = last + (size_t)(q ? LSH_LOWEST : LSH_TOTAL) * m.d_out + col + ft * 32;
-            hi[q][ft] = p[0];
-            lo[q][ft] = p[m.d_out];
-        }
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int c = 8 * (v / 4) + 4 * h + (v % 4);
-            if (!((live_mask[rt] >> c) & 1u)) continue;
-            const bool ok = (ok_mask[rt] >> c) & 1u, low = (low_mask[rt] >> c) & 1u;
-            float *o = rd.din_out + (size_t)(local0 + rt * 32 + c) * m.d_out + col;
-#pragma unroll
-            for (int ft = 0; ft < FT; ++ft) o[ft * 32] = ok ? (low ? hi[1][ft] : hi[0][ft]) + fmaf(acc[rt][ft][v], inv, low ? lo[1][ft] : lo[0][ft]) : nanv;
-        }
-        if (lane == 0) {
-            const int n_bad = __builtin_popcount(live_mask[rt] & ~ok_mask[rt]);
-            if (n_bad) atomicAdd(bad, n_bad);
-        }
+        for (int rt = 0; rt < RT; ++rt) n_bad += __builtin_popcount(live_mask[rt] & ~ok_mask[rt]);
+        if (n_bad) atomicAdd(bad, n_bad);
     }
 }
 

@@ -17,8 +17,8 @@
 // large (the line: lsh_dissimilar).  The majority is that of 64 items spread over the history: any word gives a valid
 // sum, and where it matters, where nearly all items agree, 64 show it.  Measured (2,000 items within 2 % of a prototype, d' = d = 64,
 // fp32 embeddings of N(0, 0.1); errors against 64 bits, relative, 2-norms): candidates of similarity 0.02, 0.05, 0.13, 0.26: 4.8, 5.5,
-// 5.4, 6.2 x 10^-8, where the first form has 240, 98, 40, 16; at 0.5, by the first form, 5.4.  It costs the smallest calls 1 to 4 us
-// (100 candidates, 100 items: 31 -> 35) and from a thousand items on nothing.
+// 5.4, 6.2 x 10^-8, where the first form has 240, 98, 40, 16; at 0.5, by the first form, 5.4.  It costs the smallest calls 0 to 4 us
+// (100 candidates, 100 items, fp32: 31.2 -> 32.9) and most from a thousand items on nothing.
 //
 // Signs are exact in bf16, and so are bf16 embeddings; fp32 embeddings are cut into three bf16 pieces (8 + 8 + 8
 // significant bits: exact), each a product of its own.  The contraction index t is the slow axis of both inputs as the
@@ -48,12 +48,12 @@ typedef __bf16 lsh_bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 lsh_bf16x2 __attribute__((ext_vector_type(2)));
 typedef float lsh_f32x16 __attribute__((ext_vector_type(16)));
 
-// Bit k: whether at least half of the wave's 64 words have it.
-__device__ __forceinline__ uint32_t lsh_majority(uint32_t word)
+// Bit k < BITS: whether at least half of the wave's 64 words have it.
+template <int BITS> __device__ __forceinline__ uint32_t lsh_majority(uint32_t word)
 {
     uint32_t m = 0;
 #pragma unroll
-    for (int k = 0; k < 32; ++k) m |= __builtin_popcountll(__ballot((word >> k) & 1u)) >= 32 ? 1u << k : 0u;
+    for (int k = 0; k < BITS; ++k) m |= __builtin_popcountll(__ballot((word >> k) & 1u)) >= 32 ? 1u << k : 0u;
     return m;
 }
 
@@ -185,12 +185,14 @@ __global__ __launch_bounds__(256, 2) void k_lsh_user_sums(LshModel m, LshBatch b
                 low[f] += (double)wsum;
             }
     };
-    // the majority word (of blocks that form the sums): the waves take a word of 64 items each, past four a second
+    // the majority word (of blocks that form the sums): the waves take a word of 64 items each, or a part of one, past four
+    // words a second
+    constexpr int PARTS = W < 4 ? 4 / W : 1, BITS = 32 / PARTS;
     uint32_t words[W], maj[W], sample[2];
     __shared__ uint32_t maj_shared[8];
     {
         const lsh_global<uint32_t> p = sigs + (size_t)((long)lane * rd.seq_len >> 6) * rts;
-        sample[0] = p[min(wave, rts - 1)];
+        sample[0] = p[min(wave / PARTS, rts - 1)];
         sample[1] = W > 4 ? p[min(wave + 4, rts - 1)] : 0u;
     }
     uint32_t sig = load_sig(s_lo);
@@ -198,14 +200,19 @@ __global__ __launch_bounds__(256, 2) void k_lsh_user_sums(LshModel m, LshBatch b
 #pragma unroll
     for (int q = 0; q < AHEAD; ++q) load(s_lo + q, buf[q]);
     if (sums) {
-        const uint32_t m = lsh_majority(sample[0]), m2 = W > 4 ? lsh_majority(sample[1]) : 0u;
+        const int shift = BITS * (wave % PARTS);
+        const uint32_t m = lsh_majority<BITS>(sample[0] >> shift) << shift, m2 = W > 4 ? lsh_majority<BITS>(sample[1]) : 0u;
         if (lane == 0) {
             maj_shared[wave] = m;
             maj_shared[wave + 4] = m2;
         }
         __syncthreads();
 #pragma unroll
-        for (int k = 0; k < W; ++k) maj[k] = __builtin_amdgcn_readfirstlane(maj_shared[k]);
+        for (int k = 0; k < W; ++k) {
+            maj[k] = 0u;
+#pragma unroll
+            for (int p = 0; p < PARTS; ++p) maj[k] |= (uint32_t)__builtin_amdgcn_readfirstlane((int)maj_shared[k * PARTS + p]);
+        }
     }
     auto differing = [&]() {                                    // w_t of the lane's item and of its neighbour in the pair
         int n = 0;
