@@ -24,9 +24,11 @@
  *
  * Conventions are those of aif.h: plain C, every call returns an aif_status
  * and enqueues nothing on failure, DEVICE pointers belong to the device that
- * was current at init, all work is asynchronous on the caller's stream, the
- * library owns only its context and workspace, borrows the signature table
- * for the life of the context and the request tensors until the enqueued work
+ * was current at init, all work is asynchronous and ordered with the caller's
+ * stream (a large call also uses a stream of the context's own, forked from the
+ * caller's and joined to it again: see aif_lsh_batch), the
+ * library owns only its context, workspace and that stream, borrows the signature
+ * table for the life of the context and the request tensors until the enqueued work
  * has completed.  Not capturable into a HIP graph.
  */
 #ifndef AIF_LSH_H

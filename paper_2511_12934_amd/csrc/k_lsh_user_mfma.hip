@@ -30,12 +30,12 @@
 //
 // Block = (chunk of lsh_chunk_len items, request, up to four row tiles of 32 bits); its waves take a row tile each, and
 // where there are fewer than four the chunk's items are shared out as well (lsh_user_split).  Loads run AHEAD
-// steps of 16 items ahead; there is no barrier but the one after which the waves' shares of total and lowest are added
-// (they take the steps in turn).  All partial sums are added in a fixed order, a function of the request's own history
+// steps of 16 items ahead.  Two barriers a block: the majority word's parts, formed while the first items are on their way,
+// and at the end the waves' shares of total and lowest (they take the steps in turn).  All partial sums are added in a fixed order, a function of the request's own history
 // length and the model.
 //
 // What bounds it: the loads in flight (the history's bytes would take half the time).  10^5 items of 128-bit signatures
-// and 128 bf16 features for 8 users (216 MB): 91 us, where a block that transposed both inputs through LDS, with two
+// and 128 bf16 features for 8 users (216 MB): 92 us, where a block that transposed both inputs through LDS, with two
 // barriers and a memory round trip per 64 items and tables for either value of a bit, took 328; 10^4 items, 64 bits, 64
 // features, 64 users: 35 against 68.
 #include "aif_lsh_dev.h"
