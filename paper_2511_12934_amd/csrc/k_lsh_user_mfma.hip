@@ -70,7 +70,7 @@ __global__ __launch_bounds__(256, 2) void k_lsh_user_sums(LshModel m, LshBatch b
     // fp32 embeddings: D's sums over 64 items are formed apart and then added on, one rounding at full size instead of twelve
     constexpr bool TWO = sizeof(T) == 4;
     typedef uint32_t vec __attribute__((ext_vector_type(WORDS)));
-    const int d = m.d_out, db = m.d_bits, nb = db / 8, rts = db / 32, r = blockIdx.y;
+    const int d = m.d_out, db = m.d_bits, rts = db / 32, r = blockIdx.y;
     const int groups = (rts + 3) / 4, rg = blockIdx.z % groups, cg = blockIdx.z / groups;
     const LshReqDesc rd = b.reqs[r];
     const int chunk_len = lsh_chunk_len(rd.seq_len), t_lo = blockIdx.x * chunk_len;
