@@ -54,6 +54,12 @@ template <int I, int N, class F> __device__ __forceinline__ void static_for(F &&
 
 __device__ __forceinline__ float relu(float x) { return __builtin_amdgcn_fmed3f(x, 0.f, __builtin_inff()); }
 
+// z + the ->1 layer's share of four features (after their ReLU), added in this order in every kernel
+__device__ __forceinline__ float dot4(float z, const f32x4 &w, float a0, float a1, float a2, float a3)
+{
+    return fmaf(w.w, a3, fmaf(w.z, a2, fmaf(w.y, a1, fmaf(w.x, a0, z))));
+}
+
 // Static description of the chain.  The weights of all hidden layers form ONE
 // stream of 1 KB fragments (fragment = the A operand of one MFMA: 32 output
 // features x 16 contraction indices), in the order the MFMAs consume them:
@@ -318,8 +324,7 @@ __global__ __launch_bounds__(WAVES * 64, PER_CU) void k_mlp_mfma(int64_t n_items
         constexpr int T = decltype(tc)::value, Q = decltype(qc)::value, L = C::tlayer(T), RT = C::trt(T);
         const f32x16 &a = acc[T & 1];
         if constexpr (L == C::NH - 1) {
-            zpart += wlv[Q].x * relu(a[4 * Q + 0]) + wlv[Q].y * relu(a[4 * Q + 1]) + wlv[Q].z * relu(a[4 * Q + 2]) +
-                     wlv[Q].w * relu(a[4 * Q + 3]);
+            zpart = dot4(zpart, wlv[Q], relu(a[4 * Q + 0]), relu(a[4 * Q + 1]), relu(a[4 * Q + 2]), relu(a[4 * Q + 3]));
             asm volatile("" : "+v"(zpart));         // keep the partial dot here
         } else {
             // slot s of half h <-> feature 16 j + 8 (s / 4) + 4 h + s % 4: parts 0, 1 fill k-step 2 RT, parts 2, 3 k-step 2 RT + 1

@@ -1,0 +1,42 @@
+"""The head kernel of large batches (layer 2 accumulating while layer 1 is produced) against the chain that serves small ones."""
+import numpy as np
+import pytest
+
+from paper_2511_12934_amd import workloads as wl
+
+from helpers import assert_bf16_logits_tight, oracle_scores
+from test_gpu_parity import MFMA_SHAPES, R, _say, run_batch, small_cfg, torch  # noqa: F401  (fixtures)
+
+pytestmark = pytest.mark.gpu
+
+
+# blocks of 256 candidates as multiples of the compute units: every block takes one tile more or fewer than its neighbour
+# (2.5 rounds of 3 is the chain's: 0.83), and the longest runs
+@pytest.mark.parametrize("rounds", [1.75, 2, 2.5, 2.9])
+def test_large_batches_give_the_bits_of_single_requests(R, torch, rounds):  # noqa: F811
+    cfg = small_cfg("bf16", n_items=3000, seq_len=24, **MFMA_SHAPES["c3_like"])
+    _say(f"head of large batches, {rounds} rounds")
+    rng = np.random.default_rng(41)
+    model = wl.make_model(cfg, seed=7, bias_scale=0.3)
+    table = wl.make_table_host(cfg, rng, sigma=1.0)
+    n_blk = int(rounds * torch.cuda.get_device_properties(0).multi_processor_count)
+    sizes = [256 * 39 - 1, 1, 256 * 17 + 33, 256 * 8, 256 * 64 + 255, 64]      # requests of many tiles: most tiles share a user with the next
+    users_ids, left = [], n_blk
+    while left:
+        n = min(sizes[len(users_ids) % len(sizes)], 256 * left)
+        ids = rng.integers(0, cfg.n_items, n).astype(np.int32)
+        if len(users_ids) % 3 == 0:
+            ids[[0, n // 2, n - 1]] = [-1, 2_000_000_000, cfg.n_items]
+        users_ids.append((wl.make_user(cfg, rng, sigma=1.0, seq_len=int(rng.integers(0, 25))), ids))
+        left -= (n + 255) // 256
+    zs, ys, _, ctx = run_batch(R, torch, cfg, model, R.to_device(table, "bf16"), users_ids, max_seq_len=24)
+    assert ctx.aif_stage_kind("mlp") == 1
+    for r, (u, ids) in enumerate(users_ids):
+        alone = R.upload_request(cfg, u, ids)
+        ctx.aif_score_request(alone.req)
+        torch.cuda.synchronize()
+        assert np.array_equal(alone.logits.cpu().numpy(), zs[r], equal_nan=True), r
+        assert np.array_equal(alone.scores.cpu().numpy(), ys[r], equal_nan=True), r
+        assert np.isnan(zs[r]).sum() == np.sum((ids < 0) | (ids >= cfg.n_items))
+    u, ids = users_ids[2]
+    assert_bf16_logits_tight(zs[2], oracle_scores(cfg, model, table, u, ids).logits, "against the oracle")
