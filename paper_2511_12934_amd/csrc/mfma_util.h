@@ -34,6 +34,15 @@ __device__ __forceinline__ void dma16_s(const char *sbase, uint32_t lane_off, ui
                  : "memory");
 }
 
+// As dma16_s, without keeping M0 (nothing in these kernels uses it; the compiler sets it where it needs it): lane's 16 bytes (4 bytes) of sbase + off land at lds + at + 16 (4) lane.
+template <int BYTES> __device__ __forceinline__ void dma_s(const void *sbase, uint32_t off, uint32_t lds, int at)
+{
+    if constexpr (BYTES == 16)
+        asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(sbase), "n"(at) : "memory", "scc");
+    else
+        asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds), "v"(off), "s"(sbase), "n"(at) : "memory", "scc");
+}
+
 // 16 * (lane id), computed on the spot: for a load in the middle of a long stream, where a value kept from the
 // kernel's start would be spilled and its reload would wait for every load in flight.
 __device__ __forceinline__ uint32_t lane_off16_now()

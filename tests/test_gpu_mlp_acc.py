@@ -40,3 +40,32 @@ def test_large_batches_give_the_bits_of_single_requests(R, torch, rounds):  # no
         assert np.isnan(zs[r]).sum() == np.sum((ids < 0) | (ids >= cfg.n_items))
     u, ids = users_ids[2]
     assert_bf16_logits_tight(zs[2], oracle_scores(cfg, model, table, u, ids).logits, "against the oracle")
+
+
+def test_widest_head_gives_the_bits_of_the_chain(R, torch, monkeypatch):  # noqa: F811
+    """C5's head (row tiles of 128 candidates; blocks of one, two and three tiles) against the chain, which serves the row-major
+    workspace, bit for bit: sizes around a tile, bad ids, every block's first, middle and last tile."""
+    cfg = wl.CONFIGS["C5"].scaled(n_items=20000, seq_len=24)
+    _say("widest head: loop over row tiles against the chain")
+    rng = np.random.default_rng(43)
+    model = wl.make_model(cfg, seed=9, bias_scale=0.05)
+    table = wl.make_table_host(cfg, rng, n_items=20000)
+    table_dev = R.to_device(table, "bf16")
+    users_ids = []
+    for r, n in enumerate((1, 127, 128, 129, 255, 257, 12000, 31, 20000, 9973, 17000, 500)):
+        ids = rng.integers(0, cfg.n_items, n).astype(np.int32)
+        if r % 3 == 0:
+            ids[[0, n // 2, n - 1]] = [-1, 2_000_000_000, cfg.n_items]
+        users_ids.append((wl.make_user(cfg, rng, seq_len=int(rng.integers(0, 25))), ids))
+    got, got_y, _, ctx = run_batch(R, torch, cfg, model, table_dev, users_ids, max_seq_len=24)
+    assert ctx.aif_stage_kind("mlp") == 1 and ctx.aif_mlp_layer1_width() == cfg.d_item + cfg.d_attn
+    few, _, _, _ = run_batch(R, torch, cfg, model, table_dev, users_ids[:6], max_seq_len=24)      # fewer tiles than compute units
+    monkeypatch.setenv("AIF_X_ROW_MAJOR", "1")
+    ref, ref_y, _, _ = run_batch(R, torch, cfg, model, table_dev, users_ids, max_seq_len=24)
+    for r, (u, ids) in enumerate(users_ids):
+        assert np.array_equal(got[r], ref[r], equal_nan=True) and np.array_equal(got_y[r], ref_y[r], equal_nan=True), r
+        assert np.isnan(got[r]).sum() == np.sum((ids < 0) | (ids >= cfg.n_items))
+    for r in range(6):
+        assert np.array_equal(got[r], few[r], equal_nan=True), r
+    u, ids = users_ids[5]
+    assert_bf16_logits_tight(got[5], oracle_scores(cfg, model, table, u, ids).logits, "against the oracle")
