@@ -99,6 +99,26 @@ template <typename T> __device__ __forceinline__ void st_f(T *p, float v);
 template <> __device__ __forceinline__ void st_f<float>(float *p, float v) { *p = v; }
 template <> __device__ __forceinline__ void st_f<uint16_t>(uint16_t *p, float v) { *p = f2bf(v); }
 
+// ---- kernel arguments that are indexed by a variable ----------------------
+// a kernel argument at byte `off` of the argument segment, where it lies in memory
+template <class T> using ArgPtr = const T __attribute__((address_space(4))) *;
+template <class T> __device__ __forceinline__ ArgPtr<T> kernel_arg(size_t off)
+{
+    return (ArgPtr<T>)((ArgPtr<char>)__builtin_amdgcn_kernarg_segment_ptr() + off);
+}
+template <class T> __device__ __forceinline__ T arg_copy(ArgPtr<T> p)
+{
+    static_assert(sizeof(T) % 4 == 0, "whole words");
+    uint32_t w[sizeof(T) / 4];
+#pragma unroll
+    for (int i = 0; i < (int)(sizeof(T) / 4); ++i) w[i] = ((ArgPtr<uint32_t>)p)[i];
+    T out;
+    __builtin_memcpy(&out, w, sizeof(T));
+    return out;
+}
+// a pointer that came through memory, known to be global again
+template <class T> __device__ __forceinline__ T *as_global(T *p) { return (T *)(T __attribute__((address_space(1))) *)p; }
+
 // ---- launchers (each enqueues on `s` and returns the launch status) -------
 
 // a1: X[row, 0:d_item] = table[id].  Bad ids read row 0 and bump *bad.

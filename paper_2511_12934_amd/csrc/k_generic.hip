@@ -57,15 +57,15 @@ hipError_t launch_user_fold(const Model &m, const Batch &b, const float *w1u, co
 // write the device tables the later kernels read (few_fill), the others fold.  One launch where an upload and the fold
 // were two (one fp32 request of 1,000 candidates: 5 us of 29).
 template <typename T, int N>
-__global__ __launch_bounds__(256) void k_user_fold_few(Model m, FewFill f, int n_fill, int quads, const float *__restrict__ w1u,
+__global__ __launch_bounds__(256) void k_user_fold_few(FewFill f /* first: kernel_arg */, Model m, int n_fill, int quads, const float *__restrict__ w1u,
                                                        const float *__restrict__ b1, float *__restrict__ bias1)
 {
     const int idx = blockIdx.x;
     if (idx < n_fill) {
-        few_fill<N>(f, idx * 256 + (int)threadIdx.x);
+        few_fill<N>(f, kernel_arg<FewFill>(0), idx * 256 + (int)threadIdx.x);
         return;
     }
-    user_fold_block<T>((idx - n_fill) / quads, (idx - n_fill) % quads, m, FewReqs<N>{f}, w1u, b1, bias1);
+    user_fold_block<T>((idx - n_fill) / quads, (idx - n_fill) % quads, m, FewReqs<N>{f, kernel_arg<FewFill>(0)}, w1u, b1, bias1);
 }
 
 hipError_t launch_user_fold_few(const Model &m, const FewFill &f, const float *w1u, const float *b1, float *bias1, hipStream_t s)
@@ -73,7 +73,7 @@ hipError_t launch_user_fold_few(const Model &m, const FewFill &f, const float *w
     if (f.n_req < 1 || f.n_req > FEW_MAX) return hipErrorInvalidValue;
     const int n_fill = (few_fill_items(f) + 255) / 256, quads = (m.dims[1] + FOLD_FEATS - 1) / FOLD_FEATS;
     const dim3 grid(n_fill + f.n_slots * quads);
-    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, m, f, n_fill, quads, w1u, b1, bias1); };
+    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, f, m, n_fill, quads, w1u, b1, bias1); };
     const bool one = f.n_req == 1 && f.n_slots == 1;
     if (m.dtype == 0) {
         if (one) go(k_user_fold_few<float, 1>);

@@ -23,8 +23,10 @@ struct TableReqs {
 // Descriptor tables of a batch of at most FEW_MAX requests -- the latency cases: one request, or one request cut into
 // mini-batches (Sec. 5.3) -- written by the device itself from kernel arguments (no pinned staging, no copy command,
 // nothing to wait for on the host): the requests, block -> request and block -> user slot, slot -> request, the
-// attention groups (as attn_plan_groups cuts them) and the top-k descriptors.  Every index into the argument arrays
-// is a constant after unrolling: an argument array indexed by a variable would be copied to scratch memory first.
+// attention groups (as attn_plan_groups cuts them) and the top-k descriptors.  An argument array indexed by a variable
+// would be copied to scratch memory first, so variable indices go through the address of the kernel's argument segment
+// (few_args): one load.  With every index a constant and a select per request the fold of 16 requests spent 3.5 of its 6.3 us
+// on bringing 1.3 KB of descriptors through the scalar registers.
 constexpr int FEW_MAX = 16;
 struct FewFill {
     ReqDesc rd[FEW_MAX];
@@ -38,13 +40,16 @@ struct FewFill {
     int32_t per;                // tiles per attention group at most (attn_plan_groups)
     uint32_t resident;          // bit r: request r is the resident attention kernel's (it has groups)
 };
-// N: how many entries of the argument arrays the code looks at (1: the single request; FEW_MAX otherwise)
-template <int N> __device__ __forceinline__ ReqDesc few_request(const FewFill &f, int r)
+// N: how many requests the arguments may hold (1: the single request; FEW_MAX otherwise)
+template <int N> __device__ __forceinline__ ReqDesc few_request(const FewFill &f, ArgPtr<FewFill> args, int r)
 {
-    ReqDesc out = f.rd[0];
-#pragma unroll
-    for (int i = 1; i < N; ++i)
-        if (r == i) out = f.rd[i];
+    if constexpr (N == 1) return f.rd[0];
+    ReqDesc out = arg_copy(&args->rd[r]);
+    out.user_vec = as_global(out.user_vec);
+    out.cross_vecs = as_global(out.cross_vecs);
+    out.seq_keys = as_global(out.seq_keys);
+    out.seq_vals = as_global(out.seq_vals);
+    out.cand_ids = as_global(out.cand_ids);
     return out;
 }
 template <int N> __device__ __forceinline__ int few_block_request(const FewFill &f, int blk)
@@ -59,31 +64,22 @@ template <int N> __device__ __forceinline__ int few_block_request(const FewFill 
 }
 template <int N> struct FewReqs {
     const FewFill &f;
+    ArgPtr<FewFill> args;
     __device__ __forceinline__ int block_request(int blk) const { return few_block_request<N>(f, blk); }
-    __device__ __forceinline__ ReqDesc request(int r) const { return few_request<N>(f, r); }
-    __device__ __forceinline__ ReqDesc slot_desc(int slot) const
-    {
-        int r = f.slot_req[0];
-#pragma unroll
-        for (int i = 1; i < N; ++i)
-            if (slot == i) r = f.slot_req[i];
-        return few_request<N>(f, r);
-    }
+    __device__ __forceinline__ ReqDesc request(int r) const { return few_request<N>(f, args, r); }
+    __device__ __forceinline__ ReqDesc slot_desc(int slot) const { return few_request<N>(f, args, N == 1 ? 0 : args->slot_req[slot]); }
 };
-template <int N> __device__ __forceinline__ void few_fill(const FewFill &f, int i)
+template <int N> __device__ __forceinline__ void few_fill(const FewFill &f, ArgPtr<FewFill> args, int i)
 {
-#pragma unroll
-    for (int r = 0; r < N; ++r) {
-        if (i == r && r < f.n_req) {
-            f.reqs[r] = f.rd[r];
-            if (f.topk) f.topk[r] = f.td[r];
-        }
-        if (i == r && r < f.n_slots) f.slot_req_dev[r] = f.slot_req[r];
+    if (i < N && i < f.n_req) {
+        f.reqs[i] = N == 1 ? f.rd[0] : arg_copy(&args->rd[i]);
+        if (f.topk) f.topk[i] = N == 1 ? f.td[0] : arg_copy(&args->td[i]);
     }
+    if (i < N && i < f.n_slots) f.slot_req_dev[i] = N == 1 ? f.slot_req[0] : args->slot_req[i];
     if (i < f.n_blk) {
         const int r = few_block_request<N>(f, i);
         f.blk_req[i] = r;
-        f.blk_slot[i] = r < 0 ? 0 : few_request<N>(f, r).slot;
+        f.blk_slot[i] = r < 0 ? 0 : N == 1 ? f.rd[0].slot : args->rd[r].slot;
     }
     if (i < f.n_groups) {
         // group i: the requests in order, each resident one cut evenly into ceil(tiles / per) groups

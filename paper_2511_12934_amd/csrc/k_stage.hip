@@ -89,10 +89,10 @@ __global__ __launch_bounds__(256) void k_stage_few(StageFewArgs o)
 {
     const int idx = blockIdx.x;
     if (idx < o.a.n_up) {
-        few_fill<N>(o.fill, idx * 256 + (int)threadIdx.x);
+        few_fill<N>(o.fill, kernel_arg<FewFill>(offsetof(StageFewArgs, fill)), idx * 256 + (int)threadIdx.x);
         return;
     }
-    stage_block<LOG_RV, DH>(o.a, FewReqs<N>{o.fill}, idx - o.a.n_up);
+    stage_block<LOG_RV, DH>(o.a, FewReqs<N>{o.fill, kernel_arg<FewFill>(offsetof(StageFewArgs, fill))}, idx - o.a.n_up);
 }
 
 template <int LOG_RV, int DH>

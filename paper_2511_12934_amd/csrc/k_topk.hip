@@ -113,7 +113,7 @@ __device__ __forceinline__ int value_bin(float v, float lo, float scale)
 }
 
 // FEW: the descriptors of at most TK_FEW lists arrive in the kernel's arguments (a call that has them on the host
-// needs no upload then); every index into the argument array is a constant after unrolling.
+// needs no upload then), read from there by the block's number.
 // SLOTS: logits per thread kept in registers between the passes.  The block's work per pass grows with SLOTS whether
 // the slots are filled or not (one compute unit does all of it), so the launch picks the smallest that holds the
 // longest list; a longer list still works (its tail is re-read from memory in every radix pass).
@@ -136,13 +136,11 @@ __global__ __launch_bounds__(TK_THREADS) void k_topk(const TopkDesc *__restrict_
     const int r = blockIdx.x;
     TopkDesc desc;
     if constexpr (FEW) {
-        desc = few.d[0];
-#pragma unroll
-        for (int i = 1; i < TK_FEW; ++i)
-            if (r == i) desc = few.d[i];
+        static_assert(alignof(TopkFew) == 8, "the kernel's second argument");
+        desc = arg_copy(&kernel_arg<TopkFew>(sizeof(descs))->d[r]);
     } else
         desc = descs[r];
-    const float *z = desc.logits;
+    const float *z = as_global(desc.logits);
     const int n = desc.n;
     const int tid = threadIdx.x;
     const int kk = k < n ? k : n;
