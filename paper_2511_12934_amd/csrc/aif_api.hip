@@ -30,6 +30,7 @@ namespace {
 constexpr int NSLOT = 8;
 constexpr int MAX_DEVICES = 64;
 constexpr int STATIC_MAX_GROUPS = 1024;
+static_assert(FEW_MAX <= ATTN_PLAN_FEW, "the group counts of every request whose descriptor travels in the arguments");
 std::mutex g_scratch_mutex;
 unsigned char *g_scratch_ptr[MAX_DEVICES] = {};      // device address of `scratch` on each device, set at the first init there
 
@@ -499,7 +500,7 @@ static aif_status score_impl(aif_ctx *c, const aif_request *reqs, int32_t n_req,
     const size_t goff = ((size_t)((char *)(hq + n_slots) - h) + 15) / 16 * 16;
     b.n_streamed = 0;
     AttnPlanInfo plan_info{};
-    b.n_groups = c->mfma.attn ? attn_plan_groups(m, hd, n_req, c->n_cu, (AttnGroup *)(h + goff), &b.n_streamed, &plan_info) : 0;
+    b.n_groups = c->mfma.attn ? attn_plan_groups(m, hd, n_req, c->n_cu, (AttnGroup *)(h + goff), &b.n_streamed, GROUP_MIN_TILES, &plan_info) : 0;
     b.groups = (const AttnGroup *)(d + goff);
     size_t bytes = goff + (size_t)b.n_groups * sizeof(AttnGroup);
     const size_t toff = (bytes + 15) / 16 * 16;
@@ -540,8 +541,7 @@ static aif_status score_impl(aif_ctx *c, const aif_request *reqs, int32_t n_req,
         fill.n_slots = n_slots;
         fill.n_blk = b.n_blk;
         fill.n_groups = b.n_groups;
-        fill.per = plan_info.per;
-        fill.resident = plan_info.resident;
+        for (int r = 0; r < n_req; ++r) fill.groups_of[r] = plan_info.groups[r];
     }
     if (!stage_uploads && !stage_fills) HIP_TRY(c, upload(c, slot, bytes, s));
 
@@ -683,7 +683,7 @@ aif_status aif_score_topk_static(aif_ctx *c, const aif_request *req, int32_t k, 
         return fail(c, AIF_ERANGE, "n_cand %d: more attention groups than the static call holds (%d)", q.n_cand, STATIC_MAX_GROUPS);
     int n_streamed = 0;
     AttnPlanInfo plan_info{};
-    const int n_groups = c->mfma.attn ? attn_plan_groups(m, &rd, 1, c->n_cu, tmp, &n_streamed, &plan_info) : 0;
+    const int n_groups = c->mfma.attn ? attn_plan_groups(m, &rd, 1, c->n_cu, tmp, &n_streamed, GROUP_FEWEST_TILES, &plan_info) : 0;
     size_t off = 0;
     auto take = [&](size_t bytes) {
         const size_t at = off;
@@ -725,8 +725,7 @@ aif_status aif_score_topk_static(aif_ctx *c, const aif_request *req, int32_t k, 
     f.n_slots = 1;
     f.n_blk = n_blk;
     f.n_groups = n_groups;
-    f.per = plan_info.per;
-    f.resident = plan_info.resident;
+    f.groups_of[0] = plan_info.groups[0];
     const bool fused = stage_fusable(m, c->mfma);
     const bool fold_fills = !c->mfma.attn && !c->separate_gather && attn_generic_gathers(m) && m.cross_in_mlp != 2;
     if (!fused && !fold_fills) {                 // else the staging launch, or the user fold, writes the tables

@@ -41,14 +41,15 @@ void mfma_release(MfmaPlan &plan);
 // CU's LDS goes to the resident kernel: such requests are cut into groups of tiles (about one group per CU), written to `out` (room for attn_max_groups() entries), their number returned.
 // The others are the streaming kernels': *n_streamed says how many (requests with candidates).  The choice
 // depends on the request alone, so its result does not depend on what else is in the batch.
-// info (optional): what a device-side rebuild of the groups needs (few_fill): the tiles per group at most, and which
-// of the first 32 requests are the resident kernel's.
+// min_tiles: no group has fewer tiles unless its request has.  GROUP_MIN_TILES (a tile a SIMD) gives a small batch every
+// compute unit; groups of 12 (a tile a wave) are the fewest, for a caller with little room for their table.
+// info (optional): what a device-side rebuild of the groups needs (few_fill): the groups of the first requests.
+constexpr int GROUP_MIN_TILES = 4, GROUP_FEWEST_TILES = 12, ATTN_PLAN_FEW = 16;
 struct AttnPlanInfo {
-    int32_t per;
-    uint32_t resident;
+    int32_t groups[ATTN_PLAN_FEW];
 };
 int attn_plan_groups(const Model &m, const ReqDesc *reqs /*host*/, int n_req, int n_cu, AttnGroup *out /*host*/,
-                     int *n_streamed, AttnPlanInfo *info = nullptr);
+                     int *n_streamed, int min_tiles, AttnPlanInfo *info = nullptr);
 size_t attn_max_groups(size_t x_rows, int max_users);
 
 // kv_packed: the batch's K/V are already in fragment order (launch_stage did it)

@@ -37,8 +37,7 @@ struct FewFill {
     AttnGroup *groups;
     TopkDesc *topk;             // null: the call selects nothing
     int32_t n_req, n_slots, n_blk, n_groups;
-    int32_t per;                // tiles per attention group at most (attn_plan_groups)
-    uint32_t resident;          // bit r: request r is the resident attention kernel's (it has groups)
+    int32_t groups_of[FEW_MAX]; // attention groups of each request (attn_plan_groups; 0: it is not the resident kernel's)
 };
 // N: how many requests the arguments may hold (1: the single request; FEW_MAX otherwise)
 template <int N> __device__ __forceinline__ ReqDesc few_request(const FewFill &f, ArgPtr<FewFill> args, int r)
@@ -82,18 +81,15 @@ template <int N> __device__ __forceinline__ void few_fill(const FewFill &f, ArgP
         f.blk_slot[i] = r < 0 ? 0 : N == 1 ? f.rd[0].slot : args->rd[r].slot;
     }
     if (i < f.n_groups) {
-        // group i: the requests in order, each resident one cut evenly into ceil(tiles / per) groups
+        // group i: the requests in order, each cut evenly into its groups
         int acc = 0;
         AttnGroup g{0, 0, 0, 0};
 #pragma unroll
         for (int r = 0; r < N; ++r) {
-            const int tiles = (f.rd[r].n_cand + 31) / 32;
-            if (r < f.n_req && ((f.resident >> r) & 1u) && tiles > 0) {
-                const int ng = (tiles + f.per - 1) / f.per;
-                if (i >= acc && i < acc + ng)
-                    g = AttnGroup{r, (int)((long)tiles * (i - acc) / ng), (int)((long)tiles * (i - acc + 1) / ng), 0};
-                acc += ng;
-            }
+            const int tiles = (f.rd[r].n_cand + 31) / 32, ng = r < f.n_req ? f.groups_of[r] : 0;
+            if (i >= acc && i < acc + ng)
+                g = AttnGroup{r, (int)((long)tiles * (i - acc) / ng), (int)((long)tiles * (i - acc + 1) / ng), 0};
+            acc += ng;
         }
         f.groups[i] = g;
     }
