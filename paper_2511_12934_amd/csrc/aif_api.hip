@@ -683,7 +683,9 @@ aif_status aif_score_topk_static(aif_ctx *c, const aif_request *req, int32_t k, 
         return fail(c, AIF_ERANGE, "n_cand %d: more attention groups than the static call holds (%d)", q.n_cand, STATIC_MAX_GROUPS);
     int n_streamed = 0;
     AttnPlanInfo plan_info{};
-    const int n_groups = c->mfma.attn ? attn_plan_groups(m, &rd, 1, c->n_cu, tmp, &n_streamed, GROUP_FEWEST_TILES, &plan_info) : 0;
+    // groups of like size, one a compute unit: their table's room is what it always was, and so is the largest n_cand
+    const int min_tiles = std::max(GROUP_FEWEST_TILES, ((q.n_cand + 31) / 32 + c->n_cu - 1) / c->n_cu);
+    const int n_groups = c->mfma.attn ? attn_plan_groups(m, &rd, 1, c->n_cu, tmp, &n_streamed, min_tiles, &plan_info) : 0;
     size_t off = 0;
     auto take = [&](size_t bytes) {
         const size_t at = off;
