@@ -31,6 +31,7 @@
 #include <cstdlib>
 #include <type_traits>
 
+#include "attn_groups.h"
 #include "k_mfma.h"
 #include "k_stage.h"
 #include "mfma_util.h"
@@ -1099,10 +1100,6 @@ __global__ __launch_bounds__(RES_WAVES * 64) void k_attn_res(Model m, Batch b, c
 // of like cost.  Whole calls, us, before (groups of the same number of tiles, rounded up per request, of 12 at least) / now:
 // 37 ragged requests with bridges 140 / 129; 48 x 4000 over 400 keys 125 / 105; one request of 4000 over 400 33.3 / 28.8, of
 // 10^4 in C4's shape 38.9 / 27.7 (a group of four tiles is one a SIMD).
-// The cost of a group in key tiles: a tile walks its request's key tiles in every head and costs about GROUP_TILE more
-// (rows, stores); the keys and values come once (64 x 10^4 x 500 keys: 66 us of loop, 15 of ends, 5 of loading).
-constexpr int GROUP_TILE = 4, GROUP_LOAD = 6;
-constexpr int GROUP_MAX_CU = 512;
 size_t attn_max_groups(size_t x_rows, int max_users)
 {
     const size_t fine = std::min(x_rows / (32 * GROUP_MIN_TILES), (size_t)GROUP_MAX_CU);
@@ -1119,46 +1116,31 @@ int attn_plan_groups(const Model &m, const ReqDesc *reqs, int n_req, int n_cu, A
     if (m.d_head != 64 && m.d_head != 32) return 0;       // the resident kernel has these two head widths
     n_cu = std::min(n_cu, GROUP_MAX_CU);
     auto tiles_of = [&](int r) { return res_fits(m, reqs[r].seq_len) ? (reqs[r].n_cand + 31) / 32 : 0; };
-    auto keys_of = [&](int r) { return (reqs[r].seq_len + 31) / 32; };
-    long total = 0, cost = 0;
+    int32_t tiles[GROUP_MAX_CU], keys[GROUP_MAX_CU], counts[GROUP_MAX_CU];      // of the resident requests, as far as one a unit
+    long total = 0;
     int n_res = 0;
     for (int r = 0; r < n_req; ++r) {
         const int t = tiles_of(r);
+        if (t == 0) continue;
         total += t;
-        cost += (long)t * (keys_of(r) + GROUP_TILE);
-        n_res += t > 0;
-    }
-    if (total == 0) return 0;
-    // groups of request r where no group may cost more than w: enough for its tiles, but none of fewer than min_tiles
-    auto groups_of = [&](int r, long w) {
-        const long t = tiles_of(r), room = std::max(w - GROUP_LOAD * keys_of(r), 1L);
-        return (int)std::min((t * (keys_of(r) + GROUP_TILE) + room - 1) / room, (t + min_tiles - 1) / min_tiles);
-    };
-    auto count = [&](long w) {
-        int n = 0;
-        for (int r = 0; r < n_req; ++r) n += tiles_of(r) > 0 ? groups_of(r, w) : 0;
-        return n;
-    };
-    long w = 0;
-    if (n_res <= n_cu) {            // the least such w that leaves at most one group a unit, to 1 in 64
-        long lo = std::max(cost / n_cu, 1L), hi = lo;
-        while (count(hi) > n_cu) lo = hi, hi += hi / 2 + GROUP_LOAD;
-        while (hi - lo > 1 + hi / 64) {
-            const long mid = (lo + hi) / 2;
-            (count(mid) > n_cu ? lo : hi) = mid;
+        if (n_res < n_cu) {
+            tiles[n_res] = t;
+            keys[n_res] = (reqs[r].seq_len + 31) / 32;
         }
-        w = hi;
+        ++n_res;
     }
+    if (n_res == 0) return 0;
+    if (n_res <= n_cu) plan_group_counts(n_res, tiles, keys, n_cu, min_tiles, counts);
     const long per = std::max((total + n_cu - 1) / n_cu, (long)RES_WAVES);     // more requests than units: several rounds, groups of like size
-    int n = 0;
+    int n = 0, at = 0;
     for (int r = 0; r < n_req; ++r) {
-        const int tiles = tiles_of(r);
-        if (tiles == 0) continue;
+        const int t = tiles_of(r);
+        if (t == 0) continue;
         --*n_streamed;
-        const int ng = n_res <= n_cu ? groups_of(r, w) : (int)((tiles + per - 1) / per);
+        const int ng = n_res <= n_cu ? counts[at++] : (int)((t + per - 1) / per);
         if (info && r < ATTN_PLAN_FEW) info->groups[r] = ng;
         for (int i = 0; i < ng; ++i)          // even split: sizes differ by at most one tile
-            out[n++] = AttnGroup{r, (int)((long)tiles * i / ng), (int)((long)tiles * (i + 1) / ng), 0};
+            out[n++] = AttnGroup{r, (int)((long)t * i / ng), (int)((long)t * (i + 1) / ng), 0};
     }
     return n;
 }

@@ -1,0 +1,81 @@
+"""The cut of a batch into workgroups of the resident attention kernel (csrc/attn_groups.h): host arithmetic, compiled here."""
+import ctypes
+import os
+import subprocess
+import time
+
+import numpy as np
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2511_12934_amd", "csrc")
+TILE, LOAD = 4, 6
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    d = tmp_path_factory.mktemp("attn_groups")
+    (d / "plan.cpp").write_text('#include "attn_groups.h"\n'
+                                'static_assert(aif::GROUP_TILE == %d && aif::GROUP_LOAD == %d, "");\n' % (TILE, LOAD) +
+                                'extern "C" int plan(int n, const int32_t *t, const int32_t *k, int cu, int m, int32_t *g)\n'
+                                '{ return aif::plan_group_counts(n, t, k, cu, m, g); }\n')
+    so = str(d / "plan.so")
+    subprocess.check_call(["g++", "-O3", "-std=c++17", "-shared", "-fPIC", "-I", CSRC, str(d / "plan.cpp"), "-o", so])
+    f = ctypes.CDLL(so).plan
+    f.argtypes = [ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int, ctypes.c_int, ctypes.c_void_p]
+
+    def run(tiles, keys, n_cu, min_tiles):
+        t, k = np.asarray(tiles, np.int32), np.asarray(keys, np.int32)
+        g = np.full(t.size, -1, np.int32)
+        return f(t.size, t.ctypes.data, k.ctypes.data, n_cu, min_tiles, g.ctypes.data), g.astype(np.int64)
+    run.raw = f
+    return run
+
+
+def best_groups(tiles, keys, n_cu, min_tiles):
+    """The smallest whole cost w for which one group a unit is enough, by bisection in exact integers, and the groups it gives."""
+    t, k = tiles.astype(object), keys.astype(object)
+
+    def groups(w):
+        return [min(-(-a * (b + TILE) // max(w - LOAD * b, 1)), -(-a // min_tiles)) for a, b in zip(t, k)]
+    lo, hi = 0, int(max(a * (b + TILE) + LOAD * b for a, b in zip(t, k)))
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        lo, hi = (mid, hi) if sum(groups(mid)) > n_cu else (lo, mid)
+    return hi, np.array(groups(hi), np.float64)
+
+
+@pytest.mark.parametrize("longest", [1, 5, 40, 700, 70_000, 1 << 26])       # tiles; the last is a list of 2^31 candidates
+@pytest.mark.parametrize("min_tiles", [4, 12])
+def test_groups_are_within_bounds_and_of_like_cost(plan, longest, min_tiles):
+    rng = np.random.default_rng(longest + min_tiles)
+    for n in (1, 2, 15, 16, 63, 128, 255, 256):
+        for n_cu in (256, max(n, 104), n):
+            for _ in range(4):
+                tiles = np.maximum(1, (longest * rng.random(n) ** rng.choice([0.0, 1.0, 3.0])).astype(np.int64))
+                keys = rng.integers(0, 39, n)
+                total, g = plan(tiles, keys, n_cu, min_tiles)
+                assert total == g.sum() <= n_cu and g.min() >= 1
+                assert np.all(g <= -(-tiles // min_tiles))
+                # The costliest group (tiles in proportion).  Where min_tiles bounds a request's groups they are the best
+                # plan's; the others cost at most the w that the search ended with, and its bracket, which the least w lies in, is
+                # 1 + w / 64 wide (and 2^-20 for the sums in floats).
+                def worst(groups):
+                    return float(np.max(tiles * (keys + TILE) / groups + LOAD * keys))
+                w, best = best_groups(tiles, keys, n_cu, min_tiles)
+                assert worst(g) <= max(worst(best), (w + 1) * 64 / 63) * (1 + 2.0 ** -20), (n, n_cu)
+
+
+def test_the_host_waits_little_for_the_plan(plan):
+    """256 requests: the search is on the way to the first launch.  Ten probes in 64-bit integer divisions took 18 us; the bound
+    leaves a factor of four over what this takes, for slower processors than the one it was measured on (1.4 us)."""
+    r = np.arange(256)
+    tiles = np.ascontiguousarray((10_000 - 7_500 * ((r * 0.618) % 1.0)) / 32, np.int32)
+    keys, g = np.ascontiguousarray(16 - r % 10, np.int32), np.zeros(256, np.int32)
+    args = (256, tiles.ctypes.data, keys.ctypes.data, 256, 4, g.ctypes.data)
+    best = 1e9
+    for _ in range(300):
+        t0 = time.perf_counter()
+        for _ in range(10):
+            plan.raw(*args)
+        best = min(best, (time.perf_counter() - t0) / 10)
+    assert best < 6e-6, best
