@@ -500,7 +500,7 @@ static aif_status score_impl(aif_ctx *c, const aif_request *reqs, int32_t n_req,
     const size_t goff = ((size_t)((char *)(hq + n_slots) - h) + 15) / 16 * 16;
     b.n_streamed = 0;
     AttnPlanInfo plan_info{};
-    b.n_groups = c->mfma.attn ? attn_plan_groups(m, hd, n_req, c->n_cu, (AttnGroup *)(h + goff), &b.n_streamed, GROUP_MIN_TILES, &plan_info) : 0;
+    b.n_groups = c->mfma.attn ? attn_plan_groups(m, hd, n_req, c->n_cu, (AttnGroup *)(h + goff), &b.n_streamed, GROUP_MIN_TILES, INT64_MAX, &plan_info) : 0;
     b.groups = (const AttnGroup *)(d + goff);
     size_t bytes = goff + (size_t)b.n_groups * sizeof(AttnGroup);
     const size_t toff = (bytes + 15) / 16 * 16;
@@ -685,7 +685,7 @@ aif_status aif_score_topk_static(aif_ctx *c, const aif_request *req, int32_t k, 
     AttnPlanInfo plan_info{};
     // groups of like size, one a compute unit: their table's room is what it always was, and so is the largest n_cand
     const int min_tiles = std::max(GROUP_FEWEST_TILES, ((q.n_cand + 31) / 32 + c->n_cu - 1) / c->n_cu);
-    const int n_groups = c->mfma.attn ? attn_plan_groups(m, &rd, 1, c->n_cu, tmp, &n_streamed, min_tiles, &plan_info) : 0;
+    const int n_groups = c->mfma.attn ? attn_plan_groups(m, &rd, 1, c->n_cu, tmp, &n_streamed, min_tiles, INT64_MAX, &plan_info) : 0;
     size_t off = 0;
     auto take = [&](size_t bytes) {
         const size_t at = off;

@@ -10,6 +10,8 @@ namespace aif {
 // (rows, stores); the keys and values come once (64 x 10^4 x 500 keys: 66 us of loop, 15 of ends, 5 of loading).
 constexpr int GROUP_TILE = 4, GROUP_LOAD = 6;
 constexpr int GROUP_MAX_CU = 512;
+// min_tiles of a batch: a tile a SIMD gives a small batch every compute unit; a tile a wave makes the fewest groups.
+constexpr int GROUP_MIN_TILES = 4, GROUP_FEWEST_TILES = 12;
 
 // Requests of tiles[i] > 0 candidate tiles over keys[i] key tiles, n <= n_cu <= GROUP_MAX_CU of them: groups[i] workgroups for
 // each, at most n_cu in all, so that the costliest group costs as little as that allows (to 1 in 64).  No request gets more
@@ -64,6 +66,24 @@ inline int plan_group_counts(int n, const int32_t *tiles, const int32_t *keys, i
         }
     }
     return tried == hi ? sum : count(hi);
+}
+
+// How many groups of four tiles a batch of the user network may take before it is cut into groups of twelve at least.  Its
+// candidates are the users' own histories: the groups all load their keys and values at the same time and do little else, so from
+// 5/8 of the units on (all of them for heads of 32, half the bytes) loading more often costs more than shorter groups save.
+// Users of 125 to 500 items, calls back to back, us, groups of twelve / of four (on 256 units):
+// 128 -> 64: 32 users (111 groups of four) 35.2 / 33.8; 44 (153) 36.4 / 36.0; 52 (180) 37.5 / 37.5; 64 (221) 39.1 / 39.9; 84 (290, cut
+// to 256) 41.3 / 42.8; 48 -> 32: 64 (221) 27.4 / 26.9; 80 (277) 28.6 / 28.3; 90 (312) 29.4 / 30.0.
+// (Not by the line: 92 to 120 users of 128 -> 64 take 1 to 4 % less in fours, whose groups have grown to five or six tiles there;
+// shorter histories at as many groups take 2 to 4 % more.  Scoring gains up to a group a unit: its tiles do more each.)
+inline int user_fine_groups(int n_cu, int d_head) { return d_head == 32 ? n_cu : 5 * n_cu / 8; }
+
+// min_tiles for a batch whose groups of min_tiles are wanted as long as they are at most most_fine.
+inline int groups_min_tiles(int n, const int32_t *tiles, int min_tiles, int64_t most_fine)
+{
+    int64_t fine = 0;
+    for (int i = 0; i < n; ++i) fine += (tiles[i] + min_tiles - 1) / min_tiles;
+    return fine <= most_fine ? min_tiles : std::max(min_tiles, GROUP_FEWEST_TILES);
 }
 
 }  // namespace aif

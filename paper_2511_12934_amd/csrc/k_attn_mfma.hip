@@ -31,7 +31,6 @@
 #include <cstdlib>
 #include <type_traits>
 
-#include "attn_groups.h"
 #include "k_mfma.h"
 #include "k_stage.h"
 #include "mfma_util.h"
@@ -1107,7 +1106,7 @@ size_t attn_max_groups(size_t x_rows, int max_users)
 }
 
 int attn_plan_groups(const Model &m, const ReqDesc *reqs, int n_req, int n_cu, AttnGroup *out, int *n_streamed, int min_tiles,
-                     AttnPlanInfo *info)
+                     int64_t most_fine, AttnPlanInfo *info)
 {
     if (info) *info = AttnPlanInfo{};
     *n_streamed = 0;
@@ -1130,7 +1129,7 @@ int attn_plan_groups(const Model &m, const ReqDesc *reqs, int n_req, int n_cu, A
         ++n_res;
     }
     if (n_res == 0) return 0;
-    if (n_res <= n_cu) plan_group_counts(n_res, tiles, keys, n_cu, min_tiles, counts);
+    if (n_res <= n_cu) plan_group_counts(n_res, tiles, keys, n_cu, groups_min_tiles(n_res, tiles, min_tiles, most_fine), counts);
     const long per = std::max((total + n_cu - 1) / n_cu, (long)RES_WAVES);     // more requests than units: several rounds, groups of like size
     int n = 0, at = 0;
     for (int r = 0; r < n_req; ++r) {

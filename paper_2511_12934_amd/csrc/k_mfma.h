@@ -1,6 +1,7 @@
 // MFMA (bf16) kernels of libaif: eligibility, packed weights, launchers.
 #pragma once
 #include "aif_dev.h"
+#include "attn_groups.h"
 
 namespace aif {
 
@@ -38,18 +39,18 @@ hipError_t mfma_plan(const Model &m, int max_seq_len, int max_users, size_t x_ro
 void mfma_release(MfmaPlan &plan);
 
 // Host side: which attention kernel serves which request.  A request whose packed K/V (all heads) fit in one
-// CU's LDS goes to the resident kernel: such requests are cut into groups of tiles (about one group per CU), written to `out` (room for attn_max_groups() entries), their number returned.
+// CU's LDS goes to the resident kernel: such requests are cut into groups of tiles (at most one per CU, as far as there are no more requests than CUs), written to `out` (room for attn_max_groups() entries), their number returned.
 // The others are the streaming kernels': *n_streamed says how many (requests with candidates).  The choice
 // depends on the request alone, so its result does not depend on what else is in the batch.
-// min_tiles: no group has fewer tiles unless its request has.  GROUP_MIN_TILES (a tile a SIMD) gives a small batch every
-// compute unit; groups of 12 (a tile a wave) are the fewest, for a caller with little room for their table.
+// min_tiles: a request gets at most one group for every min_tiles tiles begun, of sizes that differ by a tile at most (5 tiles in
+// fours: 2 and 3); one for every GROUP_FEWEST_TILES where the smaller ones would come to more than most_fine.
 // info (optional): what a device-side rebuild of the groups needs (few_fill): the groups of the first requests.
-constexpr int GROUP_MIN_TILES = 4, GROUP_FEWEST_TILES = 12, ATTN_PLAN_FEW = 16;
+constexpr int ATTN_PLAN_FEW = 16;
 struct AttnPlanInfo {
     int32_t groups[ATTN_PLAN_FEW];
 };
 int attn_plan_groups(const Model &m, const ReqDesc *reqs /*host*/, int n_req, int n_cu, AttnGroup *out /*host*/,
-                     int *n_streamed, int min_tiles, AttnPlanInfo *info = nullptr);
+                     int *n_streamed, int min_tiles, int64_t most_fine, AttnPlanInfo *info = nullptr);
 size_t attn_max_groups(size_t x_rows, int max_users);
 
 // kv_packed: the batch's K/V are already in fragment order (launch_stage did it)

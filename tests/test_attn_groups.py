@@ -17,17 +17,20 @@ def plan(tmp_path_factory):
     (d / "plan.cpp").write_text('#include "attn_groups.h"\n'
                                 'static_assert(aif::GROUP_TILE == %d && aif::GROUP_LOAD == %d, "");\n' % (TILE, LOAD) +
                                 'extern "C" int plan(int n, const int32_t *t, const int32_t *k, int cu, int m, int32_t *g)\n'
-                                '{ return aif::plan_group_counts(n, t, k, cu, m, g); }\n')
+                                '{ return aif::plan_group_counts(n, t, k, cu, m, g); }\n'
+                                'extern "C" int user_tiles(int n, const int32_t *t, int cu, int dh)\n'
+                                '{ return aif::groups_min_tiles(n, t, aif::GROUP_MIN_TILES, aif::user_fine_groups(cu, dh)); }\n')
     so = str(d / "plan.so")
     subprocess.check_call(["g++", "-O3", "-std=c++17", "-shared", "-fPIC", "-I", CSRC, str(d / "plan.cpp"), "-o", so])
-    f = ctypes.CDLL(so).plan
+    lib = ctypes.CDLL(so)
+    f = lib.plan
     f.argtypes = [ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int, ctypes.c_int, ctypes.c_void_p]
 
     def run(tiles, keys, n_cu, min_tiles):
         t, k = np.asarray(tiles, np.int32), np.asarray(keys, np.int32)
         g = np.full(t.size, -1, np.int32)
         return f(t.size, t.ctypes.data, k.ctypes.data, n_cu, min_tiles, g.ctypes.data), g.astype(np.int64)
-    run.raw = f
+    run.raw, run.user_tiles = f, lib.user_tiles
     return run
 
 
@@ -79,3 +82,10 @@ def test_the_host_waits_little_for_the_plan(plan):
             plan.raw(*args)
         best = min(best, (time.perf_counter() - t0) / 10)
     assert best < 6e-6, best
+
+
+@pytest.mark.parametrize("d_head, users, tiles, want", [(64, 8, 16, 4), (64, 40, 16, 4), (64, 41, 16, 12), (64, 64, 16, 12), (64, 160, 1, 4), (64, 161, 1, 12),
+                                                        (64, 53, 9, 4), (64, 54, 9, 12), (32, 64, 16, 4), (32, 65, 16, 12)])
+def test_user_network_cuts_into_fours_while_they_are_few(plan, d_head, users, tiles, want):
+    t = np.full(users, tiles, np.int32)
+    assert plan.user_tiles(users, ctypes.c_void_p(t.ctypes.data), 256, d_head) == want
