@@ -5,9 +5,13 @@
 from __future__ import annotations
 
 import os
+import shutil
 import subprocess
 import sys
+import tempfile
 from concurrent.futures import ThreadPoolExecutor
+
+from . import asmcheck
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -20,6 +24,9 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wno-unused-result"]
+
+# units that name registers in inline assembly: their assembly is read before their object is taken (asmcheck.py)
+CHECKED = ("k_mlp_acc.hip", "k_mlp_acc3.hip")
 
 
 def sources():
@@ -38,7 +45,17 @@ def _compile(src: str, force: bool) -> str:
     o = os.path.join(OBJ, src[:-4] + ".o")
     dep = max(os.path.getmtime(s), _newest_header())
     if force or not os.path.exists(o) or os.path.getmtime(o) < dep:
-        r = subprocess.run([HIPCC, *FLAGS, "-c", s, "-o", o], capture_output=True, text=True)
+        checked = tempfile.mkdtemp(dir=OBJ) if src in CHECKED else None
+        out = os.path.join(checked, os.path.basename(o)) if checked else o
+        try:
+            r = subprocess.run([HIPCC, *FLAGS, *(["-save-temps=obj"] if checked else []), "-c", s, "-o", out], capture_output=True, text=True)
+            if checked and r.returncode == 0:
+                with open(os.path.join(checked, src[:-4] + "-hip-amdgcn-amd-amdhsa-gfx950.s")) as f:
+                    asmcheck.check(f.read(), src)
+                os.replace(out, o)
+        finally:
+            if checked:
+                shutil.rmtree(checked)
         err = "\n".join(l for l in r.stderr.splitlines() if "packed-fp32-ops" not in l)
         if r.returncode != 0:
             raise RuntimeError(f"hipcc failed on {src}:\n{err}")

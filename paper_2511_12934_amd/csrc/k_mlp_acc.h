@@ -15,10 +15,12 @@ struct AccOut {
     int32_t n_cand, row_base;
 };
 
-// Layer 2's accumulators are the 256 accumulation registers, named by number.  The compiler, given 512-bit values to carry round the loops in them, copies and spills them;
-// here it has vector registers only to manage (no spill: it would take accumulation registers for that), and every
-// product is written out.  The vector ALU reads a product's result behind two more products
-// (64 cycles; it is there after 44).
+// Layer 2's accumulators are the 256 accumulation registers, named by number.  The compiler, given 512-bit values to carry
+// round the loops in them, copies and spills them; here it has vector registers only to manage, and every product is written out.
+// It knows neither that these registers are taken (reserve_acc has them counted, no more) nor how long a product's result takes, so
+// the build reads the assembly of the units that include this file and fails where the compiler uses an accumulation
+// register or spills (into one), or puts an instruction of its own behind a product it must wait for (../asmcheck.py).
+// The vector ALU reads a product's result behind two more products (64 cycles; it is there after 44).
 __device__ __forceinline__ void mfma_v(f32x16 &c, const bf16x8 &a, const bf16x8 &b)
 {
     asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
