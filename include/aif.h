@@ -261,6 +261,11 @@ AIF_API int32_t aif_stage_kind(const aif_ctx *ctx, int32_t stage);
  * every slice reads the shared result.  -1 for a NULL context, 0 before the first call. */
 AIF_API int32_t aif_last_user_slots(const aif_ctx *ctx);
 
+/* Which form of the MLP head the LAST scoring call launched: 0 = shape-agnostic fp32, 1 = the MFMA chain, 2 = MFMA, one launch
+ * per layer, 3 = MFMA, layer 2 accumulating while layer 1 is produced (large batches and the widest head; same bits
+ * as 1).  -1 for a NULL context, before the first call and after one without candidates. */
+AIF_API int32_t aif_last_mlp_kind(const aif_ctx *ctx);
+
 /* Width of the contraction that layer 1 of the MLP head computes PER CANDIDATE in this context (Sec. 2: what does
  * not depend on the candidate is done once).  D_in - d_user after the user fold; where the Hadamard cross block
  * (Sec. 3.3) is folded into each user's layer-1 weights as well -- its share sum_k W1c[n,k] u_k e_k is linear in the

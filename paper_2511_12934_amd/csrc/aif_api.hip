@@ -53,6 +53,15 @@ hipError_t scratch_of(int dev, unsigned char **out)
 // staging is not the fused launch, which would carry them.
 __global__ __launch_bounds__(256) void k_static_fill(FewFill f) { few_fill<1>(f, nullptr, blockIdx.x * 256 + threadIdx.x); }
 
+// aif_last_mlp_kind of a batch
+int mlp_kind(const Model &m, const MfmaPlan &plan, const Batch &b)
+{
+    if (b.n_blk == 0) return -1;
+    if (!plan.mlp) return 0;
+    if (plan.mlp_variant == MLP_VARIANT_LAYERS) return 2;
+    return mlp_accumulates(plan.mlp_variant, m, b.n_blk) ? 3 : 1;
+}
+
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 thread_local std::string g_init_error = "";
 
@@ -112,6 +121,7 @@ struct aif_ctx {
     int n_cu = 256;                   // compute units of the device (sizes the attention groups)
     bool attn_indexed = false;        // the last scoring call's attention kernel read the item table itself
     int last_slots = 0;               // distinct users (user slots) of the last scoring call
+    int last_mlp = -1;                // aif_last_mlp_kind
     unsigned char *scratch_dev = nullptr;   // this device's copy of the file-scope scratch array (aif_score_topk_static)
     bool separate_gather = false;     // testing (AIF_SEPARATE_GATHER=1): the gather always as blocks or a launch of its own
 
@@ -588,6 +598,7 @@ static aif_status score_impl(aif_ctx *c, const aif_request *reqs, int32_t n_req,
         HIP_TRY(c, launch_attn_generic(m, b, c->X.p, c->has_wq ? (const float *)c->wq.p : nullptr, c->wq_pieces.p,
                                        attn_indexes ? c->table : nullptr, (int32_t *)c->bad.p, c->max_seq_len, longest, s));
     HIP_TRY(c, mark(3));
+    c->last_mlp = mlp_kind(m, c->mfma, b);
     if (c->mfma.mlp) {
         const float *bf[MAX_LAYERS];
         for (int l = 0; l < m.n_layers; ++l) bf[l] = c->has_bias[l] ? (const float *)c->bias[l].p : nullptr;
@@ -780,6 +791,7 @@ aif_status aif_score_topk_static(aif_ctx *c, const aif_request *req, int32_t k, 
     else
         HIP_TRY(c, launch_attn_generic(m, b, X, c->has_wq ? (const float *)c->wq.p : nullptr, c->wq_pieces.p,
                                        attn_indexes ? c->table : nullptr, bad, c->max_seq_len, q.seq_len, s));
+    c->last_mlp = mlp_kind(m, plan, b);
     if (plan.mlp) {
         const float *bf[MAX_LAYERS];
         for (int l = 0; l < m.n_layers; ++l) bf[l] = c->has_bias[l] ? (const float *)c->bias[l].p : nullptr;
@@ -1016,6 +1028,7 @@ aif_status aif_profile_end(aif_ctx *c, double *ms_sum, int32_t *n_calls)
 }
 
 int32_t aif_last_user_slots(const aif_ctx *c) { return c ? c->last_slots : -1; }
+int32_t aif_last_mlp_kind(const aif_ctx *c) { return c ? c->last_mlp : -1; }
 int32_t aif_mlp_layer1_width(const aif_ctx *c) { return !c ? -1 : (c->m.cross_in_mlp == 2 ? c->m.d_item + c->m.d_attn : c->m.k1); }
 
 int32_t aif_stage_kind(const aif_ctx *c, int32_t stage)

@@ -94,6 +94,8 @@ bool mlp_chain_forms_cross(int variant, const Model &m);
 bool mlp_chain_folds_cross(int variant, const Model &m);
 // bytes per user slot of layer 1's weights with the Hadamard cross block folded in (k_stage.h: fold_w0_block)
 inline size_t mlp_w0_user_bytes(const Model &m) { return (size_t)m.dims[1] * (m.d_item + m.d_attn) * 2; }
+// whether the head kernel whose second layer accumulates while the first is produced serves the batch, not the chain
+bool mlp_accumulates(int variant, const Model &m, int n_blk);
 hipError_t launch_mlp_variant(int variant, const Model &m, const Batch &b, const void *X, const MlpPack &pk,
                               const float *bias1, hipStream_t s);
 hipError_t pack_frag(const void *W, int n_in, int col0, int N, int K, bool from_mfma, void *dst, hipStream_t s);

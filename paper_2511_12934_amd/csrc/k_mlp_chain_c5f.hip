@@ -4,13 +4,12 @@
 
 namespace aif {
 
-hipError_t mlp_acc_c5f(const Model &, const Batch &, const void *, const MlpPack &, const float *, hipStream_t);      // k_mlp_acc3.hip
+// (10^4 candidates a user over 64 history items, whole calls, us, chain / k_mlp_acc3: 1 user 97.9 / 92.2, 3 112.3 / 110.0, 4 180.4 /
+// 167.5, 8 237.6 / 221.9, 32 744.5 / 695.9; 1,000 candidates: 1 user 85.9 / 83.9, 8 98.6 / 94.3.  The chain is left the row-major workspace.)
+bool mlp_acc_c5f_serves(const Model &m) { return m.x_tiled; }
 
 hipError_t mlp_chain_c5f(const Model &m, const Batch &b, const void *X, const MlpPack &pk, const float *bias1, hipStream_t s)
 {
-    // (10^4 candidates a user over 64 history items, whole calls, us, chain / k_mlp_acc3: 1 user 97.9 / 92.2, 3 112.3 / 110.0, 4 180.4 /
-    // 167.5, 8 237.6 / 221.9, 32 744.5 / 695.9; 1,000 candidates: 1 user 85.9 / 83.9, 8 98.6 / 94.3.  The chain is left the row-major workspace.)
-    if (m.x_tiled) return mlp_acc_c5f(m, b, X, pk, bias1, s);
     return launch_spec<384, 1024, 512, 256, 4, 16, 4, 1, 0, 1>(m, b, X, pk, bias1, s);
 }
 

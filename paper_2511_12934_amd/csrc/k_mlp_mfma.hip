@@ -36,6 +36,10 @@ hipError_t mlp_chain_c2f(const Model &, const Batch &, const void *, const MlpPa
 hipError_t mlp_chain_c3f(const Model &, const Batch &, const void *, const MlpPack &, const float *, hipStream_t);
 hipError_t mlp_chain_c4f(const Model &, const Batch &, const void *, const MlpPack &, const float *, hipStream_t);
 hipError_t mlp_chain_c5f(const Model &, const Batch &, const void *, const MlpPack &, const float *, hipStream_t);
+hipError_t mlp_acc_c3f(const Model &, const Batch &, const void *, const MlpPack &, const float *, hipStream_t);      // k_mlp_acc.hip
+hipError_t mlp_acc_c5f(const Model &, const Batch &, const void *, const MlpPack &, const float *, hipStream_t);      // k_mlp_acc3.hip
+bool mlp_acc_c3f_serves(const Model &, int n_blk);      // beside the chains they take the place of
+bool mlp_acc_c5f_serves(const Model &);
 
 // Can the chain of this variant form the Hadamard cross block itself (Model::cross_in_mlp)?  Layer 1 after the user
 // fold must be exactly [item | attention | item (.) u] with the item width the kernel was built for.
@@ -102,10 +106,17 @@ int mlp_mfma_variant(const Model &m)
     return -1;
 }
 
+bool mlp_accumulates(int variant, const Model &m, int n_blk)
+{
+    if (m.cross_in_mlp != 2) return false;
+    return variant == 1 ? mlp_acc_c3f_serves(m, n_blk) : variant == 3 && mlp_acc_c5f_serves(m);
+}
+
 hipError_t launch_mlp_variant(int variant, const Model &m, const Batch &b, const void *X, const MlpPack &pk,
                               const float *bias1, hipStream_t s)
 {
     if (b.n_blk == 0) return hipSuccess;
+    if (mlp_accumulates(variant, m, b.n_blk)) return variant == 1 ? mlp_acc_c3f(m, b, X, pk, bias1, s) : mlp_acc_c5f(m, b, X, pk, bias1, s);
     switch (variant) {
     // cross_in_mlp: 0 the cross block is in the workspace, 1 the chain forms it from the item block, 2 it is folded into
     // the user's layer-1 weights (the `f` chains: layer 1 over [item | attention])
