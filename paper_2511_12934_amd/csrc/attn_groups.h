@@ -17,9 +17,9 @@ constexpr int GROUP_MIN_TILES = 4, GROUP_FEWEST_TILES = 12;
 // each, at most n_cu in all, so that the costliest group costs as little as that allows (to 1 in 64).  No request gets more
 // than one for every min_tiles tiles begun.  Returns their number.
 // What bounds it: a division a request and probe of the search, on the host and before the call's first launch.  256 requests
-// of 75 to 300 candidates over 100 keys, one call waited for: 106.4 us with groups of one size, 116.4 with a bisection in whole
-// numbers (ten probes, 18 us of them), about 107 with four to five probes in floats over arrays (1.0 to 1.4 us; what rounding
-// does to a count here does it to the count that is used, so the bound holds).
+// of 75 to 300 candidates over 100 keys, one call waited for: 102.4 us with groups of one size, 110.3 with a bisection in whole
+// numbers (ten probes, 18 us on another processor), 101.1 with four to five probes in floats over arrays (1.0 to 1.4 us there; what
+// rounding does to a count here does it to the count that is used, so the bound holds).
 inline int plan_group_counts(int n, const int32_t *tiles, const int32_t *keys, int n_cu, int min_tiles, int32_t *groups)
 {
     float cost[GROUP_MAX_CU], load[GROUP_MAX_CU], most[GROUP_MAX_CU];

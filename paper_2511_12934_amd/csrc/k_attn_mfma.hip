@@ -1097,8 +1097,8 @@ __global__ __launch_bounds__(RES_WAVES * 64) void k_attn_res(Model m, Batch b, c
 // A workgroup takes a compute unit alone (its LDS), so one group more than there are units is a second round, and groups of as
 // many tiles of histories of all lengths end far apart: the requests are cut into at most as many groups as there are units,
 // of like cost.  Whole calls, us, before (groups of the same number of tiles, rounded up per request, of 12 at least) / now:
-// 37 ragged requests with bridges 140 / 129; 48 x 4000 over 400 keys 125 / 105; one request of 4000 over 400 33.3 / 28.8, of
-// 10^4 in C4's shape 38.9 / 27.7 (a group of four tiles is one a SIMD).
+// 37 ragged requests with bridges 140 / 129; 48 x 4000 over 400 keys 125 / 105; 16 x 1000 over 500 46.7 / 35.7; one request of 4000 over
+// 400 33.3 / 28.8, of 10^4 in C4's shape 38.9 / 27.7 (a group of four tiles is one a SIMD).
 size_t attn_max_groups(size_t x_rows, int max_users)
 {
     const size_t fine = std::min(x_rows / (32 * GROUP_MIN_TILES), (size_t)GROUP_MAX_CU);

@@ -13,12 +13,13 @@
 // fragments) while the vector ALU turns row tile t into the next stage's operands.  Stage 0 (the edge): the previous
 // tile's last k-steps of layer 2 with its ->1 layer, then row tile 0 of this one.
 //
-// What bounds it: power.  64 x 10^4 candidates, 128 -> 512 -> 256: 187 us against the chain's 205 (1.35 against 1.23
-// PFLOP/s), matrix cores busy 0.75 of the cycles at 1.76 GHz, where a bare loop of MFMAs on such operands holds 1.81 GHz.
-// Copies of it without the barriers and waits took the same time, without the fragment reads 9 us less, without the weight
-// loads 5 us less: the clock gives back what fewer stalls gain.  With the other work in lumps (a stage's loads at once, the
-// ->1 layer at the tile's end) it took 215-224 us: one wave has nothing else to issue, so work that does not fit behind a
-// product is time lost.
+// What bounds it: the vector work that does not overlap, and power.  64 x 10^4 candidates, 128 -> 512 -> 256, this and the chain
+// in turn on one box: 192 us against 213 (187 and 205 on another; 1.31 PFLOP/s), in as many cycles, 331 k against 336 k -- every weight
+// fragment read from LDS feeds two MFMAs, and what that saves in energy comes back as clock, 1.72 against 1.58 GHz (a bare loop
+// of MFMAs on such operands holds 1.81).  Matrix cores busy 0.75 of the cycles (the chain 0.73); with the other vector instructions
+// laid end to end 0.96, so a tile gets shorter only with fewer of those or with some under an MFMA.  Copies of it without the barriers and
+// waits took the same time, without the fragment reads 9 us less, without the weight loads 5 us less.  With the other work in lumps
+// (a stage's loads at once, the ->1 layer at the tile's end) it took 215-224 us: one wave has nothing else to issue.
 #include "k_mlp_chain.h"
 #include "k_mlp_acc.h"
 

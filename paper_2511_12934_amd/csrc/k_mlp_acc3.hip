@@ -9,9 +9,11 @@
 // tile with the ->1 layer behind its products.  The weights of all that are one stream of pieces of eight 1 KB fragments
 // through a ring of 12 in LDS; in a piece every wave moves two fragments.
 //
-// What bounds it: power, as k_mlp_acc.hip.  32 x 10^4 candidates: 497 us (1.35 PFLOP/s) against the chain's 573 (1.17), matrix
-// cores busy 0.71 of the cycles at 1.86 GHz (chain: 0.56 at 2.06 GHz).  The chain's products all follow one another on one
-// accumulator and its stages' loads went out in a row; spreading the loads alone gave 1 %.
+// What bounds it: waits, and power.  32 x 10^4 candidates, this and the chain in turn on one box: 541 us (1.24 PFLOP/s) against 589
+// (497 and 573 on another), in 926 k cycles against 1178 k.  Matrix cores busy 0.71 of the cycles (the chain 0.56), in s_waitcnt or at
+// a barrier 0.23, neither matrix cores nor vector ALU 0.14; a fifth fewer cycles are 8 % less time, because the clock is 1.71 against
+// 2.00 GHz.  The chain's products all follow one another on one accumulator and its stages' loads went out in a row;
+// spreading the loads alone gave 1 %.
 #include "k_mlp_chain.h"
 #include "k_mlp_acc.h"
 
