@@ -263,7 +263,8 @@ AIF_API int32_t aif_last_user_slots(const aif_ctx *ctx);
 
 /* Which form of the MLP head the LAST scoring call launched: 0 = shape-agnostic fp32, 1 = the MFMA chain, 2 = MFMA, one launch
  * per layer, 3 = MFMA, layer 2 accumulating while layer 1 is produced (large batches and the widest head; same bits
- * as 1).  -1 for a NULL context, before the first call and after one without candidates. */
+ * as 1). A batch of few candidates may take a third form of 1 and 3, a workgroup to 32 candidates: the same bits, and
+ * not told apart here.  -1 for a NULL context, before the first call and after one without candidates. */
 AIF_API int32_t aif_last_mlp_kind(const aif_ctx *ctx);
 
 /* Width of the contraction that layer 1 of the MLP head computes PER CANDIDATE in this context (Sec. 2: what does

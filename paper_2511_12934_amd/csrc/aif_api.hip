@@ -472,7 +472,7 @@ static aif_status score_impl(aif_ctx *c, const aif_request *reqs, int32_t n_req,
         }
     }
     c->last_slots = n_slots;
-    int rows = 0, longest = 0;
+    int rows = 0, longest = 0, tiles = 0;
     for (int r = 0; r < n_req; ++r) {
         longest = std::max(longest, reqs[r].seq_len);
         const aif_request &q = reqs[r];
@@ -497,6 +497,7 @@ static aif_status score_impl(aif_ctx *c, const aif_request *reqs, int32_t n_req,
             hs[rows / ROW_BLOCK + j] = e.slot;
         }
         rows += nb * ROW_BLOCK;
+        tiles += (q.n_cand + X_TILE - 1) / X_TILE;
     }
     Batch b;
     b.reqs = (const ReqDesc *)d;
@@ -505,6 +506,7 @@ static aif_status score_impl(aif_ctx *c, const aif_request *reqs, int32_t n_req,
     b.slot_req = (const int32_t *)(d + ((char *)hq - h));
     b.n_req = n_req;
     b.n_blk = rows / ROW_BLOCK;
+    b.n_tiles = tiles;
     b.n_slots = n_slots;
     // groups of tiles for the attention kernel that keeps K/V resident, 16-byte aligned after the three tables
     const size_t goff = ((size_t)((char *)(hq + n_slots) - h) + 15) / 16 * 16;
@@ -754,6 +756,7 @@ aif_status aif_score_topk_static(aif_ctx *c, const aif_request *req, int32_t k, 
     b.groups = f.groups;
     b.n_req = 1;
     b.n_blk = n_blk;
+    b.n_tiles = (q.n_cand + X_TILE - 1) / X_TILE;
     b.n_groups = n_groups;
     b.n_streamed = n_streamed;
     b.n_slots = 1;

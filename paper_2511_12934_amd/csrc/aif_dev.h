@@ -43,6 +43,7 @@ struct Batch {
     const int32_t *slot_req;    // device, [n_slots]: a request that brings slot s's user tensors; null: slot s = request s
     int32_t n_req;
     int32_t n_blk;
+    int32_t n_tiles;            // tiles of 32 candidates, those past a request's last left out
     int32_t n_groups;
     int32_t n_streamed;         // requests left to the streaming attention kernels (K/V too long for the resident one)
     int32_t n_slots;            // distinct users of the call: the user-side staging (fold, K/V packing) runs once per slot

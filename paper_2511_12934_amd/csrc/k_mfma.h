@@ -20,6 +20,7 @@ struct MfmaPlan {
     char *hbuf[2] = {};                // layered MLP: hidden activations between launches, ping-pong (owned workspace)
     char *w0_user = nullptr;           // per user slot: layer 1's fragments with the Hadamard cross block folded in (owned workspace; Model::cross_in_mlp == 2)
     size_t w0_stride = 0;              // bytes per slot
+    bool tile = true;                  // testing (AIF_MLP_TILE=0): k_mlp_tile is left out
 };
 constexpr int MLP_VARIANT_LAYERS = 100;   // mlp_variant of the one-launch-per-layer path (k_mlp_layers.hip)
 
@@ -30,6 +31,7 @@ struct MlpPack {
     const float *blast;                // its bias (1 float), never null
     const char *w0_user;               // layer 1's fragments per user slot with the Hadamard cross block folded in (k_mlp_chain.h: UW), or null
     size_t w0_stride;                  // bytes per slot
+    bool tile;                         // few candidates may take k_mlp_tile
 };
 
 // Decide which MFMA kernels can serve the model and pack their weights
@@ -96,6 +98,9 @@ bool mlp_chain_folds_cross(int variant, const Model &m);
 inline size_t mlp_w0_user_bytes(const Model &m) { return (size_t)m.dims[1] * (m.d_item + m.d_attn) * 2; }
 // whether the head kernel whose second layer accumulates while the first is produced serves the batch, not the chain
 bool mlp_accumulates(int variant, const Model &m, int n_blk);
+// k_mlp_tile.hip: few candidates, a workgroup to a tile of 32; the same bits
+bool mlp_tile_serves(int variant, const Model &m, const Batch &b);
+hipError_t launch_mlp_tile(int variant, const Model &m, const Batch &b, const void *X, const MlpPack &pk, const float *bias1, hipStream_t s);
 hipError_t launch_mlp_variant(int variant, const Model &m, const Batch &b, const void *X, const MlpPack &pk,
                               const float *bias1, hipStream_t s);
 hipError_t pack_frag(const void *W, int n_in, int col0, int N, int K, bool from_mfma, void *dst, hipStream_t s);

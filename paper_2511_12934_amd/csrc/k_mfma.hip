@@ -31,6 +31,8 @@ hipError_t mfma_plan(const Model &m, int max_seq_len, int max_users, size_t x_ro
 
     plan.mlp_variant = mlp_mfma_variant(m);
     {
+        const char *tile = getenv("AIF_MLP_TILE");     // testing: both forms of the head must give the same bits
+        plan.tile = !(tile && tile[0] == '0');
         const char *lay = getenv("AIF_MLP_LAYERED");    // testing and measurement: one launch per layer even where a fused chain serves the shape
         if (lay && lay[0] == '1') plan.mlp_variant = -1;
     }
@@ -104,6 +106,7 @@ hipError_t launch_mlp_mfma(const Model &m, const Batch &b, const void *X, const 
     pk.blast = bias_f32[m.n_layers - 1] ? bias_f32[m.n_layers - 1] : plan.zeros;
     pk.w0_user = m.cross_in_mlp == 2 ? plan.w0_user : nullptr;
     pk.w0_stride = plan.w0_stride;
+    pk.tile = plan.tile;
     if (plan.mlp_variant == MLP_VARIANT_LAYERS) return launch_mlp_layers(m, b, X, pk, bias1, plan.hbuf, s);
     return launch_mlp_variant(plan.mlp_variant, m, b, X, pk, bias1, s);
 }

@@ -116,6 +116,7 @@ hipError_t launch_mlp_variant(int variant, const Model &m, const Batch &b, const
                               const float *bias1, hipStream_t s)
 {
     if (b.n_blk == 0) return hipSuccess;
+    if (pk.tile && mlp_tile_serves(variant, m, b)) return launch_mlp_tile(variant, m, b, X, pk, bias1, s);
     if (mlp_accumulates(variant, m, b.n_blk)) return variant == 1 ? mlp_acc_c3f(m, b, X, pk, bias1, s) : mlp_acc_c5f(m, b, X, pk, bias1, s);
     switch (variant) {
     // cross_in_mlp: 0 the cross block is in the workspace, 1 the chain forms it from the item block, 2 it is folded into

@@ -1,0 +1,49 @@
+"""The head of few candidates, a workgroup to a tile of 32, against the chain (the widest head: the accumulating kernel)."""
+import numpy as np
+import pytest
+
+from paper_2511_12934_amd import workloads as wl
+
+from helpers import assert_bf16_logits_tight, oracle_scores
+from test_gpu_parity import MFMA_SHAPES, R, _say, run_batch, small_cfg, torch  # noqa: F401  (fixtures)
+
+pytestmark = pytest.mark.gpu
+
+
+def config(shape):
+    if shape in ("B3", "C5"):
+        return wl.CONFIGS[shape].scaled(n_items=20000, seq_len=24)
+    return small_cfg("bf16", n_items=3000, seq_len=24, **MFMA_SHAPES[shape])
+
+
+# sizes round a tile and round a block of 256 rows, tiles past a request's end, one request and several, up to the last batch it
+# serves (a tile a compute unit) and the first it does not
+@pytest.mark.parametrize("sizes", [(1,), (31, 32, 33), (255, 256, 257, 1, 100), "limit", "past the limit"])
+@pytest.mark.parametrize("shape", [*MFMA_SHAPES, "B3", "C5"])
+def test_few_candidates_give_the_bits_of_many(R, torch, monkeypatch, shape, sizes):  # noqa: F811
+    cfg = config(shape)
+    _say(f"head of few candidates {shape} {sizes}")
+    rng = np.random.default_rng(47)
+    model = wl.make_model(cfg, seed=9, bias_scale=0.05)
+    table = wl.make_table_host(cfg, rng, n_items=cfg.n_items)
+    table_dev = R.to_device(table, "bf16")
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    if sizes == "limit":
+        sizes = (32 * (n_cu - 3), 90)
+    elif sizes == "past the limit":
+        sizes = (32 * (n_cu - 3), 90, 1)
+    users_ids = []
+    for r, n in enumerate(sizes):
+        ids = rng.integers(0, cfg.n_items, n).astype(np.int32)
+        if r % 2 == 0:
+            ids[[0, n // 2, n - 1]] = [-1, 2_000_000_000, cfg.n_items]
+        users_ids.append((wl.make_user(cfg, rng, seq_len=int(rng.integers(0, 25))), ids))
+    got, got_y, _, _ = run_batch(R, torch, cfg, model, table_dev, users_ids, max_seq_len=24)
+    monkeypatch.setenv("AIF_MLP_TILE", "0")
+    ref, ref_y, _, _ = run_batch(R, torch, cfg, model, table_dev, users_ids, max_seq_len=24)
+    for r, (u, ids) in enumerate(users_ids):
+        assert np.array_equal(got[r], ref[r], equal_nan=True) and np.array_equal(got_y[r], ref_y[r], equal_nan=True), r
+        assert np.isnan(got[r]).sum() == np.sum((ids < 0) | (ids >= cfg.n_items))
+    if len(sizes) > 2 and sizes[1] == 32:
+        u, ids = users_ids[1]
+        assert_bf16_logits_tight(got[1], oracle_scores(cfg, model, table, u, ids).logits, "against the oracle")
