@@ -593,7 +593,14 @@ static aif_status score_impl(aif_ctx *c, const aif_request *reqs, int32_t n_req,
         }
     }
     HIP_TRY(c, mark(2));
-    if (c->mfma.attn)
+    const float *bf[MAX_LAYERS];
+    for (int l = 0; l < m.n_layers; ++l) bf[l] = c->has_bias[l] ? (const float *)c->bias[l].p : nullptr;
+    // few candidates: attention and head as one launch (a call that is timed stage by stage keeps them apart)
+    const bool one_launch = !pe && fused && score_tile_serves(m, b, c->mfma);
+    if (one_launch)
+        HIP_TRY(c, launch_score_tile(m, b, c->X.p, c->mfma, mlp_pack(m, c->mfma, bf, (const float *)c->wt[m.n_layers - 1].p),
+                                     (const float *)c->bias1.p, attn_indexes ? c->table : nullptr, (int32_t *)c->bad.p, s));
+    else if (c->mfma.attn)
         HIP_TRY(c, launch_attn_mfma(m, b, c->X.p, c->mfma, fused || staged_proj, s, attn_indexes ? c->table : nullptr,
                                     attn_indexes ? (int32_t *)c->bad.p : nullptr));
     else
@@ -601,9 +608,8 @@ static aif_status score_impl(aif_ctx *c, const aif_request *reqs, int32_t n_req,
                                        attn_indexes ? c->table : nullptr, (int32_t *)c->bad.p, c->max_seq_len, longest, s));
     HIP_TRY(c, mark(3));
     c->last_mlp = mlp_kind(m, c->mfma, b);
-    if (c->mfma.mlp) {
-        const float *bf[MAX_LAYERS];
-        for (int l = 0; l < m.n_layers; ++l) bf[l] = c->has_bias[l] ? (const float *)c->bias[l].p : nullptr;
+    if (one_launch) {
+    } else if (c->mfma.mlp) {
         HIP_TRY(c, launch_mlp_mfma(m, b, c->X.p, c->mfma, bf, (const float *)c->wt[m.n_layers - 1].p,
                                    (const float *)c->bias1.p, s));
     } else {
@@ -789,15 +795,20 @@ aif_status aif_score_topk_static(aif_ctx *c, const aif_request *req, int32_t k, 
             HIP_TRY(c, launch_fold_w0(m, b, plan, s));
         }
     }
-    if (plan.attn)
+    const float *bf[MAX_LAYERS];
+    for (int l = 0; l < m.n_layers; ++l) bf[l] = c->has_bias[l] ? (const float *)c->bias[l].p : nullptr;
+    const bool one_launch = fused && score_tile_serves(m, b, plan);
+    if (one_launch)
+        HIP_TRY(c, launch_score_tile(m, b, X, plan, mlp_pack(m, plan, bf, (const float *)c->wt[m.n_layers - 1].p), bias1,
+                                     attn_indexes ? c->table : nullptr, bad, s));
+    else if (plan.attn)
         HIP_TRY(c, launch_attn_mfma(m, b, X, plan, fused || staged_proj, s, attn_indexes ? c->table : nullptr, attn_indexes ? bad : nullptr));
     else
         HIP_TRY(c, launch_attn_generic(m, b, X, c->has_wq ? (const float *)c->wq.p : nullptr, c->wq_pieces.p,
                                        attn_indexes ? c->table : nullptr, bad, c->max_seq_len, q.seq_len, s));
     c->last_mlp = mlp_kind(m, plan, b);
-    if (plan.mlp) {
-        const float *bf[MAX_LAYERS];
-        for (int l = 0; l < m.n_layers; ++l) bf[l] = c->has_bias[l] ? (const float *)c->bias[l].p : nullptr;
+    if (one_launch) {
+    } else if (plan.mlp) {
         HIP_TRY(c, launch_mlp_mfma(m, b, X, plan, bf, (const float *)c->wt[m.n_layers - 1].p, bias1, s));
     } else {
         MlpGenericWeights gw{};

@@ -87,6 +87,12 @@ hipError_t launch_stage(const Model &m, const Batch &b, const void *table, void 
                         const StageUpload *up = nullptr, const FewFill *few = nullptr);
 
 // bias_f32[l] / wlast_f32: the context's fp32 copies (bias of layer l or null; last layer's weight row).
+MlpPack mlp_pack(const Model &m, const MfmaPlan &plan, const float *const *bias_f32, const float *wlast_f32);
+// k_score_tile.hip: attention and head of a batch of few candidates as one launch, in place of launch_attn_mfma and
+// launch_mlp_mfma (the same bits); K/V are packed and the users' layer-1 weights made.  table, bad: as for launch_attn_mfma.
+bool score_tile_serves(const Model &m, const Batch &b, const MfmaPlan &plan);
+hipError_t launch_score_tile(const Model &m, const Batch &b, void *X, const MfmaPlan &plan, const MlpPack &pk, const float *bias1,
+                             const void *table, int32_t *bad, hipStream_t s);
 hipError_t launch_mlp_mfma(const Model &m, const Batch &b, const void *X, const MfmaPlan &plan,
                            const float *const *bias_f32, const float *wlast_f32, const float *bias1, hipStream_t s);
 

@@ -93,8 +93,7 @@ hipError_t launch_attn_mfma(const Model &m, const Batch &b, void *X, const MfmaP
     return launch_attn_variant(m, b, X, plan, kv_packed, gather_table, bad, s);
 }
 
-hipError_t launch_mlp_mfma(const Model &m, const Batch &b, const void *X, const MfmaPlan &plan,
-                           const float *const *bias_f32, const float *wlast_f32, const float *bias1, hipStream_t s)
+MlpPack mlp_pack(const Model &m, const MfmaPlan &plan, const float *const *bias_f32, const float *wlast_f32)
 {
     MlpPack pk{};
     const int nh = m.n_layers - 1;
@@ -107,6 +106,13 @@ hipError_t launch_mlp_mfma(const Model &m, const Batch &b, const void *X, const 
     pk.w0_user = m.cross_in_mlp == 2 ? plan.w0_user : nullptr;
     pk.w0_stride = plan.w0_stride;
     pk.tile = plan.tile;
+    return pk;
+}
+
+hipError_t launch_mlp_mfma(const Model &m, const Batch &b, const void *X, const MfmaPlan &plan,
+                           const float *const *bias_f32, const float *wlast_f32, const float *bias1, hipStream_t s)
+{
+    const MlpPack pk = mlp_pack(m, plan, bias_f32, wlast_f32);
     if (plan.mlp_variant == MLP_VARIANT_LAYERS) return launch_mlp_layers(m, b, X, pk, bias1, plan.hbuf, s);
     return launch_mlp_variant(plan.mlp_variant, m, b, X, pk, bias1, s);
 }

@@ -10,45 +10,23 @@
 //
 // What bounds it: the weights through one compute unit's L1 (256 -> 512 -> 256: 393 KB a workgroup, 2.6 us at 64 bytes a
 // cycle) behind three round trips (tile -> request and slot -> weights).
-#include <utility>
-
-#include "k_mlp_chain.h"
+#include "k_mlp_tile.h"
 
 namespace aif {
-
-// A head's shape, and how NW waves share it out: layer l has row tiles w, w + NW, .. of wave w.
-template <int K1, int H1, int H2, int H3, int NW> struct TileHead {
-    static constexpr int NH = H3 ? 3 : (H2 ? 2 : 1);
-    static constexpr int kin(int l) { return l == 0 ? K1 : (l == 1 ? H1 : H2); }
-    static constexpr int nout(int l) { return l == 0 ? H1 : (l == 1 ? H2 : H3); }
-    static constexpr int ks(int l) { return kin(l) / 16; }
-    static constexpr int rows(int l) { return nout(l) / 32 / NW; }             // row tiles per wave
-    static constexpr int frags(int l) { return rows(l) * ks(l); }
-    static constexpr int first(int l, int ring) { return frags(l) < ring ? frags(l) : ring; }
-    static constexpr int HL = nout(NH - 1);                                    // width entering the ->1 layer
-    // LDS: the activations of the hidden layers that are read by another (bf16 fragments), the last one's in fp32, the ->1 weights
-    static constexpr int act_at(int l) { return l == 0 ? 0 : H1 / 16 * 1024; }
-    static constexpr int last_at = (NH > 1 ? H1 / 16 * 1024 : 0) + (NH > 2 ? H2 / 16 * 1024 : 0);
-    static constexpr int wl_at = last_at + HL * 32 * 4;
-    static constexpr int lds_bytes = wl_at + HL * 4;
-    static_assert(H1 % (32 * NW) == 0 && H2 % (32 * NW) == 0 && H3 % (32 * NW) == 0, "every wave has as many row tiles");
-    static_assert(lds_bytes <= 160 * 1024 && HL / 4 <= 64 * NW, "LDS; the ->1 weights in one go");
-};
 
 template <int K1, int H1, int H2, int H3, int NW>
 __global__ __launch_bounds__(NW * 64, 2) void k_mlp_tile(int64_t n_items, const ReqDesc *__restrict__ reqs, const int32_t *__restrict__ blk_req,
                                                          const int32_t *__restrict__ blk_slot, const char *__restrict__ X, XLayout xl, MlpPack pk,
-                                                         const float *__restrict__ bias1)
+                                                         const float *__restrict__ bias1, int n_blk)
 {
     using H = TileHead<K1, H1, H2, H3, NW>;
-    constexpr int RING = 16;                                    // fragments a wave has in flight
-    constexpr int PRE = H::NH > 1 && K1 <= 256 ? H::first(1, RING) : 0;                 // ... of layer 2, before layer 1's, where there is room
     extern __shared__ __align__(16) char lds[];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), col = lane & 31, h = lane >> 5;
-    const int tile = blockIdx.x;
-    const int r = blk_req[tile / (ROW_BLOCK / 32)], slot = blk_slot[tile / (ROW_BLOCK / 32)];
+    // the first tile of every ROW_BLOCK, then the second ..: tiles past a request's end come late, behind those with work
+    const int blk = (int)blockIdx.x % n_blk, tile = blk * (ROW_BLOCK / 32) + (int)blockIdx.x / n_blk;
+    const int r = blk_req[blk], slot = blk_slot[blk];
 
-    // nothing here waits for the request: the tile's rows, the ->1 weights, layer 2's first fragments and biases
+    // nothing here waits for the request: the tile's rows, the ->1 weights, layer 2's first fragments
     bf16x8 xin[K1 / 16];
     {
         const char *xr = X + x_offset(xl, tile * 32 + col, h);
@@ -57,24 +35,8 @@ __global__ __launch_bounds__(NW * 64, 2) void k_mlp_tile(int64_t n_items, const 
     }
     const f32x4 wl = ((const f32x4 *)pk.wlast)[threadIdx.x < H::HL / 4 ? threadIdx.x : 0];
     const float blast = pk.blast[0];
-    auto frag_of = [&](auto lc, auto fc, const char *w) {       // fragment F of this wave's share of layer L
-        constexpr int L = decltype(lc)::value, F = decltype(fc)::value;
-        return *(const bf16x8 *)(w + (size_t)((F / H::ks(L) * NW + wave) * H::ks(L) + F % H::ks(L)) * 1024 + lane * 16);
-    };
-    auto bias_of = [&](const float *b, int rt, f32x16 &a) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const f32x4 v = *(const f32x4 *)(b + 32 * rt + 8 * q + 4 * h);
-            a[4 * q + 0] = v.x;
-            a[4 * q + 1] = v.y;
-            a[4 * q + 2] = v.z;
-            a[4 * q + 3] = v.w;
-        }
-    };
-    f32x16 acc[2];                                              // of the row tile under way and of the next
-    bf16x8 pre[PRE ? PRE : 1];
-    static_for<0, PRE>([&](auto fc) { pre[decltype(fc)::value] = frag_of(IC<1>{}, fc, pk.w[1]); });
-    __builtin_amdgcn_sched_barrier(0);
+    TileMlp<H> mlp(lds, lane, wave);
+    mlp.ask_later(pk);
 
     const ReqDesc *rq = reqs + r;
     const int n_cand = rq->n_cand, local = tile * 32 - rq->row_base + col;
@@ -84,79 +46,10 @@ __global__ __launch_bounds__(NW * 64, 2) void k_mlp_tile(int64_t n_items, const 
     const char *w0 = pk.w0_user + (size_t)slot * pk.w0_stride;
     const float *b0 = bias1 + (size_t)slot * H1;
     if (threadIdx.x < H::HL / 4) *(f32x4 *)(lds + H::wl_at + threadIdx.x * 16) = wl;
-
-    // Layer L: this wave's row tiles in turn, its fragments RING ahead (the first of them in `ring` already), `next`: what to ask
-    // for behind the last one.
-    auto layer = [&](auto lc, const char *w, const float *b, bf16x8 *ring) __attribute__((always_inline)) {
-        constexpr int L = decltype(lc)::value, KS = H::ks(L), R = H::rows(L), NF = H::frags(L);
-        constexpr int AHEAD = 4;                                // activations from LDS
-        bf16x8 x[L == 0 ? 1 : AHEAD];
-        const char *act = lds + (L == 0 ? 0 : H::act_at(L - 1)) + lane * 16;
-        if constexpr (L > 0)
-#pragma unroll
-            for (int k = 0; k < AHEAD; ++k) x[k] = *(const bf16x8 *)(act + k * 1024);
-        static_for<0, NF>([&](auto fc) {
-            constexpr int F = decltype(fc)::value, K = F % KS, T = F / KS;
-            if constexpr (K == 0 && T + 1 < R) bias_of(b, (T + 1) * NW + wave, acc[(T + 1) & 1]);
-            if constexpr (L == 0) {
-                acc[T & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[F % RING], xin[K], acc[T & 1], 0, 0, 0);
-            } else {
-                acc[T & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[F % RING], x[F % AHEAD], acc[T & 1], 0, 0, 0);
-                if constexpr (F + AHEAD < NF) x[F % AHEAD] = *(const bf16x8 *)(act + (F + AHEAD) % KS * 1024);
-            }
-            if constexpr (F + RING < NF) ring[F % RING] = frag_of(lc, IC<F + RING>{}, w);
-            if constexpr (K == KS - 1) {
-                const f32x16 &a = acc[T & 1];
-                const int rt = T * NW + wave;
-                if constexpr (L == H::NH - 1) {
-#pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        *(f32x4 *)(lds + H::last_at + (rt * 4 + q) * 1024 + lane * 16) =
-                            f32x4{relu(a[4 * q]), relu(a[4 * q + 1]), relu(a[4 * q + 2]), relu(a[4 * q + 3])};
-                } else {
-#pragma unroll
-                    for (int j = 0; j < 2; ++j) {               // slot s of half h <-> feature 16 j + 8 (s / 4) + 4 h + s % 4
-                        bf16x8 o;
-#pragma unroll
-                        for (int s = 0; s < 8; ++s) o[s] = (__bf16)relu(a[8 * j + s]);
-                        *(bf16x8 *)(lds + H::act_at(L) + (2 * rt + j) * 1024 + lane * 16) = o;
-                    }
-                }
-            }
-            __builtin_amdgcn_sched_barrier(0);
-        });
-    };
-    // (the barrier is hand-issued: loads in flight stay in flight)
-    auto settle = [&]() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
-
-    // layer L from its first fragment on; `met`: its input is the tile's rows, no other wave's work
-    auto from_first = [&](auto lc, const char *w, const float *b, bool met) __attribute__((always_inline)) {
-        bf16x8 ring[RING];
-        bias_of(b, wave, acc[0]);
-        static_for<0, H::first(decltype(lc)::value, RING)>([&](auto fc) { ring[decltype(fc)::value] = frag_of(lc, fc, w); });
-        __builtin_amdgcn_sched_barrier(0);
-        if (!met) settle();
-        layer(lc, w, b, ring);
-    };
-    from_first(IC<0>{}, w0, b0, true);
-    if constexpr (PRE > 0) {
-        bias_of(pk.bias[1], wave, acc[0]);
-        settle();
-        layer(IC<1>{}, pk.w[1], pk.bias[1], pre);
-    } else if constexpr (H::NH > 1)
-        from_first(IC<1>{}, pk.w[1], pk.bias[1], false);
-    if constexpr (H::NH > 2) from_first(IC<2>{}, pk.w[2], pk.bias[2], false);
-    settle();
+    mlp.template ask<0>(w0, b0);
+    mlp.run(pk, w0, b0, xin);
     if (wave != 0) return;
-    // the ->1 layer, a lane's features in the chain's order
-    float zpart = 0.f;
-#pragma unroll
-    for (int i = 0; i < H::HL / 8; ++i) {
-        const f32x4 a = *(const f32x4 *)(lds + H::last_at + i * 1024 + lane * 16);
-        const f32x4 v = *(const f32x4 *)(lds + H::wl_at + (8 * i + 4 * h) * 4);
-        zpart = dot4(zpart, v, a.x, a.y, a.z, a.w);
-    }
-    float z = zpart + __shfl_xor(zpart, 32, 64) + blast;
+    float z = mlp.logit(blast);
     if (live) {
         if (id < 0 || id >= n_items) z = __uint_as_float(0x7FC00000u);
         rq->logits_out[local] = z;
@@ -176,7 +69,7 @@ static hipError_t tile_go(const Model &m, const Batch &b, const void *X, const M
         attr_set = true;
     }
     hipLaunchKernelGGL(kern, dim3(b.n_blk * (ROW_BLOCK / 32)), dim3(NW * 64), H::lds_bytes, s, m.n_items, b.reqs, b.blk_req, b.blk_slot,
-                       (const char *)X, x_layout(m), pk, bias1);
+                       (const char *)X, x_layout(m), pk, bias1, b.n_blk);
     return hipGetLastError();
 }
 

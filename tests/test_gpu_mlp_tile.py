@@ -1,4 +1,5 @@
-"""The head of few candidates, a workgroup to a tile of 32, against the chain (the widest head: the accumulating kernel)."""
+"""Few candidates, a workgroup to a tile of 32: the head alone (the widest one) and attention and head in one launch, against the
+kernels of larger batches (the chain; the widest head: the accumulating kernel; resident and key-split attention)."""
 import numpy as np
 import pytest
 
@@ -47,3 +48,43 @@ def test_few_candidates_give_the_bits_of_many(R, torch, monkeypatch, shape, size
     if len(sizes) > 2 and sizes[1] == 32:
         u, ids = users_ids[1]
         assert_bf16_logits_tight(got[1], oracle_scores(cfg, model, table, u, ids).logits, "against the oracle")
+
+
+# a head of one run of keys (K/V that fit the resident kernel's LDS: 18 key tiles of 64 features) and of KEY_PARTS, alone and
+# mixed; no history, ragged stages, a bound that needs the true maximum (sigma 4), more than one tile a unit
+@pytest.mark.parametrize("sigma", [1.0, 4.0])
+@pytest.mark.parametrize("lens", [(0, 1, 31), (64, 65, 576), (577, 1100, 700), (1100, 30, 0, 640)])
+@pytest.mark.parametrize("shape", [*MFMA_SHAPES, "B3", "two_heads"])
+def test_attention_and_head_in_one_launch_give_the_bits_of_two(R, torch, monkeypatch, shape, lens, sigma):  # noqa: F811
+    if shape == "two_heads":
+        cfg = small_cfg("bf16", n_items=3000, seq_len=24, d_item=64, d_user=64, d_attn=64, n_heads=2, mlp_dims=(256, 256, 128, 1))
+    else:
+        cfg = config(shape)
+    _say(f"one launch {shape} {lens} sigma={sigma}")
+    rng = np.random.default_rng(53)
+    model = wl.make_model(cfg, seed=9, bias_scale=0.05)
+    table = wl.make_table_host(cfg, rng, n_items=cfg.n_items, sigma=sigma)
+    table_dev = R.to_device(table, "bf16")
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    for big in (0, 32 * (n_cu + 9)):                            # past a tile a unit: workgroups of four waves
+        users_ids = []
+        for r, l in enumerate(lens):
+            n = [33, 100, 257, 1][r] + (big if r == 0 else 0)
+            ids = rng.integers(0, cfg.n_items, n).astype(np.int32)
+            if r == 1:
+                ids[[0, n // 2, n - 1]] = [-1, 2_000_000_000, cfg.n_items]
+            users_ids.append((wl.make_user(cfg, rng, seq_len=l, sigma=sigma), ids))
+        got, got_y, _, ctx = run_batch(R, torch, cfg, model, table_dev, users_ids, max_seq_len=1100)
+        bad = ctx.aif_poll_device_errors()
+        X = [R.peek_features(ctx, cfg, r, ids.size) for r, (_, ids) in enumerate(users_ids)]
+        with monkeypatch.context() as mp:
+            mp.setenv("AIF_MLP_TILE", "0")
+            ref, ref_y, _, ctx0 = run_batch(R, torch, cfg, model, table_dev, users_ids, max_seq_len=1100)
+        assert bad == 3 and ctx0.aif_poll_device_errors() == 3
+        assert ctx.aif_stage_kind("gather") == ctx0.aif_stage_kind("gather")
+        for r, (u, ids) in enumerate(users_ids):
+            assert np.array_equal(X[r], R.peek_features(ctx0, cfg, r, ids.size)), r
+            assert np.array_equal(got[r], ref[r], equal_nan=True) and np.array_equal(got_y[r], ref_y[r], equal_nan=True), r
+        if sigma == 1.0 and not big:
+            u, ids = users_ids[2]
+            assert_bf16_logits_tight(got[2], oracle_scores(cfg, model, table, u, ids).logits, "against the oracle")
