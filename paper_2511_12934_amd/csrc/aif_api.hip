@@ -218,6 +218,22 @@ aif_status check_device(aif_ctx *c)
     return AIF_OK;
 }
 
+MlpGenericWeights generic_weights(const aif_ctx *c)
+{
+    MlpGenericWeights gw{};
+    for (int l = 0; l < c->m.n_layers; ++l) {
+        gw.wt[l] = (const float *)c->wt[l].p;
+        gw.pieces[l] = c->w_pieces[l].p;
+        gw.bias[l] = c->has_bias[l] ? (const float *)c->bias[l].p : nullptr;
+    }
+    return gw;
+}
+// whether the shape-agnostic kernels take the batch's attention and head as one launch
+bool gen_one_launch(const aif_ctx *c, const Batch &b, int longest)
+{
+    return c->mfma.tile && !c->mfma.attn && !c->mfma.mlp && gen_tile_serves(c->m, b, longest);
+}
+
 aif_status init_impl(const aif_config *cfg, const aif_weights *wts, aif_ctx *c)
 {
     if (cfg->dtype != AIF_F32 && cfg->dtype != AIF_BF16) return fail(nullptr, AIF_EINVAL, "unknown dtype %d", (int)cfg->dtype);
@@ -595,32 +611,28 @@ static aif_status score_impl(aif_ctx *c, const aif_request *reqs, int32_t n_req,
     HIP_TRY(c, mark(2));
     const float *bf[MAX_LAYERS];
     for (int l = 0; l < m.n_layers; ++l) bf[l] = c->has_bias[l] ? (const float *)c->bias[l].p : nullptr;
+    const MlpGenericWeights gw = generic_weights(c);
     // few candidates: attention and head as one launch (a call that is timed stage by stage keeps them apart)
-    const bool one_launch = !pe && fused && score_tile_serves(m, b, c->mfma);
-    if (one_launch)
+    const bool one_launch = !pe && (fused ? score_tile_serves(m, b, c->mfma) : gen_one_launch(c, b, longest));
+    const void *rows_from = attn_indexes ? c->table : nullptr;
+    const float *wq = c->has_wq ? (const float *)c->wq.p : nullptr;
+    if (one_launch && fused)
         HIP_TRY(c, launch_score_tile(m, b, c->X.p, c->mfma, mlp_pack(m, c->mfma, bf, (const float *)c->wt[m.n_layers - 1].p),
-                                     (const float *)c->bias1.p, attn_indexes ? c->table : nullptr, (int32_t *)c->bad.p, s));
+                                     (const float *)c->bias1.p, rows_from, (int32_t *)c->bad.p, s));
+    else if (one_launch)
+        HIP_TRY(c, launch_gen_tile(m, b, c->X.p, wq, c->wq_pieces.p, rows_from, (int32_t *)c->bad.p, longest, gw, (const float *)c->bias1.p, s));
     else if (c->mfma.attn)
-        HIP_TRY(c, launch_attn_mfma(m, b, c->X.p, c->mfma, fused || staged_proj, s, attn_indexes ? c->table : nullptr,
+        HIP_TRY(c, launch_attn_mfma(m, b, c->X.p, c->mfma, fused || staged_proj, s, rows_from,
                                     attn_indexes ? (int32_t *)c->bad.p : nullptr));
     else
-        HIP_TRY(c, launch_attn_generic(m, b, c->X.p, c->has_wq ? (const float *)c->wq.p : nullptr, c->wq_pieces.p,
-                                       attn_indexes ? c->table : nullptr, (int32_t *)c->bad.p, c->max_seq_len, longest, s));
+        HIP_TRY(c, launch_attn_generic(m, b, c->X.p, wq, c->wq_pieces.p, rows_from, (int32_t *)c->bad.p, c->max_seq_len, longest, s));
     HIP_TRY(c, mark(3));
     c->last_mlp = mlp_kind(m, c->mfma, b);
     if (one_launch) {
-    } else if (c->mfma.mlp) {
-        HIP_TRY(c, launch_mlp_mfma(m, b, c->X.p, c->mfma, bf, (const float *)c->wt[m.n_layers - 1].p,
-                                   (const float *)c->bias1.p, s));
-    } else {
-        MlpGenericWeights gw{};
-        for (int l = 0; l < m.n_layers; ++l) {
-            gw.wt[l] = (const float *)c->wt[l].p;
-            gw.pieces[l] = c->w_pieces[l].p;
-            gw.bias[l] = c->has_bias[l] ? (const float *)c->bias[l].p : nullptr;
-        }
+    } else if (c->mfma.mlp)
+        HIP_TRY(c, launch_mlp_mfma(m, b, c->X.p, c->mfma, bf, (const float *)c->wt[m.n_layers - 1].p, (const float *)c->bias1.p, s));
+    else
         HIP_TRY(c, launch_mlp_generic(m, b, c->X.p, gw, (const float *)c->bias1.p, s));
-    }
     HIP_TRY(c, mark(4));
     if (k > 0) {
         hipEvent_t *pt = nullptr;
@@ -797,28 +809,24 @@ aif_status aif_score_topk_static(aif_ctx *c, const aif_request *req, int32_t k, 
     }
     const float *bf[MAX_LAYERS];
     for (int l = 0; l < m.n_layers; ++l) bf[l] = c->has_bias[l] ? (const float *)c->bias[l].p : nullptr;
-    const bool one_launch = fused && score_tile_serves(m, b, plan);
-    if (one_launch)
-        HIP_TRY(c, launch_score_tile(m, b, X, plan, mlp_pack(m, plan, bf, (const float *)c->wt[m.n_layers - 1].p), bias1,
-                                     attn_indexes ? c->table : nullptr, bad, s));
+    const MlpGenericWeights gw = generic_weights(c);
+    const bool one_launch = fused ? score_tile_serves(m, b, plan) : gen_one_launch(c, b, q.seq_len);
+    const void *rows_from = attn_indexes ? c->table : nullptr;
+    const float *wq = c->has_wq ? (const float *)c->wq.p : nullptr;
+    if (one_launch && fused)
+        HIP_TRY(c, launch_score_tile(m, b, X, plan, mlp_pack(m, plan, bf, (const float *)c->wt[m.n_layers - 1].p), bias1, rows_from, bad, s));
+    else if (one_launch)
+        HIP_TRY(c, launch_gen_tile(m, b, X, wq, c->wq_pieces.p, rows_from, bad, q.seq_len, gw, bias1, s));
     else if (plan.attn)
-        HIP_TRY(c, launch_attn_mfma(m, b, X, plan, fused || staged_proj, s, attn_indexes ? c->table : nullptr, attn_indexes ? bad : nullptr));
+        HIP_TRY(c, launch_attn_mfma(m, b, X, plan, fused || staged_proj, s, rows_from, attn_indexes ? bad : nullptr));
     else
-        HIP_TRY(c, launch_attn_generic(m, b, X, c->has_wq ? (const float *)c->wq.p : nullptr, c->wq_pieces.p,
-                                       attn_indexes ? c->table : nullptr, bad, c->max_seq_len, q.seq_len, s));
+        HIP_TRY(c, launch_attn_generic(m, b, X, wq, c->wq_pieces.p, rows_from, bad, c->max_seq_len, q.seq_len, s));
     c->last_mlp = mlp_kind(m, plan, b);
     if (one_launch) {
-    } else if (plan.mlp) {
+    } else if (plan.mlp)
         HIP_TRY(c, launch_mlp_mfma(m, b, X, plan, bf, (const float *)c->wt[m.n_layers - 1].p, bias1, s));
-    } else {
-        MlpGenericWeights gw{};
-        for (int l = 0; l < m.n_layers; ++l) {
-            gw.wt[l] = (const float *)c->wt[l].p;
-            gw.pieces[l] = c->w_pieces[l].p;
-            gw.bias[l] = c->has_bias[l] ? (const float *)c->bias[l].p : nullptr;
-        }
+    else
         HIP_TRY(c, launch_mlp_generic(m, b, X, gw, bias1, s));
-    }
     if (k > 0) HIP_TRY(c, launch_topk_few(&f.td[0], 1, k, idx_out, val_out, s));
     return AIF_OK;
 }

@@ -161,6 +161,10 @@ struct MlpGenericWeights {
 hipError_t launch_mlp_generic(const Model &m, const Batch &b, const void *X, const MlpGenericWeights &w,
                               const float *bias1, hipStream_t s);
 size_t mlp_generic_lds_bytes(const Model &m);
+// Both of a batch of few candidates as one launch (the same bits).
+bool gen_tile_serves(const Model &m, const Batch &b, int longest);
+hipError_t launch_gen_tile(const Model &m, const Batch &b, void *X, const float *wq, const void *wq_pieces, const void *table, int32_t *bad,
+                           int longest, const MlpGenericWeights &w, const float *bias1, hipStream_t s);
 
 // a8: per-request radix select + sort.
 struct TopkDesc {

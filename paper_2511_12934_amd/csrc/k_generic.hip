@@ -100,19 +100,34 @@ template <int P> struct Pieces { bf16x8 p[P]; };
 
 // x = p[0] + p[1] + p[2], each piece the rest so far rounded to bf16: exact for three pieces.  A value that is not
 // finite (or rounds to infinity) makes NaN pieces: whoever multiplies them sees a NaN and takes the plain route.
-template <int P> __device__ __forceinline__ Pieces<P> split8(const float *v)
+// Two values at a time: the conversion takes a pair, and their rests come off the two halves of its word (value by value it is
+// two conversions a pair and piece).
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+template <int P> __device__ __forceinline__ void split2(float a, float b, uint32_t (&w)[P])
 {
-    Pieces<P> o;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        float r = v[j];
-#pragma unroll
-        for (int q = 0; q < P; ++q) {
-            const __bf16 h = (__bf16)r;
-            o.p[q][j] = h;
-            if (q + 1 < P) r -= (float)h;
+    for (int q = 0; q < P; ++q) {
+        w[q] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{a, b}), bf16x2));
+        if (q + 1 < P) {
+            a -= __uint_as_float(w[q] << 16);
+            b -= __uint_as_float(w[q] & 0xFFFF0000u);
         }
     }
+}
+template <int P> __device__ __forceinline__ Pieces<P> split8(const float *v)
+{
+    uint32_t w[P][4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        uint32_t x[P];
+        split2<P>(v[2 * j], v[2 * j + 1], x);
+#pragma unroll
+        for (int q = 0; q < P; ++q) w[q][j] = x[q];
+    }
+    Pieces<P> o;
+#pragma unroll
+    for (int q = 0; q < P; ++q) o.p[q] = __builtin_bit_cast(bf16x8, make_uint4(w[q][0], w[q][1], w[q][2], w[q][3]));
     return o;
 }
 
@@ -323,9 +338,9 @@ __global__ __launch_bounds__(256) void k_attn_generic(Model m, Batch b, T *__res
 // stays under 128 registers (four waves a SIMD); then the vector ALU -- per key
 // and candidate one exponential and three pieces of the weight.  Measured (L <=
 // 50, d_attn 32 of W_q, rows of 64): fp32, 16 users of 6,200 candidates on average
-// 36 us, bf16, 16 x 10^4: 38 -- 230 + 13 and 312 + 10 with a wave per candidate on
-// the vector ALU after a gather launch, 48 and 55 with the keys 32 at a time; fp32,
-// one request of 1,000: 11.5 against 22 + 6.
+// 33 us, bf16, 16 x 10^4: 35 -- 230 + 13 and 312 + 10 with a wave per candidate on
+// the vector ALU after a gather launch, 48 and 55 with the keys 32 at a time in
+// blocks of four waves; fp32, one request of 1,000: 10.4 against 22 + 6.
 // ---------------------------------------------------------------------------
 constexpr int GEN_KEYS = 32;
 
@@ -393,38 +408,40 @@ __device__ __forceinline__ float exp_neg(float x)
     return fmaf(p, e * LN2, p);
 }
 
+// fragments of a chunk of keys: K (key tile, k-step), then V (feature tile)
+__host__ __device__ constexpr int gen_chunk_frags(int ft) { return (ft + 1) / 2 * 2 + ft; }
+
 // FT: tiles of 16 features a head has.  WV: waves of the block, 16 candidates each at a time.  wqp: W_q as pieces,
 // [head][query_tiles(FT)][k-step of 32][piece][64 lanes][8], rows past the head's width zero (pack_pieces).
 // table null: the item rows are in the workspace.
 // RES: the pieces of all the request's keys, of every head, are staged at once, in dynamic LDS, and the block walks a whole
 // ROW_BLOCK of candidates with no further barrier; else 32 keys of one head at a time for 16 WV candidates.
-template <typename T, int FT, int WV, bool WQ, bool RES>
-__global__ __launch_bounds__(64 * WV, FT <= 2 ? 4 : 2) void k_attn_gen(Model m, Batch b, T *__restrict__ X, const T *__restrict__ table,
-                                                                       const bf16x8 *__restrict__ wqp, const float *__restrict__ wq,
-                                                                       int32_t *__restrict__ bad)
+// TILES: column tiles of the block from row0 on; frag: LDS for the keys, [head][chunk][fragment][piece][lane] (not RES: one chunk).
+template <typename T, int FT, int WV, bool WQ, bool RES, int TILES>
+__device__ __forceinline__ void attn_gen_block(const Model &m, const ReqDesc &rd, int row0, T *X, const T *__restrict__ table,
+                                               const bf16x8 *__restrict__ wqp, const float *__restrict__ wq, int32_t *__restrict__ bad, bf16x8 *frag)
 {
     constexpr int P = stored<T>::P, PQ = WQ ? 3 : P, KS = (FT + 1) / 2, VEC = 16 / sizeof(T);
-    constexpr int FRAGS = 2 * KS + FT;                          // fragments of a chunk of keys: K (key tile, k-step), then V (feature tile)
+    constexpr int FRAGS = gen_chunk_frags(FT);
     constexpr int PER = RES ? 2 : (FRAGS + WV - 1) / WV;        // fragments a wave has on their way
     static_assert(2 * KS == query_tiles(FT), "the query's tiles are those that are packed");
-    extern __shared__ __align__(16) char dyn[];
-    bf16x8 *frag;                                               // [head][chunk][fragment][piece][lane]; RES = false: one chunk
-    if constexpr (RES) frag = (bf16x8 *)dyn;
-    else {
-        __shared__ bf16x8 one[FRAGS * P * 64];
-        frag = one;
-    }
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), col = lane & 15, g = lane >> 4;
-    const int row0 = blockIdx.x * (RES ? ROW_BLOCK : 16 * WV);
-    const int r = b.blk_req[row0 / ROW_BLOCK];
-    if (r < 0) return;
-    const ReqDesc rd = b.reqs[r];
     const int local0 = row0 - rd.row_base;
-    if (local0 >= rd.n_cand) return;
     const int L = rd.seq_len, dh = m.d_head, da = m.d_attn, chunks = (L + GEN_KEYS - 1) / GEN_KEYS;
     const bool quad = (dh & 3) == 0;
     const float scale = 1.0f / sqrtf((float)dh);
     const T *K = (const T *)rd.seq_keys, *V = (const T *)rd.seq_vals;
+
+    // One tile: the waves share its parts -- the first its attention, the second its row (and cross block), the others the keys.
+    constexpr bool ROLES = TILES == 1;
+    static_assert(!ROLES || (RES && WV >= 4), "a wave for each part");
+    const int tile_first = ROLES ? 0 : wave;
+    // the lane's candidate in a tile, and its id: asked for ahead
+    auto cand = [&](int tile) {
+        const int at = local0 + tile * 16 + col;
+        return at < rd.n_cand ? at : rd.n_cand - 1;
+    };
+    int32_t raw = table ? rd.cand_ids[cand(tile_first)] : 0;
 
     // fragment f of the chunk of keys from t0, head columns from o: its eight values of this lane, and as pieces to LDS
     auto fetch = [&](int f, int t0, int o, float (&v)[8]) __attribute__((always_inline)) {
@@ -469,16 +486,17 @@ __global__ __launch_bounds__(64 * WV, FT <= 2 ? 4 : 2) void k_attn_gen(Model m, 
             if (wave + WV * it < FRAGS) put(wave + WV * it, t0, kv[it], frag);
     };
     if constexpr (RES) {
-        const int n = m.n_heads * chunks * FRAGS;               // dealt round the waves, PER at a time
-        for (int i0 = wave; i0 < n; i0 += PER * WV) {
+        constexpr int FIRST = ROLES ? 2 : 0, DEAL = WV - FIRST; // dealt round the waves, PER at a time
+        const int n = m.n_heads * chunks * FRAGS;
+        for (int i0 = wave < FIRST ? n : wave - FIRST; i0 < n; i0 += PER * DEAL) {
 #pragma unroll
             for (int it = 0; it < PER; ++it) {
-                const int i = i0 + it * WV, c = i / FRAGS, h = c / chunks;
+                const int i = i0 + it * DEAL, c = i / FRAGS, h = c / chunks;
                 if (i < n) fetch(i - c * FRAGS, (c - h * chunks) * GEN_KEYS, h * dh, kv[it]);
             }
 #pragma unroll
             for (int it = 0; it < PER; ++it) {
-                const int i = i0 + it * WV, c = i / FRAGS, h = c / chunks;
+                const int i = i0 + it * DEAL, c = i / FRAGS, h = c / chunks;
                 if (i < n) put(i - c * FRAGS, (c - h * chunks) * GEN_KEYS, kv[it], frag + (size_t)c * FRAGS * P * 64);
             }
         }
@@ -486,47 +504,53 @@ __global__ __launch_bounds__(64 * WV, FT <= 2 ? 4 : 2) void k_attn_gen(Model m, 
         fetch_chunk(0, 0);
 
     int n_bad = 0;
-    for (int tile = wave; tile < (RES ? ROW_BLOCK / 16 : WV); tile += WV) {
-        if (RES && local0 + tile * 16 >= rd.n_cand) {           // a wave past the end: nothing left but the barrier after the keys
-            if (tile == wave) __syncthreads();
-            break;
-        }
+    if (ROLES ? wave > 1 : RES && local0 + wave * 16 >= rd.n_cand) {
+        __syncthreads();                                        // nothing left but the barrier after the keys
+        return;
+    }
+    for (int tile = tile_first; tile < TILES; tile += WV) {
+        if (RES && local0 + tile * 16 >= rd.n_cand) break;
         // a1: the lane's candidate and its item row
         const int at = local0 + tile * 16 + col;
         const bool live = at < rd.n_cand;
         const int c = live ? at : rd.n_cand - 1;
         T *xr = X + (size_t)(rd.row_base + c) * m.ldx;
         const T *er = xr;
-        if (table) {
-            int64_t id = rd.cand_ids[c];
+        auto locate = [&]() __attribute__((always_inline)) {
+            if (!table) return;
+            int64_t id = raw;
             if (id < 0 || id >= m.n_items) {
                 id = 0;
-                if (live && g == 0) ++n_bad;
+                if (live && g == 0 && (!ROLES || wave == 0)) ++n_bad;
             }
             er = table + (size_t)id * m.d_item;
-        }
+            if (tile + WV < TILES) raw = rd.cand_ids[cand(tile + WV)];
+        };
+        if (!ROLES || wave == 1) locate();
         // the row into the workspace, and the Hadamard block beside it
-        {
+        if (!ROLES || wave == 1) {
             const T *uc = (const T *)rd.cross_vecs;
             const bool had = m.cross_mode == 1 && !m.cross_in_mlp;
             constexpr int U = 4;
             const int pieces = m.d_item / VEC;
             if (table || had)
                 for (int p0 = 0; p0 < pieces; p0 += 4 * U) {
-                    uint4 v[U];
+                    uint4 v[U], w[U];
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
                         const int p = p0 + 4 * u + g;
                         v[u] = *(const uint4 *)(er + (size_t)(p < pieces ? p : 0) * VEC);
                     }
+                    if (had)
+#pragma unroll
+                        for (int u = 0; u < U; ++u) w[u] = *(const uint4 *)(uc + (size_t)(p0 + 4 * u + g < pieces ? p0 + 4 * u + g : 0) * VEC);
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
                         const int p = p0 + 4 * u + g;
                         if (p >= pieces || !live) continue;
                         if (table) *(uint4 *)(xr + (size_t)p * VEC) = v[u];
                         if (had) {
-                            const uint4 w = *(const uint4 *)(uc + (size_t)p * VEC);
-                            const T *e = (const T *)&v[u], *x = (const T *)&w;
+                            const T *e = (const T *)&v[u], *x = (const T *)&w[u];
                             __align__(16) T o[VEC];
 #pragma unroll
                             for (int k = 0; k < VEC; ++k) st_f<T>(o + k, ld_f<T>(x + k) * ld_f<T>(e + k));
@@ -535,7 +559,7 @@ __global__ __launch_bounds__(64 * WV, FT <= 2 ? 4 : 2) void k_attn_gen(Model m, 
                     }
                 }
         }
-        if (!m.cross_in_mlp && (m.cross_mode == 2 || m.cross_mode == 3)) {
+        if ((!ROLES || wave == 1) && !m.cross_in_mlp && (m.cross_mode == 2 || m.cross_mode == 3)) {
             const T *uc = (const T *)rd.cross_vecs;
             const int S = m.cross_mode == 2 ? m.d_item / m.d_cv : 1;
             T *xc = xr + m.d_item + da;
@@ -553,6 +577,26 @@ __global__ __launch_bounds__(64 * WV, FT <= 2 ? 4 : 2) void k_attn_gen(Model m, 
                 }
         }
 
+        if (ROLES && wave == 1) {
+            __syncthreads();                                    // the keys are staged
+            return;
+        }
+        // W_q's k-steps, UQ at a time where there are registers for it
+        constexpr int UQ = WQ && KS == 1 && !ROLES && P == 1 ? 2 : 1;
+        const int ksn = (m.d_item + 31) / 32;
+        Pieces<P> wf[UQ][2 * KS];
+        auto ask_wq = [&](int h, int ks0) __attribute__((always_inline)) {
+            const bf16x8 *wh = wqp + (size_t)h * query_tiles(FT) * ksn * P * 64 + lane;
+#pragma unroll
+            for (int u = 0; u < UQ; ++u)
+#pragma unroll
+                for (int f = 0; f < 2 * KS; ++f)
+#pragma unroll
+                    for (int q = 0; q < P; ++q) wf[u][f].p[q] = wh[((size_t)(f * ksn + min(ks0 + u, ksn - 1)) * P + q) * 64];
+        };
+        
+        if (ROLES) locate();
+
         for (int h = 0; h < m.n_heads; ++h) {
             const int o = h * dh;
             if (!RES && h > 0 && L > 0) fetch_chunk(0, o);      // the first keys on their way (head 0's: since the start)
@@ -562,19 +606,19 @@ __global__ __launch_bounds__(64 * WV, FT <= 2 ? 4 : 2) void k_attn_gen(Model m, 
                 f32x4 qb[2 * KS], qs[2 * KS];
 #pragma unroll
                 for (int f = 0; f < 2 * KS; ++f) qb[f] = qs[f] = f32x4{0.f, 0.f, 0.f, 0.f};
-                const int ksn = (m.d_item + 31) / 32;
-                const bf16x8 *wh = wqp + (size_t)h * query_tiles(FT) * ksn * P * 64 + lane;
-                for (int ks = 0; ks < ksn; ++ks) {
-                    float v[8];
-                    load8<T>(er + 32 * ks + 8 * g, m.d_item - 32 * ks - 8 * g, v);
-                    const Pieces<P> e = split8<P>(v);
+                ask_wq(h, 0);
+                for (int ks0 = 0; ks0 < ksn; ks0 += UQ) {
+                    float v[UQ][8];
 #pragma unroll
-                    for (int f = 0; f < 2 * KS; ++f) {
-                        Pieces<P> w;
+                    for (int u = 0; u < UQ; ++u) load8<T>(er + 32 * (ks0 + u) + 8 * g, m.d_item - 32 * (ks0 + u) - 8 * g, v[u]);
 #pragma unroll
-                        for (int q = 0; q < P; ++q) w.p[q] = wh[((size_t)(f * ksn + ks) * P + q) * 64];
-                        mfma_pieces(w, e, qb[f], qs[f]);
+                    for (int u = 0; u < UQ; ++u) {
+                        if (ks0 + u >= ksn) continue;
+                        const Pieces<P> e = split8<P>(v[u]);
+#pragma unroll
+                        for (int f = 0; f < 2 * KS; ++f) mfma_pieces(wf[u][f], e, qb[f], qs[f]);
                     }
+                    if (ks0 + UQ < ksn) ask_wq(h, ks0 + UQ);
                 }
 #pragma unroll
                 for (int s = 0; s < KS; ++s) {
@@ -703,12 +747,36 @@ __global__ __launch_bounds__(64 * WV, FT <= 2 ? 4 : 2) void k_attn_gen(Model m, 
     if (n_bad) atomicAdd(bad, n_bad);
 }
 
+template <typename T, int FT, int WV, bool WQ, bool RES>
+__global__ __launch_bounds__(64 * WV, FT <= 2 ? 4 : 2) void k_attn_gen(Model m, Batch b, T *__restrict__ X, const T *__restrict__ table,
+                                                                       const bf16x8 *__restrict__ wqp, const float *__restrict__ wq,
+                                                                       int32_t *__restrict__ bad)
+{
+    extern __shared__ __align__(16) char dyn[];
+    const int row0 = blockIdx.x * (RES ? ROW_BLOCK : 16 * WV);
+    const int r = b.blk_req[row0 / ROW_BLOCK];
+    if (r < 0) return;
+    const ReqDesc rd = b.reqs[r];
+    if (row0 - rd.row_base >= rd.n_cand) return;
+    if constexpr (RES) attn_gen_block<T, FT, WV, WQ, RES, ROW_BLOCK / 16>(m, rd, row0, X, table, wqp, wq, bad, (bf16x8 *)dyn);
+    else {
+        __shared__ bf16x8 one[gen_chunk_frags(FT) * stored<T>::P * 64];
+        attn_gen_block<T, FT, WV, WQ, RES, WV>(m, rd, row0, X, table, wqp, wq, bad, one);
+    }
+}
+
 size_t attn_generic_lds_bytes(const Model &m, int max_seq_len)
 {
     return (size_t)4 * (m.d_item + m.d_attn + max_seq_len) * sizeof(float);
 }
 
 bool attn_generic_gathers(const Model &m) { return m.d_head <= GEN_MAX_HEAD; }
+
+// bytes of LDS the pieces of all keys of a history take
+template <typename T, int FT> static size_t gen_keys_lds(const Model &m, int longest)
+{
+    return (size_t)m.n_heads * ((longest + GEN_KEYS - 1) / GEN_KEYS) * gen_chunk_frags(FT) * stored<T>::P * 1024;
+}
 
 template <typename T, int FT, int WV, bool RES>
 static void attn_gen_go(const Model &m, const Batch &b, void *X, const void *table, const void *wqp, const float *wq, int32_t *bad,
@@ -726,26 +794,36 @@ static void attn_gen_go(const Model &m, const Batch &b, void *X, const void *tab
 // Three forms of the same arithmetic (the same bits): a batch of many ROW_BLOCKs whose longest keys leave room for two
 // blocks on a compute unit keeps them resident, a block of eight waves to a whole ROW_BLOCK; other large batches take blocks of
 // eight waves and half a ROW_BLOCK, 32 keys at a time; small ones blocks of four.
-// The lines, us a call with the keys resident | 32 at a time (queries of W_q; layers 72, 40, 1):
-// heads of up to 32, blocks   256: fp32, 50 keys  70.7 |  67.9   bf16, 50 keys 53.3 | 46.8   bf16, 512 keys  81.0 |  72.5
-//                             384:                90.0 |  89.3                 66.5 | 61.9                  112.3 |  97.6
-//                             512:               109.8 | 110.9                 73.4 | 73.3                  120.3 | 120.3
-//                           1,024:               191.5 | 191.0                123.3 | 124.0                 205.9 | 215.4
-//                           2,560:               492.7 | 486.5                265.9 | 274.2                 456.5 | 487.4
-// heads of 64, blocks         128: fp32, 50 keys  63.6 |  53.1   bf16, 128 keys 50.7 | 40.8
+// The lines, us a launch with the keys resident | 32 at a time (queries of W_q; 512 blocks of resident keys are a round):
+// heads of up to 32, blocks   384: fp32, 50 keys  33.8 |  33.3   bf16, 50 keys  27.9 | 24.2   bf16, 200 keys  44.0 | 38.3
+//                             424:                33.1 |  34.5 (lists of all lengths)
+//                             432:                34.5 |  39.0                  28.0 | 28.1                   44.0 | 45.9
+//                             520:                54.1 |  46.4                  37.9 | 32.8                   58.9 | 55.0
+//                             640:                                              37.8 | 34.2
+//                             800:                66.4 |  63.4                  46.0 | 44.0                   75.3 | 74.6
+//                             880:                69.7 |  65.4                  46.4 | 44.8                   75.2 | 77.2
+//                           1,120:               103.9 |  88.9                  57.1 | 55.4                   92.8 | 95.4
+//                whole calls, 2,560:             492.7 | 486.5                 265.9 | 274.2     512 keys    456.5 | 487.4
+// heads of 64, blocks         128: fp32, 50 keys  63.6 |  53.1   bf16, 128 keys 50.7 | 40.8     (whole calls)
 //                             144:                70.4 |  73.2                  57.3 | 59.8
 //                             512:               143.0 | 152.4                  89.0 | 108.1
-// so from two blocks a compute unit on for narrow heads, and for wide ones as soon as half-ROW_BLOCKs, one to a unit, need a
-// second round.  LDS: two blocks fit up to 80 KB; at 64 to 80 KB resident keys are 7 % faster on
-// 2,560 blocks and 5 % slower on 640; at 96 to 128 KB (one block a unit) 7 to 35 % slower.
+// so, narrow heads, in rounds at least 4/5 full: the only one, or histories of more than two chunks (beyond one round blocks of
+// few keys end unevenly enough to need no rounds); wide ones as soon as half-ROW_BLOCKs, one to a unit, need a second round.  LDS:
+// two blocks fit up to 80 KB; at 64 to 80 KB resident keys are 7 % faster on 2,560 blocks and 5 % slower on 640; at 96 to 128 KB
+// (one block a unit) 7 to 35 % slower.
 constexpr int GEN_SMALL = 256, GEN_RES_BLOCKS = 512;
 constexpr size_t GEN_RES_LDS = 64 * 1024;
+static bool narrow_keys_stay(int n_blk, int longest)
+{
+    const int rounds = (n_blk + GEN_RES_BLOCKS - 1) / GEN_RES_BLOCKS;
+    return 5 * n_blk >= 4 * rounds * GEN_RES_BLOCKS && (rounds == 1 || longest > 2 * GEN_KEYS);
+}
 template <typename T, int FT>
 static void attn_gen_ft(const Model &m, const Batch &b, void *X, const void *table, const void *wqp, const float *wq, int32_t *bad,
                         int longest, hipStream_t s)
 {
-    const size_t lds = (size_t)m.n_heads * ((longest + GEN_KEYS - 1) / GEN_KEYS) * ((FT + 1) / 2 * 2 + FT) * stored<T>::P * 1024;
-    if (b.n_blk >= (FT <= 2 ? GEN_RES_BLOCKS : GEN_SMALL / 2 + 1) && lds <= GEN_RES_LDS) attn_gen_go<T, FT, 8, true>(m, b, X, table, wqp, wq, bad, lds, s);
+    const size_t lds = gen_keys_lds<T, FT>(m, longest);
+    if ((FT <= 2 ? narrow_keys_stay(b.n_blk, longest) : b.n_blk > GEN_SMALL / 2) && lds <= GEN_RES_LDS) attn_gen_go<T, FT, 8, true>(m, b, X, table, wqp, wq, bad, lds, s);
     else if (b.n_blk >= GEN_SMALL / 2) attn_gen_go<T, FT, 8, false>(m, b, X, table, wqp, wq, bad, 0, s);
     else attn_gen_go<T, FT, 4, false>(m, b, X, table, wqp, wq, bad, 0, s);
 }
@@ -799,10 +877,10 @@ hipError_t launch_attn_generic(const Model &m, const Batch &b, void *X, const fl
 // What bounds it: a block's chain of round trips (descriptors, rows, weights from
 // the L2s), so several blocks share a compute unit: a layer overwrites its input
 // once every wave has read it, and a block is four waves and 32 candidates.
-// Measured (160 -> 128 -> 64 -> 1, fp32): 10^5 candidates 61 us, where a thread per
-// feature and 16 candidates on the vector ALU took 210 (78 with 64 candidates, eight
-// waves and two buffers a block); 1,000 candidates 7 against 30; bf16, 160,000
-// candidates 47 against 301.
+// Measured (160 -> 128 -> 64 -> 1, fp32): 10^5 candidates 59 us, where a thread per
+// feature and 16 candidates on the vector ALU took 210 (81 with 64 candidates, eight
+// waves a block; 61 with the pieces cut value by value); 1,000 candidates 7 against 30; bf16, 160,000
+// candidates 44 against 301.
 // ---------------------------------------------------------------------------
 constexpr int MLP_TS = 16;              // candidates of a column tile
 
@@ -897,18 +975,14 @@ __device__ __forceinline__ void mlp_rows(const bf16x8 *__restrict__ wp, int ksn,
     }
 }
 
+// act: the block's LDS (mlp_gen_lds)
 template <typename T, int NC, int WV, bool SPLIT>
-__global__ __launch_bounds__(64 * WV, NC == 1 ? 2 : sizeof(T) == 4 ? 3 : 4) void k_mlp_gen(Model m, Batch b, const T *__restrict__ X, GenMlp gm, const float *__restrict__ bias1)
+__device__ __forceinline__ void mlp_gen_block(const Model &m, const ReqDesc &rd, int row0, const T *X, const GenMlp &gm,
+                                              const float *__restrict__ bias1, char *act)
 {
-    extern __shared__ __align__(16) char act[];
     constexpr int P = stored<T>::P;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, col = lane & 15, g = lane >> 4;
-    const int row0 = blockIdx.x * (16 * NC);
-    const int r = b.blk_req[row0 / ROW_BLOCK];
-    if (r < 0) return;
-    const ReqDesc rd = b.reqs[r];
     const int local0 = row0 - rd.row_base, nrows = min(rd.n_cand - local0, 16 * NC);
-    if (nrows <= 0) return;
     const MlpGenericWeights &w = gm.w;
     const bool in_place = gm.off1 == 0;
     // the ids of the candidates whose logits this lane stores (the first wave's, at the end): asked for now
@@ -1008,17 +1082,12 @@ __global__ __launch_bounds__(64 * WV, NC == 1 ? 2 : sizeof(T) == 4 ? 3 : 4) void
 #pragma unroll
                         for (int j = 0; j < 4; ++j) v[j] = fmaxf(v[j], 0.f);
                         if constexpr (SPLIT) {
-                            float rest[4] = {v[0], v[1], v[2], v[3]};
+                            uint32_t lo[3], hi[3];
+                            split2<3>(v[0], v[1], lo);
+                            split2<3>(v[2], v[3], hi);
 #pragma unroll
-                            for (int q = 0; q < 3; ++q) {
-                                bf16x4 p;
-#pragma unroll
-                                for (int j = 0; j < 4; ++j) {
-                                    p[j] = (__bf16)rest[j];
-                                    rest[j] -= (float)p[j];
-                                }
-                                *(bf16x4 *)(out + (((size_t)(ks * 3 + q) * NC + n) * 64 + dst) * 16 + half * 8) = p;
-                            }
+                            for (int q = 0; q < 3; ++q)
+                                *(uint2 *)(out + (((size_t)(ks * 3 + q) * NC + n) * 64 + dst) * 16 + half * 8) = make_uint2(lo[q], hi[q]);
                         } else
                             ((float4 *)out)[(size_t)(ks * NC + n) * 128 + half * 64 + dst] = make_float4(v[0], v[1], v[2], v[3]);
                     }
@@ -1074,6 +1143,44 @@ __global__ __launch_bounds__(64 * WV, NC == 1 ? 2 : sizeof(T) == 4 ? 3 : 4) void
                                   (float *)act + (size_t)mlp_plain_widest(m) * MLP_TS, rd, local0 + n * MLP_TS);
 }
 
+template <typename T, int NC, int WV, bool SPLIT>
+__global__ __launch_bounds__(64 * WV, NC == 1 ? 2 : sizeof(T) == 4 ? 3 : 4) void k_mlp_gen(Model m, Batch b, const T *__restrict__ X, GenMlp gm, const float *__restrict__ bias1)
+{
+    extern __shared__ __align__(16) char act[];
+    const int row0 = blockIdx.x * (16 * NC);
+    const int r = b.blk_req[row0 / ROW_BLOCK];
+    if (r < 0) return;
+    const ReqDesc rd = b.reqs[r];
+    if (row0 - rd.row_base >= rd.n_cand) return;
+    mlp_gen_block<T, NC, WV, SPLIT>(m, rd, row0, X, gm, bias1, act);
+}
+
+// ---------------------------------------------------------------------------
+// Both for few candidates: a block of eight waves takes one column tile of 16 from its table rows to its logits.  A small call
+// is its launches and their starts; here the head follows in the block that formed the features.  The waves split the keys
+// for the one that owns the tile, meet, and share out the head's row tiles; the features go through the workspace all the
+// same (aif_peek_features shows them), a trip to the L2 and back.  The arithmetic is that of the two kernels: the same bits.
+// (One fp32 request of 1,000 over 50 keys: 13.2 us where the two took 10.4 and 7.0; W_q's fragments asked for ahead of the row
+// spill at two blocks a unit: 14.5.)
+// ---------------------------------------------------------------------------
+constexpr int GEN_TILE_WAVES = 8;
+template <typename T, int FT, bool WQ>
+__global__ __launch_bounds__(64 * GEN_TILE_WAVES, FT <= 2 ? 4 : 2) void k_gen_tile(Model m, Batch b, T *X, const T *__restrict__ table, const bf16x8 *__restrict__ wqp,
+                                                                                  const float *__restrict__ wq, int32_t *__restrict__ bad, GenMlp gm,
+                                                                                  const float *__restrict__ bias1)
+{
+    extern __shared__ __align__(16) char dyn[];                 // the keys, then the activations
+    // the first tile of every ROW_BLOCK, then the second ..: tiles past a request's end come late, behind those with work
+    const int blk = (int)blockIdx.x % b.n_blk, row0 = blk * ROW_BLOCK + (int)blockIdx.x / b.n_blk * 16;
+    const int r = b.blk_req[blk];
+    if (r < 0) return;
+    const ReqDesc rd = b.reqs[r];
+    if (row0 - rd.row_base >= rd.n_cand) return;
+    attn_gen_block<T, FT, GEN_TILE_WAVES, WQ, true, 1>(m, rd, row0, X, table, wqp, wq, bad, (bf16x8 *)dyn);
+    __syncthreads();                                            // the features are in memory, the keys have been read
+    mlp_gen_block<T, 1, GEN_TILE_WAVES, true>(m, rd, row0, X, gm, bias1, dyn);
+}
+
 // Bytes of LDS a block of k_mlp_gen takes: one activation buffer where every hidden layer is done in one go (its results
 // wait in registers until all waves have read its input), else two in turn; and at least what the plain route needs.
 static size_t mlp_gen_lds(const Model &m, int nc, int waves, bool split, int32_t *off1)
@@ -1121,6 +1228,68 @@ hipError_t launch_mlp_generic(const Model &m, const Batch &b, const void *X, con
 {
     if (b.n_blk == 0) return hipSuccess;
     return m.dtype == 0 ? mlp_gen_launch<float>(m, b, X, w, bias1, s) : mlp_gen_launch<uint16_t>(m, b, X, w, bias1, s);
+}
+
+// k_gen_tile: batches whose keys, and the head's activations, fit a compute unit's LDS, of one round of blocks.  Whole calls, us, two
+// launches | one, by candidates (a block to 16; two blocks a unit where LDS and registers allow):
+//             160-128-64 fp32, 50 keys | bf16, 50 keys | fp32, 200 keys (one block a unit) | 192-512-256 fp32, 60 keys (one)
+//         60        22.0 | 18.8           21.4 | 17.5      29.3 | 23.1                       34.7 | 30.1
+//      1,000        23.5 | 18.9           20.8 | 18.5
+//      4,000        26.1 | 20.6           23.3 | 19.1      31.8 | 24.2                       37.9 | 32.0
+//      6,000                                               34.2 | 42.0                       50.3 | 57.2
+//      8,000        30.1 | 24.1           25.7 | 21.4
+//     12,000        32.2 | 34.6           26.7 | 29.7
+template <typename T, int FT>
+static size_t gen_tile_lds(const Model &m, int longest)
+{
+    int32_t off;
+    return std::max(gen_keys_lds<T, FT>(m, longest), mlp_gen_lds(m, 1, GEN_TILE_WAVES, true, &off));
+}
+template <class F> static void gen_head_tiles(const Model &m, F &&f)       // f(storage type, tiles of 16 features of a head)
+{
+    auto type = [&](auto t) {
+        switch (attn_gen_tiles(m.d_head)) {
+        case 1: f(t, std::integral_constant<int, 1>{}); break;
+        case 2: f(t, std::integral_constant<int, 2>{}); break;
+        case 4: f(t, std::integral_constant<int, 4>{}); break;
+        default: f(t, std::integral_constant<int, 8>{}); break;
+        }
+    };
+    if (m.dtype == 0) type(float{});
+    else type(uint16_t{});
+}
+
+bool gen_tile_serves(const Model &m, const Batch &b, int longest)
+{
+    if (m.d_head > GEN_MAX_HEAD || b.n_blk == 0) return false;
+    size_t lds = 0;
+    gen_head_tiles(m, [&](auto t, auto ft) { lds = gen_tile_lds<decltype(t), decltype(ft)::value>(m, longest); });
+    const int blocks_per_cu = attn_gen_tiles(m.d_head) <= 2 && lds <= 80 * 1024 ? 2 : 1;
+    return lds <= 160 * 1024 && 2 * b.n_tiles <= blocks_per_cu * GEN_SMALL;
+}
+
+hipError_t launch_gen_tile(const Model &m, const Batch &b, void *X, const float *wq, const void *wq_pieces, const void *table, int32_t *bad,
+                           int longest, const MlpGenericWeights &w, const float *bias1, hipStream_t s)
+{
+    if (b.n_blk == 0) return hipSuccess;
+    if (!gen_tile_serves(m, b, longest)) return hipErrorInvalidValue;
+    hipError_t e = hipSuccess;
+    gen_head_tiles(m, [&](auto t, auto ft) {
+        using T = decltype(t);
+        constexpr int FT = decltype(ft)::value;
+        GenMlp gm{w, 0};
+        (void)mlp_gen_lds(m, 1, GEN_TILE_WAVES, true, &gm.off1);
+        const size_t lds = gen_tile_lds<T, FT>(m, longest);
+        auto go = [&](auto kern, const void *wp, const float *wf) {
+            (void)hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+            hipLaunchKernelGGL(kern, dim3(b.n_blk * (ROW_BLOCK / 16)), dim3(64 * GEN_TILE_WAVES), lds, s, m, b, (T *)X, (const T *)table,
+                               (const bf16x8 *)wp, wf, bad, gm, bias1);
+            e = hipGetLastError();
+        };
+        if (wq) go(k_gen_tile<T, FT, true>, wq_pieces, wq);
+        else go(k_gen_tile<T, FT, false>, nullptr, nullptr);
+    });
+    return e;
 }
 
 // ---------------------------------------------------------------------------

@@ -20,7 +20,7 @@ struct MfmaPlan {
     char *hbuf[2] = {};                // layered MLP: hidden activations between launches, ping-pong (owned workspace)
     char *w0_user = nullptr;           // per user slot: layer 1's fragments with the Hadamard cross block folded in (owned workspace; Model::cross_in_mlp == 2)
     size_t w0_stride = 0;              // bytes per slot
-    bool tile = true;                  // testing (AIF_MLP_TILE=0): k_mlp_tile is left out
+    bool tile = true;                  // testing (AIF_MLP_TILE=0): the kernels of few candidates are left out, k_gen_tile too
 };
 constexpr int MLP_VARIANT_LAYERS = 100;   // mlp_variant of the one-launch-per-layer path (k_mlp_layers.hip)
 

@@ -10,6 +10,8 @@ hipError_t mfma_plan(const Model &m, int max_seq_len, int max_users, size_t x_ro
 {
     plan.attn = false;
     plan.mlp = false;
+    const char *tile = getenv("AIF_MLP_TILE");      // testing: the kernels of few candidates must give the bits of the others
+    plan.tile = !(tile && tile[0] == '0');
     const char *force = getenv("AIF_FORCE_GENERIC");
     if (force && force[0] == '1') return hipSuccess;
 
@@ -31,8 +33,6 @@ hipError_t mfma_plan(const Model &m, int max_seq_len, int max_users, size_t x_ro
 
     plan.mlp_variant = mlp_mfma_variant(m);
     {
-        const char *tile = getenv("AIF_MLP_TILE");     // testing: both forms of the head must give the same bits
-        plan.tile = !(tile && tile[0] == '0');
         const char *lay = getenv("AIF_MLP_LAYERED");    // testing and measurement: one launch per layer even where a fused chain serves the shape
         if (lay && lay[0] == '1') plan.mlp_variant = -1;
     }
