@@ -35,6 +35,7 @@ struct aif_lsh_ctx {
     void *parts = nullptr;                                  // partial tier counts of a batch whose histories are cut into parts
     void *din_pieces = nullptr;                             // the requests' LSH-DIN tables as bf16 matrix operands (or null: LSH-DIN on the vector ALU)
     size_t hist_stride = 0;
+    bool separate = false;                                  // testing (AIF_LSH_SEPARATE=1): a small call's launches kept apart
     char *h_stage = nullptr, *h_stage_dev = nullptr;        // pinned ring of descriptor tables, its device mapping (or null)
     void *d_stage = nullptr;
     size_t slot_bytes = 0;
@@ -125,7 +126,7 @@ aif_status linit(const aif_lsh_config *cfg, const uint8_t *table, aif_lsh_ctx *c
     c->max_seq_len = cfg->max_seq_len;
     c->max_candidates = cfg->max_candidates;
     c->max_users = cfg->max_users;
-    c->max_chunks = std::min(LSH_MAX_CHUNKS, (cfg->max_seq_len + LSH_TCHUNK - 1) / LSH_TCHUNK);   // a shorter history never has more chunks than a longer one's cap
+    c->max_chunks = lsh_most_chunks(cfg->max_seq_len);
     LSH_TRY(nullptr, hipGetDevice(&c->device));
     const size_t tab = (size_t)lsh_rows(m.d_bits) * m.d_out * 4;
     c->part_stride = (c->max_chunks > 0 ? c->max_chunks : 1) * lsh_user_split(m.d_bits);
@@ -143,6 +144,10 @@ aif_status linit(const aif_lsh_config *cfg, const uint8_t *table, aif_lsh_ctx *c
         const char *valu = getenv("AIF_LSH_DIN_VALU");          // testing and measurement: LSH-DIN on the vector ALU whatever the shape
         if (lsh_din_on_mfma(m) && !(valu && valu[0] == '1'))
             LSH_TRY(nullptr, hipMalloc(&c->din_pieces, lsh_din_pieces_stride(m) * 16 * (size_t)c->max_users));
+    }
+    {
+        const char *sep = getenv("AIF_LSH_SEPARATE");
+        c->separate = sep && sep[0] == '1';
     }
     LSH_TRY(nullptr, hipMalloc(&c->bad, 16));
     LSH_TRY(nullptr, hipMemset(c->bad, 0, 16));
@@ -239,6 +244,33 @@ aif_status aif_lsh_batch(aif_lsh_ctx *c, const aif_lsh_request *reqs, int32_t n_
     b.n_req = n_req;
     b.n_blk = slots / LSH_BLOCK;
     const size_t bytes = (size_t)n_req * sizeof(LshReqDesc) + (size_t)b.n_blk * sizeof(int32_t);
+
+    // A small call (one that runs in line and is not timed stage by stage) in three launches; the descriptors of few requests
+    // travel in the first one's arguments, and the device never reads the slot's pinned memory: no event guards it.
+    const bool timed = c->prof_on && c->prof_calls < c->prof_max;
+    if (c->hist && c->din_pieces && !c->separate && !timed && !(c->side && pairs >= LSH_SIDE_PAIRS)) {
+        LshFew few;
+        const bool in_args = n_req <= LSH_FEW;
+        if (in_args) {
+            std::copy(hd, hd + n_req, few.rd);
+            few.reqs = (LshReqDesc *)d;
+            few.blk_req = (int32_t *)(d + (size_t)n_req * sizeof(LshReqDesc));
+            few.n_req = n_req;
+            few.n_blk = b.n_blk;
+        } else
+            LSH_TRY(c, staging_upload(c->h_stage, c->h_stage_dev, (size_t)slot * c->slot_bytes, d, bytes, s));
+        const LshPiecesArgs p{(const float *)c->part, (float *)c->A, c->din_pieces, lsh_din_pieces_stride(m), c->part_stride, lsh_pieces_blocks(m)};
+        LSH_TRY(c, launch_lsh_stage(m, b, in_args ? &few : nullptr, max_chunks, c->part_stride, (float *)c->part, c->hist, c->hist_stride, longest, s));
+        if (b.n_blk > 0) {
+            const int n_parts = lsh_small_parts(b.n_blk, longest);
+            LSH_TRY(c, launch_lsh_count(m, b, c->table, c->hist, c->hist_stride, c->parts, n_parts, p, s));
+            LSH_TRY(c, launch_lsh_result(m, b, c->table, (const float *)c->A, c->din_pieces, (int32_t *)c->bad, lsh_simtier_shift(m), c->parts,
+                                         n_parts, s));
+        }
+        if (!in_args) LSH_TRY(c, hipEventRecord(c->ev[slot], s));
+        c->ev_live[slot] = !in_args;
+        return AIF_OK;
+    }
     LSH_TRY(c, staging_upload(c->h_stage, c->h_stage_dev, (size_t)slot * c->slot_bytes, d, bytes, s));
 
     hipEvent_t *pe = nullptr;

@@ -8,17 +8,28 @@ namespace aif {
 constexpr int LSH_BLOCK = 256;          // candidates per scheduling block
 constexpr int LSH_TCHUNK = 1024;        // history items whose user-side sums one block forms (more for a long history)
 constexpr int LSH_MAX_CHUNKS = 64;      // chunks of one history at most
-// Chunk length of a history of L items, a multiple of 64: LSH_TCHUNK, or an even share of a history that would have more
-// than LSH_MAX_CHUNKS chunks -- every chunk's partial sums ((d' + 2) d floats) are written to memory and read back.  A
-// function of the request's own history only, like everything that decides the order of its sums.
+// Chunk length of a history of L items, a multiple of 64: a tenth of it, but no shorter than LSH_TCHUNK_MIN and no longer than
+// LSH_TCHUNK, and an even share of a history that would have more than LSH_MAX_CHUNKS chunks -- every chunk's partial sums
+// ((d' + 2) d floats) are written to memory and read back, and a block walks its chunk in a chain of loads.  A function of the
+// request's own history only, like everything that decides the order of its sums.
+constexpr int LSH_TCHUNK_MIN = 128, LSH_FEW_CHUNKS = 10;
 __host__ __device__ inline int lsh_chunk_len(int L)
 {
-    return L <= LSH_TCHUNK * LSH_MAX_CHUNKS ? LSH_TCHUNK : ((L - 1) / LSH_MAX_CHUNKS + 64) / 64 * 64;
+    if (L > LSH_TCHUNK * LSH_MAX_CHUNKS) return ((L - 1) / LSH_MAX_CHUNKS + 64) / 64 * 64;
+    const int share = ((L + LSH_FEW_CHUNKS - 1) / LSH_FEW_CHUNKS + 63) / 64 * 64;
+    return share < LSH_TCHUNK_MIN ? LSH_TCHUNK_MIN : share > LSH_TCHUNK ? LSH_TCHUNK : share;
 }
 __host__ __device__ inline int lsh_chunks(int L)
 {
     const int len = lsh_chunk_len(L);
     return (L + len - 1) / len;
+}
+// the most chunks a history of at most L items has
+inline int lsh_most_chunks(int L)
+{
+    const int fine = (L + LSH_TCHUNK_MIN - 1) / LSH_TCHUNK_MIN, coarse = (L + LSH_TCHUNK - 1) / LSH_TCHUNK;
+    const int few = fine < LSH_FEW_CHUNKS ? fine : LSH_FEW_CHUNKS, most = few > coarse ? few : coarse;
+    return most < LSH_MAX_CHUNKS ? most : LSH_MAX_CHUNKS;
 }
 constexpr int LSH_MAX_TIERS = 8;
 // How many ways a block of k_lsh_user_sums shares out its chunk's items: its four waves take a row tile of 32 bits each,
@@ -46,6 +57,27 @@ __device__ __forceinline__ float lsh_sum_parts(const float *p, size_t stride, in
     }
     for (; c < n; ++c) acc += p[(size_t)c * stride];
     return acc;
+}
+// two such sums at a time: sixteen loads in flight
+__device__ __forceinline__ void lsh_sum_parts2(const float *p, const float *q, size_t stride, int n, float &a, float &b)
+{
+    a = b = 0.f;
+    int c = 0;
+    for (; c + 8 <= n; c += 8) {
+        float v[8], w[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = p[(size_t)(c + i) * stride];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) w[i] = q[(size_t)(c + i) * stride];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) a += v[i];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) b += w[i];
+    }
+    for (; c < n; ++c) {
+        a += p[(size_t)c * stride];
+        b += q[(size_t)c * stride];
+    }
 }
 // the same for a sum of 64 bits: each partial is p[0] + p[d]
 __device__ __forceinline__ double lsh_sum_totals(const float *p, size_t stride, int d, int n)
@@ -85,6 +117,16 @@ struct LshBatch {
     int32_t n_blk;
 };
 
+// Descriptors of a batch of at most LSH_FEW requests in a kernel's arguments: its blocks read them there and the first of them write
+// the batch's device tables, which the later kernels read.
+constexpr int LSH_FEW = 16;
+struct LshFew {
+    LshReqDesc rd[LSH_FEW];
+    LshReqDesc *reqs;
+    int32_t *blk_req;
+    int32_t n_req, n_blk;
+};
+
 struct LshModel {
     int64_t n_items;
     int32_t d_bits, d_out, n_tiers;
@@ -122,5 +164,25 @@ size_t lsh_hist_stride(const LshModel &m, int max_seq_len);
 size_t lsh_simtier_parts_bytes();
 hipError_t launch_lsh_simtier_mfma(const LshModel &m, const LshBatch &b, const uint8_t *sig_table, void *hist, size_t req_stride,
                                    int longest, void *parts, hipStream_t s);
+
+// A small call in three launches instead of seven (SimTier and LSH-DIN both on the matrix cores): what the user's side needs
+// (sums, the history expanded, the tables of a batch of few requests); SimTier beside D's pieces; LSH-DIN beside SimTier's finish.
+// few: null, or the descriptors (nothing has been uploaded then).  n_parts: lsh_small_parts() for both launches that take it.
+struct LshPiecesArgs {
+    const float *part;
+    float *A;
+    void *pieces;
+    size_t stride;              // lsh_din_pieces_stride()
+    int32_t part_stride, per_req;       // per_req: lsh_pieces_blocks()
+};
+inline int lsh_pieces_blocks(const LshModel &m) { return (m.d_bits / 16 + 1) * (m.d_out / 32); }
+int lsh_small_parts(int n_blk, int longest);
+int lsh_simtier_shift(const LshModel &m);
+hipError_t launch_lsh_stage(const LshModel &m, const LshBatch &b, const LshFew *few, int grid_chunks, int part_stride, float *part, void *hist,
+                            size_t req_stride, int longest, hipStream_t s);
+hipError_t launch_lsh_count(const LshModel &m, const LshBatch &b, const uint8_t *sig_table, const void *hist, size_t req_stride, void *parts,
+                            int n_parts, const LshPiecesArgs &p, hipStream_t s);
+hipError_t launch_lsh_result(const LshModel &m, const LshBatch &b, const uint8_t *sig_table, const float *A, const void *pieces, int32_t *bad,
+                             int sh, const void *parts, int n_parts, hipStream_t s);
 
 }  // namespace aif

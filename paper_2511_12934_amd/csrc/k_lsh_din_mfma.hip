@@ -14,7 +14,7 @@
 // What bounds it: the bytes.  64 x 10^4 candidates, d' = d = 64: 71 us for 164 MB of results and 82 MB of signature lines
 // (8 of 128 bytes used); 8 x 10^4, d' = d = 128: 36 us, where twice the columns, staged through LDS, took 64 (79 above).
 // Streaming stores: 75.
-#include "aif_lsh_dev.h"
+#include "k_lsh_blocks.h"
 
 #include <type_traits>
 
@@ -23,85 +23,29 @@ namespace aif {
 typedef __bf16 din_bf16x8 __attribute__((ext_vector_type(8)));
 typedef float din_f32x16 __attribute__((ext_vector_type(16)));
 
-__device__ __forceinline__ uint32_t bf16_rne_bits(float x)
-{
-    const uint32_t u = __float_as_uint(x);
-    return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;          // finite inputs (sums of embeddings)
-}
-
-// Block = (k-step, feature tile): 16 bits x 32 features, a thread per sum; the blocks past the last k-step add up total and
-// lowest, eight threads each per feature.
 __global__ __launch_bounds__(512) void k_lsh_din_pieces(LshModel m, LshBatch b, int part_stride, const float *__restrict__ part,
                                                         float *__restrict__ A, uint4 *__restrict__ out, size_t req_stride)
 {
-    __shared__ float D[16][33];
-    __shared__ double S[16][33];
-    const int ft_n = m.d_out / 32, ks_n = m.d_bits / 16, ft = blockIdx.x % ft_n, ks = blockIdx.x / ft_n, r = blockIdx.y;
-    const int k = threadIdx.x >> 5, j = threadIdx.x & 31, shares = lsh_chunks(b.reqs[r].seq_len) * lsh_user_split(m.d_bits);
-    const size_t n = (size_t)lsh_rows(m.d_bits) * m.d_out;
-    const float *p = part + (size_t)r * part_stride * n + ft * 32 + j;
-    if (ks == ks_n) {
-        float *a = A + (size_t)r * n + (size_t)m.d_bits * m.d_out;
-        const int row = k & 1 ? LSH_LOWEST : LSH_TOTAL, from = k >> 1;
-        S[k][j] = lsh_sum_totals(p + (size_t)(m.d_bits + row) * m.d_out + from * n, 8 * n, m.d_out, (shares - from + 7) / 8);
-        __syncthreads();
-        if (k < 2) {
-            double t = 0.0;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) t += S[2 * i + k][j];
-            t *= k == 0 ? 0.5 : 1.0 / m.d_bits;
-            a += row * m.d_out + ft * 32 + j;
-            a[0] = (float)t;
-            a[m.d_out] = (float)(t - (double)(float)t);
-        } else if (k == 2 && ft == 0 && j < 8)
-            a[LSH_MAJORITY * m.d_out + j] = shares > 0 ? p[(size_t)(m.d_bits + LSH_MAJORITY) * m.d_out] : 0.f;
-        return;
-    }
-    D[k][j] = lsh_sum_parts(p + (size_t)(16 * ks + k) * m.d_out, n, shares);
-    __syncthreads();
-    if (threadIdx.x >= 64) return;
-    const int lane = threadIdx.x, c = lane & 31, h = lane >> 5;    // lane = (feature of the tile, which 8 of the k-step's bits)
-    uint32_t piece[3][4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        uint32_t half[3][2];
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            const float w = D[8 * h + 2 * u + s][c];
-            const uint32_t hi = bf16_rne_bits(w);
-            const float r1 = w - __uint_as_float(hi << 16);
-            const uint32_t mid = bf16_rne_bits(r1);
-            const float r2 = r1 - __uint_as_float(mid << 16);
-            half[0][s] = bf16_rne_bits(r2);                 // accumulated first
-            half[1][s] = mid;
-            half[2][s] = hi;
-        }
-#pragma unroll
-        for (int q = 0; q < 3; ++q) piece[q][u] = half[q][0] | (half[q][1] << 16);
-    }
-    uint4 *o = out + (size_t)r * req_stride;
-#pragma unroll
-    for (int q = 0; q < 3; ++q)
-        o[((size_t)(q * ks_n + ks) * ft_n + ft) * 64 + lane] = make_uint4(piece[q][0], piece[q][1], piece[q][2], piece[q][3]);
+    lsh_pieces_block<512>(m, b.reqs[blockIdx.y], blockIdx.y, blockIdx.x, part_stride, part, A, out, req_stride);
 }
 
 hipError_t launch_lsh_din_pieces(const LshModel &m, const LshBatch &b, int part_stride, const float *part, float *A, void *pieces, hipStream_t s)
 {
     if (b.n_req == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_lsh_din_pieces, dim3((m.d_bits / 16 + 1) * (m.d_out / 32), b.n_req), dim3(512), 0, s, m, b, part_stride, part, A,
+    hipLaunchKernelGGL(k_lsh_din_pieces, dim3(lsh_pieces_blocks(m), b.n_req), dim3(512), 0, s, m, b, part_stride, part, A,
                        (uint4 *)pieces, lsh_din_pieces_stride(m));
     return hipGetLastError();
 }
 
-// FT: feature tiles (d = 32 FT)
-template <int FT>
-__global__ __launch_bounds__(256, 2) void k_lsh_din_mfma(LshModel m, LshBatch b, const uint8_t *__restrict__ sig_table,
-                                                      const float *__restrict__ A, const uint4 *__restrict__ pieces, size_t req_stride,
-                                                      int32_t *__restrict__ bad)
+// RT: row tiles of 32 candidates a wave takes; FT: feature tiles, from ft0 on (ALL: all of them, d = 32 FT); the block's first candidate is
+// number `first` of its LSH_BLOCK.
+template <int RT, int FT, bool ALL>
+__device__ __forceinline__ void lsh_din_block(const LshModel &m, const LshBatch &b, const uint8_t *__restrict__ sig_table, const float *__restrict__ A,
+                                              const uint4 *__restrict__ pieces, size_t req_stride, int32_t *__restrict__ bad, int blk, int first, int ft0)
 {
-    constexpr int RT = 2;
-    int blk = blockIdx.x;                                       // a contiguous run of blocks per XCD: a user's pieces in one L2
-    {
+    constexpr int AHEAD = FT == 1 ? 8 : 3;                      // fragments of every tile in flight
+    const int n_ft = ALL ? FT : m.d_out / 32;
+    {                                                           // a contiguous run of blocks per XCD: a user's pieces in one L2
         const int per_xcd = b.n_blk >> 3;
         if (blk < 8 * per_xcd) blk = (blk & 7) * per_xcd + (blk >> 3);
     }
@@ -109,7 +53,7 @@ __global__ __launch_bounds__(256, 2) void k_lsh_din_mfma(LshModel m, LshBatch b,
     if (r < 0) return;
     const LshReqDesc rd = b.reqs[r];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, col = lane & 31, h = lane >> 5;
-    const int local0 = blk * LSH_BLOCK - rd.cand_base + wave * 32 * RT;
+    const int local0 = blk * LSH_BLOCK + first - rd.cand_base + wave * 32 * RT;
     const int nrows = min(32 * RT, rd.n_cand - local0);
     if (nrows <= 0) return;
     const int nw = m.d_bits / 32, ks_n = m.d_bits / 16;
@@ -118,15 +62,14 @@ __global__ __launch_bounds__(256, 2) void k_lsh_din_mfma(LshModel m, LshBatch b,
     // whether it exists, whether its id is valid
     const uint4 *src = pieces + (size_t)r * req_stride + lane;
     const int steps = 3 * ks_n;
-    uint4 w[3][FT];
+    uint4 w[AHEAD][FT];
     auto fetch = [&](int i, uint4 (&f)[FT]) __attribute__((always_inline)) {
         i = i < steps ? i : steps - 1;
 #pragma unroll
-        for (int ft = 0; ft < FT; ++ft) f[ft] = src[(size_t)(i * FT + ft) * 64];
+        for (int ft = 0; ft < FT; ++ft) f[ft] = src[(size_t)(i * n_ft + ft0 + ft) * 64];
     };
-    fetch(0, w[0]);
-    fetch(1, w[1]);
-    fetch(2, w[2]);
+#pragma unroll
+    for (int q = 0; q < AHEAD; ++q) fetch(q, w[q]);
     const float *last = A + ((size_t)r * lsh_rows(m.d_bits) + m.d_bits) * m.d_out;
     // the majority word, a part per lane (d >= 32; those past the signature's are not looked at)
     const int maj_lanes = (int)__float_as_uint(last[LSH_MAJORITY * m.d_out + (lane & 7)]);
@@ -135,7 +78,7 @@ __global__ __launch_bounds__(256, 2) void k_lsh_din_mfma(LshModel m, LshBatch b,
     auto load_base = [&](int row, float (&hi)[FT], float (&lo)[FT]) __attribute__((always_inline)) {
 #pragma unroll
         for (int ft = 0; ft < FT; ++ft) {
-            const float *p = last + (size_t)row * m.d_out + col + ft * 32;
+            const float *p = last + (size_t)row * m.d_out + col + (ft0 + ft) * 32;
             hi[ft] = p[0];
             lo[ft] = p[m.d_out];
         }
@@ -209,11 +152,11 @@ __global__ __launch_bounds__(256, 2) void k_lsh_din_mfma(LshModel m, LshBatch b,
         ks = ks + 1 == ks_n ? 0 : ks + 1;
     };
     auto all = [&](auto odd_c) __attribute__((always_inline)) {
-        for (int i = 0; i < steps; i += 3) {
+        for (int i = 0; i < steps; i += AHEAD) {
 #pragma unroll
-            for (int q = 0; q < 3; ++q) {
+            for (int q = 0; q < AHEAD; ++q) {
                 step(odd_c, i + q, w[q]);
-                fetch(i + q + 3, w[q]);
+                fetch(i + q + AHEAD, w[q]);
             }
         }
     };
@@ -231,7 +174,7 @@ __global__ __launch_bounds__(256, 2) void k_lsh_din_mfma(LshModel m, LshBatch b,
                 const int c = 8 * (v / 4) + 4 * h + (v % 4);
                 if (!((live_mask[rt] >> c) & 1u)) continue;
                 const bool ok = (ok_mask[rt] >> c) & 1u, low = ODD && ((low_mask[rt] >> c) & 1u);
-                float *o = rd.din_out + (size_t)(local0 + rt * 32 + c) * m.d_out + col;
+                float *o = rd.din_out + (size_t)(local0 + rt * 32 + c) * m.d_out + ft0 * 32 + col;
 #pragma unroll
                 for (int ft = 0; ft < FT; ++ft)
                     o[ft * 32] = ok ? (low ? low_hi[ft] : hi[ft]) + fmaf(acc[rt][ft][v], inv, low ? low_lo[ft] : lo[ft]) : nanv;
@@ -248,12 +191,46 @@ __global__ __launch_bounds__(256, 2) void k_lsh_din_mfma(LshModel m, LshBatch b,
         if constexpr (EARLY) finish(std::false_type{});
     }
     if constexpr (!EARLY) finish(std::true_type{});
-    if (lane == 0) {
+    if (lane == 0 && ft0 == 0) {
         int n_bad = 0;
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) n_bad += __builtin_popcount(live_mask[rt] & ~ok_mask[rt]);
         if (n_bad) atomicAdd(bad, n_bad);
     }
+}
+
+// FT: feature tiles (d = 32 FT)
+template <int FT>
+__global__ __launch_bounds__(256, 2) void k_lsh_din_mfma(LshModel m, LshBatch b, const uint8_t *__restrict__ sig_table, const float *__restrict__ A,
+                                                      const uint4 *__restrict__ pieces, size_t req_stride, int32_t *__restrict__ bad)
+{
+    lsh_din_block<2, FT, true>(m, b, sig_table, A, pieces, req_stride, bad, blockIdx.x, 0, 0);
+}
+
+// The same for few candidates, a wave to one row tile and one feature tile, beside the blocks that add up the histories' parts of Eq. 9.
+__global__ __launch_bounds__(256, 4) void k_lsh_result(LshModel m, LshBatch b, const uint8_t *__restrict__ sig_table, const float *__restrict__ A,
+                                                    const uint4 *__restrict__ pieces, size_t req_stride, int32_t *__restrict__ bad, int sh,
+                                                    const int32_t *__restrict__ parts, int n_parts)
+{
+    int idx = blockIdx.x;
+    const int n_din = 2 * b.n_blk * (m.d_out / 32);
+    if (idx < n_din) {
+        const int half = idx & 1, blk = (idx >> 1) % b.n_blk, ft = (idx >> 1) / b.n_blk;
+        lsh_din_block<1, 1, false>(m, b, sig_table, A, pieces, req_stride, bad, blk, half * 128, ft);
+        return;
+    }
+    lsh_finish_block(m, b, sh, parts, n_parts, idx - n_din);
+}
+
+hipError_t launch_lsh_result(const LshModel &m, const LshBatch &b, const uint8_t *sig_table, const float *A, const void *pieces, int32_t *bad,
+                             int sh, const void *parts, int n_parts, hipStream_t s)
+{
+    if (b.n_blk == 0) return hipSuccess;
+    if (!lsh_din_on_mfma(m) || !pieces) return hipErrorInvalidValue;
+    const dim3 grid(2 * b.n_blk * (m.d_out / 32) + (n_parts > 1 ? b.n_blk : 0));
+    hipLaunchKernelGGL(k_lsh_result, grid, dim3(256), 0, s, m, b, sig_table, A, (const uint4 *)pieces, lsh_din_pieces_stride(m), bad, sh,
+                       (const int32_t *)parts, n_parts);
+    return hipGetLastError();
 }
 
 bool lsh_din_on_mfma(const LshModel &m) { return m.d_out % 32 == 0 && m.d_out <= 128 && m.d_bits <= 256; }

@@ -25,17 +25,17 @@
 // Two corrections at the end: the rows past the history's end are zero vectors, which count as d' / 2 equal bits and
 // are taken off that tier again; a signature equal to the candidate's in every bit gives tier index N, whose one-hot
 // byte is empty -- the last tier's count is the history length less all the others.
-#include "aif_lsh_dev.h"
+#include <algorithm>
+
+#include "k_lsh_blocks.h"
 
 namespace aif {
 
-typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v8i __attribute__((ext_vector_type(8)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 
 constexpr int SMT_PART_BLOCKS = 2048; // a batch of fewer blocks than this has its histories cut into parts, a block each
 constexpr int SMT_MAX_PARTS = 16;
-constexpr int SMT_TILE = 64;         // history items of a row tile: two a row
 constexpr int SMT_GROUP = 4;         // row tiles per pass of the adder network: 32 words per column tile
 // Column tiles of 32 candidates a wave keeps (a row tile's bytes serve them all; what the registers allow): the block's 256
 // candidates are SMT_GROUPS groups of columns, and the SMT_SHARE waves that have a group in common halve the history.
@@ -46,64 +46,10 @@ constexpr int SMT_COLS = 4, SMT_GROUPS = LSH_BLOCK / (32 * SMT_COLS), SMT_SHARE 
 constexpr int smt_planes(int ks) { return ks <= 2 ? 5 : 6; }
 constexpr int smt_flush(int ks) { return ks <= 2 ? 30 : 62; }
 
-// thirty-two signature bits -> thirty-two fp4 values (-1)^bit, bit j in nibble j
-__device__ __forceinline__ v4i fp4_signs(uint32_t bits)
-{
-    v4i r;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        uint32_t x = (bits >> (8 * q)) & 0xFFu;                                             // bit i of the eight to nibble i
-        x = (x | x << 12) & 0x000F000Fu;
-        x = (x | x << 6) & 0x03030303u;
-        x = (x | x << 3) & 0x11111111u;
-        r[q] = (int)(x << 3 | 0x22222222u);                                                 // 1.0 is 0010, the sign bit on top
-    }
-    return r;
-}
-
-// The history of every request as the instruction's row operand: [row tile][k-step of 32 bits][lane] of 16 bytes; lane =
-// (row of the tile, which of the row's two items: item 32 h + row of the tile).  Items past the end are zero vectors.
-template <int KS>
-__global__ __launch_bounds__(256) void k_lsh_expand(LshBatch b, v4i *__restrict__ out, size_t req_stride)
-{
-    const LshReqDesc rd = b.reqs[blockIdx.y];
-    const int nrt = (rd.seq_len + SMT_TILE - 1) / SMT_TILE;
-    const int idx = blockIdx.x * 256 + threadIdx.x;
-    if (idx >= nrt * KS * 64) return;
-    const int lane = idx & 63, s = (idx >> 6) % KS, rt = idx / (64 * KS);
-    const int item = rt * SMT_TILE + lane;
-    v4i v = {0, 0, 0, 0};
-    if (item < rd.seq_len) v = fp4_signs(((const uint32_t *)rd.seq_sigs)[(size_t)item * KS + s]);
-    out[(size_t)blockIdx.y * req_stride + idx] = v;
-}
-
 __device__ __forceinline__ void csa(uint32_t &sum, uint32_t &carry, uint32_t a, uint32_t b, uint32_t c)
 {
     sum = __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);          // a ^ b ^ c
     carry = __builtin_amdgcn_bitop3_b32(a, b, c, 0xE8);        // majority
-}
-
-// The counts of one candidate as they come out of the planes -> Eq. 9's tiers.  Two corrections: the rows past the
-// history's end were zero vectors and counted as d' / 2 equal bits; the last tier is the history less all the others.
-__device__ __forceinline__ void simtier_store(const LshModel &m, const LshReqDesc &rd, int local, int sh, const int32_t (&n)[LSH_MAX_TIERS])
-{
-    const int64_t id = rd.cand_ids[local];
-    int32_t *o = rd.tier_out + (size_t)local * m.n_tiers;
-    if (id < 0 || id >= m.n_items) {
-        for (int t = 0; t < m.n_tiers; ++t) o[t] = -1;
-        return;
-    }
-    const int pad_tier = m.d_bits >> sh, pad = (rd.seq_len + SMT_TILE - 1) / SMT_TILE * SMT_TILE - rd.seq_len;
-    int32_t below = 0;
-#pragma unroll
-    for (int t = 0; t < LSH_MAX_TIERS; ++t) {
-        if (t < m.n_tiers - 1) {
-            const int32_t v = n[t] - (t == pad_tier ? pad : 0);
-            o[t] = v;
-            below += v;
-        }
-    }
-    o[m.n_tiers - 1] = rd.seq_len - below;
 }
 
 // KS: k-steps of 32 bits (d' = 32 KS); a wave's candidates' operands stay in registers, 16 KS of them.  gridDim.y > 1: the
@@ -111,15 +57,14 @@ __device__ __forceinline__ void simtier_store(const LshModel &m, const LshReqDes
 // k_lsh_simtier_finish -- for batches too small to fill the chip otherwise (a handful of users with long histories).
 // Every wave reads its row tiles from L2 itself, two to four tiles in flight.
 template <int KS>
-__global__ __launch_bounds__(256, KS <= 2 ? 3 : 2) void k_lsh_simtier_mfma(LshModel m, LshBatch b, const uint8_t *__restrict__ sig_table,
-                                                             const v4i *__restrict__ hist, size_t req_stride, int sh,
-                                                             int32_t *__restrict__ parts)
+__device__ __forceinline__ void lsh_simtier_block(const LshModel &m, const LshBatch &b, const uint8_t *__restrict__ sig_table,
+                                                  const v4i *__restrict__ hist, size_t req_stride, int sh, int32_t *__restrict__ parts,
+                                                  int blk, int part_no, int n_parts)
 {
     constexpr int SMT_PLANES = smt_planes(KS), SMT_FLUSH = smt_flush(KS);
     static_assert(SMT_FLUSH % 2 == 0 && 32 * SMT_FLUSH + 24 < 32 << SMT_PLANES, "the planes count every word between read-outs");
     __shared__ int32_t cnt[LSH_MAX_TIERS][LSH_BLOCK];
     // as in the vector-ALU kernel: the blocks of one user go to one XCD, whose L2 then holds that user's history
-    int blk = blockIdx.x;
     {
         const int per_xcd = b.n_blk >> 3;
         if (blk < 8 * per_xcd) blk = (blk & 7) * per_xcd + (blk >> 3);
@@ -148,8 +93,8 @@ __global__ __launch_bounds__(256, KS <= 2 ? 3 : 2) void k_lsh_simtier_mfma(LshMo
     __syncthreads();
 
     const int nrt = (rd.seq_len + SMT_TILE - 1) / SMT_TILE;
-    const int per_part = (nrt + (int)gridDim.y - 1) / (int)gridDim.y;          // row tiles of this block ...
-    const int part_begin = min(nrt, (int)blockIdx.y * per_part), part_end = min(nrt, part_begin + per_part);
+    const int per_part = (nrt + n_parts - 1) / n_parts;          // row tiles of this block ...
+    const int part_begin = min(nrt, part_no * per_part), part_end = min(nrt, part_begin + per_part);
     const int per_wave = (part_end - part_begin + SMT_SHARE - 1) / SMT_SHARE;           // ... and of this wave
     const int rt_begin = min(part_end, part_begin + hh * per_wave), rt_end = min(part_end, rt_begin + per_wave);
     const v4i *__restrict__ hrow = hist + (size_t)r * req_stride + lane;
@@ -347,8 +292,8 @@ __global__ __launch_bounds__(256, KS <= 2 ? 3 : 2) void k_lsh_simtier_mfma(LshMo
     __syncthreads();
 
     const int local = first + tid;
-    if (gridDim.y > 1) {            // raw counts; the slot exists whether or not a candidate sits in it
-        int32_t *o = parts + ((size_t)blockIdx.y * b.n_blk * LSH_BLOCK + (size_t)blk * LSH_BLOCK + tid) * LSH_MAX_TIERS;
+    if (n_parts > 1) {              // raw counts; the slot exists whether or not a candidate sits in it
+        int32_t *o = parts + ((size_t)part_no * b.n_blk * LSH_BLOCK + (size_t)blk * LSH_BLOCK + tid) * LSH_MAX_TIERS;
 #pragma unroll
         for (int t = 0; t < LSH_MAX_TIERS; ++t) o[t] = cnt[t][tid];
         return;
@@ -360,23 +305,39 @@ __global__ __launch_bounds__(256, KS <= 2 ? 3 : 2) void k_lsh_simtier_mfma(LshMo
     simtier_store(m, rd, local, sh, n);
 }
 
+template <int KS>
+__global__ __launch_bounds__(256, KS <= 2 ? 3 : 2) void k_lsh_simtier_mfma(LshModel m, LshBatch b, const uint8_t *__restrict__ sig_table,
+                                                                         const v4i *__restrict__ hist, size_t req_stride, int sh,
+                                                                         int32_t *__restrict__ parts)
+{
+    lsh_simtier_block<KS>(m, b, sig_table, hist, req_stride, sh, parts, blockIdx.x, blockIdx.y, gridDim.y);
+}
+
+// The same beside the blocks that cut D into pieces (they come first: the shorter ones).
+template <int KS>
+__global__ __launch_bounds__(256, KS <= 2 ? 3 : 2) void k_lsh_count(LshModel m, LshBatch b, const uint8_t *__restrict__ sig_table, const v4i *__restrict__ hist,
+                                                                  size_t req_stride, int sh, int32_t *__restrict__ parts, int n_parts, LshPiecesArgs p)
+{
+    const int n_pieces = p.per_req * b.n_req;
+    int idx = blockIdx.x;
+    if (idx < n_pieces) {
+        const int r = idx / p.per_req;
+        lsh_pieces_block<256>(m, b.reqs[r], r, idx - r * p.per_req, p.part_stride, p.part, p.A, (uint4 *)p.pieces, p.stride);
+        return;
+    }
+    idx -= n_pieces;
+    lsh_simtier_block<KS>(m, b, sig_table, hist, req_stride, sh, parts, idx % b.n_blk, idx / b.n_blk, n_parts);
+}
+
+template <int KS>
+__global__ __launch_bounds__(256) void k_lsh_expand(LshBatch b, v4i *__restrict__ out, size_t req_stride)
+{
+    lsh_expand_block<KS, 1>(b.reqs[blockIdx.y], blockIdx.y, blockIdx.x, out, req_stride);
+}
+
 __global__ __launch_bounds__(256) void k_lsh_simtier_finish(LshModel m, LshBatch b, int sh, const int32_t *__restrict__ parts, int n_parts)
 {
-    const int blk = blockIdx.x, r = b.blk_req[blk];
-    if (r < 0) return;
-    const LshReqDesc rd = b.reqs[r];
-    const int local = blk * LSH_BLOCK - rd.cand_base + (int)threadIdx.x;
-    if (local >= rd.n_cand) return;
-    int32_t n[LSH_MAX_TIERS];
-#pragma unroll
-    for (int t = 0; t < LSH_MAX_TIERS; ++t) n[t] = 0;
-    for (int p = 0; p < n_parts; ++p) {
-        const int4 *q = (const int4 *)(parts + ((size_t)p * b.n_blk * LSH_BLOCK + (size_t)blk * LSH_BLOCK + threadIdx.x) * LSH_MAX_TIERS);
-        const int4 lo = q[0], hi = q[1];
-        n[0] += lo.x, n[1] += lo.y, n[2] += lo.z, n[3] += lo.w;
-        n[4] += hi.x, n[5] += hi.y, n[6] += hi.z, n[7] += hi.w;
-    }
-    simtier_store(m, rd, local, sh, n);
+    lsh_finish_block(m, b, sh, parts, n_parts, blockIdx.x);
 }
 
 static int simtier_shift(const LshModel &m)                     // 2 d' / N = 2^shift, or -1
@@ -384,6 +345,13 @@ static int simtier_shift(const LshModel &m)                     // 2 d' / N = 2^
     int sh = 0;
     while (sh < 9 && (1 << sh) * m.n_tiers < 2 * m.d_bits) ++sh;
     return (1 << sh) * m.n_tiers == 2 * m.d_bits ? sh : -1;
+}
+
+// Parts a history is cut into: enough blocks to fill the chip a few times over, each with at least two passes of the adder network per wave
+static int simtier_parts(int n_blk, int nrt)
+{
+    const int n = std::min(SMT_PART_BLOCKS / n_blk, nrt / (4 * SMT_GROUP));
+    return std::max(1, std::min(n, SMT_MAX_PARTS));
 }
 
 bool lsh_simtier_on_mfma(const LshModel &m)
@@ -417,10 +385,7 @@ hipError_t launch_lsh_simtier_mfma(const LshModel &m, const LshBatch &b, const u
         default: hipLaunchKernelGGL(k_lsh_expand<4>, grid, dim3(256), 0, s, b, (v4i *)hist, req_stride); break;
         }
     }
-    // parts: enough blocks to fill the chip a few times over, each with at least two passes of the adder network per wave
-    int n_parts = SMT_PART_BLOCKS / b.n_blk;
-    n_parts = n_parts < nrt / (4 * SMT_GROUP) ? n_parts : nrt / (4 * SMT_GROUP);
-    n_parts = n_parts > SMT_MAX_PARTS ? SMT_MAX_PARTS : n_parts < 1 ? 1 : n_parts;
+    const int n_parts = simtier_parts(b.n_blk, nrt);
     const dim3 grid(b.n_blk, n_parts);
     int32_t *pp = (int32_t *)parts;
     switch (ks) {
@@ -431,5 +396,33 @@ hipError_t launch_lsh_simtier_mfma(const LshModel &m, const LshBatch &b, const u
     if (n_parts > 1) hipLaunchKernelGGL(k_lsh_simtier_finish, dim3(b.n_blk), dim3(256), 0, s, m, b, sh, (const int32_t *)pp, n_parts);
     return hipGetLastError();
 }
+
+// A small call's finish costs no launch: parts of one pass a wave, up to two blocks a compute unit (1 x 3,000 candidates x 3,000 items
+// 32.2 -> 29.3 us, 3 x 1,495 x 1,330 of 128 bits 43.0 -> 38.6; of half a pass 29.1 and 37.6, but 8 x 1,000 x 2,000 50.0 -> 52.4)
+int lsh_small_parts(int n_blk, int longest)
+{
+    const int nrt = (longest + SMT_TILE - 1) / SMT_TILE;
+    const int n = std::min(SMT_PART_BLOCKS / 4 / n_blk, nrt / (2 * SMT_GROUP));
+    return std::max(simtier_parts(n_blk, nrt), std::min(n, SMT_MAX_PARTS));
+}
+
+hipError_t launch_lsh_count(const LshModel &m, const LshBatch &b, const uint8_t *sig_table, const void *hist, size_t req_stride, void *parts,
+                            int n_parts, const LshPiecesArgs &p, hipStream_t s)
+{
+    if (!lsh_simtier_on_mfma(m) || !hist || !parts || !p.pieces) return hipErrorInvalidValue;
+    const int sh = simtier_shift(m);
+    const dim3 grid(p.per_req * b.n_req + b.n_blk * n_parts);
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, m, b, sig_table, (const v4i *)hist, req_stride, sh, (int32_t *)parts, n_parts, p);
+    };
+    switch (m.d_bits / 32) {
+    case 1: go(k_lsh_count<1>); break;
+    case 2: go(k_lsh_count<2>); break;
+    default: go(k_lsh_count<4>); break;
+    }
+    return hipGetLastError();
+}
+
+int lsh_simtier_shift(const LshModel &m) { return simtier_shift(m); }
 
 }  // namespace aif

@@ -28,7 +28,7 @@
 // of the signatures a lane fetches one item's word per 64 items and every lane of a row tile receives the words of its
 // eight items by ds_bpermute, shifts its own bit to the top, and merges two signs into a pair of bf16 ones.
 //
-// Block = (chunk of lsh_chunk_len items, request, up to four row tiles of 32 bits); its waves take a row tile each, and
+// Block = (chunk of lsh_chunk_len items -- 10^4 items as chunks of 640 cost 64 users 3 us --, request, up to four row tiles of 32 bits); its waves take a row tile each, and
 // where there are fewer than four the chunk's items are shared out as well (lsh_user_split).  Loads run AHEAD
 // steps of 16 items ahead.  Two barriers a block: the majority word's parts, formed while the first items are on their way,
 // and at the end the waves' shares of total and lowest (they take the steps in turn).  All partial sums are added in a fixed order, a function of the request's own history
@@ -38,8 +38,10 @@
 // and 128 bf16 features for 8 users (216 MB): 92 us, where a block that transposed both inputs through LDS, with two
 // barriers and a memory round trip per 64 items and tables for either value of a bit, took 328; 10^4 items, 64 bits, 64
 // features, 64 users: 35 against 68.
-#include "aif_lsh_dev.h"
+#include "aif_dev.h"
+#include "k_lsh_blocks.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace aif {
@@ -62,18 +64,18 @@ template <int BITS> __device__ __forceinline__ uint32_t lsh_majority(uint32_t wo
 template <typename T> using lsh_global = const T __attribute__((address_space(1))) *;
 
 // T: storage of the embeddings; VW: neighbouring columns a lane owns (32 VW columns a block); W: words a signature has at most
+// chunk, z: which of the history's chunks, which group of row tiles and of columns
 template <typename T, int VW, int W>
-__global__ __launch_bounds__(256, 2) void k_lsh_user_sums(LshModel m, LshBatch b, int part_stride, float *__restrict__ part)
+__device__ __forceinline__ void lsh_user_sums_block(const LshModel &m, const LshReqDesc &rd, int r, int chunk, int z, int part_stride, float *__restrict__ part)
 {
     constexpr int P = sizeof(T) == 4 ? 3 : 1, WORDS = sizeof(T) == 4 ? VW : (VW + 1) / 2;   // 32-bit words of a lane's columns
     constexpr int AHEAD = 4;                                    // steps of 16 items in flight
     // fp32 embeddings: D's sums over 64 items are formed apart and then added on, one rounding at full size instead of twelve
     constexpr bool TWO = sizeof(T) == 4;
     typedef uint32_t vec __attribute__((ext_vector_type(WORDS)));
-    const int d = m.d_out, db = m.d_bits, rts = db / 32, r = blockIdx.y;
-    const int groups = (rts + 3) / 4, rg = blockIdx.z % groups, cg = blockIdx.z / groups;
-    const LshReqDesc rd = b.reqs[r];
-    const int chunk_len = lsh_chunk_len(rd.seq_len), t_lo = blockIdx.x * chunk_len;
+    const int d = m.d_out, db = m.d_bits, rts = db / 32;
+    const int groups = (rts + 3) / 4, rg = z % groups, cg = z / groups;
+    const int chunk_len = lsh_chunk_len(rd.seq_len), t_lo = chunk * chunk_len;
     if (t_lo >= rd.seq_len) return;
     const int t_hi = min(rd.seq_len, t_lo + chunk_len);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), col = lane & 31, h = lane >> 5;
@@ -249,7 +251,7 @@ __global__ __launch_bounds__(256, 2) void k_lsh_user_sums(LshModel m, LshBatch b
             if (sums) weights = differing();
         }
     }
-    float *out = part + ((size_t)r * part_stride + blockIdx.x * split + sub) * lsh_rows(db) * d;
+    float *out = part + ((size_t)r * part_stride + chunk * split + sub) * lsh_rows(db) * d;
     auto store = [&](float *p, const float *v) {
         if constexpr (VW == 4) *(float4 *)p = make_float4(v[0], v[1], v[2], v[3]);
         else if constexpr (VW == 2) *(float2 *)p = make_float2(v[0], v[1]);
@@ -295,28 +297,85 @@ __global__ __launch_bounds__(256, 2) void k_lsh_user_sums(LshModel m, LshBatch b
         store(out + (size_t)(db + LSH_LOWEST) * d + j0, v[2]);
         store(out + (size_t)(db + LSH_LOWEST + 1) * d + j0, v[3]);
     }
-    if (blockIdx.x == 0 && sub == 0 && cg == 0) {
+    if (chunk == 0 && sub == 0 && cg == 0) {
 #pragma unroll
         for (int k = 0; k < W; ++k)
             if (lane == k && k < rts) ((uint32_t *)out)[(size_t)(db + LSH_MAJORITY) * d + k] = maj[k];
     }
 }
 
-hipError_t launch_lsh_user_sums(const LshModel &m, const LshBatch &b, int grid_chunks, int part_stride, float *part, hipStream_t s)
+template <typename T, int VW, int W>
+__global__ __launch_bounds__(256, 2) void k_lsh_user_sums(LshModel m, LshBatch b, int part_stride, float *__restrict__ part)
 {
-    if (b.n_req == 0 || grid_chunks == 0) return hipSuccess;
-    // a lane's loads are at most eight bytes: four columns of fp32 leave no registers for a second wave a SIMD (1 x 10^3
-    // candidates, 2,000 items, d' = d = 128: 92 us a call against 122)
-    const int vw = m.d_out > 64 && m.dtype != 0 ? 4 : m.d_out > 32 ? 2 : 1;
-    const dim3 grid(grid_chunks, b.n_req, ((m.d_bits / 32 + 3) / 4) * ((m.d_out + 32 * vw - 1) / (32 * vw)));
-    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, m, b, part_stride, part); };
+    lsh_user_sums_block<T, VW, W>(m, b.reqs[blockIdx.y], blockIdx.y, blockIdx.x, blockIdx.z, part_stride, part);
+}
+
+// The same beside the blocks that expand the histories for SimTier, in the first launch of a small call; FEW: its first blocks write the
+// batch's tables.  KS: words of a signature.
+// A small call is bound by its launches (2.2 us of host time each, the upload and an event besides) and by each kernel's chain of
+// loads.  Three launches where seven were, chunks of a tenth of the history where they were of 1,024 items, LSH-DIN a wave to one
+// tile of features: 1 x 100 candidates x 500 items (64 bits) 37.4 -> 21.6 us a call, 1 x 3,000 x 3,000 64.0 -> 31.8, 3 x 1,495 x 1,330
+// (128 bits) 78.0 -> 39.7, 8 x 1,000 x 2,000 (128, fp32) 89.1 -> 48.8, 64 x 400 x 10^4 101.5 -> 87.6, 8 x 300 x 90,000 159 -> 146 (168
+// with each request's expansion behind its own sums: the last sums began late; 191 with a piece a thread there).
+struct LshStageArgs {
+    LshFew few;
+    LshModel m;
+    LshBatch b;
+    float *part;
+    v4i *hist;
+    size_t req_stride;
+    int32_t part_stride, chunks, groups, expand, n_fill;        // chunks, groups, expand: blocks a request
+};
+constexpr int EXPAND_PIECES = 8;        // a thread's: the blocks have the registers of the sums, two to a compute unit
+template <bool FEW, typename T, int VW, int KS>
+__global__ __launch_bounds__(256, 2) void k_lsh_stage(LshStageArgs a)
+{
+    int idx = blockIdx.x;
+    if constexpr (FEW) {
+        if (idx < a.n_fill) {
+            const int i = idx * 256 + (int)threadIdx.x;
+            const auto args = kernel_arg<LshFew>(0);
+            if (i < a.few.n_req) a.few.reqs[i] = arg_copy(&args->rd[i]);
+            if (i < a.few.n_blk) {
+                int r = 0;
+                for (int q = 1; q < a.few.n_req; ++q)           // (a request without candidates has its successor's base)
+                    if (args->rd[q].n_cand > 0 && i >= args->rd[q].cand_base / LSH_BLOCK) r = q;
+                a.few.blk_req[i] = r;
+            }
+            return;
+        }
+        idx -= a.n_fill;
+    }
+    // the sums' blocks first, the longer ones
+    const bool sums = idx < a.b.n_req * a.chunks * a.groups;
+    if (!sums) idx -= a.b.n_req * a.chunks * a.groups;
+    const int per = sums ? a.chunks * a.groups : a.expand, r = idx / per;
+    idx -= r * per;
+    LshReqDesc rd;
+    if constexpr (FEW) rd = arg_copy(&kernel_arg<LshFew>(0)->rd[r]);
+    else rd = a.b.reqs[r];
+    if (sums) lsh_user_sums_block<T, VW, KS>(a.m, rd, r, idx % a.chunks, idx / a.chunks, a.part_stride, a.part);
+    else lsh_expand_block<KS, EXPAND_PIECES>(rd, r, idx, a.hist, a.req_stride);
+}
+
+// columns a lane owns; and blocks a chunk takes: a lane's loads are at most eight bytes: four columns of fp32 leave no registers for
+// a second wave a SIMD (1 x 10^3 candidates, 2,000 items, d' = d = 128: 92 us a call against 122)
+static int user_sums_vw(const LshModel &m) { return m.d_out > 64 && m.dtype != 0 ? 4 : m.d_out > 32 ? 2 : 1; }
+static int user_sums_groups(const LshModel &m)
+{
+    const int vw = user_sums_vw(m);
+    return ((m.d_bits / 32 + 3) / 4) * ((m.d_out + 32 * vw - 1) / (32 * vw));
+}
+// f(storage type, words of a signature at most, columns a lane owns)
+template <class F> static void user_sums_kernel(const LshModel &m, F &&f)
+{
+    const int vw = user_sums_vw(m);
     auto words = [&](auto t, auto w) {
         using T = decltype(t);
-        constexpr int W = decltype(w)::value;
         if constexpr (sizeof(T) == 2)
-            if (vw == 4) return go(k_lsh_user_sums<T, 4, W>);
-        if (vw == 2) go(k_lsh_user_sums<T, 2, W>);
-        else go(k_lsh_user_sums<T, 1, W>);
+            if (vw == 4) return f(t, w, std::integral_constant<int, 4>{});
+        if (vw == 2) f(t, w, std::integral_constant<int, 2>{});
+        else f(t, w, std::integral_constant<int, 1>{});
     };
     auto type = [&](auto t) {
         if (m.d_bits <= 32) words(t, std::integral_constant<int, 1>{});
@@ -326,6 +385,47 @@ hipError_t launch_lsh_user_sums(const LshModel &m, const LshBatch &b, int grid_c
     };
     if (m.dtype == 0) type(float{});
     else type(uint16_t{});
+}
+
+hipError_t launch_lsh_user_sums(const LshModel &m, const LshBatch &b, int grid_chunks, int part_stride, float *part, hipStream_t s)
+{
+    if (b.n_req == 0 || grid_chunks == 0) return hipSuccess;
+    const dim3 grid(grid_chunks, b.n_req, user_sums_groups(m));
+    user_sums_kernel(m, [&](auto t, auto w, auto vw) {
+        hipLaunchKernelGGL((k_lsh_user_sums<decltype(t), decltype(vw)::value, decltype(w)::value>), grid, dim3(256), 0, s, m, b, part_stride, part);
+    });
+    return hipGetLastError();
+}
+
+hipError_t launch_lsh_stage(const LshModel &m, const LshBatch &b, const LshFew *few, int grid_chunks, int part_stride, float *part, void *hist,
+                            size_t req_stride, int longest, hipStream_t s)
+{
+    if (b.n_req == 0) return hipSuccess;
+    if (!hist || (m.d_bits != 32 && m.d_bits != 64 && m.d_bits != 128) || (few && (few->n_req != b.n_req || b.n_req > LSH_FEW))) return hipErrorInvalidValue;
+    LshStageArgs a{};
+    a.m = m;
+    a.b = b;
+    a.part = part;
+    a.hist = (v4i *)hist;
+    a.req_stride = req_stride;
+    a.part_stride = part_stride;
+    a.chunks = grid_chunks;
+    a.groups = user_sums_groups(m);
+    a.expand = ((longest + SMT_TILE - 1) / SMT_TILE * (m.d_bits / 32) * 64 + 256 * EXPAND_PIECES - 1) / (256 * EXPAND_PIECES);
+    if (few) {
+        a.few = *few;
+        a.n_fill = (std::max(few->n_req, few->n_blk) + 255) / 256;
+    }
+    const dim3 grid(a.n_fill + b.n_req * (a.chunks * a.groups + a.expand));
+    if (grid.x == 0) return hipSuccess;
+    user_sums_kernel(m, [&](auto t, auto w, auto vw) {
+        using T = decltype(t);
+        constexpr int W = decltype(w)::value, VW = decltype(vw)::value;
+        if constexpr (W <= 4) {
+            if (few) hipLaunchKernelGGL((k_lsh_stage<true, T, VW, W>), grid, dim3(256), 0, s, a);
+            else hipLaunchKernelGGL((k_lsh_stage<false, T, VW, W>), grid, dim3(256), 0, s, a);
+        }
+    });
     return hipGetLastError();
 }
 
