@@ -8,6 +8,7 @@
 #include "aif_user_dev.h"
 #include "k_mfma.h"
 
+#include <algorithm>
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
@@ -37,6 +38,7 @@ struct aif_user_ctx {
     char *h_stage = nullptr, *h_stage_dev = nullptr;   // pinned ring of descriptor tables, its device mapping (or null)
     void *d_stage = nullptr;
     size_t slot_bytes = 0;
+    bool upload = false;                               // testing (AIF_USER_UPLOAD=1): the descriptors of few users uploaded like those of many
     hipEvent_t ev[USER_NSLOT] = {};
     bool ev_live[USER_NSLOT] = {};
     int next_slot = 0;
@@ -166,6 +168,10 @@ aif_status uinit(const aif_user_config *cfg, const aif_user_weights *wts, aif_us
     const size_t sb = (size_t)c->max_users * (sizeof(ReqDesc) + sizeof(UserDesc)) + (n_blk_max + 4) * sizeof(int32_t) + 16 +
                       attn_max_groups(c->x_rows, c->max_users) * sizeof(AttnGroup);
     c->slot_bytes = (sb + 255) / 256 * 256;
+    {
+        const char *up = getenv("AIF_USER_UPLOAD");
+        c->upload = up && up[0] == '1';
+    }
     USER_TRY(nullptr, staging_alloc(c->slot_bytes * USER_NSLOT, &c->h_stage, &c->h_stage_dev));
     USER_TRY(nullptr, hipMalloc(&c->d_stage, c->slot_bytes * USER_NSLOT));
     for (int i = 0; i < USER_NSLOT; ++i)
@@ -258,15 +264,31 @@ aif_status aif_user_precompute(aif_user_ctx *c, const aif_user_request *users, i
     b.n_groups = c->mfma.attn ? attn_plan_groups(m, hr, n_users, c->n_cu, (AttnGroup *)(h + goff), &b.n_streamed, GROUP_MIN_TILES,
                                                  user_fine_groups(c->n_cu, m.d_head)) : 0;
     b.groups = (const AttnGroup *)(d + goff);
-    USER_TRY(c, staging_upload(c->h_stage, c->h_stage_dev, (size_t)slot * c->slot_bytes, d,
-                               goff + (size_t)b.n_groups * sizeof(AttnGroup), s));
+    // few users: their descriptors travel in the projection's arguments, and the device never reads the slot's pinned memory
+    const bool in_args = n_users <= USER_FEW && !c->upload;
+    UserFew few;
+    if (in_args) {
+        std::copy(hu, hu + n_users, few.ud);
+        std::fill(few.groups_of, few.groups_of + n_users, (uint16_t)0);
+        const AttnGroup *hg = (const AttnGroup *)(h + goff);
+        for (int i = 0; i < b.n_groups; ++i) ++few.groups_of[hg[i].r];
+        few.reqs = (ReqDesc *)d;
+        few.users = (UserDesc *)(d + (size_t)n_users * sizeof(ReqDesc));
+        few.blk_req = (int32_t *)(d + (size_t)n_users * (sizeof(ReqDesc) + sizeof(UserDesc)));
+        few.groups = (AttnGroup *)(d + goff);
+        few.n_users = n_users;
+        few.n_blk = b.n_blk;
+        few.n_groups = b.n_groups;
+    } else
+        USER_TRY(c, staging_upload(c->h_stage, c->h_stage_dev, (size_t)slot * c->slot_bytes, d,
+                                   goff + (size_t)b.n_groups * sizeof(AttnGroup), s));
 
     hipEvent_t *pe = nullptr;
     if (c->prof_on && c->prof_calls < c->prof_max) pe = &c->prof[(size_t)USER_EV_PER_CALL * c->prof_calls++];
     if (pe) USER_TRY(c, hipEventRecord(pe[0], s));
     const UserPack pack{c->mfma.kvpack, c->mfma.pack_stride, c->mfma.kmax, c->mfma.nktp};
     const bool packs = c->mfma.attn && c->w.wseq_frag && (m.d_head == 64 || m.d_head == 32);
-    USER_TRY(c, launch_user_project(c->w, du, b.blk_req, b.n_blk, n_users, c->X, packs ? &pack : nullptr, s));
+    USER_TRY(c, launch_user_project(c->w, du, b.blk_req, b.n_blk, n_users, c->X, packs ? &pack : nullptr, in_args ? &few : nullptr, s));
     if (pe) USER_TRY(c, hipEventRecord(pe[1], s));
     if (c->mfma.attn)
         USER_TRY(c, launch_attn_mfma(m, b, c->X, c->mfma, packs, s));
@@ -280,8 +302,8 @@ aif_status aif_user_precompute(aif_user_ctx *c, const aif_user_request *users, i
         USER_TRY(c, launch_user_combine(c->w, du, n_users, c->X, (const float *)c->part, s));
     }
     if (pe) USER_TRY(c, hipEventRecord(pe[3], s));
-    USER_TRY(c, hipEventRecord(c->ev[slot], s));
-    c->ev_live[slot] = true;
+    if (!in_args) USER_TRY(c, hipEventRecord(c->ev[slot], s));
+    c->ev_live[slot] = !in_args;
     return AIF_OK;
 }
 

@@ -20,6 +20,19 @@ struct UserDesc {
     int32_t row_base;           // multiple of ROW_BLOCK
 };
 
+// A call of at most USER_FEW users: their descriptors travel in the projection's arguments, its blocks read them there, and its first
+// blocks write the device tables the later kernels read.  (64 of 40 bytes: the arguments of a launch hold 4 KB.)
+constexpr int USER_FEW = 64;
+struct UserFew {
+    UserDesc ud[USER_FEW];
+    uint16_t groups_of[USER_FEW];       // attention groups of each user
+    ReqDesc *reqs;
+    UserDesc *users;
+    int32_t *blk_req;
+    AttnGroup *groups;
+    int32_t n_users, n_blk, n_groups, n_fill;       // n_fill: blocks that write the tables
+};
+
 struct UserWeights {
     const float *wseq_t;        // [d_raw, d] fp32: W_seq transposed
     const float *wprof;         // [d, d_raw] fp32: W_profile as given (row-major)
@@ -42,8 +55,9 @@ struct UserPack {
 
 // Eq. 1: X[row, 0:d] = W x for every sequence position and the profile; U^_seq also to the user's seq_out.
 // pack (optional, MFMA projection, d = 32 or 64): the rows are left packed as well (launch_attn_mfma: kv_packed).
+// few (optional, on the host; n_fill is set here): nothing has been uploaded, the launch writes the tables.
 hipError_t launch_user_project(const UserWeights &w, const UserDesc *users /*device*/, const int32_t *blk_req /*device*/,
-                               int n_blk, int n_users, void *X, const UserPack *pack, hipStream_t s);
+                               int n_blk, int n_users, void *X, const UserPack *pack, UserFew *few, hipStream_t s);
 size_t user_project_lds_bytes(int d_raw);
 
 // FFN of Eq. 2 on the attention rows X[row, d:2d] of the sequence positions and their sum over each block of

@@ -9,11 +9,76 @@
 #include "aif_user_dev.h"
 #include "k_stage.h"
 
+#include <algorithm>
+#include <type_traits>
+
 namespace aif {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+// Where a block of the projection finds its user: in the call's device tables, or in the launch's own arguments (their first).
+struct UserTables {
+    const UserDesc *users;
+    const int32_t *blk_req;
+    __device__ __forceinline__ int user_of(int blk) const { return blk_req[blk]; }
+    __device__ __forceinline__ UserDesc desc(int u) const { return users[u]; }
+};
+struct UserArguments {
+    int n_users;
+    __device__ __forceinline__ int user_of(int blk) const      // every user has a block: the last whose first is not past this one
+    {
+        const int i = threadIdx.x & 63;
+        const int first = kernel_arg<UserFew>(0)->ud[i < n_users ? i : 0].row_base / ROW_BLOCK;
+        return __popcll(__ballot(i < n_users && first <= blk)) - 1;
+    }
+    __device__ __forceinline__ UserDesc desc(int u) const { return arg_copy(&kernel_arg<UserFew>(0)->ud[__builtin_amdgcn_readfirstlane(u)]); }
+};
+static_assert(USER_FEW <= 64, "a lane a user");
+
+// the tables of such a call, by its first blocks of 256 threads
+__device__ __forceinline__ void user_fill(const UserFew &f, int i)
+{
+    __shared__ int first_blk[USER_FEW], first_group[USER_FEW];
+    const auto args = kernel_arg<UserFew>(0);
+    if (threadIdx.x < 64) {
+        const int u = threadIdx.x < f.n_users ? threadIdx.x : 0, ng = threadIdx.x < f.n_users ? args->groups_of[u] : 0;
+        int sum = ng;                                           // of the users up to this one
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int before = __shfl_up(sum, o, 64);
+            sum += (int)threadIdx.x >= o ? before : 0;
+        }
+        if ((int)threadIdx.x < f.n_users) {
+            first_blk[threadIdx.x] = args->ud[u].row_base / ROW_BLOCK;
+            first_group[threadIdx.x] = sum - ng;
+        }
+    }
+    __syncthreads();
+    auto last_not_past = [&](const int *first, int x) {
+        int r = 0;
+        for (int u = 1; u < f.n_users; ++u) r = first[u] <= x ? u : r;
+        return r;
+    };
+    if (i < f.n_users) {
+        const UserDesc ud = arg_copy(&args->ud[i]);
+        f.users[i] = ud;
+        ReqDesc e{};                                            // (aif_user_precompute has the same)
+        e.seq_keys = e.seq_vals = ud.seq_out;
+        e.seq_len = ud.seq_len;
+        e.n_cand = ud.seq_len + 1;
+        e.row_base = ud.row_base;
+        e.index = e.slot = i;
+        f.reqs[i] = e;
+    }
+    if (i < f.n_blk) f.blk_req[i] = last_not_past(first_blk, i);
+    if (i < f.n_groups) {
+        // (a user without groups has its successor's first: the last one not past i is the one that has it)
+        const int r = last_not_past(first_group, i), ng = args->groups_of[r], at = i - first_group[r], tiles = (args->ud[r].seq_len + 1 + 31) / 32;
+        f.groups[i] = AttnGroup{r, (int)((long)tiles * at / ng), (int)((long)tiles * (at + 1) / ng), 0};
+    }
+}
 
 // The projected profile: four adjacent lanes share an output feature, each takes a quarter of the input
 // features (d_raw is a multiple of four), they meet in a fixed two-step butterfly.  All of a thread's loads are
@@ -29,7 +94,7 @@ __device__ __forceinline__ void project_profile(const UserWeights &w, const User
         if (n < d) {
             const float *wr = w.wprof + (size_t)n * w.d_raw + q * chunk;
             const T *px = pr + q * chunk;
-#pragma unroll 8
+#pragma unroll 32
             for (int m = 0; m < chunk; ++m) acc = fmaf(wr[m], ld_f<T>(px + m), acc);
         }
         acc += __shfl_xor(acc, 1, 64);
@@ -50,19 +115,18 @@ __device__ __forceinline__ void project_profile(const UserWeights &w, const User
 // 64-key stages of the attention that follows, and the block packs them from LDS as keys and values as well (one launch
 // where two were: 64 users of up to 500 positions 11.6 us instead of 12.2 + 5.9).  The blocks past the sequences' project the profiles, one user each, beside them instead of after a
 // block's own rows.
-template <int D, bool PACK>
-__global__ __launch_bounds__(256) void k_user_project_mfma(UserWeights w, const UserDesc *__restrict__ users,
-                                                           const int32_t *__restrict__ blk_req, int n_row_blk, uint16_t *__restrict__ X, UserPack pk)
+template <int D, bool PACK, class Users>
+__device__ __forceinline__ void user_project_mfma_block(int blk, const UserWeights &w, const Users &src, int n_row_blk, uint16_t *__restrict__ X, const UserPack &pk)
 {
     constexpr int FT = D / 32, ROWS = 128, SUB = ROW_BLOCK / ROWS;
-    if ((int)blockIdx.x >= n_row_blk) {
-        project_profile<uint16_t>(w, users[blockIdx.x - n_row_blk], X, 256);
+    if (blk >= n_row_blk) {
+        project_profile<uint16_t>(w, src.desc(blk - n_row_blk), X, 256);
         return;
     }
-    const int u = blk_req[blockIdx.x / SUB];
+    const int u = src.user_of(blk / SUB);
     if (u < 0) return;
-    const UserDesc ud = users[u];
-    const int row0 = blockIdx.x * ROWS, local0 = row0 - ud.row_base, L = ud.seq_len;
+    const UserDesc ud = src.desc(u);
+    const int row0 = blk * ROWS, local0 = row0 - ud.row_base, L = ud.seq_len;
     constexpr int LD = D + 8;                                   // LDS row: 16 bytes of padding
     __shared__ __align__(16) uint16_t rows[ROWS * LD];
     if (local0 >= L) return;
@@ -130,6 +194,23 @@ __global__ __launch_bounds__(256) void k_user_project_mfma(UserWeights w, const 
 #pragma unroll
         for (int s = 0; s < ROWS / 64; ++s) pack_kv_stage<D>(u, 0, local0 / 64 + s, L, 1, key, key, pk.kvpack, pk.stride, pk.kmax, pk.nktp);
     }
+}
+
+template <int D, bool PACK>
+__global__ __launch_bounds__(256) void k_user_project_mfma(UserWeights w, const UserDesc *__restrict__ users,
+                                                           const int32_t *__restrict__ blk_req, int n_row_blk, uint16_t *__restrict__ X, UserPack pk)
+{
+    user_project_mfma_block<D, PACK>(blockIdx.x, w, UserTables{users, blk_req}, n_row_blk, X, pk);
+}
+// An upload of 2 - 3 us and its wait saved: 64 users of up to 500 positions 39.0 us a call -> 34.2, 6 of 60 positions 21.4 -> 15.7.
+template <int D, bool PACK>
+__global__ __launch_bounds__(256) void k_user_project_mfma_few(UserFew few /* first: kernel_arg */, UserWeights w, int n_row_blk, uint16_t *__restrict__ X, UserPack pk)
+{
+    if ((int)blockIdx.x < few.n_fill) {
+        user_fill(few, blockIdx.x * 256 + threadIdx.x);
+        return;
+    }
+    user_project_mfma_block<D, PACK>((int)blockIdx.x - few.n_fill, w, UserArguments{few.n_users}, n_row_blk, X, pk);
 }
 
 // ---------------------------------------------------------------------------
@@ -224,6 +305,46 @@ __global__ __launch_bounds__(1024) void k_user_ffn_pool(UserWeights w, const Use
     out[D + n] = X[(size_t)(ud.row_base + L) * (2 * D) + D + n];               // Eq. 3: the profile row's attention
 }
 
+// The two kernels of fp32 arithmetic below are chains of loads: rows into LDS sixteen at a time, weights 32 at a time (2 users of 60
+// positions, FFN: 12.2 us one at a time, 8.9 so).
+// A feature's rows lie in quads at 4 (quad ^ feature mod RT / 4): neighbouring lanes hold neighbouring features, and rows at one place would
+// share a bank, all 64 of them.
+template <int RT> __device__ __forceinline__ int user_row_at(int m, int r) { return m * RT + (r ^ 4 * (m & (RT / 4 - 1))); }
+template <int RT, class Get> __device__ __forceinline__ void user_stage_rows(float *xs, int width, const Get &get)
+{
+    constexpr int U = 16;
+    for (int i0 = threadIdx.x; i0 < RT * width; i0 += 256 * U) {
+        float v[U];
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            const int idx = min(i0 + 256 * q, RT * width - 1), r = idx / width;
+            v[q] = get(r, idx - r * width);
+        }
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            const int idx = min(i0 + 256 * q, RT * width - 1), r = idx / width;
+            xs[user_row_at<RT>(idx - r * width, r)] = v[q];              // (past the end: the last one again)
+        }
+    }
+}
+template <int U, class Weight, class Use> __device__ __forceinline__ void user_walk_in(int &m, int n, const Weight &weight, const Use &use)
+{
+    for (; m + U <= n; m += U) {
+        float wv[U];
+#pragma unroll
+        for (int q = 0; q < U; ++q) wv[q] = weight(m + q);
+#pragma unroll
+        for (int q = 0; q < U; ++q) use(m + q, wv[q]);
+    }
+}
+template <class Weight, class Use> __device__ __forceinline__ void user_walk(int n, const Weight &weight, const Use &use)      // use(m, weight(m)) in order
+{
+    int m = 0;
+    user_walk_in<32>(m, n, weight, use);
+    user_walk_in<4>(m, n, weight, use);
+    for (; m < n; ++m) use(m, weight(m));
+}
+
 // ---------------------------------------------------------------------------
 // Eq. 1.  One block = USER_PROJ_ROWS rows of one user.  The rows are staged in
 // LDS transposed (xs[m][row]) so that a thread reads the eight rows it owns for
@@ -231,26 +352,24 @@ __global__ __launch_bounds__(1024) void k_user_ffn_pool(UserWeights w, const Use
 // the transposed weights, one coalesced load per input feature reused for its
 // eight rows.
 // ---------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(256) void k_user_project(UserWeights w, const UserDesc *__restrict__ users,
-                                                      const int32_t *__restrict__ blk_req, T *__restrict__ X)
+template <typename T, class Users>
+__device__ __forceinline__ void user_project_block(int blk, const UserWeights &w, const Users &src, int n_row_blk, T *__restrict__ X, float *xs)
 {
-    extern __shared__ __align__(16) float xs[];                 // [d_raw][USER_PROJ_ROWS]
     constexpr int RT = USER_PROJ_ROWS, SUB = ROW_BLOCK / RT;
-    const int u = blk_req[blockIdx.x / SUB];
+    if (blk >= n_row_blk) {                                     // the profiles, a block each
+        project_profile<T>(w, src.desc(blk - n_row_blk), X, 256);
+        return;
+    }
+    const int u = src.user_of(blk / SUB);
     if (u < 0) return;
-    const UserDesc ud = users[u];
-    const int row0 = blockIdx.x * RT;
+    const UserDesc ud = src.desc(u);
+    const int row0 = blk * RT;
     const int local0 = row0 - ud.row_base;
     const int L = ud.seq_len;
-    if (local0 > L) return;                                     // rows 0..L (L = the profile) exist
+    if (local0 >= L) return;
     const int d_raw = w.d_raw, d = w.d;
     const T *seq = (const T *)ud.seq;
-    for (int idx = threadIdx.x; idx < RT * d_raw; idx += 256) {
-        const int r = idx / d_raw, m = idx - r * d_raw;
-        const int i = local0 + r;
-        xs[m * RT + r] = i < L ? ld_f<T>(seq + (size_t)i * d_raw + m) : 0.f;
-    }
+    user_stage_rows<RT>(xs, d_raw, [&](int r, int m) { return local0 + r < L ? ld_f<T>(seq + (size_t)(local0 + r) * d_raw + m) : 0.f; });
     __syncthreads();
     const int nl = threadIdx.x & 63, g = threadIdx.x >> 6;      // 4 row groups of 8
     T *so = (T *)ud.seq_out;
@@ -258,9 +377,8 @@ __global__ __launch_bounds__(256) void k_user_project(UserWeights w, const UserD
         float acc[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) acc[i] = 0.f;
-        for (int m = 0; m < d_raw; ++m) {
-            const float wv = w.wseq_t[(size_t)m * d + n];
-            const float4 a = *(const float4 *)(xs + m * RT + g * 8), b = *(const float4 *)(xs + m * RT + g * 8 + 4);
+        user_walk(d_raw, [&](int m) { return w.wseq_t[(size_t)m * d + n]; }, [&](int m, float wv) {
+            const float4 a = *(const float4 *)(xs + user_row_at<RT>(m, g * 8)), b = *(const float4 *)(xs + user_row_at<RT>(m, g * 8 + 4));
             acc[0] = fmaf(wv, a.x, acc[0]);
             acc[1] = fmaf(wv, a.y, acc[1]);
             acc[2] = fmaf(wv, a.z, acc[2]);
@@ -269,7 +387,7 @@ __global__ __launch_bounds__(256) void k_user_project(UserWeights w, const UserD
             acc[5] = fmaf(wv, b.y, acc[5]);
             acc[6] = fmaf(wv, b.z, acc[6]);
             acc[7] = fmaf(wv, b.w, acc[7]);
-        }
+        });
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             const int li = local0 + g * 8 + i;
@@ -279,41 +397,70 @@ __global__ __launch_bounds__(256) void k_user_project(UserWeights w, const UserD
             }
         }
     }
-    // the profile row, if it falls into this block
-    if (L >= local0 && L < local0 + RT) project_profile<T>(w, ud, X, 256);
+}
+template <typename T>
+__global__ __launch_bounds__(256) void k_user_project(UserWeights w, const UserDesc *__restrict__ users, const int32_t *__restrict__ blk_req, int n_row_blk, T *__restrict__ X)
+{
+    extern __shared__ __align__(16) float xs[];                 // [d_raw][USER_PROJ_ROWS]
+    user_project_block<T>(blockIdx.x, w, UserTables{users, blk_req}, n_row_blk, X, xs);
+}
+template <typename T>
+__global__ __launch_bounds__(256) void k_user_project_few(UserFew few /* first: kernel_arg */, UserWeights w, int n_row_blk, T *__restrict__ X)
+{
+    extern __shared__ __align__(16) float xs[];
+    if ((int)blockIdx.x < few.n_fill) {
+        user_fill(few, blockIdx.x * 256 + threadIdx.x);
+        return;
+    }
+    user_project_block<T>((int)blockIdx.x - few.n_fill, w, UserArguments{few.n_users}, n_row_blk, X, xs);
 }
 
 size_t user_project_lds_bytes(int d_raw) { return (size_t)d_raw * USER_PROJ_ROWS * sizeof(float); }
 
 hipError_t launch_user_project(const UserWeights &w, const UserDesc *users, const int32_t *blk_req, int n_blk, int n_users, void *X,
-                               const UserPack *pack, hipStream_t s)
+                               const UserPack *pack, UserFew *few, hipStream_t s)
 {
     if (n_blk == 0) return hipSuccess;
     if (pack && !w.wseq_frag) return hipErrorInvalidValue;
+    int n_fill = 0;
+    if (few) {
+        if (few->n_users != n_users || n_users > USER_FEW || few->n_blk != n_blk) return hipErrorInvalidValue;
+        n_fill = few->n_fill = (std::max(std::max(n_users, n_blk), few->n_groups) + 255) / 256;
+    }
     if (w.wseq_frag) {
         const int n_row_blk = n_blk * (ROW_BLOCK / 128);
         const UserPack pk = pack ? *pack : UserPack{};
-        auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(n_row_blk + n_users), dim3(256), 0, s, w, users, blk_req, n_row_blk, (uint16_t *)X, pk); };
+        const dim3 grid(n_fill + n_row_blk + n_users);
+        auto go = [&](auto d, auto packs) {
+            constexpr int D = decltype(d)::value;
+            constexpr bool PACK = decltype(packs)::value;
+            if (few) hipLaunchKernelGGL((k_user_project_mfma_few<D, PACK>), grid, dim3(256), 0, s, *few, w, n_row_blk, (uint16_t *)X, pk);
+            else hipLaunchKernelGGL((k_user_project_mfma<D, PACK>), grid, dim3(256), 0, s, w, users, blk_req, n_row_blk, (uint16_t *)X, pk);
+        };
+        using Yes = std::true_type;
+        using No = std::false_type;
         switch (w.d) {
-        case 32: pack ? go(k_user_project_mfma<32, true>) : go(k_user_project_mfma<32, false>); break;
-        case 64: pack ? go(k_user_project_mfma<64, true>) : go(k_user_project_mfma<64, false>); break;
+        case 32: pack ? go(std::integral_constant<int, 32>{}, Yes{}) : go(std::integral_constant<int, 32>{}, No{}); break;
+        case 64: pack ? go(std::integral_constant<int, 64>{}, Yes{}) : go(std::integral_constant<int, 64>{}, No{}); break;
         case 128:
             if (pack) return hipErrorInvalidValue;
-            go(k_user_project_mfma<128, false>);
+            go(std::integral_constant<int, 128>{}, No{});
             break;
         default: return hipErrorInvalidValue;
         }
         return hipGetLastError();
     }
     const size_t lds = user_project_lds_bytes(w.d_raw);
-    const dim3 grid(n_blk * (ROW_BLOCK / USER_PROJ_ROWS));
-    if (w.dtype == 0) {
-        (void)hipFuncSetAttribute((const void *)k_user_project<float>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        hipLaunchKernelGGL(k_user_project<float>, grid, dim3(256), lds, s, w, users, blk_req, (float *)X);
-    } else {
-        (void)hipFuncSetAttribute((const void *)k_user_project<uint16_t>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        hipLaunchKernelGGL(k_user_project<uint16_t>, grid, dim3(256), lds, s, w, users, blk_req, (uint16_t *)X);
-    }
+    const int n_row_blk = n_blk * (ROW_BLOCK / USER_PROJ_ROWS);
+    const dim3 grid(n_fill + n_row_blk + n_users);
+    auto go = [&](auto t) {
+        using T = decltype(t);
+        (void)hipFuncSetAttribute(few ? (const void *)k_user_project_few<T> : (const void *)k_user_project<T>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (few) hipLaunchKernelGGL(k_user_project_few<T>, grid, dim3(256), lds, s, *few, w, n_row_blk, (T *)X);
+        else hipLaunchKernelGGL(k_user_project<T>, grid, dim3(256), lds, s, w, users, blk_req, n_row_blk, (T *)X);
+    };
+    if (w.dtype == 0) go(float{});
+    else go(uint16_t{});
     return hipGetLastError();
 }
 
@@ -338,10 +485,7 @@ __global__ __launch_bounds__(256) void k_user_ffn_partial(UserWeights w, const U
     if (local0 >= L) return;
     const int d = w.d;
     float *gs = as + (size_t)d * RT;
-    for (int idx = threadIdx.x; idx < RT * d; idx += 256) {
-        const int r = idx / d, m = idx - r * d;
-        as[m * RT + r] = local0 + r < L ? ld_f<T>(X + (size_t)(row0 + r) * (2 * d) + d + m) : 0.f;
-    }
+    user_stage_rows<RT>(as, d, [&](int r, int m) { return local0 + r < L ? ld_f<T>(X + (size_t)(row0 + r) * (2 * d) + d + m) : 0.f; });
     __syncthreads();
     const int nl = threadIdx.x & 63, g = threadIdx.x >> 6;      // 4 row groups of 16
     for (int n = nl; n < d; n += 64) {
@@ -349,18 +493,16 @@ __global__ __launch_bounds__(256) void k_user_ffn_partial(UserWeights w, const U
         const float b0 = w.b_ffn ? w.b_ffn[n] : 0.f;
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[i] = b0;
-        for (int m = 0; m < d; ++m) {
-            const float wv = w.wffn_t[(size_t)m * d + n];
-            const float *ap = as + m * RT + g * 16;
+        user_walk(d, [&](int m) { return w.wffn_t[(size_t)m * d + n]; }, [&](int m, float wv) {
 #pragma unroll
             for (int i4 = 0; i4 < 4; ++i4) {
-                const float4 a = *(const float4 *)(ap + 4 * i4);
+                const float4 a = *(const float4 *)(as + user_row_at<RT>(m, g * 16 + 4 * i4));
                 acc[4 * i4 + 0] = fmaf(wv, a.x, acc[4 * i4 + 0]);
                 acc[4 * i4 + 1] = fmaf(wv, a.y, acc[4 * i4 + 1]);
                 acc[4 * i4 + 2] = fmaf(wv, a.z, acc[4 * i4 + 2]);
                 acc[4 * i4 + 3] = fmaf(wv, a.w, acc[4 * i4 + 3]);
             }
-        }
+        });
         float sum = 0.f;
 #pragma unroll
         for (int i = 0; i < 16; ++i)
