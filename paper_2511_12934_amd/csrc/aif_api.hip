@@ -338,11 +338,12 @@ aif_status init_impl(const aif_config *cfg, const aif_weights *wts, aif_ctx *c)
             c->w_pieces[l].want(pieces_bytes(m.dtype, 1, layer_tiles(m.dims[l + 1]), m.dims[l] - (l == 0 ? m.d_user : 0)), &total);
         if (total) HIP_TRY(nullptr, c->weight_pieces.alloc(total));
         c->wq_pieces.place(c->weight_pieces);
-        if (wq_pieces) HIP_TRY(nullptr, launch_pack_pieces(m.dtype, wts->w_q, m.n_heads, m.d_head, head_tiles, m.d_item, 0, m.d_item, c->wq_pieces.p, s));
+        if (wq_pieces) HIP_TRY(nullptr, launch_pack_pieces(m.dtype, wts->w_q, m.n_heads, m.d_head, head_tiles, m.d_item, 0, m.d_item, false, c->wq_pieces.p, s));
         for (int l = 0; l < m.n_layers && !c->mfma.mlp; ++l) {
             const int col0 = l == 0 ? m.d_user : 0;
             c->w_pieces[l].place(c->weight_pieces);
-            HIP_TRY(nullptr, launch_pack_pieces(m.dtype, wts->w[l], 1, m.dims[l + 1], layer_tiles(m.dims[l + 1]), m.dims[l], col0, m.dims[l] - col0, c->w_pieces[l].p, s));
+            HIP_TRY(nullptr, launch_pack_pieces(m.dtype, wts->w[l], 1, m.dims[l + 1], layer_tiles(m.dims[l + 1]), m.dims[l], col0, m.dims[l] - col0, l > 0, c->w_pieces[l].p,
+                                                s));
         }
     }
     // both consumers of the workspace read MFMA fragments: keep it in fragment order (x_offset)

@@ -161,6 +161,9 @@ struct MlpGenericWeights {
 hipError_t launch_mlp_generic(const Model &m, const Batch &b, const void *X, const MlpGenericWeights &w,
                               const float *bias1, hipStream_t s);
 size_t mlp_generic_lds_bytes(const Model &m);
+// The same for large batches and heads of up to 128 features a hidden layer (k_generic_chain.hip; the same bits).
+bool gen_chain_serves(const Model &m, const Batch &b);
+hipError_t launch_gen_chain(const Model &m, const Batch &b, const void *X, const MlpGenericWeights &w, const float *bias1, hipStream_t s);
 // Both of a batch of few candidates as one launch (the same bits).
 bool gen_tile_serves(const Model &m, const Batch &b, int longest);
 hipError_t launch_gen_tile(const Model &m, const Batch &b, void *X, const float *wq, const void *wq_pieces, const void *table, int32_t *bad,
@@ -185,7 +188,8 @@ hipError_t launch_pack_transposed(int dtype, const void *w, int n_out, int n_in,
 // ... and as bf16 pieces in MFMA fragment order (k_generic.hip): `groups` matrices of `rows` rows each, one below the other,
 // each as `tiles` row tiles of 16 (zeros past its rows); pieces_bytes: what `out` has to hold
 size_t pieces_bytes(int dtype, int groups, int tiles, int ncols);
-hipError_t launch_pack_pieces(int dtype, const void *w, int groups, int rows, int tiles, int n_in, int col0, int ncols, void *out, hipStream_t s);
+hipError_t launch_pack_pieces(int dtype, const void *w, int groups, int rows, int tiles, int n_in, int col0, int ncols, bool in_place, void *out,
+                              hipStream_t s);
 // Row tiles of a layer's weights: whole k-steps of the layer that reads its outputs.
 constexpr int layer_tiles(int rows) { return (rows + 31) / 32 * 2; }
 // Row tiles of W_q per head.  Three places agree on it: the room for the pieces, their packing, and the kernel, whose

@@ -8,6 +8,7 @@
 // cost accordingly less (three products against an fp32 activation).  Every
 // candidate is a column of its own: results do not depend on how a candidate
 // list is sliced into requests.
+#include "k_pieces.h"
 #include "k_stage.h"
 
 #include <algorithm>
@@ -85,85 +86,6 @@ hipError_t launch_user_fold_few(const Model &m, const FewFill &f, const float *w
     return hipGetLastError();
 }
 
-// ---------------------------------------------------------------------------
-// Values as bf16 pieces, and the products of pieces.
-// ---------------------------------------------------------------------------
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-template <typename T> struct stored;
-template <> struct stored<float> { static constexpr int P = 3; };       // pieces of a tensor of this storage type
-template <> struct stored<uint16_t> { static constexpr int P = 1; };
-
-template <int P> struct Pieces { bf16x8 p[P]; };
-
-// x = p[0] + p[1] + p[2], each piece the rest so far rounded to bf16: exact for three pieces.  A value that is not
-// finite (or rounds to infinity) makes NaN pieces: whoever multiplies them sees a NaN and takes the plain route.
-// Two values at a time: the conversion takes a pair, and their rests come off the two halves of its word (value by value it is
-// two conversions a pair and piece).
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-template <int P> __device__ __forceinline__ void split2(float a, float b, uint32_t (&w)[P])
-{
-#pragma unroll
-    for (int q = 0; q < P; ++q) {
-        w[q] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{a, b}), bf16x2));
-        if (q + 1 < P) {
-            a -= __uint_as_float(w[q] << 16);
-            b -= __uint_as_float(w[q] & 0xFFFF0000u);
-        }
-    }
-}
-template <int P> __device__ __forceinline__ Pieces<P> split8(const float *v)
-{
-    uint32_t w[P][4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        uint32_t x[P];
-        split2<P>(v[2 * j], v[2 * j + 1], x);
-#pragma unroll
-        for (int q = 0; q < P; ++q) w[q][j] = x[q];
-    }
-    Pieces<P> o;
-#pragma unroll
-    for (int q = 0; q < P; ++q) o.p[q] = __builtin_bit_cast(bf16x8, make_uint4(w[q][0], w[q][1], w[q][2], w[q][3]));
-    return o;
-}
-
-// acc += a * b over the k-step's 32 terms.  The product of the leading pieces goes to `big`, the others, at most 2^-8 of
-// it, to `small`: they are added to each other first, so `big` is rounded once per k-step.
-template <int PA, int PB>
-__device__ __forceinline__ void mfma_pieces(const Pieces<PA> &a, const Pieces<PB> &b, f32x4 &big, f32x4 &small)
-{
-#pragma unroll
-    for (int i = PA - 1; i >= 0; --i)
-#pragma unroll
-        for (int j = PB - 1; j >= 0; --j)
-            if (i + j > 0 && i + j <= 2) small = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.p[i], b.p[j], small, 0, 0, 0);
-    big = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.p[0], b.p[0], big, 0, 0, 0);
-}
-
-// eight consecutive elements (16-byte aligned for fp32 in halves of four) as fp32; elements at and past `n` are zero
-template <typename T> __device__ __forceinline__ void load8(const T *p, int n, float *v);
-template <> __device__ __forceinline__ void load8<float>(const float *p, int n, float *v)
-{
-    float4 a = make_float4(0, 0, 0, 0), b = a;
-    if (n > 0) a = *(const float4 *)p;
-    if (n > 4) b = *(const float4 *)(p + 4);
-    v[0] = a.x, v[1] = a.y, v[2] = a.z, v[3] = a.w, v[4] = b.x, v[5] = b.y, v[6] = b.z, v[7] = b.w;
-}
-template <> __device__ __forceinline__ void load8<uint16_t>(const uint16_t *p, int n, float *v)
-{
-    uint4 a = make_uint4(0, 0, 0, 0);
-    if (n > 0) a = *(const uint4 *)p;
-    const uint32_t w[4] = {a.x, a.y, a.z, a.w};
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        v[2 * j] = __uint_as_float(w[j] << 16);
-        v[2 * j + 1] = __uint_as_float(w[j] & 0xFFFF0000u);
-    }
-}
 // four consecutive elements at p + f of a row of n; `quad`: n is a multiple of four and the row 4-element aligned
 template <typename T> __device__ __forceinline__ void load4(const T *p, int f, int n, bool quad, float *v)
 {
@@ -880,7 +802,7 @@ hipError_t launch_attn_generic(const Model &m, const Batch &b, void *X, const fl
 // Measured (160 -> 128 -> 64 -> 1, fp32): 10^5 candidates 59 us, where a thread per
 // feature and 16 candidates on the vector ALU took 210 (81 with 64 candidates, eight
 // waves a block; 61 with the pieces cut value by value); 1,000 candidates 7 against 30; bf16, 160,000
-// candidates 44 against 301.
+// candidates 44 against 301 (k_generic_chain.hip: 27).
 // ---------------------------------------------------------------------------
 constexpr int MLP_TS = 16;              // candidates of a column tile
 
@@ -1017,7 +939,7 @@ __device__ __forceinline__ void mlp_gen_block(const Model &m, const ReqDesc &rd,
             }
         }
     }
-    float odd[NC];                      // per candidate of the lane: NaN once a value that is not finite has come up
+    float odd[NC];                      // per candidate of the lane: NaN where a value that is not finite has reached the logit
 #pragma unroll
     for (int n = 0; n < NC; ++n) odd[n] = 0.f;
     char *in = act, *out = act + gm.off1;
@@ -1064,13 +986,11 @@ __device__ __forceinline__ void mlp_gen_block(const Model &m, const ReqDesc &rd,
                 for (int n = 0; n < NC; ++n) {
                     float v[4];
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        v[j] = big[i][n][j] + small[i][n][j];
-                        odd[n] = fmaf(v[j], 0.f, odd[n]);
-                    }
+                    for (int j = 0; j < 4; ++j) v[j] = big[i][n][j] + small[i][n][j];
                     const int f = 16 * (rt + i) + 4 * g;
                     if (last) {
                         const int c = n * 16 + col;
+                        odd[n] = fmaf(v[0], 0.f, odd[n]);
                         if (g == 0 && c < nrows) {
                             float z = v[0];
                             if (ids[n] < 0 || ids[n] >= m.n_items) z = __uint_as_float(0x7FC00000u);
@@ -1078,18 +998,18 @@ __device__ __forceinline__ void mlp_gen_block(const Model &m, const ReqDesc &rd,
                             if (rd.scores_out) rd.scores_out[local0 + c] = 1.0f / (1.0f + expf(-z));
                         }
                     } else {
-                        const int ks = f >> 5, dst = ((f & 31) >> 3) * 16 + col, half = (f >> 2) & 1;
+                        const int ks = f >> 5, half = (f >> 4) & 1;         // in place: the next layer's weights are packed in this order
 #pragma unroll
-                        for (int j = 0; j < 4; ++j) v[j] = fmaxf(v[j], 0.f);
+                        for (int j = 0; j < 4; ++j) v[j] = relu_nan(v[j]);
                         if constexpr (SPLIT) {
                             uint32_t lo[3], hi[3];
                             split2<3>(v[0], v[1], lo);
                             split2<3>(v[2], v[3], hi);
 #pragma unroll
                             for (int q = 0; q < 3; ++q)
-                                *(uint2 *)(out + (((size_t)(ks * 3 + q) * NC + n) * 64 + dst) * 16 + half * 8) = make_uint2(lo[q], hi[q]);
+                                *(uint2 *)(out + (((size_t)(ks * 3 + q) * NC + n) * 64 + lane) * 16 + half * 8) = make_uint2(lo[q], hi[q]);
                         } else
-                            ((float4 *)out)[(size_t)(ks * NC + n) * 128 + half * 64 + dst] = make_float4(v[0], v[1], v[2], v[3]);
+                            ((float4 *)out)[(size_t)(ks * NC + n) * 128 + half * 64 + lane] = make_float4(v[0], v[1], v[2], v[3]);
                     }
                 }
         };
@@ -1210,7 +1130,7 @@ static hipError_t mlp_gen_go(const Model &m, const Batch &b, const void *X, GenM
     return hipGetLastError();
 }
 
-// Blocks of four waves and 32 candidates where the batch fills the chip with such blocks and they fit, else eight waves
+// What k_generic_chain.hip leaves: blocks of four waves and 32 candidates where the batch fills the chip with such blocks and they fit, else eight waves
 // share 16 candidates: the shortest chain.
 template <typename T>
 static hipError_t mlp_gen_launch(const Model &m, const Batch &b, const void *X, const MlpGenericWeights &w, const float *bias1, hipStream_t s)
@@ -1227,6 +1147,7 @@ hipError_t launch_mlp_generic(const Model &m, const Batch &b, const void *X, con
                               const float *bias1, hipStream_t s)
 {
     if (b.n_blk == 0) return hipSuccess;
+    if (gen_chain_serves(m, b)) return launch_gen_chain(m, b, X, w, bias1, s);
     return m.dtype == 0 ? mlp_gen_launch<float>(m, b, X, w, bias1, s) : mlp_gen_launch<uint16_t>(m, b, X, w, bias1, s);
 }
 
@@ -1294,10 +1215,11 @@ hipError_t launch_gen_tile(const Model &m, const Batch &b, void *X, const float 
 
 // ---------------------------------------------------------------------------
 // Weights as pieces in A-fragment order: [group][row tile of 16][k-step of 32][piece][lane][8], lane (row = lane % 16,
-// g = lane / 16) holding W[group rows_per_group + 16 rt + row][32 ks + 8 g + j]; zero outside the matrix.
+// g = lane / 16) holding W[group rows_per_group + 16 rt + row][32 ks + 8 g + j]; zero outside the matrix.  in_place: column
+// 32 ks + 16 (j / 4) + 4 g + j % 4 instead, the order in which two row tiles of a 16x16 result leave a lane its features.
 // ---------------------------------------------------------------------------
 template <typename T>
-__global__ void k_pack_pieces(const T *__restrict__ w, int n_in, int col0, int rows, int ncols, int ksn, int rt_n, size_t total,
+__global__ void k_pack_pieces(const T *__restrict__ w, int n_in, int col0, int rows, int ncols, int ksn, int rt_n, bool in_place, size_t total,
                               bf16x8 *__restrict__ out)
 {
     constexpr int P = stored<T>::P;
@@ -1310,7 +1232,7 @@ __global__ void k_pack_pieces(const T *__restrict__ w, int n_in, int col0, int r
     float v[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-        const int k = 32 * ks + 8 * (lane >> 4) + j;
+        const int k = 32 * ks + (in_place ? 16 * (j >> 2) + 4 * (lane >> 4) + (j & 3) : 8 * (lane >> 4) + j);
         v[j] = row < rows && k < ncols ? ld_f<T>(w + ((size_t)group * rows + row) * n_in + col0 + k) : 0.f;
     }
     const Pieces<P> p = split8<P>(v);
@@ -1332,16 +1254,16 @@ size_t pieces_bytes(int dtype, int groups, int tiles, int ncols)
     return (size_t)groups * tiles * ((ncols + 31) / 32) * (dtype == 0 ? 3 : 1) * 1024;
 }
 
-hipError_t launch_pack_pieces(int dtype, const void *w, int groups, int rows, int tiles, int n_in, int col0, int ncols, void *out, hipStream_t s)
+hipError_t launch_pack_pieces(int dtype, const void *w, int groups, int rows, int tiles, int n_in, int col0, int ncols, bool in_place, void *out, hipStream_t s)
 {
     if (16 * tiles < rows) return hipErrorInvalidValue;
     const int ksn = (ncols + 31) / 32, rt_n = tiles;
     const size_t total = (size_t)groups * rt_n * ksn * 64;
     const dim3 grid((unsigned)((total + 255) / 256));
     if (dtype == 0)
-        hipLaunchKernelGGL(k_pack_pieces<float>, grid, dim3(256), 0, s, (const float *)w, n_in, col0, rows, ncols, ksn, rt_n, total, (bf16x8 *)out);
+        hipLaunchKernelGGL(k_pack_pieces<float>, grid, dim3(256), 0, s, (const float *)w, n_in, col0, rows, ncols, ksn, rt_n, in_place, total, (bf16x8 *)out);
     else
-        hipLaunchKernelGGL(k_pack_pieces<uint16_t>, grid, dim3(256), 0, s, (const uint16_t *)w, n_in, col0, rows, ncols, ksn, rt_n, total, (bf16x8 *)out);
+        hipLaunchKernelGGL(k_pack_pieces<uint16_t>, grid, dim3(256), 0, s, (const uint16_t *)w, n_in, col0, rows, ncols, ksn, rt_n, in_place, total, (bf16x8 *)out);
     return hipGetLastError();
 }
 
