@@ -88,10 +88,7 @@ __host__ __device__ inline size_t x_offset(const XLayout &l, uint32_t row, uint3
 __device__ __forceinline__ float bf2f(uint16_t b) { return __uint_as_float(((uint32_t)b) << 16); }
 __device__ __forceinline__ uint16_t f2bf(float f)
 {
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7FFFFFFFu) > 0x7F800000u) return (uint16_t)((u >> 16) | 0x40u);
-    u += 0x7FFFu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
+    return __builtin_bit_cast(uint16_t, (__bf16)f);
 }
 template <typename T> __device__ __forceinline__ float ld_f(const T *p);
 template <> __device__ __forceinline__ float ld_f<float>(const float *p) { return *p; }
