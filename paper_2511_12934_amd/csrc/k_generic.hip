@@ -330,6 +330,24 @@ __device__ __forceinline__ float exp_neg(float x)
     return fmaf(p, e * LN2, p);
 }
 
+// f over the four groups' values of a candidate, in every lane: (0, 1), (2, 3), then both -- as a butterfly over lanes 16 and 32 away has
+// them for an f that commutes, on the vector ALU's own swaps.
+template <class F> __device__ __forceinline__ float groups_join(float v, F f)
+{
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = f(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return f(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+
+// v / s for 1 <= s, 1 / s rounded in r: the quotient's estimate and one correction round as the division does (Markstein), in three
+// instructions instead of twelve -- nothing needs scaling where s is neither large nor small.
+__device__ __forceinline__ float quotient(float v, float s, float r)
+{
+    const float q = v * r;
+    return fmaf(fmaf(-q, s, v), r, q);
+}
+
 // fragments of a chunk of keys: K (key tile, k-step), then V (feature tile)
 __host__ __device__ constexpr int gen_chunk_frags(int ft) { return (ft + 1) / 2 * 2 + ft; }
 
@@ -530,15 +548,14 @@ __device__ __forceinline__ void attn_gen_block(const Model &m, const ReqDesc &rd
                 for (int f = 0; f < 2 * KS; ++f) qb[f] = qs[f] = f32x4{0.f, 0.f, 0.f, 0.f};
                 ask_wq(h, 0);
                 for (int ks0 = 0; ks0 < ksn; ks0 += UQ) {
-                    float v[UQ][8];
+                    Pieces<P> e[UQ];
 #pragma unroll
-                    for (int u = 0; u < UQ; ++u) load8<T>(er + 32 * (ks0 + u) + 8 * g, m.d_item - 32 * (ks0 + u) - 8 * g, v[u]);
+                    for (int u = 0; u < UQ; ++u) e[u] = load_pieces(er + 32 * (ks0 + u) + 8 * g, m.d_item - 32 * (ks0 + u) - 8 * g);
 #pragma unroll
                     for (int u = 0; u < UQ; ++u) {
                         if (ks0 + u >= ksn) continue;
-                        const Pieces<P> e = split8<P>(v[u]);
 #pragma unroll
-                        for (int f = 0; f < 2 * KS; ++f) mfma_pieces(wf[u][f], e, qb[f], qs[f]);
+                        for (int f = 0; f < 2 * KS; ++f) mfma_pieces(wf[u][f], e[u], qb[f], qs[f]);
                     }
                     if (ks0 + UQ < ksn) ask_wq(h, ks0 + UQ);
                 }
@@ -599,9 +616,8 @@ __device__ __forceinline__ void attn_gen_block(const Model &m, const ReqDesc &rd
                 if (ragged)
 #pragma unroll
                     for (int j = 0; j < 8; ++j) sc[j] = past(j) ? -INFINITY : sc[j];
-                float top = fmaxf(fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3])), fmaxf(fmaxf(sc[4], sc[5]), fmaxf(sc[6], sc[7])));
-                top = fmaxf(top, __shfl_xor(top, 16, 64));
-                top = fmaxf(top, __shfl_xor(top, 32, 64));
+                auto higher = [](float a, float b) { return __builtin_elementwise_maximum(a, b); };      // three at a time; NaN stays
+                const float top = groups_join(higher(higher(higher(sc[0], sc[1]), sc[2]), higher(higher(higher(sc[3], sc[4]), sc[5]), higher(sc[6], sc[7]))), higher);
                 if (__any(top > mx)) {                          // (the first chunk: 0 times what is 0)
                     const float now = fmaxf(mx, top), f = ch == 0 ? 0.f : exp_neg(mx - now);
                     mx = now;
@@ -631,9 +647,9 @@ __device__ __forceinline__ void attn_gen_block(const Model &m, const ReqDesc &rd
                 }
             }
             // the block's result; `odd` is NaN if a lane met a value that is not finite
-            sum += __shfl_xor(sum, 16, 64);
-            sum += __shfl_xor(sum, 32, 64);
+            sum = groups_join(sum, [](float a, float b) { return a + b; });
             float odd = sum * 0.f;
+            const float inv = 1.0f / sum;                       // sum: 1 (the highest score's weight) to L
 #pragma unroll
             for (int f = 0; f < FT; ++f) {
                 float v[4];
@@ -641,7 +657,7 @@ __device__ __forceinline__ void attn_gen_block(const Model &m, const ReqDesc &rd
                 for (int i = 0; i < 4; ++i) {
                     v[i] = ob[f][i] + os[f][i];
                     odd = fmaf(v[i], 0.f, odd);
-                    v[i] = L > 0 ? v[i] / sum : 0.f;
+                    v[i] = L > 0 ? quotient(v[i], sum, inv) : 0.f;
                 }
                 const int k = 16 * f + 4 * g;
                 T *out = xr + m.d_item + o + k;

@@ -84,4 +84,16 @@ template <> __device__ __forceinline__ void load8<uint16_t>(const uint16_t *p, i
         v[2 * j + 1] = __uint_as_float(w[j] & 0xFFFF0000u);
     }
 }
+// the same as pieces: a bf16 element is one
+__device__ __forceinline__ Pieces<3> load_pieces(const float *p, int n)
+{
+    float v[8];
+    load8<float>(p, n, v);
+    return split8<3>(v);
+}
+__device__ __forceinline__ Pieces<1> load_pieces(const uint16_t *p, int n)
+{
+    return {{__builtin_bit_cast(bf16x8, n > 0 ? *(const uint4 *)p : make_uint4(0, 0, 0, 0))}};
+}
+
 }  // namespace aif
