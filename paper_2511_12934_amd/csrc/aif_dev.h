@@ -183,9 +183,10 @@ hipError_t launch_topk_few(const TopkDesc *descs /*host*/, int n_req, int k, int
 hipError_t launch_pack_transposed(int dtype, const void *w, int n_out, int n_in, int col0, int ncols,
                                   float *wt /*[ncols, n_out]*/, hipStream_t s);
 // ... and as bf16 pieces in MFMA fragment order (k_generic.hip): `groups` matrices of `rows` rows each, one below the other,
-// each as `tiles` row tiles of 16 (zeros past its rows); pieces_bytes: what `out` has to hold
+// each as `tiles` row tiles of 16 (zeros past its rows); hidden: they meet a hidden layer's outputs as the kernels hold them;
+// pieces_bytes: what `out` has to hold
 size_t pieces_bytes(int dtype, int groups, int tiles, int ncols);
-hipError_t launch_pack_pieces(int dtype, const void *w, int groups, int rows, int tiles, int n_in, int col0, int ncols, bool in_place, void *out,
+hipError_t launch_pack_pieces(int dtype, const void *w, int groups, int rows, int tiles, int n_in, int col0, int ncols, bool hidden, void *out,
                               hipStream_t s);
 // Row tiles of a layer's weights: whole k-steps of the layer that reads its outputs.
 constexpr int layer_tiles(int rows) { return (rows + 31) / 32 * 2; }

@@ -1016,7 +1016,7 @@ __device__ __forceinline__ void mlp_gen_block(const Model &m, const ReqDesc &rd,
                     } else {
                         const int ks = f >> 5, half = (f >> 4) & 1;         // in place: the next layer's weights are packed in this order
 #pragma unroll
-                        for (int j = 0; j < 4; ++j) v[j] = relu_nan(v[j]);
+                        for (int j = 0; j < 4; ++j) v[j] = relu_twice(v[j]);
                         if constexpr (SPLIT) {
                             uint32_t lo[3], hi[3];
                             split2<3>(v[0], v[1], lo);
@@ -1231,11 +1231,12 @@ hipError_t launch_gen_tile(const Model &m, const Batch &b, void *X, const float 
 
 // ---------------------------------------------------------------------------
 // Weights as pieces in A-fragment order: [group][row tile of 16][k-step of 32][piece][lane][8], lane (row = lane % 16,
-// g = lane / 16) holding W[group rows_per_group + 16 rt + row][32 ks + 8 g + j]; zero outside the matrix.  in_place: column
-// 32 ks + 16 (j / 4) + 4 g + j % 4 instead, the order in which two row tiles of a 16x16 result leave a lane its features.
+// g = lane / 16) holding W[group rows_per_group + 16 rt + row][32 ks + 8 g + j]; zero outside the matrix.  hidden: column
+// 32 ks + 16 (j / 4) + 4 g + j % 4 instead, the order in which two row tiles of a 16x16 result leave a lane its features, and half
+// the weight (relu_twice).
 // ---------------------------------------------------------------------------
 template <typename T>
-__global__ void k_pack_pieces(const T *__restrict__ w, int n_in, int col0, int rows, int ncols, int ksn, int rt_n, bool in_place, size_t total,
+__global__ void k_pack_pieces(const T *__restrict__ w, int n_in, int col0, int rows, int ncols, int ksn, int rt_n, bool hidden, size_t total,
                               bf16x8 *__restrict__ out)
 {
     constexpr int P = stored<T>::P;
@@ -1248,8 +1249,8 @@ __global__ void k_pack_pieces(const T *__restrict__ w, int n_in, int col0, int r
     float v[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-        const int k = 32 * ks + (in_place ? 16 * (j >> 2) + 4 * (lane >> 4) + (j & 3) : 8 * (lane >> 4) + j);
-        v[j] = row < rows && k < ncols ? ld_f<T>(w + ((size_t)group * rows + row) * n_in + col0 + k) : 0.f;
+        const int k = 32 * ks + (hidden ? 16 * (j >> 2) + 4 * (lane >> 4) + (j & 3) : 8 * (lane >> 4) + j);
+        v[j] = (hidden ? 0.5f : 1.f) * (row < rows && k < ncols ? ld_f<T>(w + ((size_t)group * rows + row) * n_in + col0 + k) : 0.f);
     }
     const Pieces<P> p = split8<P>(v);
 #pragma unroll
@@ -1270,16 +1271,16 @@ size_t pieces_bytes(int dtype, int groups, int tiles, int ncols)
     return (size_t)groups * tiles * ((ncols + 31) / 32) * (dtype == 0 ? 3 : 1) * 1024;
 }
 
-hipError_t launch_pack_pieces(int dtype, const void *w, int groups, int rows, int tiles, int n_in, int col0, int ncols, bool in_place, void *out, hipStream_t s)
+hipError_t launch_pack_pieces(int dtype, const void *w, int groups, int rows, int tiles, int n_in, int col0, int ncols, bool hidden, void *out, hipStream_t s)
 {
     if (16 * tiles < rows) return hipErrorInvalidValue;
     const int ksn = (ncols + 31) / 32, rt_n = tiles;
     const size_t total = (size_t)groups * rt_n * ksn * 64;
     const dim3 grid((unsigned)((total + 255) / 256));
     if (dtype == 0)
-        hipLaunchKernelGGL(k_pack_pieces<float>, grid, dim3(256), 0, s, (const float *)w, n_in, col0, rows, ncols, ksn, rt_n, in_place, total, (bf16x8 *)out);
+        hipLaunchKernelGGL(k_pack_pieces<float>, grid, dim3(256), 0, s, (const float *)w, n_in, col0, rows, ncols, ksn, rt_n, hidden, total, (bf16x8 *)out);
     else
-        hipLaunchKernelGGL(k_pack_pieces<uint16_t>, grid, dim3(256), 0, s, (const uint16_t *)w, n_in, col0, rows, ncols, ksn, rt_n, in_place, total, (bf16x8 *)out);
+        hipLaunchKernelGGL(k_pack_pieces<uint16_t>, grid, dim3(256), 0, s, (const uint16_t *)w, n_in, col0, rows, ncols, ksn, rt_n, hidden, total, (bf16x8 *)out);
     return hipGetLastError();
 }
 

@@ -194,7 +194,7 @@ __global__ __launch_bounds__(64 * CHAIN_WAVES, 2) void k_mlp_gen_chain(Model m, 
         };
         auto activate = [&](float (&v)[8]) __attribute__((always_inline)) {
 #pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = relu_nan(v[j]);
+            for (int j = 0; j < 8; ++j) v[j] = relu_twice(v[j]);
             return split8<3>(v);
         };
         Pieces<3> y[NC][Q1];

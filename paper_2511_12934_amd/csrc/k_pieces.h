@@ -48,8 +48,9 @@ template <int P> __device__ __forceinline__ Pieces<P> split8(const float *v)
     return o;
 }
 
-// max(x, 0), NaN for a NaN: whatever is not finite comes up again in the pieces and in all that follows from them
-__device__ __forceinline__ float relu_nan(float x) { return __builtin_elementwise_maximum(x, 0.f); }
+// 2 max(x, 0) in one instruction, NaN for a NaN and for minus infinity (a sum of pieces may overflow where the plain one does not): whatever
+// is not finite comes up again in the pieces and in all that follows from them.  The weights that meet it are packed halved.
+__device__ __forceinline__ float relu_twice(float x) { return x + __builtin_fabsf(x); }
 
 // acc += a * b over the k-step's 32 terms.  The product of the leading pieces goes to `big`, the others, at most 2^-8 of
 // it, to `small`: they are added to each other first, so `big` is rounded once per k-step.
