@@ -37,10 +37,12 @@ struct UserArguments {
 };
 static_assert(USER_FEW <= 64, "a lane a user");
 
-// the tables of such a call, by its first blocks of 256 threads
-__device__ __forceinline__ void user_fill(const UserFew &f, int i)
+// the tables of such a call, by its first blocks of 256 threads; room: USER_FILL_ROOM in LDS (the caller's: a widest projection's rows
+// leave no other)
+constexpr int USER_FILL_ROOM = 2 * USER_FEW;
+__device__ __forceinline__ void user_fill(const UserFew &f, int i, int *room)
 {
-    __shared__ int first_blk[USER_FEW], first_group[USER_FEW];
+    int *const first_blk = room, *const first_group = room + USER_FEW;
     const auto args = kernel_arg<UserFew>(0);
     if (threadIdx.x < 64) {
         const int u = threadIdx.x < f.n_users ? threadIdx.x : 0, ng = threadIdx.x < f.n_users ? args->groups_of[u] : 0;
@@ -207,7 +209,8 @@ template <int D, bool PACK>
 __global__ __launch_bounds__(256) void k_user_project_mfma_few(UserFew few /* first: kernel_arg */, UserWeights w, int n_row_blk, uint16_t *__restrict__ X, UserPack pk)
 {
     if ((int)blockIdx.x < few.n_fill) {
-        user_fill(few, blockIdx.x * 256 + threadIdx.x);
+        __shared__ int room[USER_FILL_ROOM];
+        user_fill(few, blockIdx.x * 256 + threadIdx.x, room);
         return;
     }
     user_project_mfma_block<D, PACK>((int)blockIdx.x - few.n_fill, w, UserArguments{few.n_users}, n_row_blk, X, pk);
@@ -408,8 +411,9 @@ template <typename T>
 __global__ __launch_bounds__(256) void k_user_project_few(UserFew few /* first: kernel_arg */, UserWeights w, int n_row_blk, T *__restrict__ X)
 {
     extern __shared__ __align__(16) float xs[];
+    static_assert(USER_FILL_ROOM <= 4 * USER_PROJ_ROWS, "the narrowest rows are 16 bytes");
     if ((int)blockIdx.x < few.n_fill) {
-        user_fill(few, blockIdx.x * 256 + threadIdx.x);
+        user_fill(few, blockIdx.x * 256 + threadIdx.x, (int *)xs);
         return;
     }
     user_project_block<T>((int)blockIdx.x - few.n_fill, w, UserArguments{few.n_users}, n_row_blk, X, xs);
@@ -453,15 +457,17 @@ hipError_t launch_user_project(const UserWeights &w, const UserDesc *users, cons
     const size_t lds = user_project_lds_bytes(w.d_raw);
     const int n_row_blk = n_blk * (ROW_BLOCK / USER_PROJ_ROWS);
     const dim3 grid(n_fill + n_row_blk + n_users);
+    hipError_t e = hipSuccess;
     auto go = [&](auto t) {
         using T = decltype(t);
-        (void)hipFuncSetAttribute(few ? (const void *)k_user_project_few<T> : (const void *)k_user_project<T>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        e = hipFuncSetAttribute(few ? (const void *)k_user_project_few<T> : (const void *)k_user_project<T>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return;
         if (few) hipLaunchKernelGGL(k_user_project_few<T>, grid, dim3(256), lds, s, *few, w, n_row_blk, (T *)X);
         else hipLaunchKernelGGL(k_user_project<T>, grid, dim3(256), lds, s, w, users, blk_req, n_row_blk, (T *)X);
     };
     if (w.dtype == 0) go(float{});
     else go(uint16_t{});
-    return hipGetLastError();
+    return e != hipSuccess ? e : hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------

@@ -30,3 +30,17 @@ def test_descriptors_in_the_arguments_and_uploaded_give_the_same_bits(R, torch, 
     for r, (a, b) in enumerate(zip(got, ref)):
         assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1]), r
     check_user(dtype, got[0], oracle_user(model, users[0]), d, f"L={lens[0]}")
+
+
+# the widest rows that a context takes: 160 KB of LDS a block of the projection off the matrix cores
+@pytest.mark.parametrize("n_users", [3, 65])
+@pytest.mark.parametrize("dtype,d", [("f32", 8), ("bf16", 16)])
+def test_few_users_of_the_widest_rows(R, torch, dtype, d, n_users):  # noqa: F811
+    cfg = wl.UserNetConfig("T", 17, dtype, n_users, 40, 1280, d)
+    _say(f"few users {dtype} 1280 -> {d}, {n_users}")
+    model = wl.make_user_net_model(cfg, bias_scale=0.05)
+    rng = np.random.default_rng(23)
+    users = [wl.make_raw_user(cfg, rng, seq_len=int(l)) for l in [40, 0, 33, *rng.integers(0, 41, n_users)][:n_users]]
+    got, _, _ = run_users(R, torch, cfg, model, users)
+    for r in range(3):
+        check_user(dtype, got[r], oracle_user(model, users[r]), d, f"user {r}")
