@@ -472,6 +472,9 @@ __device__ __forceinline__ void attn_gen_block(const Model &m, const ReqDesc &rd
             const T *uc = (const T *)rd.cross_vecs;
             const bool had = m.cross_mode == 1 && !m.cross_in_mlp;
             constexpr int U = 4;
+            // the user's pieces asked for beside the row's, but where their 16 registers cost the second block of a unit: resident keys
+            // of heads of up to 64 (those of fp32 with W_q have one block anyway)
+            constexpr bool ASK = !(RES && !ROLES && FT == 4 && !(WQ && P == 3));
             const int pieces = m.d_item / VEC;
             if (table || had)
                 for (int p0 = 0; p0 < pieces; p0 += 4 * U) {
@@ -481,7 +484,7 @@ __device__ __forceinline__ void attn_gen_block(const Model &m, const ReqDesc &rd
                         const int p = p0 + 4 * u + g;
                         v[u] = *(const uint4 *)(er + (size_t)(p < pieces ? p : 0) * VEC);
                     }
-                    if (had)
+                    if (ASK && had)
 #pragma unroll
                         for (int u = 0; u < U; ++u) w[u] = *(const uint4 *)(uc + (size_t)(p0 + 4 * u + g < pieces ? p0 + 4 * u + g : 0) * VEC);
 #pragma unroll
@@ -490,6 +493,7 @@ __device__ __forceinline__ void attn_gen_block(const Model &m, const ReqDesc &rd
                         if (p >= pieces || !live) continue;
                         if (table) *(uint4 *)(xr + (size_t)p * VEC) = v[u];
                         if (had) {
+                            if constexpr (!ASK) w[u] = *(const uint4 *)(uc + (size_t)p * VEC);
                             const T *e = (const T *)&v[u], *x = (const T *)&w[u];
                             __align__(16) T o[VEC];
 #pragma unroll
@@ -523,18 +527,20 @@ __device__ __forceinline__ void attn_gen_block(const Model &m, const ReqDesc &rd
         }
         // W_q's k-steps, UQ at a time where there are registers for it
         constexpr int UQ = WQ && KS == 1 && !ROLES && P == 1 ? 2 : 1;
+        constexpr bool ASK_WQ = RES || WV != 4 || KS * P <= 6;  // a k-step ahead (the widest fp32 heads' small blocks: 96 registers, which are not there)
         const int ksn = (m.d_item + 31) / 32;
         Pieces<P> wf[UQ][2 * KS];
-        auto ask_wq = [&](int h, int ks0) __attribute__((always_inline)) {
+        auto ask_wq_tile = [&](int h, int ks0, int f) __attribute__((always_inline)) {
             const bf16x8 *wh = wqp + (size_t)h * query_tiles(FT) * ksn * P * 64 + lane;
 #pragma unroll
             for (int u = 0; u < UQ; ++u)
 #pragma unroll
-                for (int f = 0; f < 2 * KS; ++f)
-#pragma unroll
-                    for (int q = 0; q < P; ++q) wf[u][f].p[q] = wh[((size_t)(f * ksn + min(ks0 + u, ksn - 1)) * P + q) * 64];
+                for (int q = 0; q < P; ++q) wf[u][f].p[q] = wh[((size_t)(f * ksn + min(ks0 + u, ksn - 1)) * P + q) * 64];
         };
-        
+        auto ask_wq = [&](int h, int ks0) __attribute__((always_inline)) {
+#pragma unroll
+            for (int f = 0; f < 2 * KS; ++f) ask_wq_tile(h, ks0, f);
+        };
         if (ROLES) locate();
 
         for (int h = 0; h < m.n_heads; ++h) {
@@ -546,7 +552,7 @@ __device__ __forceinline__ void attn_gen_block(const Model &m, const ReqDesc &rd
                 f32x4 qb[2 * KS], qs[2 * KS];
 #pragma unroll
                 for (int f = 0; f < 2 * KS; ++f) qb[f] = qs[f] = f32x4{0.f, 0.f, 0.f, 0.f};
-                ask_wq(h, 0);
+                if (ASK_WQ) ask_wq(h, 0);
                 for (int ks0 = 0; ks0 < ksn; ks0 += UQ) {
                     Pieces<P> e[UQ];
 #pragma unroll
@@ -555,9 +561,12 @@ __device__ __forceinline__ void attn_gen_block(const Model &m, const ReqDesc &rd
                     for (int u = 0; u < UQ; ++u) {
                         if (ks0 + u >= ksn) continue;
 #pragma unroll
-                        for (int f = 0; f < 2 * KS; ++f) mfma_pieces(wf[u][f], e[u], qb[f], qs[f]);
+                        for (int f = 0; f < 2 * KS; ++f) {
+                            if (!ASK_WQ) ask_wq_tile(h, ks0, f);
+                            mfma_pieces(wf[u][f], e[u], qb[f], qs[f]);
+                        }
                     }
-                    if (ks0 + UQ < ksn) ask_wq(h, ks0 + UQ);
+                    if (ASK_WQ && ks0 + UQ < ksn) ask_wq(h, ks0 + UQ);
                 }
 #pragma unroll
                 for (int s = 0; s < KS; ++s) {
