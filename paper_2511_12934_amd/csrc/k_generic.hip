@@ -741,36 +741,57 @@ static void attn_gen_go(const Model &m, const Batch &b, void *X, const void *tab
 // Three forms of the same arithmetic (the same bits): a batch of many ROW_BLOCKs whose longest keys leave room for two
 // blocks on a compute unit keeps them resident, a block of eight waves to a whole ROW_BLOCK; other large batches take blocks of
 // eight waves and half a ROW_BLOCK, 32 keys at a time; small ones blocks of four.
-// The lines, us a launch with the keys resident | 32 at a time (queries of W_q; 512 blocks of resident keys are a round):
-// heads of up to 32, blocks   384: fp32, 50 keys  33.8 |  33.3   bf16, 50 keys  27.9 | 24.2   bf16, 200 keys  44.0 | 38.3
-//                             424:                33.1 |  34.5 (lists of all lengths)
-//                             432:                34.5 |  39.0                  28.0 | 28.1                   44.0 | 45.9
-//                             520:                54.1 |  46.4                  37.9 | 32.8                   58.9 | 55.0
-//                             640:                                              37.8 | 34.2
-//                             800:                66.4 |  63.4                  46.0 | 44.0                   75.3 | 74.6
-//                             880:                69.7 |  65.4                  46.4 | 44.8                   75.2 | 77.2
-//                           1,120:               103.9 |  88.9                  57.1 | 55.4                   92.8 | 95.4
-//                whole calls, 2,560:             492.7 | 486.5                 265.9 | 274.2     512 keys    456.5 | 487.4
-// heads of 64, blocks         128: fp32, 50 keys  63.6 |  53.1   bf16, 128 keys 50.7 | 40.8     (whole calls)
-//                             144:                70.4 |  73.2                  57.3 | 59.8
-//                             512:               143.0 | 152.4                  89.0 | 108.1
-// so, narrow heads, in rounds at least 4/5 full: the only one, or histories of more than two chunks (beyond one round blocks of
-// few keys end unevenly enough to need no rounds); wide ones as soon as half-ROW_BLOCKs, one to a unit, need a second round.  LDS:
-// two blocks fit up to 80 KB; at 64 to 80 KB resident keys are 7 % faster on 2,560 blocks and 5 % slower on 640; at 96 to 128 KB
-// (one block a unit) 7 to 35 % slower.
-constexpr int GEN_SMALL = 256, GEN_RES_BLOCKS = 512;
+// The lines, us a call with the keys resident | 32 at a time (one build; queries of W_q over rows of 64, a head of one hidden layer):
+// heads of 32, blocks    fp32, 50 keys    fp32, 128 keys    bf16, 50 keys    bf16, 200 keys
+//       384               69.7 |  68.8     73.2 |  74.0      42.0 |  41.9     56.6 |  53.6    (500 keys 84.5 | 76.5)
+//       432               72.7 |  77.8     76.4 |  83.9      42.8 |  46.2     57.3 |  60.9
+//       512               81.4 |  84.7     84.2 |  90.5      44.5 |  47.5     58.6 |  62.3
+//       528               96.4 |  91.1    101.8 |  98.6      56.7 |  53.7     74.7 |  72.4
+//       640              103.9 |  99.5    109.5 | 107.1      57.6 |  54.8     75.5 |  73.5
+//       656              133.0 | 134.1    138.6 | 141.6      85.7 |  86.5                     (8 users; the others 16)
+//       768              114.5 | 116.3    120.1 | 123.7      60.8 |  61.8     78.7 |  84.1
+//       832              126.6 | 125.3    132.2 | 134.8      69.6 |  68.4     93.8 |  94.3    (bf16, 128 keys: 32 at a time 1.5 % faster)
+//       960              136.1 | 140.2    141.8 | 150.2      71.0 |  73.5     95.1 | 103.1
+//     1,024              141.3 | 145.5    149.9 | 155.3      72.0 |  74.8     96.0 | 104.3
+//     1,120              159.6 | 156.4    169.4 | 168.8      82.4 |  81.1    111.4 | 114.5
+//     1,280              186.2 | 183.4    192.8 | 194.9      84.9 |  87.5    113.5 | 124.5
+//     2,048              369.5 | 370.7    380.2 | 381.7     168.5 | 173.9    212.7 | 231.6
+//     2,560              459.6 | 458.3    472.4 | 469.5     206.6 | 213.6    261.0 | 285.8
+// lists and histories of all lengths, 492: 82.6 |  85.5    85.9 |  92.1      48.4 |  50.3     60.6 |  61.7
+//     653                111.5 | 105.8    116.6 | 112.6      65.0 |  60.1     80.0 |  72.5
+//     731                117.4 | 113.8    124.7 | 121.7      66.9 |  62.7     80.5 |  76.8
+//     969                139.0 | 141.3    146.4 | 151.8      74.6 |  75.1     93.2 |  93.1
+//   1,255                181.3 | 177.8    191.9 | 191.3      89.7 |  87.8    109.7 | 109.7
+//   1,922                334.4 | 334.4    345.0 | 343.4     149.3 | 151.4    177.9 | 184.0
+// heads of 64, blocks     fp32, 50 keys    no W_q            bf16, 50 keys    bf16, 128 keys
+//       128               54.4 |  42.3     50.0 |  40.5      38.1 |  30.7     42.3 |  33.8
+//       144               54.1 |  56.1     50.9 |  51.6      34.6 |  40.5     39.5 |  47.9
+//       384               91.6 |  87.4     73.9 |  80.1      49.3 |  56.1     56.4 |  66.4
+//       512              101.4 | 110.5     90.2 | 100.8      50.5 |  65.6     57.8 |  79.9
+//     1,280              250.4 | 269.4    233.0 | 247.1      97.3 | 131.3    113.2 | 166.6
+// Blocks of resident keys go 256 at a time (two share a unit), half-ROW_BLOCKs at 128 ROW_BLOCKs a time: the streamed form is the faster where
+// it saves half of one.  So, narrow heads: resident in the only round of 512 if it is 4/5 full; then from seven times 128 on by the parity, long
+// histories also where the other rounds make up for the half (bf16) or nothing is lost (fp32, seven); not at six, where lists of all
+// lengths lose 3 to 7 % and like ones gain 2 to 6, and fp32 of short histories not beyond eight (within 1.5 % either way).
+// Wide ones as soon as half-ROW_BLOCKs, one to a unit, need a second round.  LDS: two blocks fit up to 80 KB; at 64 to 80 KB resident keys
+// are 7 % faster on 2,560 blocks and 5 % slower on 640; at 96 to 128 KB (one block a unit) 7 to 35 % slower.
+constexpr int GEN_SMALL = 256;
 constexpr size_t GEN_RES_LDS = 64 * 1024;
-static bool narrow_keys_stay(int n_blk, int longest)
+static bool narrow_keys_stay(int dtype, int n_blk, int longest)
 {
-    const int rounds = (n_blk + GEN_RES_BLOCKS - 1) / GEN_RES_BLOCKS;
-    return 5 * n_blk >= 4 * rounds * GEN_RES_BLOCKS && (rounds == 1 || longest > 2 * GEN_KEYS);
+    if (n_blk <= 2 * GEN_SMALL) return 5 * n_blk >= 8 * GEN_SMALL;
+    const int halves = (n_blk + GEN_SMALL / 2 - 1) / (GEN_SMALL / 2);
+    const bool lengthy = longest > 2 * GEN_KEYS, bf16 = dtype == 1;
+    if (halves < 7) return false;
+    if (halves % 2) return lengthy && (bf16 ? halves > 10 : halves == 7);
+    return halves == 8 || lengthy || (bf16 && halves > 10);
 }
 template <typename T, int FT>
 static void attn_gen_ft(const Model &m, const Batch &b, void *X, const void *table, const void *wqp, const float *wq, int32_t *bad,
                         int longest, hipStream_t s)
 {
     const size_t lds = gen_keys_lds<T, FT>(m, longest);
-    if ((FT <= 2 ? narrow_keys_stay(b.n_blk, longest) : b.n_blk > GEN_SMALL / 2) && lds <= GEN_RES_LDS) attn_gen_go<T, FT, 8, true>(m, b, X, table, wqp, wq, bad, lds, s);
+    if ((FT <= 2 ? narrow_keys_stay(m.dtype, b.n_blk, longest) : b.n_blk > GEN_SMALL / 2) && lds <= GEN_RES_LDS) attn_gen_go<T, FT, 8, true>(m, b, X, table, wqp, wq, bad, lds, s);
     else if (b.n_blk >= GEN_SMALL / 2) attn_gen_go<T, FT, 8, false>(m, b, X, table, wqp, wq, bad, 0, s);
     else attn_gen_go<T, FT, 4, false>(m, b, X, table, wqp, wq, bad, 0, s);
 }
