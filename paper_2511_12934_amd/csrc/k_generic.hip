@@ -775,12 +775,11 @@ static void attn_gen_go(const Model &m, const Batch &b, void *X, const void *tab
 // lengths lose 3 to 7 % and like ones gain 2 to 6, and fp32 of short histories not beyond eight (within 1.5 % either way).
 // Wide ones as soon as half-ROW_BLOCKs, one to a unit, need a second round.  LDS: two blocks fit up to 80 KB; at 64 to 80 KB resident keys
 // are 7 % faster on 2,560 blocks and 5 % slower on 640; at 96 to 128 KB (one block a unit) 7 to 35 % slower.
-constexpr int GEN_SMALL = 256;
 constexpr size_t GEN_RES_LDS = 64 * 1024;
 static bool narrow_keys_stay(int dtype, int n_blk, int longest)
 {
-    if (n_blk <= 2 * GEN_SMALL) return 5 * n_blk >= 8 * GEN_SMALL;
-    const int halves = (n_blk + GEN_SMALL / 2 - 1) / (GEN_SMALL / 2);
+    const int units = compute_units(), half = units / 2, halves = (n_blk + half - 1) / half;
+    if (n_blk <= 2 * units) return 5 * n_blk >= 8 * units;
     const bool lengthy = longest > 2 * GEN_KEYS, bf16 = dtype == 1;
     if (halves < 7) return false;
     if (halves % 2) return lengthy && (bf16 ? halves > 10 : halves == 7);
@@ -791,8 +790,8 @@ static void attn_gen_ft(const Model &m, const Batch &b, void *X, const void *tab
                         int longest, hipStream_t s)
 {
     const size_t lds = gen_keys_lds<T, FT>(m, longest);
-    if ((FT <= 2 ? narrow_keys_stay(m.dtype, b.n_blk, longest) : b.n_blk > GEN_SMALL / 2) && lds <= GEN_RES_LDS) attn_gen_go<T, FT, 8, true>(m, b, X, table, wqp, wq, bad, lds, s);
-    else if (b.n_blk >= GEN_SMALL / 2) attn_gen_go<T, FT, 8, false>(m, b, X, table, wqp, wq, bad, 0, s);
+    if ((FT <= 2 ? narrow_keys_stay(m.dtype, b.n_blk, longest) : b.n_blk > compute_units() / 2) && lds <= GEN_RES_LDS) attn_gen_go<T, FT, 8, true>(m, b, X, table, wqp, wq, bad, lds, s);
+    else if (b.n_blk >= compute_units() / 2) attn_gen_go<T, FT, 8, false>(m, b, X, table, wqp, wq, bad, 0, s);
     else attn_gen_go<T, FT, 4, false>(m, b, X, table, wqp, wq, bad, 0, s);
 }
 template <typename T>
@@ -1184,7 +1183,7 @@ static hipError_t mlp_gen_launch(const Model &m, const Batch &b, const void *X, 
     constexpr size_t LDS = 160 * 1024;
     GenMlp gm{w, 0};
     int32_t off;
-    if (b.n_blk * (ROW_BLOCK / 32) >= GEN_SMALL && mlp_gen_lds(m, 2, 4, true, &off) <= LDS) return mlp_gen_go<T, 2, 4, true>(m, b, X, gm, bias1, s);
+    if (b.n_blk * (ROW_BLOCK / 32) >= compute_units() && mlp_gen_lds(m, 2, 4, true, &off) <= LDS) return mlp_gen_go<T, 2, 4, true>(m, b, X, gm, bias1, s);
     if (mlp_gen_lds(m, 1, 8, true, &off) <= LDS) return mlp_gen_go<T, 1, 8, true>(m, b, X, gm, bias1, s);
     return mlp_gen_go<T, 1, 8, false>(m, b, X, gm, bias1, s);
 }
@@ -1232,7 +1231,7 @@ bool gen_tile_serves(const Model &m, const Batch &b, int longest)
     size_t lds = 0;
     gen_head_tiles(m, [&](auto t, auto ft) { lds = gen_tile_lds<decltype(t), decltype(ft)::value>(m, longest); });
     const int blocks_per_cu = attn_gen_tiles(m.d_head) <= 2 && lds <= 80 * 1024 ? 2 : 1;
-    return lds <= 160 * 1024 && 2 * b.n_tiles <= blocks_per_cu * GEN_SMALL;
+    return lds <= 160 * 1024 && 2 * b.n_tiles <= blocks_per_cu * compute_units();
 }
 
 hipError_t launch_gen_tile(const Model &m, const Batch &b, void *X, const float *wq, const void *wq_pieces, const void *table, int32_t *bad,

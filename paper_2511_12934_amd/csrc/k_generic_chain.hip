@@ -262,18 +262,6 @@ __global__ __launch_bounds__(64 * CHAIN_WAVES, 2) void k_mlp_gen_chain(Model m, 
     }
 }
 
-static int compute_units()
-{
-    static int n = 0;
-    if (!n) {
-        int dev = 0;
-        hipDeviceProp_t prop;
-        n = (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess && prop.multiProcessorCount > 0)
-                ? prop.multiProcessorCount : 256;
-    }
-    return n;
-}
-
 static bool gen_chain_plan(const Model &m, const MlpGenericWeights &w, GenChain &gc, size_t &lds)
 {
     const int n_hidden = m.n_layers - 1;

@@ -5,6 +5,18 @@
 
 namespace aif {
 
+// what the launch rules of these kernels go by
+inline int compute_units()
+{
+    static const int n = [] {
+        int dev = 0;
+        hipDeviceProp_t prop;
+        return hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess && prop.multiProcessorCount > 0
+                   ? prop.multiProcessorCount : 256;
+    }();
+    return n;
+}
+
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
