@@ -73,7 +73,8 @@ AIF_API aif_status aif_lsh_init(const aif_lsh_config *config, const uint8_t *sig
  * it again: work enqueued on hip_stream afterwards finds both results.  A candidate id outside
  * [0, n_items) cannot fault: it reads row 0, its DIN row is NaN, its tiers are -1 and a counter read by
  * aif_lsh_poll_device_errors is bumped.  Results do not depend on how a candidate list is cut into
- * requests.  Errors: AIF_EINVAL (NULL, negative sizes, misaligned tensors), AIF_ERANGE (beyond the limits
+ * requests, nor on a request's company (the order in which a history's sums are formed is that of the context: one for max_users
+ * of up to 16, one for more).  Errors: AIF_EINVAL (NULL, negative sizes, misaligned tensors), AIF_ERANGE (beyond the limits
  * of the context), AIF_EDEVICE. */
 AIF_API aif_status aif_lsh_batch(aif_lsh_ctx *ctx, const aif_lsh_request *reqs, int32_t n_req, void *hip_stream);
 

@@ -126,7 +126,8 @@ aif_status linit(const aif_lsh_config *cfg, const uint8_t *table, aif_lsh_ctx *c
     c->max_seq_len = cfg->max_seq_len;
     c->max_candidates = cfg->max_candidates;
     c->max_users = cfg->max_users;
-    c->max_chunks = lsh_most_chunks(cfg->max_seq_len);
+    m.fine = cfg->max_users <= LSH_FEW;
+    c->max_chunks = lsh_most_chunks(m.fine, cfg->max_seq_len);
     LSH_TRY(nullptr, hipGetDevice(&c->device));
     const size_t tab = (size_t)lsh_rows(m.d_bits) * m.d_out * 4;
     c->part_stride = (c->max_chunks > 0 ? c->max_chunks : 1) * lsh_user_split(m.d_bits);
@@ -233,7 +234,7 @@ aif_status aif_lsh_batch(aif_lsh_ctx *c, const aif_lsh_request *reqs, int32_t n_
         const int nb = (q.n_cand + LSH_BLOCK - 1) / LSH_BLOCK;
         for (int j = 0; j < nb; ++j) hb[slots / LSH_BLOCK + j] = r;
         slots += nb * LSH_BLOCK;
-        const int ch = lsh_chunks(q.seq_len);
+        const int ch = lsh_chunks(m.fine, q.seq_len);
         if (ch > max_chunks) max_chunks = ch;
         pairs += (int64_t)q.n_cand * q.seq_len;
         if (q.seq_len > longest) longest = q.seq_len;

@@ -8,27 +8,30 @@ namespace aif {
 constexpr int LSH_BLOCK = 256;          // candidates per scheduling block
 constexpr int LSH_TCHUNK = 1024;        // history items whose user-side sums one block forms (more for a long history)
 constexpr int LSH_MAX_CHUNKS = 64;      // chunks of one history at most
-// Chunk length of a history of L items, a multiple of 64: a tenth of it, but no shorter than LSH_TCHUNK_MIN and no longer than
-// LSH_TCHUNK, and an even share of a history that would have more than LSH_MAX_CHUNKS chunks -- every chunk's partial sums
-// ((d' + 2) d floats) are written to memory and read back, and a block walks its chunk in a chain of loads.  A function of the
-// request's own history only, like everything that decides the order of its sums.
-constexpr int LSH_TCHUNK_MIN = 128, LSH_FEW_CHUNKS = 10;
-__host__ __device__ inline int lsh_chunk_len(int L)
+// Chunk length of a history of L items, a multiple of 64: LSH_TCHUNK, or an even share of a history that would have more than
+// LSH_MAX_CHUNKS chunks -- every chunk's partial sums ((d' + 2) d floats) are written to memory and read back, and a block walks its
+// chunk in a chain of loads.  fine, contexts of at most LSH_FEW users: a tenth of the history instead, no shorter than LSH_TCHUNK_MIN, because
+// there the chain is what a call waits for; with more users the blocks are enough and each one's start counts.  us a call, 1,024 | fine:
+// 1 user x 1,000 candidates x 1,000 items 31.8 | 22.0, 8 x 1,000 x 2,000 (128 bits, fp32) 73.2 | 49.1, 16 x 2,000 x 1,000 48.5 | 40.0,
+// 16 x 10^4 x 3,000 94.7 | 95.0; 24 x 10^4 x 3,000 112.3 | 115.8, 64 x 10^4 x 1,000 131.0 | 141.9, 200 x 4,000 x 1,000 163 | 188, 1,000 x 1,000 x 400 213 | 272.
+// A function of the request's history, the model and the context's size alone, like everything that decides the order of its sums.
+constexpr int LSH_FEW = 16, LSH_TCHUNK_MIN = 128, LSH_FEW_CHUNKS = 10;
+__host__ __device__ inline int lsh_chunk_len(bool fine, int L)
 {
     if (L > LSH_TCHUNK * LSH_MAX_CHUNKS) return ((L - 1) / LSH_MAX_CHUNKS + 64) / 64 * 64;
     const int share = ((L + LSH_FEW_CHUNKS - 1) / LSH_FEW_CHUNKS + 63) / 64 * 64;
-    return share < LSH_TCHUNK_MIN ? LSH_TCHUNK_MIN : share > LSH_TCHUNK ? LSH_TCHUNK : share;
+    return !fine || share > LSH_TCHUNK ? LSH_TCHUNK : share < LSH_TCHUNK_MIN ? LSH_TCHUNK_MIN : share;
 }
-__host__ __device__ inline int lsh_chunks(int L)
+__host__ __device__ inline int lsh_chunks(bool fine, int L)
 {
-    const int len = lsh_chunk_len(L);
+    const int len = lsh_chunk_len(fine, L);
     return (L + len - 1) / len;
 }
 // the most chunks a history of at most L items has
-inline int lsh_most_chunks(int L)
+inline int lsh_most_chunks(bool fine, int L)
 {
-    const int fine = (L + LSH_TCHUNK_MIN - 1) / LSH_TCHUNK_MIN, coarse = (L + LSH_TCHUNK - 1) / LSH_TCHUNK;
-    const int few = fine < LSH_FEW_CHUNKS ? fine : LSH_FEW_CHUNKS, most = few > coarse ? few : coarse;
+    const int shortest = (L + LSH_TCHUNK_MIN - 1) / LSH_TCHUNK_MIN, coarse = (L + LSH_TCHUNK - 1) / LSH_TCHUNK;
+    const int few = !fine ? 0 : shortest < LSH_FEW_CHUNKS ? shortest : LSH_FEW_CHUNKS, most = few > coarse ? few : coarse;
     return most < LSH_MAX_CHUNKS ? most : LSH_MAX_CHUNKS;
 }
 constexpr int LSH_MAX_TIERS = 8;
@@ -119,7 +122,6 @@ struct LshBatch {
 
 // Descriptors of a batch of at most LSH_FEW requests in a kernel's arguments: its blocks read them there and the first of them write
 // the batch's device tables, which the later kernels read.
-constexpr int LSH_FEW = 16;
 struct LshFew {
     LshReqDesc rd[LSH_FEW];
     LshReqDesc *reqs;
@@ -131,6 +133,7 @@ struct LshModel {
     int64_t n_items;
     int32_t d_bits, d_out, n_tiers;
     int32_t dtype;              // storage of U~: 0 fp32, 1 bf16
+    int32_t fine;               // lsh_chunk_len
     int32_t tier_mul;           // ceil(2^20 / d_bits): (x * tier_mul) >> 20 == x / d_bits for x <= 2048
 };
 

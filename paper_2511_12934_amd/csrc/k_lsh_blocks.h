@@ -104,7 +104,7 @@ __device__ __forceinline__ void lsh_pieces_block(const LshModel &m, const LshReq
     __shared__ float D[16][33];
     __shared__ double S[16][33];
     const int ft_n = m.d_out / 32, ks_n = m.d_bits / 16, ft = part_no % ft_n, ks = part_no / ft_n;
-    const int j = threadIdx.x & 31, shares = lsh_chunks(rd.seq_len) * lsh_user_split(m.d_bits);
+    const int j = threadIdx.x & 31, shares = lsh_chunks(m.fine, rd.seq_len) * lsh_user_split(m.d_bits);
     const size_t n = (size_t)lsh_rows(m.d_bits) * m.d_out;
     const float *p = part + (size_t)r * part_stride * n + ft * 32 + j;
     if (ks == ks_n) {

@@ -28,7 +28,7 @@
 // of the signatures a lane fetches one item's word per 64 items and every lane of a row tile receives the words of its
 // eight items by ds_bpermute, shifts its own bit to the top, and merges two signs into a pair of bf16 ones.
 //
-// Block = (chunk of lsh_chunk_len items -- 10^4 items as chunks of 640 cost 64 users 3 us --, request, up to four row tiles of 32 bits); its waves take a row tile each, and
+// Block = (chunk of lsh_chunk_len items, request, up to four row tiles of 32 bits); its waves take a row tile each, and
 // where there are fewer than four the chunk's items are shared out as well (lsh_user_split).  Loads run AHEAD
 // steps of 16 items ahead.  Two barriers a block: the majority word's parts, formed while the first items are on their way,
 // and at the end the waves' shares of total and lowest (they take the steps in turn).  All partial sums are added in a fixed order, a function of the request's own history
@@ -75,7 +75,7 @@ __device__ __forceinline__ void lsh_user_sums_block(const LshModel &m, const Lsh
     typedef uint32_t vec __attribute__((ext_vector_type(WORDS)));
     const int d = m.d_out, db = m.d_bits, rts = db / 32;
     const int groups = (rts + 3) / 4, rg = z % groups, cg = z / groups;
-    const int chunk_len = lsh_chunk_len(rd.seq_len), t_lo = chunk * chunk_len;
+    const int chunk_len = lsh_chunk_len(m.fine, rd.seq_len), t_lo = chunk * chunk_len;
     if (t_lo >= rd.seq_len) return;
     const int t_hi = min(rd.seq_len, t_lo + chunk_len);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), col = lane & 31, h = lane >> 5;
@@ -433,7 +433,7 @@ hipError_t launch_lsh_stage(const LshModel &m, const LshBatch &b, const LshFew *
 __global__ __launch_bounds__(256) void k_lsh_user_reduce(LshModel m, LshBatch b, int part_stride, const float *__restrict__ part,
                                                          float *__restrict__ A)
 {
-    const int r = blockIdx.y, shares = lsh_chunks(b.reqs[r].seq_len) * lsh_user_split(m.d_bits);
+    const int r = blockIdx.y, shares = lsh_chunks(m.fine, b.reqs[r].seq_len) * lsh_user_split(m.d_bits);
     const size_t n = (size_t)lsh_rows(m.d_bits) * m.d_out, nd = (size_t)m.d_bits * m.d_out;
     const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
     const float *p = part + (size_t)r * part_stride * n;

@@ -29,7 +29,7 @@ def din_tolerance(u_seq, L, d_bits):
     """Per output feature j.  DIN = total / 2 + (1 / 2 d') sum_k c_k D[k] with D[k] = sum_t c_tk U~[t, j].  Every U~[t, j] enters
     each of the d' sums D[k] once, and these enter the result divided by 2 d': the standard bound for a sum, n u sum|x| with
     u = 2^-24, over the d' copies gives (n / 2) 2^-24 sum_t |U~[t, j]|.  n, fp32 additions in a row: a share of the history
-    (a chunk of 1,024 items, or of ceil(L / 64) if that is more, divided among the waves that have no bits of their own) takes
+    (a chunk of at most 1,024 items, or of ceil(L / 64) if that is more, divided among the waves that have no bits of their own) takes
     one matrix instruction per 16 items and piece of the embedding, three pieces at most, two roundings each; then the
     shares' sums; then the d' bits.  Total is summed in 64 bits, eight items at a time in fp32 before that (8 / 2), and
     the two terms are put together with two roundings.  A candidate unlike the history has weighted sums in total's
