@@ -249,7 +249,7 @@ aif_status aif_lsh_batch(aif_lsh_ctx *c, const aif_lsh_request *reqs, int32_t n_
     // A small call (one that runs in line and is not timed stage by stage) in three launches; the descriptors of few requests
     // travel in the first one's arguments, and the device never reads the slot's pinned memory: no event guards it.
     const bool timed = c->prof_on && c->prof_calls < c->prof_max;
-    if (c->hist && c->din_pieces && !c->separate && !timed && !(c->side && pairs >= LSH_SIDE_PAIRS)) {
+    if (c->hist && c->din_pieces && !c->separate && !timed && !(c->side && pairs >= LSH_SIDE_PAIRS) && lsh_call_is_small(m, n_req, b.n_blk)) {
         LshFew few;
         const bool in_args = n_req <= LSH_FEW;
         if (in_args) {

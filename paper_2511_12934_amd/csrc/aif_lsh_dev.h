@@ -178,6 +178,16 @@ struct LshPiecesArgs {
     size_t stride;              // lsh_din_pieces_stride()
     int32_t part_stride, per_req;       // per_req: lsh_pieces_blocks()
 };
+// Whether a call is small: its last launch takes a wave to a tile of 32 candidates and one of 32 features, and from 1,024 blocks of 256
+// candidates x 32 features on (2,560 where the descriptors travel in the arguments) that costs more than the launches.  us a call, seven
+// launches | three: 128 users x 1,000 candidates x 300 items (64 bits: 1,024) 66.8 | 66.6, 256 x 300 x 300 (1,024) 68.0 | 65.0,
+// 128 x 100 x 300 (128 bits: 512) 74.4 | 68.1, 256 x 1,000 x 300 (32 bits: 1,024) 72.2 | 65.8; 64 x 3,000 x 500 (64 bits: 1,536) 72.8 | 73.9,
+// 128 x 1,000 x 300 (128 bits: 2,048) 88.3 | 104.2, 600 x 100 x 300 (128 bits: 2,400) 153.8 | 179.4, 128 x 3,000 x 500 (6,144) 164.5 | 202.7;
+// 16 x 10^4 x 500 (128 bits: 2,560) 110.2 | 96.4.
+inline bool lsh_call_is_small(const LshModel &m, int n_req, int n_blk)
+{
+    return (int64_t)n_blk * (m.d_out / 32) <= (n_req <= LSH_FEW ? 2560 : 1024);
+}
 inline int lsh_pieces_blocks(const LshModel &m) { return (m.d_bits / 16 + 1) * (m.d_out / 32); }
 int lsh_small_parts(int n_blk, int longest);
 int lsh_simtier_shift(const LshModel &m);
