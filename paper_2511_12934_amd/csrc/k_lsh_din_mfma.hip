@@ -43,7 +43,7 @@ template <int RT, int FT, bool ALL>
 __device__ __forceinline__ void lsh_din_block(const LshModel &m, const LshBatch &b, const uint8_t *__restrict__ sig_table, const float *__restrict__ A,
                                               const uint4 *__restrict__ pieces, size_t req_stride, int32_t *__restrict__ bad, int blk, int first, int ft0)
 {
-    constexpr int AHEAD = FT == 1 ? 8 : 3;                      // fragments of every tile in flight
+    constexpr int AHEAD = ALL ? 3 : 8;                          // fragments of every tile in flight
     const int n_ft = ALL ? FT : m.d_out / 32;
     {                                                           // a contiguous run of blocks per XCD: a user's pieces in one L2
         const int per_xcd = b.n_blk >> 3;
