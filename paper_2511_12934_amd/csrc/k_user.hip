@@ -84,8 +84,8 @@ __device__ __forceinline__ void user_fill(const UserFew &f, int i, int *room)
 
 // The projected profile: four adjacent lanes share an output feature, each takes a quarter of the input
 // features (d_raw is a multiple of four), they meet in a fixed two-step butterfly.  All of a thread's loads are
-// independent, so the row costs about one round trip to memory.
-template <typename T>
+// independent, U of them on their way, so the row costs about one round trip to memory.
+template <typename T, int U>
 __device__ __forceinline__ void project_profile(const UserWeights &w, const UserDesc &ud, T *X, int nthreads)
 {
     const T *pr = (const T *)ud.profile;
@@ -96,7 +96,7 @@ __device__ __forceinline__ void project_profile(const UserWeights &w, const User
         if (n < d) {
             const float *wr = w.wprof + (size_t)n * w.d_raw + q * chunk;
             const T *px = pr + q * chunk;
-#pragma unroll 32
+#pragma unroll U
             for (int m = 0; m < chunk; ++m) acc = fmaf(wr[m], ld_f<T>(px + m), acc);
         }
         acc += __shfl_xor(acc, 1, 64);
@@ -122,7 +122,7 @@ __device__ __forceinline__ void user_project_mfma_block(int blk, const UserWeigh
 {
     constexpr int FT = D / 32, ROWS = 128, SUB = ROW_BLOCK / ROWS;
     if (blk >= n_row_blk) {
-        project_profile<uint16_t>(w, src.desc(blk - n_row_blk), X, 256);
+        project_profile<uint16_t, 32>(w, src.desc(blk - n_row_blk), X, 256);
         return;
     }
     const int u = src.user_of(blk / SUB);
@@ -308,27 +308,36 @@ __global__ __launch_bounds__(1024) void k_user_ffn_pool(UserWeights w, const Use
     out[D + n] = X[(size_t)(ud.row_base + L) * (2 * D) + D + n];               // Eq. 3: the profile row's attention
 }
 
-// The two kernels of fp32 arithmetic below are chains of loads: rows into LDS sixteen at a time, weights 32 at a time (2 users of 60
-// positions, FFN: 12.2 us one at a time, 8.9 so).
+// The two kernels of fp32 arithmetic below are chains of loads: rows into LDS and weights sixteen at a time.  32 weights at a time are
+// more rows of them than a compute unit's L1 holds for four waves and several blocks.  us a call, one | 32 | 16 at a time, 1 user of
+// 20 positions, 256 -> 128, fp32: 87 | 77 | 58, 200 of 60: 226 | 266 to 286 | 162, 65 of 250: 169 | 163 | 119; 1,000 of 30, 40 -> 72, bf16:
+// 220 | 252 | 195.  (Rows of few features: no more passes than they have; 200 of 60, 12 -> 8: 28.9 | 28.9, with sixteen whatever the width 38.4.)
 // A feature's rows lie in quads at 4 (quad ^ feature mod RT / 4): neighbouring lanes hold neighbouring features, and rows at one place would
 // share a bank, all 64 of them.
 template <int RT> __device__ __forceinline__ int user_row_at(int m, int r) { return m * RT + (r ^ 4 * (m & (RT / 4 - 1))); }
-template <int RT, class Get> __device__ __forceinline__ void user_stage_rows(float *xs, int width, const Get &get)
+template <int RT, int U, class Get> __device__ __forceinline__ void user_stage_in(float *xs, int width, int &pass, int n, const Get &get)
 {
-    constexpr int U = 16;
-    for (int i0 = threadIdx.x; i0 < RT * width; i0 += 256 * U) {
+    for (; pass + U <= n; pass += U) {
         float v[U];
 #pragma unroll
         for (int q = 0; q < U; ++q) {
-            const int idx = min(i0 + 256 * q, RT * width - 1), r = idx / width;
+            const int idx = min(threadIdx.x + 256 * (pass + q), RT * width - 1), r = idx / width;
             v[q] = get(r, idx - r * width);
         }
 #pragma unroll
         for (int q = 0; q < U; ++q) {
-            const int idx = min(i0 + 256 * q, RT * width - 1), r = idx / width;
+            const int idx = min(threadIdx.x + 256 * (pass + q), RT * width - 1), r = idx / width;
             xs[user_row_at<RT>(idx - r * width, r)] = v[q];              // (past the end: the last one again)
         }
     }
+}
+template <int RT, class Get> __device__ __forceinline__ void user_stage_rows(float *xs, int width, const Get &get)
+{
+    const int n = (RT * width + 255) / 256;
+    int pass = 0;
+    user_stage_in<RT, 16>(xs, width, pass, n, get);
+    user_stage_in<RT, 4>(xs, width, pass, n, get);
+    user_stage_in<RT, 1>(xs, width, pass, n, get);
 }
 template <int U, class Weight, class Use> __device__ __forceinline__ void user_walk_in(int &m, int n, const Weight &weight, const Use &use)
 {
@@ -343,7 +352,7 @@ template <int U, class Weight, class Use> __device__ __forceinline__ void user_w
 template <class Weight, class Use> __device__ __forceinline__ void user_walk(int n, const Weight &weight, const Use &use)      // use(m, weight(m)) in order
 {
     int m = 0;
-    user_walk_in<32>(m, n, weight, use);
+    user_walk_in<16>(m, n, weight, use);
     user_walk_in<4>(m, n, weight, use);
     for (; m < n; ++m) use(m, weight(m));
 }
@@ -360,7 +369,7 @@ __device__ __forceinline__ void user_project_block(int blk, const UserWeights &w
 {
     constexpr int RT = USER_PROJ_ROWS, SUB = ROW_BLOCK / RT;
     if (blk >= n_row_blk) {                                     // the profiles, a block each
-        project_profile<T>(w, src.desc(blk - n_row_blk), X, 256);
+        project_profile<T, 16>(w, src.desc(blk - n_row_blk), X, 256);
         return;
     }
     const int u = src.user_of(blk / SUB);
