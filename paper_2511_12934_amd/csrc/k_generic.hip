@@ -763,6 +763,9 @@ static void attn_gen_go(const Model &m, const Batch &b, void *X, const void *tab
 //     969                139.0 | 141.3    146.4 | 151.8      74.6 |  75.1     93.2 |  93.1
 //   1,255                181.3 | 177.8    191.9 | 191.3      89.7 |  87.8    109.7 | 109.7
 //   1,922                334.4 | 334.4    345.0 | 343.4     149.3 | 151.4    177.9 | 184.0
+// one request a block, of few candidates (30 and 100 keys):
+//       600 of 130      118.8 | 124.6    130.4 | 136.8      63.2 |  67.1     73.1 |  77.8
+//       800 of 100      138.1 | 154.4    148.1 | 171.8      65.5 |  75.5     75.2 |  90.7
 // heads of 64, blocks     fp32, 50 keys    no W_q            bf16, 50 keys    bf16, 128 keys
 //       128               54.4 |  42.3     50.0 |  40.5      38.1 |  30.7     42.3 |  33.8
 //       144               54.1 |  56.1     50.9 |  51.6      34.6 |  40.5     39.5 |  47.9
@@ -772,15 +775,17 @@ static void attn_gen_go(const Model &m, const Batch &b, void *X, const void *tab
 // Blocks of resident keys go 256 at a time (two share a unit), half-ROW_BLOCKs at 128 ROW_BLOCKs a time: the streamed form is the faster where
 // it saves half of one.  So, narrow heads: resident in the only round of 512 if it is 4/5 full; then from seven times 128 on by the parity, long
 // histories also where the other rounds make up for the half (bf16) or nothing is lost (fp32, seven); not at six, where lists of all
-// lengths lose 3 to 7 % and like ones gain 2 to 6, and fp32 of short histories not beyond eight (within 1.5 % either way).
+// lengths lose 3 to 7 % and like ones gain 2 to 6, and fp32 of short histories not beyond eight (within 1.5 % either way).  Blocks of
+// few candidates (5/8 full at most) always: their keys are staged once, not for either half.
 // Wide ones as soon as half-ROW_BLOCKs, one to a unit, need a second round.  LDS: two blocks fit up to 80 KB; at 64 to 80 KB resident keys
 // are 7 % faster on 2,560 blocks and 5 % slower on 640; at 96 to 128 KB (one block a unit) 7 to 35 % slower.
 constexpr size_t GEN_RES_LDS = 64 * 1024;
-static bool narrow_keys_stay(int dtype, int n_blk, int longest)
+static bool narrow_keys_stay(const Model &m, const Batch &b, int longest)
 {
-    const int units = compute_units(), half = units / 2, halves = (n_blk + half - 1) / half;
+    const int n_blk = b.n_blk, units = compute_units(), half = units / 2, halves = (n_blk + half - 1) / half;
     if (n_blk <= 2 * units) return 5 * n_blk >= 8 * units;
-    const bool lengthy = longest > 2 * GEN_KEYS, bf16 = dtype == 1;
+    if (b.n_tiles <= n_blk * (ROW_BLOCK / X_TILE) * 5 / 8) return true;
+    const bool lengthy = longest > 2 * GEN_KEYS, bf16 = m.dtype == 1;
     if (halves < 7) return false;
     if (halves % 2) return lengthy && (bf16 ? halves > 10 : halves == 7);
     return halves == 8 || lengthy || (bf16 && halves > 10);
@@ -790,7 +795,7 @@ static void attn_gen_ft(const Model &m, const Batch &b, void *X, const void *tab
                         int longest, hipStream_t s)
 {
     const size_t lds = gen_keys_lds<T, FT>(m, longest);
-    if ((FT <= 2 ? narrow_keys_stay(m.dtype, b.n_blk, longest) : b.n_blk > compute_units() / 2) && lds <= GEN_RES_LDS) attn_gen_go<T, FT, 8, true>(m, b, X, table, wqp, wq, bad, lds, s);
+    if ((FT <= 2 ? narrow_keys_stay(m, b, longest) : b.n_blk > compute_units() / 2) && lds <= GEN_RES_LDS) attn_gen_go<T, FT, 8, true>(m, b, X, table, wqp, wq, bad, lds, s);
     else if (b.n_blk >= compute_units() / 2) attn_gen_go<T, FT, 8, false>(m, b, X, table, wqp, wq, bad, 0, s);
     else attn_gen_go<T, FT, 4, false>(m, b, X, table, wqp, wq, bad, 0, s);
 }
