@@ -263,9 +263,19 @@ AIF_API int32_t aif_last_user_slots(const aif_ctx *ctx);
 
 /* Which form of the MLP head the LAST scoring call launched: 0 = shape-agnostic fp32, 1 = the MFMA chain, 2 = MFMA, one launch
  * per layer, 3 = MFMA, layer 2 accumulating while layer 1 is produced (large batches and the widest head; same bits
- * as 1). A batch of few candidates may take a third form of 1 and 3, a workgroup to 32 candidates: the same bits, and
- * not told apart here.  -1 for a NULL context, before the first call and after one without candidates. */
+ * as 1). Batches of few candidates and the shape-agnostic heads have further forms of 0, 1 and 3 of the same bits:
+ * aif_last_forms tells them apart.  -1 for a NULL context, before the first call and after one without candidates. */
 AIF_API int32_t aif_last_mlp_kind(const aif_ctx *ctx);
+
+/* Which of the kernels that serve only some batches the LAST scoring call launched, all of the bits of the ones they stand in
+ * for: the sum of
+ *   1  attention and head of few candidates in one launch,
+ *   2  the head alone, a workgroup to a tile of 32 candidates,
+ *   4  the shape-agnostic head of a bf16 model with the activations in registers,
+ *   8  the shape-agnostic attention with all keys resident.
+ * -1 for a NULL context, before the first call and after one without candidates. */
+enum { AIF_FORM_ONE_LAUNCH = 1, AIF_FORM_HEAD_TILE = 2, AIF_FORM_HEAD_REGISTERS = 4, AIF_FORM_KEYS_RESIDENT = 8 };
+AIF_API int32_t aif_last_forms(const aif_ctx *ctx);
 
 /* Width of the contraction that layer 1 of the MLP head computes PER CANDIDATE in this context (Sec. 2: what does
  * not depend on the candidate is done once).  D_in - d_user after the user fold; where the Hadamard cross block

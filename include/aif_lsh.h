@@ -100,9 +100,15 @@ AIF_API int32_t aif_lsh_simtier_kind(const aif_lsh_ctx *ctx);
  * context. */
 AIF_API int32_t aif_lsh_din_kind(const aif_lsh_ctx *ctx);
 
+/* How the LAST aif_lsh_batch was launched (the same bits either way): 0 = a launch for each step, 1 = the same with Eq. 8 beside
+ * Eq. 9 (a large call), 2 = three launches (a small one), 3 = three whose first brings the descriptors along (of up to 16
+ * requests).  -1 for a NULL context and before the first call. */
+AIF_API int32_t aif_lsh_last_form(const aif_lsh_ctx *ctx);
+
 /* Per-kernel timing with HIP events on the caller's stream, as aif_profile_begin / _end of aif.h:
  * stages AIF_LSH_STAGE_USER (user-side sums), _DIN, _SIMTIER; ms[] and calls[] have AIF_LSH_N_STAGES
- * entries. */
+ * entries.  A timed call has a launch for each step, one after the other, whatever it is untimed (aif_lsh_last_form): the sum of
+ * its stages is not the time of an untimed small or large call. */
 typedef enum { AIF_LSH_STAGE_USER = 0, AIF_LSH_STAGE_DIN = 1, AIF_LSH_STAGE_SIMTIER = 2, AIF_LSH_N_STAGES = 3 } aif_lsh_stage;
 AIF_API aif_status aif_lsh_profile_begin(aif_lsh_ctx *ctx, int32_t max_calls);
 AIF_API aif_status aif_lsh_profile_end(aif_lsh_ctx *ctx, double *ms, int32_t *calls);

@@ -89,6 +89,10 @@ AIF_API const char *aif_user_last_error(const aif_user_ctx *ctx);
  * fp32 kernel, 1 = bf16 MFMA kernels. */
 AIF_API int32_t aif_user_attention_kind(const aif_user_ctx *ctx);
 
+/* How the LAST aif_user_precompute brought its descriptors: 0 = a launch of their own, 1 = in the projection's arguments (up to 64
+ * users).  -1 for a NULL context and before the first call. */
+AIF_API int32_t aif_user_last_form(const aif_user_ctx *ctx);
+
 /* Per-kernel timing with HIP events on the caller's stream, as aif_profile_begin / _end of aif.h:
  * stages AIF_USER_STAGE_PROJECT (Eq. 1), _ATTENTION (the attentions of Eq. 2 and Eq. 3), _FFN_POOL
  * (FFN, pooling, combined vector); ms[] and calls[] have AIF_USER_N_STAGES entries. */

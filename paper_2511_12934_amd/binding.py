@@ -22,13 +22,15 @@ EXPORTS = ("aif_score_init", "aif_score_request", "aif_score_batch", "aif_topk",
            "aif_last_error", "aif_poll_device_errors", "aif_peek_features", "aif_profile_begin",
            "aif_profile_end", "aif_stage_kind", "aif_update_rows", "aif_swap_table", "aif_score_topk",
            "aif_profile_begin_stages", "aif_profile_begin_sampled", "aif_last_user_slots", "aif_score_topk_static",
-           "aif_mlp_layer1_width", "aif_last_mlp_kind")
+           "aif_mlp_layer1_width", "aif_last_mlp_kind", "aif_last_forms")
+FORM_ONE_LAUNCH, FORM_HEAD_TILE, FORM_HEAD_REGISTERS, FORM_KEYS_RESIDENT = 1, 2, 4, 8
 STAGES = ("gather", "user_fold", "attention", "mlp", "topk")
 LSH_EXPORTS = ("aif_lsh_init", "aif_lsh_batch", "aif_lsh_destroy", "aif_lsh_last_error",
-               "aif_lsh_poll_device_errors", "aif_lsh_simtier_kind", "aif_lsh_din_kind", "aif_lsh_profile_begin", "aif_lsh_profile_end")
+               "aif_lsh_poll_device_errors", "aif_lsh_simtier_kind", "aif_lsh_din_kind", "aif_lsh_last_form", "aif_lsh_profile_begin",
+               "aif_lsh_profile_end")
 LSH_STAGES = ("user", "din", "simtier")
 USER_EXPORTS = ("aif_user_init", "aif_user_precompute", "aif_user_destroy", "aif_user_last_error",
-                "aif_user_attention_kind", "aif_user_profile_begin", "aif_user_profile_end")
+                "aif_user_attention_kind", "aif_user_last_form", "aif_user_profile_begin", "aif_user_profile_end")
 USER_STAGES = ("project", "attention", "ffn_pool")
 
 
@@ -122,6 +124,8 @@ def load():
     lib.aif_last_user_slots.argtypes = [vp]
     lib.aif_last_mlp_kind.restype = C.c_int32
     lib.aif_last_mlp_kind.argtypes = [vp]
+    lib.aif_last_forms.restype = C.c_int32
+    lib.aif_last_forms.argtypes = [vp]
     lib.aif_mlp_layer1_width.restype = C.c_int32
     lib.aif_mlp_layer1_width.argtypes = [vp]
     lib.aif_score_topk.restype = C.c_int
@@ -144,6 +148,8 @@ def load():
     lib.aif_lsh_simtier_kind.argtypes = [vp]
     lib.aif_lsh_din_kind.restype = C.c_int32
     lib.aif_lsh_din_kind.argtypes = [vp]
+    lib.aif_lsh_last_form.restype = C.c_int32
+    lib.aif_lsh_last_form.argtypes = [vp]
     lib.aif_lsh_profile_begin.restype = C.c_int
     lib.aif_lsh_profile_begin.argtypes = [vp, C.c_int32]
     lib.aif_lsh_profile_end.restype = C.c_int
@@ -158,6 +164,8 @@ def load():
     lib.aif_user_last_error.argtypes = [vp]
     lib.aif_user_attention_kind.restype = C.c_int32
     lib.aif_user_attention_kind.argtypes = [vp]
+    lib.aif_user_last_form.restype = C.c_int32
+    lib.aif_user_last_form.argtypes = [vp]
     lib.aif_user_profile_begin.restype = C.c_int
     lib.aif_user_profile_begin.argtypes = [vp, C.c_int32]
     lib.aif_user_profile_end.restype = C.c_int
@@ -312,6 +320,9 @@ class Context:
     def aif_last_mlp_kind(self) -> int:
         return int(self._lib.aif_last_mlp_kind(self._h))
 
+    def aif_last_forms(self) -> int:
+        return int(self._lib.aif_last_forms(self._h))
+
     def aif_mlp_layer1_width(self) -> int:
         return int(self._lib.aif_mlp_layer1_width(self._h))
 
@@ -383,6 +394,9 @@ class LshContext:
     def aif_lsh_simtier_kind(self) -> int:
         return int(self._lib.aif_lsh_simtier_kind(self._h))
 
+    def aif_lsh_last_form(self) -> int:
+        return int(self._lib.aif_lsh_last_form(self._h))
+
     def aif_lsh_din_kind(self) -> int:
         return int(self._lib.aif_lsh_din_kind(self._h))
 
@@ -450,6 +464,9 @@ class UserContext:
     def aif_user_precompute(self, reqs: Sequence[UserRequest], packed=None, stream: Optional[int] = None):
         arr = pack_user_requests(reqs) if packed is None else packed
         self._check(self._lib.aif_user_precompute(self._h, arr, len(reqs), _stream() if stream is None else stream))
+
+    def aif_user_last_form(self) -> int:
+        return int(self._lib.aif_user_last_form(self._h))
 
     def aif_user_attention_kind(self) -> int:
         return int(self._lib.aif_user_attention_kind(self._h))

@@ -122,6 +122,7 @@ struct aif_ctx {
     bool attn_indexed = false;        // the last scoring call's attention kernel read the item table itself
     int last_slots = 0;               // distinct users (user slots) of the last scoring call
     int last_mlp = -1;                // aif_last_mlp_kind
+    int last_forms = -1;              // aif_last_forms
     unsigned char *scratch_dev = nullptr;   // this device's copy of the file-scope scratch array (aif_score_topk_static)
     bool separate_gather = false;     // testing (AIF_SEPARATE_GATHER=1): the gather always as blocks or a launch of its own
 
@@ -232,6 +233,18 @@ MlpGenericWeights generic_weights(const aif_ctx *c)
 bool gen_one_launch(const aif_ctx *c, const Batch &b, int longest)
 {
     return c->mfma.tile && !c->mfma.attn && !c->mfma.mlp && gen_tile_serves(c->m, b, longest);
+}
+
+// aif_last_forms of a batch
+int call_forms(const Model &m, const MfmaPlan &plan, const Batch &b, bool one_launch, int longest)
+{
+    if (b.n_blk == 0) return -1;
+    if (one_launch) return AIF_FORM_ONE_LAUNCH;
+    int f = 0;
+    if (plan.mlp && plan.mlp_variant != MLP_VARIANT_LAYERS && plan.tile && mlp_tile_serves(plan.mlp_variant, m, b)) f |= AIF_FORM_HEAD_TILE;
+    if (!plan.mlp && gen_chain_serves(m, b)) f |= AIF_FORM_HEAD_REGISTERS;
+    if (!plan.attn && attn_generic_keys_stay(m, b, longest)) f |= AIF_FORM_KEYS_RESIDENT;
+    return f;
 }
 
 aif_status init_impl(const aif_config *cfg, const aif_weights *wts, aif_ctx *c)
@@ -629,6 +642,7 @@ static aif_status score_impl(aif_ctx *c, const aif_request *reqs, int32_t n_req,
         HIP_TRY(c, launch_attn_generic(m, b, c->X.p, wq, c->wq_pieces.p, rows_from, (int32_t *)c->bad.p, c->max_seq_len, longest, s));
     HIP_TRY(c, mark(3));
     c->last_mlp = mlp_kind(m, c->mfma, b);
+    c->last_forms = call_forms(m, c->mfma, b, one_launch, longest);
     if (one_launch) {
     } else if (c->mfma.mlp)
         HIP_TRY(c, launch_mlp_mfma(m, b, c->X.p, c->mfma, bf, (const float *)c->wt[m.n_layers - 1].p, (const float *)c->bias1.p, s));
@@ -823,6 +837,7 @@ aif_status aif_score_topk_static(aif_ctx *c, const aif_request *req, int32_t k, 
     else
         HIP_TRY(c, launch_attn_generic(m, b, X, wq, c->wq_pieces.p, rows_from, bad, c->max_seq_len, q.seq_len, s));
     c->last_mlp = mlp_kind(m, plan, b);
+    c->last_forms = call_forms(m, plan, b, one_launch, q.seq_len);
     if (one_launch) {
     } else if (plan.mlp)
         HIP_TRY(c, launch_mlp_mfma(m, b, X, plan, bf, (const float *)c->wt[m.n_layers - 1].p, bias1, s));
@@ -1052,6 +1067,8 @@ aif_status aif_profile_end(aif_ctx *c, double *ms_sum, int32_t *n_calls)
 
 int32_t aif_last_user_slots(const aif_ctx *c) { return c ? c->last_slots : -1; }
 int32_t aif_last_mlp_kind(const aif_ctx *c) { return c ? c->last_mlp : -1; }
+
+int32_t aif_last_forms(const aif_ctx *c) { return c ? c->last_forms : -1; }
 int32_t aif_mlp_layer1_width(const aif_ctx *c) { return !c ? -1 : (c->m.cross_in_mlp == 2 ? c->m.d_item + c->m.d_attn : c->m.k1); }
 
 int32_t aif_stage_kind(const aif_ctx *c, int32_t stage)

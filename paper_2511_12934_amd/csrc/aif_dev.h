@@ -147,6 +147,7 @@ hipError_t launch_user_fold(const Model &m, const Batch &b, const float *w1u, co
 hipError_t launch_attn_generic(const Model &m, const Batch &b, void *X, const float *wq, const void *wq_pieces, const void *table,
                                int32_t *bad, int max_seq_len, int longest, hipStream_t s);
 bool attn_generic_gathers(const Model &m);
+bool attn_generic_keys_stay(const Model &m, const Batch &b, int longest);      // all keys of a block at once (k_generic.hip)
 size_t attn_generic_lds_bytes(const Model &m, int max_seq_len);
 
 // a6-a7, any shape, fp32 precision.

@@ -35,6 +35,7 @@ struct aif_lsh_ctx {
     void *parts = nullptr;                                  // partial tier counts of a batch whose histories are cut into parts
     void *din_pieces = nullptr;                             // the requests' LSH-DIN tables as bf16 matrix operands (or null: LSH-DIN on the vector ALU)
     size_t hist_stride = 0;
+    int last_form = -1;                                     // aif_lsh_last_form
     bool separate = false;                                  // testing (AIF_LSH_SEPARATE=1): a small call's launches kept apart
     char *h_stage = nullptr, *h_stage_dev = nullptr;        // pinned ring of descriptor tables, its device mapping (or null)
     void *d_stage = nullptr;
@@ -270,6 +271,7 @@ aif_status aif_lsh_batch(aif_lsh_ctx *c, const aif_lsh_request *reqs, int32_t n_
         }
         if (!in_args) LSH_TRY(c, hipEventRecord(c->ev[slot], s));
         c->ev_live[slot] = !in_args;
+        c->last_form = in_args ? 3 : 2;
         return AIF_OK;
     }
     LSH_TRY(c, staging_upload(c->h_stage, c->h_stage_dev, (size_t)slot * c->slot_bytes, d, bytes, s));
@@ -315,10 +317,13 @@ aif_status aif_lsh_batch(aif_lsh_ctx *c, const aif_lsh_request *reqs, int32_t n_
     if (pe) LSH_TRY(c, hipEventRecord(pe[3], s));
     LSH_TRY(c, hipEventRecord(c->ev[slot], s));
     c->ev_live[slot] = true;
+    c->last_form = beside ? 1 : 0;
     return AIF_OK;
 }
 
 int32_t aif_lsh_simtier_kind(const aif_lsh_ctx *ctx) { return !ctx ? -1 : (ctx->hist ? 1 : 0); }
+
+int32_t aif_lsh_last_form(const aif_lsh_ctx *ctx) { return ctx ? ctx->last_form : -1; }
 
 int32_t aif_lsh_din_kind(const aif_lsh_ctx *ctx) { return !ctx ? -1 : (ctx->din_pieces ? 1 : 0); }
 

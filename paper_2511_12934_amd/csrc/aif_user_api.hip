@@ -38,6 +38,7 @@ struct aif_user_ctx {
     char *h_stage = nullptr, *h_stage_dev = nullptr;   // pinned ring of descriptor tables, its device mapping (or null)
     void *d_stage = nullptr;
     size_t slot_bytes = 0;
+    int last_form = -1;                                // aif_user_last_form
     bool upload = false;                               // testing (AIF_USER_UPLOAD=1): the descriptors of few users uploaded like those of many
     hipEvent_t ev[USER_NSLOT] = {};
     bool ev_live[USER_NSLOT] = {};
@@ -202,6 +203,8 @@ void aif_user_destroy(aif_user_ctx *ctx) { udestroy(ctx); }
 
 const char *aif_user_last_error(const aif_user_ctx *ctx) { return ctx ? ctx->err.c_str() : g_user_init_error.c_str(); }
 
+int32_t aif_user_last_form(const aif_user_ctx *ctx) { return ctx ? ctx->last_form : -1; }
+
 int32_t aif_user_attention_kind(const aif_user_ctx *ctx) { return !ctx ? -1 : (ctx->mfma.attn ? 1 : 0); }
 
 aif_status aif_user_precompute(aif_user_ctx *c, const aif_user_request *users, int32_t n_users, void *hip_stream)
@@ -304,6 +307,7 @@ aif_status aif_user_precompute(aif_user_ctx *c, const aif_user_request *users, i
     if (pe) USER_TRY(c, hipEventRecord(pe[3], s));
     if (!in_args) USER_TRY(c, hipEventRecord(c->ev[slot], s));
     c->ev_live[slot] = !in_args;
+    c->last_form = in_args;
     return AIF_OK;
 }
 

@@ -790,12 +790,15 @@ static bool narrow_keys_stay(const Model &m, const Batch &b, int longest)
     if (halves % 2) return lengthy && (bf16 ? halves > 10 : halves == 7);
     return halves == 8 || lengthy || (bf16 && halves > 10);
 }
+template <typename T, int FT> static bool attn_gen_keys_stay(const Model &m, const Batch &b, int longest)
+{
+    return (FT <= 2 ? narrow_keys_stay(m, b, longest) : b.n_blk > compute_units() / 2) && gen_keys_lds<T, FT>(m, longest) <= GEN_RES_LDS;
+}
 template <typename T, int FT>
 static void attn_gen_ft(const Model &m, const Batch &b, void *X, const void *table, const void *wqp, const float *wq, int32_t *bad,
                         int longest, hipStream_t s)
 {
-    const size_t lds = gen_keys_lds<T, FT>(m, longest);
-    if ((FT <= 2 ? narrow_keys_stay(m, b, longest) : b.n_blk > compute_units() / 2) && lds <= GEN_RES_LDS) attn_gen_go<T, FT, 8, true>(m, b, X, table, wqp, wq, bad, lds, s);
+    if (attn_gen_keys_stay<T, FT>(m, b, longest)) attn_gen_go<T, FT, 8, true>(m, b, X, table, wqp, wq, bad, gen_keys_lds<T, FT>(m, longest), s);
     else if (b.n_blk >= compute_units() / 2) attn_gen_go<T, FT, 8, false>(m, b, X, table, wqp, wq, bad, 0, s);
     else attn_gen_go<T, FT, 4, false>(m, b, X, table, wqp, wq, bad, 0, s);
 }
@@ -1228,6 +1231,14 @@ template <class F> static void gen_head_tiles(const Model &m, F &&f)       // f(
     };
     if (m.dtype == 0) type(float{});
     else type(uint16_t{});
+}
+
+bool attn_generic_keys_stay(const Model &m, const Batch &b, int longest)
+{
+    bool stay = false;
+    if (m.d_head <= GEN_MAX_HEAD && b.n_blk > 0)
+        gen_head_tiles(m, [&](auto t, auto ft) { stay = attn_gen_keys_stay<decltype(t), decltype(ft)::value>(m, b, longest); });
+    return stay;
 }
 
 bool gen_tile_serves(const Model &m, const Batch &b, int longest)

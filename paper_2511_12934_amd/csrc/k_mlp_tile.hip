@@ -73,13 +73,13 @@ static hipError_t tile_go(const Model &m, const Batch &b, const void *X, const M
     return hipGetLastError();
 }
 
-// One workgroup a compute unit at a time, but for the smallest head: batches of at most as many tiles as there are units.  Whole
-// calls over 100 history items, us, the chain (the widest head: k_mlp_acc3) | here, 1 request of 71, 1,000, 8,000 and 10,000 candidates
-// (313 tiles: a second round):
-//   512, 256        24.0 | 22.2    24.9 | 22.6    27.4 | 24.4    27.7 | 30.1
-//   256 (of 256)    22.2 | 21.6    23.4 | 22.4    25.8 | 25.0    26.3 | 28.1
-//   256, 128        18.6 | 19.4    19.6 | 19.9    23.0 | 22.2    23.1 | 23.5     (over 1,000 items 21.1 | 19.9, 22.3 | 20.7, 24.4 | 22.5, 27.4 | 26.6)
-//   1024, 512, 256  82.4 | 60.2    83.7 | 61.1    91.8 | 70.2    92.6 | 89.9
+// One workgroup a compute unit at a time, but for the smallest head: batches of at most as many tiles as there are units.  What comes here
+// is the widest head, and of the others what k_score_tile.hip does not take: several heads with a history that is streamed (and
+// calls that time a stage).  Whole calls, us, the chain (the widest head: k_mlp_acc3) | here, 1 request of 71, 1,000, 4,000 and 8,000 candidates:
+//   512, 256        (2 heads, 1,000 items)  26.6 | 22.6    28.0 | 23.5    29.0 | 24.8    30.3 | 26.6
+//   256 (of 256)    (4 heads, 500 items)    25.5 | 24.1    27.8 | 26.2    29.2 | 27.6    30.9 | 29.5
+//   256, 128        (2 heads, 600 items)    22.0 | 20.2    22.7 | 21.0    23.6 | 22.1    24.9 | 23.9     (2,000 items 24.1 | 22.8 to 28.3 | 26.6)
+//   1024, 512, 256  (100 items)             82.4 | 60.2    83.7 | 61.1                   91.8 | 70.2     (10,000, a second round: 92.6 | 89.9)
 bool mlp_tile_serves(int variant, const Model &m, const Batch &b)
 {
     return m.cross_in_mlp == 2 && m.x_tiled && variant >= 0 && variant <= 3 && b.n_tiles <= n_cu();

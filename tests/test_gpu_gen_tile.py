@@ -3,6 +3,7 @@ stay resident in batches of nearly a full round of blocks."""
 import numpy as np
 import pytest
 
+from paper_2511_12934_amd import binding as B
 from paper_2511_12934_amd import workloads as wl
 
 from helpers import assert_logits_close, oracle_scores
@@ -42,16 +43,20 @@ def test_one_launch_gives_the_bits_of_two(R, torch, monkeypatch, shape, dtype, o
     rng = np.random.default_rng(59)
     model = wl.make_model(cfg, seed=9, bias_scale=0.3)
     table = wl.make_table_host(cfg, rng, n_items=3000, sigma=1.0)
-    users_ids = requests(cfg, rng, (1, 33, 16, 257, 15, 256), (70, 0, 1, 32, 33, 64))
+    # (three pieces of two heads of 72: the keys of 32 items fit LDS beside the head)
+    lens = (30, 0, 1, 32, 17, 32) if dtype == "f32" and shape == "two_heads_of_72" else (70, 0, 1, 32, 33, 64)
+    users_ids = requests(cfg, rng, (1, 33, 16, 257, 15, 256), lens)
     if odd:
         table[users_ids[3][1][[3, 200]], 5] = np.inf, np.nan
         users_ids[4][0].seq_vals[2, 3] = -np.inf
     table_dev = R.to_device(table, dtype)
     got, got_y, _, ctx = run_batch(R, torch, cfg, model, table_dev, users_ids, max_seq_len=70)
+    assert ctx.aif_last_forms() == B.FORM_ONE_LAUNCH
     bad = ctx.aif_poll_device_errors()
     X = [R.peek_features(ctx, cfg, r, ids.size) for r, (_, ids) in enumerate(users_ids)]
     monkeypatch.setenv("AIF_MLP_TILE", "0")
     ref, ref_y, _, ctx0 = run_batch(R, torch, cfg, model, table_dev, users_ids, max_seq_len=70)
+    assert ctx0.aif_last_forms() == 0
     assert bad == 3 and ctx0.aif_poll_device_errors() == 3
     for r, (u, ids) in enumerate(users_ids):
         assert np.array_equal(X[r], R.peek_features(ctx0, cfg, r, ids.size), equal_nan=True), r
@@ -73,8 +78,10 @@ def test_resident_keys_give_the_bits_of_single_requests(R, torch, monkeypatch, d
     table = wl.make_table_host(cfg, rng, sigma=1.0)
     users_ids = requests(cfg, rng, rng.integers(3, 257, n_req), [seq_len, *rng.integers(0, seq_len + 1, n_req - 1)])
     zs, _, _, ctx = run_batch(R, torch, cfg, model, R.to_device(table, dtype), users_ids, max_seq_len=seq_len)
+    assert ctx.aif_last_forms() & B.FORM_KEYS_RESIDENT
     for r in (0, 1, 70, n_req - 1):
         alone = R.upload_request(cfg, *users_ids[r])
         ctx.aif_score_request(alone.req)
         torch.cuda.synchronize()
+        assert ctx.aif_last_forms() == B.FORM_ONE_LAUNCH
         assert np.array_equal(alone.logits.cpu().numpy(), zs[r], equal_nan=True), r

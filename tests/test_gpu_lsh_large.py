@@ -37,10 +37,12 @@ def test_a_large_call_gives_the_bits_of_its_requests(R, torch, dtype, bits, d, u
                        max_candidates=N, max_users=users)
     ctx.aif_lsh_batch(reqs)
     torch.cuda.synchronize()
+    assert ctx.aif_lsh_last_form() == 1
     whole = [(a.clone(), b.clone()) for a, b in outs]
     for r, (a, b) in enumerate(outs):
         a.fill_(7.0)
         b.fill_(7)
         ctx.aif_lsh_batch([reqs[r]])
         torch.cuda.synchronize()
+        assert ctx.aif_lsh_last_form() == (3 if ctx.aif_lsh_simtier_kind() == ctx.aif_lsh_din_kind() == 1 else 0)
         assert torch.equal(a, whole[r][0]) and torch.equal(b, whole[r][1]), lens[r]

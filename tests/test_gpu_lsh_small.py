@@ -34,6 +34,8 @@ def test_three_launches_give_the_results_of_seven(R, torch, monkeypatch, dtype, 
         emb = torch.from_numpy(rng.standard_normal((L, d)).astype(np.float32) * 0.1).to(t)
         users.append((sig, emb, ids))
 
+    forms = []
+
     def run():
         din = [torch.full((n, d), 7.0, device="cuda") for n, _ in sizes]
         tier = [torch.full((n, 8), 7, dtype=torch.int32, device="cuda") for n, _ in sizes]
@@ -43,12 +45,14 @@ def test_three_launches_give_the_results_of_seven(R, torch, monkeypatch, dtype, 
         for _ in range(2):
             ctx.aif_lsh_batch(reqs)
             torch.cuda.synchronize()
+        forms.append(ctx.aif_lsh_last_form())
         assert ctx.aif_lsh_poll_device_errors() == 2 * 2 * sum(n > 30 for n, _ in sizes)
         return [a.cpu().numpy() for a in din], [b.cpu().numpy() for b in tier]
 
     din, tier = run()
     monkeypatch.setenv("AIF_LSH_SEPARATE", "1")
     din0, tier0 = run()
+    assert forms == [3 if len(sizes) <= 16 else 2, 0]           # the launches that are compared
     for r, (sig, emb, ids) in enumerate(users):
         assert np.array_equal(din[r], din0[r], equal_nan=True) and np.array_equal(tier[r], tier0[r]), r
         if len(ids) == 0 or len(sig) == 0:

@@ -3,6 +3,7 @@ kernels of larger batches (the chain; the widest head: the accumulating kernel; 
 import numpy as np
 import pytest
 
+from paper_2511_12934_amd import binding as B
 from paper_2511_12934_amd import workloads as wl
 
 from helpers import assert_bf16_logits_tight, oracle_scores
@@ -39,9 +40,12 @@ def test_few_candidates_give_the_bits_of_many(R, torch, monkeypatch, shape, size
         if r % 2 == 0:
             ids[[0, n // 2, n - 1]] = [-1, 2_000_000_000, cfg.n_items]
         users_ids.append((wl.make_user(cfg, rng, seq_len=int(rng.integers(0, 25))), ids))
-    got, got_y, _, _ = run_batch(R, torch, cfg, model, table_dev, users_ids, max_seq_len=24)
+    got, got_y, _, ctx = run_batch(R, torch, cfg, model, table_dev, users_ids, max_seq_len=24)
+    few = sum(-(-n // 32) for n in sizes) <= n_cu               # (the others' one launch goes on to two tiles a unit)
+    assert ctx.aif_last_forms() == ((B.FORM_HEAD_TILE if few else 0) if shape == "C5" else B.FORM_ONE_LAUNCH)
     monkeypatch.setenv("AIF_MLP_TILE", "0")
-    ref, ref_y, _, _ = run_batch(R, torch, cfg, model, table_dev, users_ids, max_seq_len=24)
+    ref, ref_y, _, ctx0 = run_batch(R, torch, cfg, model, table_dev, users_ids, max_seq_len=24)
+    assert ctx0.aif_last_forms() == 0
     for r, (u, ids) in enumerate(users_ids):
         assert np.array_equal(got[r], ref[r], equal_nan=True) and np.array_equal(got_y[r], ref_y[r], equal_nan=True), r
         assert np.isnan(got[r]).sum() == np.sum((ids < 0) | (ids >= cfg.n_items))
@@ -75,11 +79,16 @@ def test_attention_and_head_in_one_launch_give_the_bits_of_two(R, torch, monkeyp
                 ids[[0, n // 2, n - 1]] = [-1, 2_000_000_000, cfg.n_items]
             users_ids.append((wl.make_user(cfg, rng, seq_len=l, sigma=sigma), ids))
         got, got_y, _, ctx = run_batch(R, torch, cfg, model, table_dev, users_ids, max_seq_len=1100)
+        # several heads: one launch while all K/V fit the resident kernel's LDS, else the head alone, up to a tile a unit
+        dh = cfg.d_attn // cfg.n_heads
+        streamed = any(cfg.n_heads * ((-(-l // 32) + 1) // 2 * 2) * (dh // 8) > 152 for l in lens)
+        assert ctx.aif_last_forms() == (B.FORM_ONE_LAUNCH if cfg.n_heads == 1 or not streamed else 0 if big else B.FORM_HEAD_TILE)
         bad = ctx.aif_poll_device_errors()
         X = [R.peek_features(ctx, cfg, r, ids.size) for r, (_, ids) in enumerate(users_ids)]
         with monkeypatch.context() as mp:
             mp.setenv("AIF_MLP_TILE", "0")
             ref, ref_y, _, ctx0 = run_batch(R, torch, cfg, model, table_dev, users_ids, max_seq_len=1100)
+        assert ctx0.aif_last_forms() == 0
         assert bad == 3 and ctx0.aif_poll_device_errors() == 3
         assert ctx.aif_stage_kind("gather") == ctx0.aif_stage_kind("gather")
         for r, (u, ids) in enumerate(users_ids):
@@ -88,3 +97,22 @@ def test_attention_and_head_in_one_launch_give_the_bits_of_two(R, torch, monkeyp
         if sigma == 1.0 and not big:
             u, ids = users_ids[2]
             assert_bf16_logits_tight(got[2], oracle_scores(cfg, model, table, u, ids).logits, "against the oracle")
+
+
+# the last batch that is one launch and the first that is not: two tiles a unit, six where every history is streamed
+@pytest.mark.parametrize("shape,seq_len,per_unit", [("c2_like", 20, 2), ("c3_like", 600, 6), ("c4_like", 20, 2)])
+def test_where_one_launch_ends(R, torch, monkeypatch, shape, seq_len, per_unit):  # noqa: F811
+    cfg = config(shape)
+    _say(f"end of one launch {shape} L={seq_len}")
+    rng = np.random.default_rng(57)
+    model = wl.make_model(cfg, seed=9, bias_scale=0.05)
+    table_dev = R.to_device(wl.make_table_host(cfg, rng, n_items=cfg.n_items), "bf16")
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    users_ids = [(wl.make_user(cfg, rng, seq_len=seq_len), rng.integers(0, cfg.n_items, n).astype(np.int32)) for n in (32 * (per_unit * n_cu - 3), 90, 1)]
+    for n, form in ((2, B.FORM_ONE_LAUNCH), (3, 0)):
+        got, _, _, ctx = run_batch(R, torch, cfg, model, table_dev, users_ids[:n], max_seq_len=seq_len)
+        assert ctx.aif_last_forms() == form
+        with monkeypatch.context() as mp:
+            mp.setenv("AIF_MLP_TILE", "0")
+            ref, _, _, _ = run_batch(R, torch, cfg, model, table_dev, users_ids[:n], max_seq_len=seq_len)
+        assert all(np.array_equal(a, b) for a, b in zip(got, ref))

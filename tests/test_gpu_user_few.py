@@ -22,11 +22,13 @@ def test_descriptors_in_the_arguments_and_uploaded_give_the_same_bits(R, torch, 
     lens = [longest, 0, longest - 33, *rng.integers(0, longest + 1, n_users)][:n_users]
     users = [wl.make_raw_user(cfg, rng, seq_len=int(l)) for l in lens]
     got, dev, ctx = run_users(R, torch, cfg, model, users)
+    assert ctx.aif_user_last_form() == (n_users <= 64)
     ctx.aif_user_precompute([v.req for v in dev[:1]])                   # a smaller call on the same context
     torch.cuda.synchronize()
     assert np.array_equal(R.from_device_f32(dev[0].user_vec), got[0][0])
     monkeypatch.setenv("AIF_USER_UPLOAD", "1")
-    ref, _, _ = run_users(R, torch, cfg, model, users)
+    ref, _, ctx0 = run_users(R, torch, cfg, model, users)
+    assert ctx0.aif_user_last_form() == 0
     for r, (a, b) in enumerate(zip(got, ref)):
         assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1]), r
     check_user(dtype, got[0], oracle_user(model, users[0]), d, f"L={lens[0]}")
