@@ -228,7 +228,9 @@ AIF_API aif_status aif_peek_features(aif_ctx *ctx, int32_t request, int32_t firs
  * Between aif_profile_begin and aif_profile_end every aif_score_batch records
  * an event before and after each of its kernels, and every aif_topk around
  * its kernel, for at most max_calls calls of each kind (later calls are not
- * recorded).  aif_profile_end synchronises on the recorded events and returns
+ * recorded).  A call of few candidates whose attention and head are one launch (aif_last_forms) has them apart where the
+ * attention or the MLP stage is timed: their times are then those of two launches, which together take longer than the call
+ * does untimed.  aif_profile_end synchronises on the recorded events and returns
  * the summed milliseconds per stage in ms_sum[AIF_STAGE_COUNT] and the number
  * of recorded calls per stage in n_calls[AIF_STAGE_COUNT] (both HOST). */
 enum { AIF_STAGE_GATHER = 0, AIF_STAGE_USER_FOLD = 1, AIF_STAGE_ATTENTION = 2, AIF_STAGE_MLP = 3,

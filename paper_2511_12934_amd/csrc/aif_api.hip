@@ -626,8 +626,9 @@ static aif_status score_impl(aif_ctx *c, const aif_request *reqs, int32_t n_req,
     const float *bf[MAX_LAYERS];
     for (int l = 0; l < m.n_layers; ++l) bf[l] = c->has_bias[l] ? (const float *)c->bias[l].p : nullptr;
     const MlpGenericWeights gw = generic_weights(c);
-    // few candidates: attention and head as one launch (a call that is timed stage by stage keeps them apart)
-    const bool one_launch = !pe && (fused ? score_tile_serves(m, b, c->mfma) : gen_one_launch(c, b, longest));
+    // few candidates: attention and head as one launch (a call that times either of them keeps them apart)
+    const bool apart = pe && (c->prof_mask & (1u << AIF_STAGE_ATTENTION | 1u << AIF_STAGE_MLP));
+    const bool one_launch = !apart && (fused ? score_tile_serves(m, b, c->mfma) : gen_one_launch(c, b, longest));
     const void *rows_from = attn_indexes ? c->table : nullptr;
     const float *wq = c->has_wq ? (const float *)c->wq.p : nullptr;
     if (one_launch && fused)

@@ -116,3 +116,20 @@ def test_where_one_launch_ends(R, torch, monkeypatch, shape, seq_len, per_unit):
             mp.setenv("AIF_MLP_TILE", "0")
             ref, _, _, _ = run_batch(R, torch, cfg, model, table_dev, users_ids[:n], max_seq_len=seq_len)
         assert all(np.array_equal(a, b) for a, b in zip(got, ref))
+
+
+def test_a_timed_call_keeps_the_stages_apart_that_it_times(R, torch):  # noqa: F811
+    cfg = config("c3_like")
+    rng = np.random.default_rng(58)
+    model = wl.make_model(cfg, seed=9, bias_scale=0.05)
+    table_dev = R.to_device(wl.make_table_host(cfg, rng, n_items=cfg.n_items), "bf16")
+    ui = [(wl.make_user(cfg, rng, seq_len=24), rng.integers(0, cfg.n_items, 200).astype(np.int32))]
+    z, _, drs, ctx = run_batch(R, torch, cfg, model, table_dev, ui, max_seq_len=24)
+    for stages, form in ((("attention",), B.FORM_HEAD_TILE), (("mlp",), B.FORM_HEAD_TILE), (("user_fold",), B.FORM_ONE_LAUNCH), (("gather", "topk"), B.FORM_ONE_LAUNCH)):
+        ctx.aif_profile_begin_stages(1, stages)
+        drs[0].logits.fill_(float("nan"))
+        ctx.aif_score_batch([drs[0].req])
+        torch.cuda.synchronize()
+        ctx.aif_profile_end()
+        assert ctx.aif_last_forms() == form, stages
+        assert np.array_equal(drs[0].logits.cpu().numpy(), z[0])
