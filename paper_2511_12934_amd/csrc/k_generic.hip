@@ -260,7 +260,7 @@ __global__ __launch_bounds__(256) void k_attn_generic(Model m, Batch b, T *__res
 // stays under 128 registers (four waves a SIMD); then the vector ALU -- per key
 // and candidate one exponential and three pieces of the weight.  Measured (L <=
 // 50, d_attn 32 of W_q, rows of 64): fp32, 16 users of 6,200 candidates on average
-// 33 us, bf16, 16 x 10^4: 35 -- 230 + 13 and 312 + 10 with a wave per candidate on
+// 32 us, bf16, 16 x 10^4: 32 -- 230 + 13 and 312 + 10 with a wave per candidate on
 // the vector ALU after a gather launch, 48 and 55 with the keys 32 at a time in
 // blocks of four waves; fp32, one request of 1,000: 10.4 against 22 + 6.
 // ---------------------------------------------------------------------------
@@ -855,7 +855,7 @@ hipError_t launch_attn_generic(const Model &m, const Batch &b, void *X, const fl
 // Measured (160 -> 128 -> 64 -> 1, fp32): 10^5 candidates 59 us, where a thread per
 // feature and 16 candidates on the vector ALU took 210 (81 with 64 candidates, eight
 // waves a block; 61 with the pieces cut value by value); 1,000 candidates 7 against 30; bf16, 160,000
-// candidates 44 against 301 (k_generic_chain.hip: 27).
+// candidates 44 against 301 (k_generic_chain.hip: 28).
 // ---------------------------------------------------------------------------
 constexpr int MLP_TS = 16;              // candidates of a column tile
 

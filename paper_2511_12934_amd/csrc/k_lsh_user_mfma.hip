@@ -313,7 +313,7 @@ __global__ __launch_bounds__(256, 2) void k_lsh_user_sums(LshModel m, LshBatch b
 // The same beside the blocks that expand the histories for SimTier, in the first launch of a small call; FEW: its first blocks write the
 // batch's tables.  KS: words of a signature.
 // A small call is bound by its launches (2.2 us of host time each, the upload and an event besides) and by each kernel's chain of
-// loads.  Three launches where seven were, chunks of a tenth of the history where they were of 1,024 items, LSH-DIN a wave to one
+// loads.  Three launches where seven were, chunks of a tenth of the history (up to 16 users) where they were of 1,024 items, LSH-DIN a wave to one
 // tile of features: 1 x 100 candidates x 500 items (64 bits) 37.4 -> 21.6 us a call, 1 x 3,000 x 3,000 64.0 -> 31.8, 3 x 1,495 x 1,330
 // (128 bits) 78.0 -> 39.7, 8 x 1,000 x 2,000 (128, fp32) 89.1 -> 48.8, 64 x 400 x 10^4 101.5 -> 87.6, 8 x 300 x 90,000 159 -> 146 (168
 // with each request's expansion behind its own sums: the last sums began late; 191 with a piece a thread there).
